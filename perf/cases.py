@@ -1,0 +1,200 @@
+"""The work this framework is measured on: sparse-linear attention as its users call it.
+
+A case is one attention layer on tokens of a (t, h, w) grid.  Its `mode` says which part of a
+program it stands for:
+  train    a fine-tuning step: sla_attention (mask and forward) and its gradients
+           (O, dQ, dK, dV, dProj come back)
+  infer    one layer of a sampling step: block mask and forward pass, no gradients (M_c, O)
+  reuse    a later sampling step that keeps the mask of an earlier one: the forward pass alone,
+           through the buffer-level binding with the buffers such a program holds (O)
+Q, K, V are smooth random Fourier features of the token's grid position plus noise, the synthetic
+stand-in for video and image activations that this repository's workloads use, drawn here on the GPU.
+"""
+from __future__ import annotations
+
+import math
+
+import torch
+
+from paper_2509_24006_amd import autograd as attn
+from paper_2509_24006_amd import binding as sla
+
+_DTYPES = {"bf16": torch.bfloat16, "fp32": torch.float32}
+_MAX_TOKENS = 40 * 75600          # tokens x heads of the largest layer
+
+
+def _case(name, mode, dtype, B, H, d, grid, k_h, k_l=0.10, phi="softmax", bq=64, layout="head"):
+    c = {"mode": mode, "dtype": dtype, "B": B, "H": H, "d": d, "t": grid[0], "h": grid[1], "w": grid[2],
+         "k_h": k_h, "k_l": k_l, "phi": phi, "bq": bq, "layout": layout}
+    if name:
+        c["name"] = name
+    return c
+
+
+def listed():
+    return [
+        # the smallest calls: a test-sized float layer, where launches and host work are all there is
+        _case("tiny_fp32_train", "train", "fp32", 1, 2, 64, (4, 16, 16), 0.10),
+        # a float fine-tuning step of a short clip (gradient checks, float reference runs)
+        _case("clip_fp32_train", "train", "fp32", 1, 4, 128, (5, 30, 52), 0.05),
+        # small bf16 layers with ragged ends (1110 and 902 tokens)
+        _case("small_bf16_train", "train", "bf16", 1, 2, 128, (3, 10, 37), 0.10),
+        _case("small_bf16_d64_infer", "infer", "bf16", 1, 3, 64, (2, 11, 41), 0.12, 0.15),
+        # image generation, 512 x 512 pixels -> 32 x 32 latents: many short sequences, 87.5 % sparsity;
+        # training on head-major tensors, sampling on token-major ones as the projections leave them
+        _case("image_train", "train", "bf16", 16, 16, 64, (1, 32, 32), 0.125),
+        _case("image_infer_token_major", "infer", "bf16", 16, 16, 64, (1, 32, 32), 0.125, layout="token"),
+        # a shorter clip (an odd number of tokens), the other feature map, mask per 128 queries
+        _case("clip_elu_bq128_train", "train", "bf16", 1, 12, 128, (7, 31, 43), 0.05, phi="elu1", bq=128),
+        # the video layer (12 heads, 21 x 30 x 52 latents): a sampling step, a later one with a kept
+        # mask on the slices of a fused QKV projection, fine-tuning at two sparsities
+        _case("video_infer", "infer", "bf16", 1, 12, 128, (21, 30, 52), 0.05),
+        _case("video_reuse_fused_qkv", "reuse", "bf16", 1, 12, 128, (21, 30, 52), 0.05, layout="fused"),
+        _case("video_train", "train", "bf16", 1, 12, 128, (21, 30, 52), 0.05),
+        _case("video_train_kh20", "train", "bf16", 1, 12, 128, (21, 30, 52), 0.20),
+        # the large video layer (40 heads, 21 x 45 x 80 latents), fine-tuning
+        _case("long_train", "train", "bf16", 1, 40, 128, (21, 45, 80), 0.05),
+    ]
+
+
+def _log_uniform(rng, lo, hi):
+    return math.exp(rng.uniform(math.log(lo), math.log(hi)))
+
+
+def draw(rng):
+    largest = listed()[-1]
+    while True:
+        fp32 = rng.random() < 0.2
+        d = rng.choice((64, 128))
+        n = _log_uniform(rng, 300, 10000 if fp32 else 75600)
+        # a grid of about n tokens: one frame (image) or several
+        t = 1 if rng.random() < 0.3 else rng.randint(2, 21)
+        h = max(4, int(math.sqrt(n / t) * rng.uniform(0.6, 1.0)))
+        w = max(4, round(n / (t * h)))
+        N = t * h * w
+        bh = max(1, int(_log_uniform(rng, 1, 16 if fp32 else 256)))
+        B = rng.choice((1, 1, 2, 4, 8))
+        H = max(1, bh // B)
+        # (a kept mask belongs to sampling, which runs in bf16)
+        mode = rng.choice(("train", "infer") if fp32 else ("train", "train", "infer", "infer", "reuse"))
+        c = _case(None, mode, "fp32" if fp32 else "bf16", B, H, d, (t, h, w),
+                  round(_log_uniform(rng, 0.025, 0.2), 4), rng.choice((0.10, 0.10, 0.15, 0.0)),
+                  rng.choice(("softmax", "softmax", "softmax", "elu1")), rng.choice((64, 64, 64, 128, 256)),
+                  rng.choice(("head", "token")) if mode != "reuse" else rng.choice(("head", "fused")))
+        if not 256 <= N <= 80000 or B * H * N > _MAX_TOKENS or c["k_h"] * -(-N // 64) < 0.5:
+            continue   # (at least one critical block per row)
+        # float layers cost about twenty times a bf16 layer of the same size
+        if work(c)["flops"] * (20 if fp32 else 1) <= work(largest)["flops"]:
+            return c
+
+
+# ---------------------------------------------------------------- inputs
+
+def _phi(c):
+    return sla.SLA_PHI_SOFTMAX if c["phi"] == "softmax" else sla.SLA_PHI_ELU1
+
+
+def _features(c, gen, dev, names):
+    """Q, K, V as [B, H, N, d] tensors: F G + 0.3 noise, scaled to unit variance."""
+    B, H, d = c["B"], c["H"], c["d"]
+    t, h, w = c["t"], c["h"], c["w"]
+    N, BH, dt = t * h * w, B * H, _DTYPES[c["dtype"]]
+    n = torch.arange(N, device=dev)
+    pos = torch.stack([(n // (h * w)) / t, (n // w) % h / h, n % w / w], dim=1).float()
+    omega = torch.randn(BH, 3, 8, generator=gen, device=dev)
+    beta = 2 * math.pi * torch.rand(BH, 1, 8, generator=gen, device=dev)
+    out = {k: torch.empty(BH, N, d, dtype=dt, device=dev) for k in names}
+    step = max(1, min(BH, (1 << 26) // (N * d)))
+    for b in range(0, BH, step):
+        e = min(BH, b + step)
+        F = math.sqrt(2.0) * torch.cos(2 * math.pi * torch.matmul(pos, omega[b:e]) + beta[b:e])
+        for k in names:
+            G = torch.randn(e - b, 8, d, generator=gen, device=dev) * math.sqrt(1.0 / 8.0)
+            x = torch.randn(e - b, N, d, generator=gen, device=dev).mul_(0.3)
+            x += torch.matmul(F, G)
+            out[k][b:e] = x.mul_(1.0 / math.sqrt(1.09))
+    return {k: v.view(B, H, N, d) for k, v in out.items()}
+
+
+def prepare(case, seed):
+    c, dev = case, torch.device("cuda")
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(seed)
+    B, H, d, dt = c["B"], c["H"], c["d"], _DTYPES[c["dtype"]]
+    N = c["t"] * c["h"] * c["w"]
+    x = _features(c, gen, dev, ("Q", "K", "V"))
+    W = (0.02 * torch.randn(d, d, generator=gen, device=dev)).to(dt)
+    token = c["layout"] == "token"
+    if token:
+        x = {k: v.transpose(1, 2).contiguous() for k, v in x.items()}
+    s = {"case": c, "W": W, "token": token, **x}
+    if c["mode"] == "train":
+        for k in ("Q", "K", "V", "W"):
+            s[k].requires_grad_(True)
+        s["dO"] = torch.randn(s["Q"].shape, generator=gen, device=dev, dtype=dt)
+    elif c["mode"] == "reuse":
+        if c["layout"] == "fused":   # Q, K, V are the slices of one projection output [B, N, 3, H, d]
+            qkv = torch.empty(B, N, 3, H, d, dtype=dt, device=dev)
+            for i, k in enumerate(("Q", "K", "V")):
+                qkv[:, :, i] = s[k].transpose(1, 2)
+                s[k] = qkv[:, :, i].transpose(1, 2)
+            p = sla.make_params(B, H, N, d, c["k_h"], c["k_l"], dt, phi=_phi(c), bq=c["bq"],
+                                layout=sla.SLA_STRIDED, strides=s["Q"].stride()[:3])
+            s["O"] = torch.empty_strided(s["Q"].shape, s["Q"].stride(), dtype=dt, device=dev)
+        else:
+            p = sla.make_params(B, H, N, d, c["k_h"], c["k_l"], dt, phi=_phi(c), bq=c["bq"])
+            s["O"] = torch.empty_like(s["Q"])
+        s["p"] = p
+        s["Mc"], s["luts"], _ = sla.sla_build_mask(p, s["Q"], s["K"])
+        s["ws"] = torch.empty(sla.sla_sizes(p).ws_forward_bytes, dtype=torch.uint8, device=dev)
+    return s
+
+
+def run(state):
+    s, c = state, state["case"]
+    if c["mode"] == "train":
+        O = attn.sla_attention(s["Q"], s["K"], s["V"], s["W"], c["k_h"], c["k_l"], _phi(c),
+                               token_major=s["token"], bq=c["bq"])
+        return (O,) + torch.autograd.grad(O, (s["Q"], s["K"], s["V"], s["W"]), s["dO"])
+    if c["mode"] == "infer":
+        with torch.no_grad():
+            mask = attn.build_mask(s["Q"], s["K"], c["k_h"], c["k_l"], _phi(c), s["token"], c["bq"])
+            O = attn.sla_attention(s["Q"], s["K"], s["V"], s["W"], mask=mask, token_major=s["token"])
+        return mask[1], O
+    O, _ = sla.sla_forward(s["p"], s["Q"], s["K"], s["V"], s["W"], s["Mc"], s["luts"], O=s["O"],
+                           workspace=s["ws"], need_saved=False)
+    return O
+
+
+# ---------------------------------------------------------------- what a pass cannot do without
+
+def work(case):
+    """Inputs read once and outputs written once; operations of the critical blocks (4 r c d forward,
+    10 r c d backward), of the linear branch without its block sums (6 and 12 N d^2 per head) and of
+    the block scores."""
+    c = case
+    B, H, d = c["B"], c["H"], c["d"]
+    N = c["t"] * c["h"] * c["w"]
+    esz = 2 if c["dtype"] == "bf16" else 4
+    T, Tq = -(-N // 64), -(-N // c["bq"])
+    n_h = min(T, math.floor(c["k_h"] * T + 0.5))
+    BH, tensor = B * H, B * H * N * d * esz
+    pairs = BH * N * min(N, 64 * n_h)
+    train = c["mode"] == "train"
+    flops = (14 if train else 4) * pairs * d + (18 if train else 6) * BH * N * d * d
+    nbytes = (8 if train else 4) * tensor + d * d * esz * (2 if train else 1)
+    if c["mode"] != "reuse":
+        flops += 2 * BH * Tq * T * d
+    if c["mode"] == "infer":
+        nbytes += BH * Tq * T          # the mask comes back
+    return {"bytes": nbytes, "flops": flops}
+
+
+def tolerance(case):
+    """About four times the largest relative error of any output against the same layer written out
+    densely in float64: O 1.7e-3 and gradients up to 4.6e-3 (dQ) with bf16 tensors, O 3.4e-7 and
+    gradients up to 7.6e-7 with float tensors."""
+    train = case["mode"] == "train"
+    if case["dtype"] == "bf16":
+        return {"rel": 1.5e-2 if train else 7e-3}
+    return {"rel": 4e-6 if train else 2e-6}
