@@ -116,22 +116,31 @@ def _features(c, gen, dev, names):
     return {k: v.view(B, H, N, d) for k, v in out.items()}
 
 
-def prepare(case, seed):
-    c, dev = case, torch.device("cuda")
+def _inputs(c, seed):
+    """Q, K, V in the case's memory order, the Proj weight W and, for a training step, dO."""
+    dev = torch.device("cuda")
     gen = torch.Generator(device=dev)
     gen.manual_seed(seed)
+    d, dt = c["d"], _DTYPES[c["dtype"]]
+    x = _features(c, gen, dev, ("Q", "K", "V"))
+    x["W"] = (0.02 * torch.randn(d, d, generator=gen, device=dev)).to(dt)
+    if c["layout"] == "token":
+        for k in ("Q", "K", "V"):
+            x[k] = x[k].transpose(1, 2).contiguous()
+    if c["mode"] == "train":
+        x["dO"] = torch.randn(x["Q"].shape, generator=gen, device=dev, dtype=dt)
+    return x
+
+
+def prepare(case, seed):
+    c = case
     B, H, d, dt = c["B"], c["H"], c["d"], _DTYPES[c["dtype"]]
     N = c["t"] * c["h"] * c["w"]
-    x = _features(c, gen, dev, ("Q", "K", "V"))
-    W = (0.02 * torch.randn(d, d, generator=gen, device=dev)).to(dt)
-    token = c["layout"] == "token"
-    if token:
-        x = {k: v.transpose(1, 2).contiguous() for k, v in x.items()}
-    s = {"case": c, "W": W, "token": token, **x}
+    s = {"case": c, "token": c["layout"] == "token", **_inputs(c, seed)}
+    dev = s["Q"].device
     if c["mode"] == "train":
         for k in ("Q", "K", "V", "W"):
             s[k].requires_grad_(True)
-        s["dO"] = torch.randn(s["Q"].shape, generator=gen, device=dev, dtype=dt)
     elif c["mode"] == "reuse":
         if c["layout"] == "fused":   # Q, K, V are the slices of one projection output [B, N, 3, H, d]
             qkv = torch.empty(B, N, 3, H, d, dtype=dt, device=dev)
@@ -198,3 +207,85 @@ def tolerance(case):
     if case["dtype"] == "bf16":
         return {"rel": 1.5e-2 if train else 7e-3}
     return {"rel": 4e-6 if train else 2e-6}
+
+
+# ---------------------------------------------------------------- the same layer in 64 bits
+
+_ROWS = 1 << 16                   # critical keys that are gathered at a time
+
+
+def _phi64(x, name):
+    return torch.softmax(x, dim=-1) if name == "softmax" else torch.nn.functional.elu(x) + 1
+
+
+def _mask64(q, k, c):
+    """Labels of one head: 1 for the n_h highest block scores of a row, -1 for the n_l lowest, 0 else."""
+    N, d = q.shape
+    T = -(-N // 64)
+    pool = lambda x, b: torch.stack([x[i:i + b].mean(0) for i in range(0, N, b)])
+    sc = torch.matmul(pool(q, c["bq"]), pool(k, 64).T.contiguous()) / math.sqrt(d)
+    n_h = min(T, math.floor(c["k_h"] * T + 0.5))
+    n_l = min(T - n_h, math.floor(c["k_l"] * T + 0.5))
+    order = torch.sort(sc, dim=1, descending=True, stable=True).indices
+    m = torch.zeros_like(sc)
+    m.scatter_(1, order[:, :n_h], 1.0)
+    m.scatter_(1, order[:, T - n_l:], -1.0)
+    return m.repeat_interleave(c["bq"] // 64, 0)[:T], n_h
+
+
+def _head64(q, k, v, W, dO, c):
+    """O of one head, [N, d]; with dO the gradients are added to q, k, v and W."""
+    N, d = q.shape
+    T, pad = -(-N // 64), -N % 64
+    with torch.no_grad():
+        m, n_h = _mask64(q, k, c)
+        crit = (m == 1).nonzero()[:, 1].view(T, n_h)
+    blocks = lambda x: torch.nn.functional.pad(x, (0, 0, 0, pad)).view(T, 64, d)
+    kb, vb = blocks(k), blocks(v)
+    fk = blocks(_phi64(k, c["phi"]))
+    marg = (m == 0).double()
+    Hs = torch.matmul(marg, torch.bmm(fk.transpose(1, 2).contiguous(), vb).view(T, d * d))
+    Zs = torch.matmul(marg, fk.sum(1))
+    cut = [x.detach().requires_grad_(dO is not None) for x in (Hs, Zs, kb, vb)]
+    live = (torch.arange(T * 64, device=q.device) < N).view(T, 64)
+    out = []
+    step = max(1, min(T, _ROWS // (64 * n_h)))
+    for a in range(0, T, step):
+        e = min(T, a + step)
+        n = min(N, e * 64) - a * 64
+        qc = torch.nn.functional.pad(q[a * 64:min(N, e * 64)], (0, 0, 0, (e - a) * 64 - n)).view(e - a, 64, d)
+        idx = crit[a:e].reshape(-1)
+        kc = cut[2].index_select(0, idx).view(e - a, n_h * 64, d)
+        vc = cut[3].index_select(0, idx).view(e - a, n_h * 64, d)
+        S = torch.bmm(qc, kc.transpose(1, 2).contiguous()) / math.sqrt(d)
+        S = S.masked_fill(~live[idx].view(e - a, 1, n_h * 64), -math.inf)
+        fq = _phi64(qc, c["phi"])
+        den = torch.bmm(fq, cut[1][a:e].unsqueeze(2))
+        Ol = torch.bmm(fq, cut[0][a:e].view(e - a, d, d)) / torch.where(den > 0, den, torch.ones_like(den))
+        O = (torch.bmm(torch.softmax(S, dim=-1), vc) + torch.matmul(Ol, W)).view(-1, d)[:n]
+        out.append(O.detach())
+        if dO is not None:
+            O.backward(dO[a * 64:a * 64 + n])
+    if dO is not None:
+        torch.autograd.backward((Hs, Zs, kb, vb), [x.grad for x in cut])
+    return torch.cat(out)
+
+
+def exact(case, seed):
+    """What run() returns for these inputs, computed in float64 from the formulas of the layer."""
+    c, train = case, case["mode"] == "train"
+    x = _inputs(c, seed)
+    token = c["layout"] == "token"
+    head = (lambda t, b, h: t[b, :, h]) if token else (lambda t, b, h: t[b, h])
+    new = lambda: torch.empty(x["Q"].shape, dtype=torch.float64, device=x["Q"].device)
+    O, grads = new(), [new() for _ in range(3)] if train else []
+    W = x["W"].double().requires_grad_(train)
+    for b in range(c["B"]):
+        for h in range(c["H"]):
+            q, k, v = (head(x[n], b, h).double().requires_grad_(train) for n in ("Q", "K", "V"))
+            head(O, b, h).copy_(_head64(q, k, v, W, head(x["dO"], b, h).double() if train else None, c))
+            for g, t in zip(grads, (q, k, v)):
+                head(g, b, h).copy_(t.grad)
+    if train:
+        return (O, *grads, W.grad)
+    return (None, O) if c["mode"] == "infer" else O
