@@ -112,7 +112,7 @@ void fill_sizes(const Shape& s, sla_sizes_t* o) {
   // [0, state): H_i, Z_i when the caller passes no `saved`; then the key-block states
   const size_t hz_ws = s.dtype == SLA_BF16 ? mfma_forward_ws_bytes(s) : state;
   o->ws_forward_bytes = state + hz_ws;
-  o->ws_backward_bytes = simt_backward_ws_bytes(s);
+  o->ws_backward_bytes = backward_ws_bytes(s);
 }
 
 inline bool misaligned(const void* p) { return ((uintptr_t)p & 15u) != 0; }
@@ -255,7 +255,7 @@ int sla_forward(const sla_params* p, const void* Q, const void* K, const void* V
   a.hz = (float*)(ws + state);
   a.HZ = sv ? (float*)(sv + z.saved_HZ) : (float*)ws;
   if (s.dtype == SLA_BF16) return hip_status(mfma_forward(s, a, ws + state, (hipStream_t)stream));
-  return hip_status(simt_forward(s, a, (hipStream_t)stream));
+  return hip_status(f32_forward(s, a, (hipStream_t)stream));
 }
 
 int sla_backward(const sla_params* p, const void* Q, const void* K, const void* V, const void* W,
@@ -291,7 +291,7 @@ int sla_backward(const sla_params* p, const void* Q, const void* K, const void* 
   a.dQ = dQ; a.dK = dK; a.dV = dV;
   a.dW = dW;
   a.ws = (char*)workspace;
-  return hip_status(simt_backward(s, a, (hipStream_t)stream));
+  return hip_status(backward(s, a, (hipStream_t)stream));
 }
 
 int sla_aggregate_ws_bytes(const sla_params* p, int method, uint64_t* bytes) {

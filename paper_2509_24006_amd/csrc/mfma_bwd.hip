@@ -373,12 +373,6 @@ __global__ __launch_bounds__(256, 2) void bwd_dkdv_mfma_kernel(
   store_rows_bf16<HT>(stage, dkT, dK + o0, lay.ts, cols - 32 * kh, l);
 }
 
-#define SLA_TRY(x)                   \
-  do {                               \
-    hipError_t e_ = (x);             \
-    if (e_ != hipSuccess) return e_; \
-  } while (0)
-
 template <int D>
 hipError_t sparse_impl(const Shape& s, const BwdArgs& a, const float* Ds, const void* dHZcol, hipStream_t st) {
   const float* dZcol = dHZcol ? reinterpret_cast<const float*>((const char*)dHZcol + state_z_offset(s)) : nullptr;

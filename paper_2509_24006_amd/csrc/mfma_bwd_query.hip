@@ -616,12 +616,6 @@ __global__ __launch_bounds__(256, 2) void dw_mfma_kernel(const bf16* __restrict_
   }
 }
 
-#define SLA_TRY(x)                   \
-  do {                               \
-    hipError_t e_ = (x);             \
-    if (e_ != hipSuccess) return e_; \
-  } while (0)
-
 // dW partial sums of the whole call (launched between the query side and the column sums)
 template <int D>
 hipError_t dw_impl(const Shape& s, const BwdArgs& a, float* dWpart, int nparts, hipStream_t st) {

@@ -525,15 +525,8 @@ __global__ void fill_zero_f32_kernel(float* __restrict__ p, size_t n) {
     p[i] = 0.0f;
 }
 
-#define SLA_TRY(x)                   \
-  do {                               \
-    hipError_t e_ = (x);             \
-    if (e_ != hipSuccess) return e_; \
-  } while (0)
-
 template <int D>
 hipError_t forward_impl(const Shape& s, const FwdArgs& a, bf16* hz16, bf16* WTp, hipStream_t st) {
-  const int row_len = s.state_row();
   float* Zs = reinterpret_cast<float*>(reinterpret_cast<char*>(a.HZ) + state_z_offset(s));
   if (s.n_0 > 0) {
     {
@@ -543,8 +536,7 @@ hipError_t forward_impl(const Shape& s, const FwdArgs& a, bf16* hz16, bf16* WTp,
     }
     SLA_TRY(mfma_aggregate(hz16, a.ind, s, a.HZ, Zs, st));
   } else if (a.Os) {   // saved states must read as zero
-    KernelTimer kt("fill_zero", st);
-    fill_zero_f32_kernel<<<1024, 256, 0, st>>>(a.HZ, (size_t)s.BH * s.T * row_len);
+    SLA_TRY(launch_fill_zero(a.HZ, (size_t)s.BH * s.T * s.state_row(), st));
   }
   constexpr int lds = FwdLds<D>::BYTES;
   auto launch = [&](auto kern, int qt) -> hipError_t {
@@ -563,6 +555,12 @@ hipError_t forward_impl(const Shape& s, const FwdArgs& a, bf16* hz16, bf16* WTp,
 }
 
 }  // namespace
+
+hipError_t launch_fill_zero(float* p, size_t n, hipStream_t st) {
+  KernelTimer kt("fill_zero", st);
+  fill_zero_f32_kernel<<<1024, 256, 0, st>>>(p, n);
+  return hipGetLastError();
+}
 
 size_t mfma_forward_ws_bytes(const Shape& s) {
   return align_up((size_t)s.BH * s.T * s.state_row() * 2) + align_up((size_t)s.d * s.d * 2);

@@ -6,6 +6,12 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#define SLA_TRY(x)                      \
+  do {                                  \
+    hipError_t e_ = (x);                \
+    if (e_ != hipSuccess) return e_;    \
+  } while (0)
+
 namespace sla {
 
 constexpr int kBlk = 64;  // tile of every kernel: b_kv, and b_q or the unit b_q is a multiple of (Section 6.1)
@@ -52,7 +58,10 @@ hipError_t launch_mask_small(const float* qbar, const float* kbar, const float* 
                              int8_t* Mc, int32_t* row_idx, unsigned long long* ind, unsigned long long* indT,
                              int32_t* col_ptr, int32_t* col_order, int32_t* col_rows, hipStream_t st);
 
-// ---- float-arithmetic path (simt_kernels.hip): every contraction in fp32 FMA
+// n floats from p on become 0 (mfma_fwd.hip)
+hipError_t launch_fill_zero(float* p, size_t n, hipStream_t st);
+
+// ---- float path (mfma_f32.hip)
 struct FwdArgs {
   const void *Q, *K, *V, *W;
   const int8_t* Mc;
@@ -64,7 +73,9 @@ struct FwdArgs {
   float* HZ;       // [BH,T] state rows (saved or workspace)
   float* hz;       // [BH,T] state rows of the key blocks (workspace)
 };
-hipError_t simt_forward(const Shape& s, const FwdArgs& a, hipStream_t st);
+hipError_t f32_forward(const Shape& s, const FwdArgs& a, hipStream_t st);
+// out[i] = sum over k with bit k of ind[i] set of the float state rows in[k]
+hipError_t f32_aggregate(const float* in, const unsigned long long* ind, const Shape& s, float* out, hipStream_t st);
 
 struct BwdArgs {
   const void *Q, *K, *V, *W, *dO;
@@ -77,13 +88,17 @@ struct BwdArgs {
   float* dW;
   char* ws;  // workspace, ws_backward_bytes
 };
-size_t simt_backward_ws_bytes(const Shape& s);
+size_t backward_ws_bytes(const Shape& s);   // (backward.hip)
+hipError_t launch_dw_reduce(const float* part, int nparts, int dd, float* dW, hipStream_t st);
 // critical-block gradients on the matrix cores (mfma_bwd.hip).  dQlin: linear-branch part of dQ.
 // dHZcol: dH and dZ summed over the marginal blocks of each key block (bf16 matrices, then float
 // vectors at state_z_offset); the dK/dV kernel turns them into the linear-branch parts of dK and
 // dV itself.  Both may be null (no marginal block).
 hipError_t mfma_backward_sparse(const Shape& s, const BwdArgs& a, const float* Ds, const void* dHZcol, hipStream_t st);
-hipError_t simt_backward(const Shape& s, const BwdArgs& a, hipStream_t st);
+// the float path's backward pass; the workspace pieces are carved by backward()
+hipError_t f32_backward(const Shape& s, const BwdArgs& a, float* Ds, float* dHZ, float* dHZcol, float* dWpart,
+                        int nparts, hipStream_t st);
+hipError_t backward(const Shape& s, const BwdArgs& a, hipStream_t st);
 
 // ---- bf16 matrix-core path (mfma_fwd.hip)
 size_t mfma_forward_ws_bytes(const Shape& s);

@@ -1,0 +1,38 @@
+"""GPU parity of the float path at the edges of its tiles, against the CPU oracle."""
+import numpy as np
+import pytest
+
+from tests.gpu_util import run_gpu
+from tests.test_gpu_parity import _full_case
+
+pytestmark = pytest.mark.gpu
+
+
+def _inputs(N, d, H=2):
+    rng = np.random.default_rng(N + d)
+    x = {k: rng.standard_normal((1, H, N, d)).astype(np.float32) for k in ("Q", "K", "V", "dO")}
+    x["Proj"] = (rng.standard_normal((d, d)) * 0.05).astype(np.float32)
+    return x
+
+
+# one key and one key more than a group of 16, 32 and 64; 34 blocks (aggregation with 64 rows per
+# wave), 129 blocks (a second tile of 128 rows with one row, a third indicator word with one bit)
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("N,d,phi", [(1, 128, 0), (17, 128, 1), (33, 64, 1), (65, 128, 0), (33 * 64 + 7, 128, 0),
+                                     (128 * 64 + 1, 64, 1)])
+def test_float_tile_edges(oracle, N, d, phi):
+    _full_case(oracle, _inputs(N, d), "fp32", 0.1, 0.2, phi=phi, floor_rms=0.05 if N < 200 else 0.0)
+
+
+@pytest.mark.parametrize("T", [12, 40, 130])
+def test_a_state_that_is_not_finite_reaches_only_the_rows_that_add_it(oracle, T):
+    x = _inputs(64 * T, 64, H=1)
+    x["V"][0, 0, 64 * 3 + 5, 7] = np.inf
+    x["V"][0, 0, 64 * (T - 1), 9] = np.nan
+    Mc = oracle.build_mask(x["Q"], x["K"], 0.1, 0.4)
+    f = oracle.forward(x["Q"], x["K"], x["V"], x["Proj"], Mc)
+    r = run_gpu(x, "fp32", 0.1, 0.4, backward=False)
+    fin = np.isfinite(f["Hi"])
+    assert not fin.all() and fin.any()
+    assert np.array_equal(np.isfinite(r["Hi"]), fin)
+    assert np.abs(r["Hi"][fin] - f["Hi"][fin]).max() <= 1e-5 * np.abs(f["Hi"][fin]).max()
