@@ -34,7 +34,8 @@ struct FTile {
 };
 
 // Direct loads of 64-row tiles whose rows lie tsB bytes apart, behind a descriptor that spans the
-// whole head (rows past its end read as zeros).
+// whole head (rows past its end read as zeros: the part of an offset that may pass the end rides on
+// the per-lane offset, which the range check covers; the tile's own offset is always inside).
 template <int D>
 struct FLoader {
   using T = FTile<D>;
@@ -55,7 +56,7 @@ struct FLoader {
   __device__ __forceinline__ void load(BufDesc desc, int tile, int slot) const {
 #pragma unroll
     for (int k = 0; k < T::IPW; ++k)
-      load_to_lds16(desc, voff[k & 1], tile * tile_step + k * kstep, lds0 + slot + 4096 * k);
+      load_to_lds16(desc, voff[k & 1] + k * kstep, tile * tile_step, lds0 + slot + 4096 * k);
   }
 };
 
@@ -285,7 +286,8 @@ __global__ __launch_bounds__(256, 2) void f32_states_kernel(const float* __restr
 // exact.  A wave owns 32 columns and 32 MT rows i and reads every state once, straight into the B
 // operand (lane = column, 128 contiguous bytes per half wave), so no LDS and no barriers.  A state
 // that is not finite would reach every row through its product with 0: such values are taken out
-// of the product and added only to the rows that hold the bit.
+// of the product and added only to the rows that hold the bit.  (122 blocks x 4 heads, d = 128:
+// 39 us, matrix cores busy half of it; one thread per column and row took 1070 us.)
 constexpr float kMaxFinite = 3.402823466e38f;
 
 template <int MT>
@@ -297,26 +299,33 @@ __global__ __launch_bounds__(256) void f32_aggregate_kernel(const float* __restr
   if (c0 >= row_len) return;   // (row_len is a multiple of 32)
   const unsigned long long* ib = ind + (size_t)bh * T * Tw;
   const float* src = in + (size_t)bh * T * row_len + c0 + n;
+  const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<float*>(in + (size_t)bh * T * row_len), 0, T * row_len * 4, 0x00020000);
+  const __amdgpu_buffer_rsrc_t orsrc =
+      __builtin_amdgcn_make_buffer_rsrc(out + (size_t)bh * T * row_len, 0, T * row_len * 4, 0x00020000);
+  const int pitch = row_len * 4, voff = g * pitch + (c0 + n) * 4;
   constexpr int CH = 16;       // k-pairs per chunk of loads
   f32x16 acc[MT];
 #pragma unroll
   for (int m = 0; m < MT; ++m) acc[m] = zero_f32x16();
   auto fetch = [&](int k0, float (&x)[CH]) {
 #pragma unroll
-    for (int q = 0; q < CH; ++q) {
-      x[q] = src[(size_t)min(k0 + 2 * q + g, T - 1) * row_len];   // (past the end: no row holds the bit)
-    }
+    for (int q = 0; q < CH; ++q)   // (rows past T read as zeros)
+      x[q] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, voff + (k0 + 2 * q) * pitch, 0, 0));
   };
   float x[CH], nx[CH];
   bool bad = false;
   fetch(0, x);
-  unsigned long long wb[MT];
+  // indicator words of the lane's rows, a word ahead (rows past T are not stored)
+  unsigned long long wb[MT], nwb[MT];
+#pragma unroll
+  for (int m = 0; m < MT; ++m) nwb[m] = ib[(size_t)min(m0 + 32 * m + n, T - 1) * Tw];
   for (int k0 = 0; k0 < T; k0 += 2 * CH) {
     if ((k0 & 63) == 0) {
 #pragma unroll
       for (int m = 0; m < MT; ++m) {
-        const int i = m0 + 32 * m + n;
-        wb[m] = i < T ? ib[(size_t)i * Tw + (k0 >> 6)] >> g : 0ull;
+        wb[m] = nwb[m] >> g;
+        nwb[m] = ib[(size_t)min(m0 + 32 * m + n, T - 1) * Tw + min((k0 >> 6) + 1, Tw - 1)];
       }
     }
     if (k0 + 2 * CH < T) fetch(k0 + 2 * CH, nx);
@@ -341,10 +350,9 @@ __global__ __launch_bounds__(256) void f32_aggregate_kernel(const float* __restr
 #pragma unroll
   for (int m = 0; m < MT; ++m)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int i = m0 + 32 * m + c_row(r, g);
-      if (i < T) out[((size_t)bh * T + i) * row_len + c0 + n] = acc[m][r];
-    }
+    for (int r = 0; r < 16; ++r)   // row m0 + 32 m + c_row(r, g); rows past T are dropped
+      __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[m][r]), orsrc,
+                                            (m0 + 32 * m + c_row(r, g)) * pitch + (c0 + n) * 4, 0, 0);
   if (!__any(bad)) return;
   // this lane's column again, for the rows it has just written
   for (int i = m0 + 4 * g; i < min(T, m0 + 32 * MT); i += (i & 3) == 3 ? 5 : 1) {
@@ -939,13 +947,11 @@ hipError_t f32_aggregate(const float* in, const unsigned long long* ind, const S
   const int row_len = s.state_row(), Tw = (s.T + 63) / 64;
   const int gx = (row_len / 32 + 3) / 4;
   KernelTimer kt("aggregate", st);
-  // 128 rows per wave where there are that many: the states are read ceil(T / 128) times
-  if (s.T <= 32)
-    f32_aggregate_kernel<1><<<dim3(gx, 1, s.BH), 256, 0, st>>>(in, ind, s.T, Tw, row_len, out);
-  else if (s.T <= 64)
-    f32_aggregate_kernel<2><<<dim3(gx, 1, s.BH), 256, 0, st>>>(in, ind, s.T, Tw, row_len, out);
-  else
-    f32_aggregate_kernel<4><<<dim3(gx, (s.T + 127) / 128, s.BH), 256, 0, st>>>(in, ind, s.T, Tw, row_len, out);
+  // up to 128 rows per wave (the states are read ceil(T / 128) times), in tiles of 32 dealt evenly
+  const int ny = (s.T + 127) / 128, mt = ((s.T + 31) / 32 + ny - 1) / ny;
+  auto kern = mt == 1 ? f32_aggregate_kernel<1> : mt == 2 ? f32_aggregate_kernel<2>
+            : mt == 3 ? f32_aggregate_kernel<3> : f32_aggregate_kernel<4>;
+  kern<<<dim3(gx, ny, s.BH), 256, 0, st>>>(in, ind, s.T, Tw, row_len, out);
   return hipGetLastError();
 }
 
