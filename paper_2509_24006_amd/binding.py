@@ -102,12 +102,17 @@ def sla_sizes(p: sla_params) -> sla_sizes_t:
     return z
 
 
-def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+# Small calls are bound by the host (2 heads x 1110 tokens, one training step: 150 us, of which the
+# kernels are 105): addresses go to ctypes as plain integers (the argument types make pointers of
+# them), and the stream of the current device is asked for by its handle -- building a
+# torch.cuda.Stream object for it took 5 us a call, a tenth of such a step over its three calls.
+
+def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
+    return None if t is None else t.data_ptr()
 
 
-def _stream() -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+def _stream() -> int:
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _buf(nbytes: int, device) -> torch.Tensor:
@@ -125,18 +130,18 @@ def _dense(t: torch.Tensor, p: sla_params, what: str) -> torch.Tensor:
         raise SLAError(f"{what}: expected a {_tdtype(p)} tensor, got {getattr(t, 'dtype', type(t))}")
     if p.layout == SLA_STRIDED:
         want, st = (p.B, p.H, p.N, p.d), (p.stride_b, p.stride_h, p.stride_n, 1)
-        if tuple(t.shape) != want or tuple(t.stride()) != st or not t.is_cuda:
+        if t.shape != want or t.stride() != st or not t.is_cuda:
             raise SLAError(f"{what}: expected a device tensor (view) of shape {want} with strides {st}")
         return t
     want = (p.B, p.N, p.H, p.d) if p.layout == SLA_BNHD else (p.B, p.H, p.N, p.d)
-    if tuple(t.shape) != want or not t.is_contiguous() or not t.is_cuda:
+    if t.shape != want or not t.is_contiguous() or not t.is_cuda:
         raise SLAError(f"{what}: expected a contiguous device tensor of shape {want}")
     return t
 
 
 def _packed(t: torch.Tensor, shape, dtype: torch.dtype, what: str) -> torch.Tensor:
     """a contiguous device tensor of exactly this shape and type (W, M_c, dW, block scores)"""
-    if (not isinstance(t, torch.Tensor) or t.dtype != dtype or tuple(t.shape) != tuple(shape)
+    if (not isinstance(t, torch.Tensor) or t.dtype != dtype or t.shape != tuple(shape)
             or not t.is_contiguous() or not t.is_cuda):
         raise SLAError(f"{what}: expected a contiguous {dtype} device tensor of shape {tuple(shape)}, got "
                        f"{getattr(t, 'dtype', type(t))} {tuple(getattr(t, 'shape', ()))}")
@@ -291,6 +296,7 @@ def sla_profile_enable(on: bool) -> None:
 def sla_profile_mfma_peak(iters: int = 4096) -> float:
     """Sustained TFLOP/s of a register-only bf16 MFMA loop on this device (waits for it)."""
     out = ctypes.c_double()
+    torch.cuda.init()   # (no tensor argument that would have done it)
     _check(lib().sla_profile_mfma_peak(iters, ctypes.byref(out), _stream()), "sla_profile_mfma_peak")
     return out.value
 
