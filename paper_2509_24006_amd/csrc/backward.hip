@@ -5,28 +5,46 @@
 namespace sla {
 namespace {
 
-// dW = sum of the partial d x d sums.  A workgroup owns 64 consecutive elements; its four waves
-// take every fourth partial each (one element per lane, 256 contiguous bytes per load) and meet
-// in LDS.
-__global__ __launch_bounds__(256) void dw_reduce_kernel(const float* __restrict__ part, int nparts, int dd,
+// dW = sum of the partial d x d sums.  Bound by the latency of its loads (64 partials of 16 KB and
+// up, 512 of them in a large call), so a workgroup owns only 32 consecutive elements (128 bytes) and
+// deals the partials to 64 groups of eight lanes: up to 512 partials, every load of a thread is in
+// flight at once.  The groups meet by shuffles and in LDS, in an order fixed by nparts alone.
+__global__ __launch_bounds__(512) void dw_reduce_kernel(const float* __restrict__ part, int nparts, int dd,
                                                         float* __restrict__ dW) {
-  __shared__ float red[4][64];
-  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-  const int idx = blockIdx.x * 64 + l;
-  float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f, s3 = 0.0f;
-  if (idx < dd) {
-    int p = w;
-    for (; p + 12 < nparts; p += 16) {
-      s0 += part[(size_t)p * dd + idx];
-      s1 += part[(size_t)(p + 4) * dd + idx];
-      s2 += part[(size_t)(p + 8) * dd + idx];
-      s3 += part[(size_t)(p + 12) * dd + idx];
+  __shared__ __attribute__((aligned(16))) float red[8][32];
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63, q = threadIdx.x & 7;
+  const float* src = part + blockIdx.x * 32 + 4 * q;   // (dd is a multiple of 32)
+  float4 s = {0.0f, 0.0f, 0.0f, 0.0f};
+  for (int p0 = threadIdx.x >> 3; p0 < nparts; p0 += 512) {
+    float4 x[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {   // (past the end: the last partial again, not added)
+      x[k] = *reinterpret_cast<const float4*>(src + (size_t)min(p0 + 64 * k, nparts - 1) * dd);
     }
-    for (; p < nparts; p += 4) s0 += part[(size_t)p * dd + idx];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      if (p0 + 64 * k >= nparts) break;
+      s.x += x[k].x;
+      s.y += x[k].y;
+      s.z += x[k].z;
+      s.w += x[k].w;
+    }
   }
-  red[w][l] = (s0 + s1) + (s2 + s3);
+#pragma unroll
+  for (int o = 8; o < 64; o <<= 1) {
+    s.x += __shfl_xor(s.x, o);
+    s.y += __shfl_xor(s.y, o);
+    s.z += __shfl_xor(s.z, o);
+    s.w += __shfl_xor(s.w, o);
+  }
+  if (l < 8) *reinterpret_cast<float4*>(&red[w][4 * q]) = s;
   __syncthreads();
-  if (w == 0 && idx < dd) dW[idx] = (red[0][l] + red[1][l]) + (red[2][l] + red[3][l]);
+  if (threadIdx.x < 32) {
+    float t = red[0][threadIdx.x];
+#pragma unroll
+    for (int k = 1; k < 8; ++k) t += red[k][threadIdx.x];
+    dW[blockIdx.x * 32 + threadIdx.x] = t;
+  }
 }
 
 struct BwdWs {
@@ -74,7 +92,7 @@ size_t backward_ws_bytes(const Shape& s) { return carve_bwd(s, nullptr).bytes; }
 
 hipError_t launch_dw_reduce(const float* part, int nparts, int dd, float* dW, hipStream_t st) {
   KernelTimer kt("dw_reduce", st);
-  dw_reduce_kernel<<<(dd + 63) / 64, 256, 0, st>>>(part, nparts, dd, dW);
+  dw_reduce_kernel<<<dd / 32, 512, 0, st>>>(part, nparts, dd, dW);
   return hipGetLastError();
 }
 
