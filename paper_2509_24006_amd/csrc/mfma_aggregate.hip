@@ -36,6 +36,17 @@ __device__ __forceinline__ unsigned bits2bf(unsigned x, int s) {
   return (((y << 15) | y) & 0x00010001u) * 0x3f80u;
 }
 
+// The main kernel's form, half the instructions: bits K and K + 16 of x -> the same dword.  It keeps
+// the rows of a stage in the order that makes neighbours of rows 16 apart (stage_row), so that the
+// two bits of a dword already lie 16 apart in the indicator word.
+template <int K>
+__device__ __forceinline__ unsigned bits16bf(unsigned x) {
+  static_assert(K <= 7, "the factor keeps every bit of 0x3f80");
+  return (x & (0x00010001u << K)) * (0x3f80u >> K);
+}
+// which of a k-step's 64 state rows is row r of the stage
+__device__ __forceinline__ int stage_row(int r) { return (r & 32) | ((r >> 1) & 15) | ((r & 1) << 4); }
+
 // Column tile ct < dd / 128: columns [128 ct, +128) of the matrix part, written in bf16; column
 // tile dd / 128: the vector part (the last d entries of a state row), written in float.
 // blockIdx.x = 8 (mtiles cg + mh) + x for column tile 8 cg + x and row tile mh: the round-robin
@@ -70,7 +81,7 @@ __global__ __launch_bounds__(256, 2) void aggregate_mfma_kernel(const bf16* __re
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
     const int row = 4 * (4 * k + w) + (l >> 4), pc = l & 15;
-    vo[k] = row * pitch + nbase * 2 + ((pc ^ swz<128>(row)) << 4);
+    vo[k] = stage_row(row) * pitch + nbase * 2 + ((pc ^ swz<128>(row)) << 4);
   }
   int iks = 0, istage = 0;   // the next tile to request and its stage
   auto issue_next = [&]() {
@@ -114,8 +125,9 @@ __global__ __launch_bounds__(256, 2) void aggregate_mfma_kernel(const bf16* __re
     for (int q = 0; q < 8; ++q) {
       const int ks = ks0 + q;
       if (ks >= ksteps) break;
-      // the lane's bits of this k-step, moved so that k = 16 u + 4 g sits at bit 16 u
-      const unsigned long long x0 = wb[0][q] >> (4 * g), x1 = wb[1][q] >> (4 * g);
+      // the lane's bits of this k-step, moved so that those of lane half g sit where those of half 0 do
+      const unsigned xs[2][2] = {{(unsigned)wb[0][q] >> (2 * g), (unsigned)(wb[0][q] >> 32) >> (2 * g)},
+                                 {(unsigned)wb[1][q] >> (2 * g), (unsigned)(wb[1][q] >> 32) >> (2 * g)}};
       // the tile has landed; the kStages - 2 tiles requested after it may still be in flight
       if (ks + kStages - 2 < ksteps) wait_vm<4 * (kStages - 2)>();
       else wait_vm0();
@@ -125,15 +137,14 @@ __global__ __launch_bounds__(256, 2) void aggregate_mfma_kernel(const bf16* __re
       stage = stage == kStages - 1 ? 0 : stage + 1;
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        // slots 0..3 <- k = 16 u + 4 g .. + 3, slots 4..7 <- k = 16 u + 8 + 4 g .. + 3: the order
-        // in which the transposing read hands over the state rows
+        // slots 0..3 <- stage rows 16 u + 4 g .. + 3, slots 4..7 <- 16 u + 8 + 4 g .. + 3 (the order in
+        // which the transposing read hands over the rows): bits 8 (u & 1) + 2 g + {0, 1, 4, 5}, and the
+        // bits 16 above them, of half u >> 1 of the word
         bf16x8 b[2];
 #pragma unroll
         for (int mt = 0; mt < 2; ++mt) {
-          const unsigned long long x = mt ? x1 : x0;
-          const unsigned half = u < 2 ? (unsigned)x : (unsigned)(x >> 32);
-          const int sh = 16 * (u & 1);
-          u32x4 packed = {bits2bf(half, sh), bits2bf(half, sh + 2), bits2bf(half, sh + 8), bits2bf(half, sh + 10)};
+          const unsigned x = xs[mt][u >> 1] >> (8 * (u & 1));
+          u32x4 packed = {bits16bf<0>(x), bits16bf<1>(x), bits16bf<4>(x), bits16bf<5>(x)};
           b[mt] = *reinterpret_cast<bf16x8*>(&packed);
         }
 #pragma unroll
