@@ -276,6 +276,31 @@ def test_classify_given_scores_with_ties(oracle):
     check_luts(ref, v["row_idx"], v["col_ptr"], v["col_rows"], v["ind"], v["ind_t"], v["col_order"])
 
 
+@pytest.mark.parametrize("T,bq", [(65, 64), (128, 64), (129, 64), (192, 128), (193, 192), (256, 64), (257, 64),
+                                  (384, 128), (385, 64), (513, 192), (641, 256), (832, 64), (833, 128), (1025, 256),
+                                  (1216, 128), (1217, 256), (1409, 256), (1728, 256), (1729, 256), (2049, 256),
+                                  (3072, 256)])
+def test_classification_and_tables_at_the_edges_of_the_row_lengths(oracle, T, bq):
+    # whole numbers, so the comparison is exact: one row of ties only, one of two values, one of
+    # small integers, the rest distinct (where the threshold search ends early)
+    from paper_2509_24006_amd import binding as sla
+    rng = np.random.default_rng(T)
+    p = sla.make_params(1, 2, T * 64, 64, 0.04, 0.1, torch.bfloat16, bq=bq)
+    z = sla.sla_sizes(p)
+    s = rng.standard_normal((1, 2, z.Tq, z.T)).astype(np.float32)
+    s[0, 0, 0] = 0.25
+    s[0, 0, 1] = np.where(np.arange(z.T) % 3 == 0, 1.0, -1.0)
+    s[0, 1, 0] = rng.integers(-4, 5, size=z.T)
+    nh, nl = oracle.counts(z.T, 0.04, 0.1)
+    ref = oracle.classify(s, nh, nl)
+    Mc, luts = sla.sla_classify_scores(p, torch.from_numpy(s).cuda())
+    torch.cuda.synchronize()
+    assert np.array_equal(Mc.cpu().numpy(), ref)
+    v = {k: t.cpu().numpy() for k, t in sla.lut_views(p, luts).items()}
+    check_luts(per_tile(ref, bq // 64, z.T), v["row_idx"], v["col_ptr"], v["col_rows"], v["ind"], v["ind_t"],
+               v["col_order"])
+
+
 @pytest.mark.parametrize("bq,N", [(128, 130 * 64), (192, 130 * 64 - 40), (256, 33 * 64)])
 def test_classify_given_scores_with_ties_and_larger_query_blocks(oracle, bq, N):
     # rectangular score matrices (one row per block of bq queries), heavy ties; N is chosen so that
