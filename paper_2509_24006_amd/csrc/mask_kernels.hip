@@ -294,60 +294,69 @@ __global__ __launch_bounds__(256) void classify_kernel(const float* __restrict__
 
 // ---------------------------------------------------------------- column tables (CSC)
 
-// tile[r][c] = label of query tile i0 + r and key block j0 + c (row (i0 + r) / rq of the head's
-// M_c) for a 64 x 64 tile, 2 outside the matrix.  When rows are 16-byte aligned (T % 16 == 0)
-// thread t brings piece t % 4 (16 bytes) of row t / 4 in one load.
-__device__ __forceinline__ uint4 mask_piece(const int8_t* __restrict__ src, int T, int rq, int i0, int j0, int tid) {
-  const int r = tid >> 2, p = tid & 3;
-  const int i = i0 + r, j = j0 + 16 * p;
-  uint4 v = {0x02020202u, 0x02020202u, 0x02020202u, 0x02020202u};
-  if (i < T && j < T) v = *reinterpret_cast<const uint4*>(src + (size_t)(i / rq) * T + j);   // (j + 15 < T: T % 16 == 0)
-  return v;
-}
-__device__ __forceinline__ void put_piece(int8_t (*tile)[68], uint4 v, int tid) {
-  uint32_t* dst = reinterpret_cast<uint32_t*>(&tile[tid >> 2][16 * (tid & 3)]);
-  dst[0] = v.x;
-  dst[1] = v.y;
-  dst[2] = v.z;
-  dst[3] = v.w;
-}
-__device__ __forceinline__ void load_mask_tile_bytes(int8_t (*tile)[68], const int8_t* __restrict__ src, int T, int rq,
-                                                     int i0, int j0, int l, int w) {
-  for (int r = w; r < 64; r += 4) {
-    const int i = i0 + r, j = j0 + l;
-    tile[r][l] = (i < T && j < T) ? src[(size_t)(i / rq) * T + j] : (int8_t)2;
+// Labels of query tiles i0 .. i0 + R - 1 (tile i has the labels of row i / rq of the head's M_c) in
+// column j = j0 + lane, as bit masks over the tiles: the wave walks the rows, one byte per lane and
+// row, all R rows in flight, and every lane collects the bits of its own column, so that nothing
+// crosses lanes and nothing goes through LDS.  With ROWS, lane r also receives the marginal bits of
+// row i0 + r.  Columns past T have no bits.
+template <int R>
+struct ColumnVotes {
+  unsigned crit[(R + 31) / 32], marg[(R + 31) / 32];
+  unsigned long long row;
+};
+template <int R, bool ROWS>
+__device__ __forceinline__ ColumnVotes<R> column_votes(const int8_t* __restrict__ src, int T, int rq, int i0, int j0,
+                                                       int lane) {
+  ColumnVotes<R> v = {};
+  const bool jok = j0 + lane < T;
+  const int8_t* col = src + min(j0 + lane, T - 1);
+  int q = i0 / rq, rem = i0 - q * rq;   // row of M_c of the next tile, its place in that row's group
+  const int qlast = (T - 1) / rq;
+  int8_t x[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    x[r] = col[(size_t)min(q, qlast) * T];   // (past the last tile: the last row again, no bits)
+    if (++rem == rq) {
+      rem = 0;
+      ++q;
+    }
   }
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const bool ok = jok && i0 + r < T;
+    const bool m = ok && x[r] == 0;
+    v.crit[r >> 5] |= (ok && x[r] == 1) ? 1u << (r & 31) : 0u;
+    v.marg[r >> 5] |= m ? 1u << (r & 31) : 0u;
+    if (ROWS) {
+      const unsigned long long b = __ballot(m);
+      if (lane == r) v.row = b;
+    }
+  }
+  return v;
 }
 
 // Marginal indicator as bit masks and the column counts, over query tiles i (of 64 tokens: label
 // m(i, j) = Mc[i / rq][j]).  Bit b of ind[i][q] is set iff m(i, 64 q + b) == 0 (and the column
 // exists), bit b of indT[j][q] iff m(64 q + b, j) == 0;
 // cnt[j] (cleared by the classification kernel) receives the number of critical blocks of column
-// j.  A workgroup takes a 64 x 64 tile of Mc through LDS; each wave votes 16 rows and 16 columns
-// of it into 64-bit words.
+// j.  A workgroup takes a 64 x 64 tile of Mc, sixteen rows per wave.  (40 heads x 1182 blocks: 102 ->
+// 47 us a launch, 12 x 146: 10.2 -> 4.7 us.)
 __global__ __launch_bounds__(256) void indicator_kernel(const int8_t* __restrict__ Mc, int Tq, int rq, int T, int Tw,
                                                         unsigned long long* __restrict__ ind,
                                                         unsigned long long* __restrict__ indT,
                                                         int32_t* __restrict__ cnt) {
-  __shared__ int8_t tile[64][68];
+  __shared__ __attribute__((aligned(8))) unsigned short marg[64][4], crit[64][4];   // [column][wave]
+  const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int bh = blockIdx.z, i0 = blockIdx.y * 64, j0 = blockIdx.x * 64;
-  const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int8_t* src = Mc + (size_t)bh * Tq * T;
-  if (T % 16 == 0) put_piece(tile, mask_piece(src, T, rq, i0, j0, threadIdx.x), threadIdx.x);
-  else load_mask_tile_bytes(tile, src, T, rq, i0, j0, l, w);
+  const ColumnVotes<16> v = column_votes<16, true>(Mc + (size_t)bh * Tq * T, T, rq, i0 + 16 * w, j0, l);
+  if (l < 16 && i0 + 16 * w + l < T) ind[((size_t)bh * T + i0 + 16 * w + l) * Tw + blockIdx.x] = v.row;
+  marg[l][w] = (unsigned short)v.marg[0];
+  crit[l][w] = (unsigned short)v.crit[0];
   __syncthreads();
-  for (int r = w; r < 64; r += 4) {
-    const unsigned long long rowbits = __ballot(tile[r][l] == 0);
-    const int8_t cv = tile[l][r];
-    const unsigned long long colbits = __ballot(cv == 0);
-    const int ncrit = __popcll(__ballot(cv == 1));
-    if (l == 0) {
-      if (i0 + r < T) ind[((size_t)bh * T + i0 + r) * Tw + blockIdx.x] = rowbits;
-      if (j0 + r < T) {
-        indT[((size_t)bh * T + j0 + r) * Tw + blockIdx.y] = colbits;
-        if (ncrit) atomicAdd(cnt + (size_t)bh * T + j0 + r, ncrit);
-      }
-    }
+  if (w == 0 && j0 + l < T) {
+    indT[((size_t)bh * T + j0 + l) * Tw + blockIdx.y] = *reinterpret_cast<const unsigned long long*>(marg[l]);
+    const int ncrit = __popcll(*reinterpret_cast<const unsigned long long*>(crit[l]));
+    if (ncrit) atomicAdd(cnt + (size_t)bh * T + j0 + l, ncrit);
   }
 }
 
@@ -355,33 +364,48 @@ __global__ __launch_bounds__(256) void indicator_kernel(const int8_t* __restrict
 // (col_order[rank] = j, rank = position of column j under count descending, index ascending: the
 // column-wise backward kernel takes the longest lists first) and col_rows (the critical rows of
 // every column, ascending).  A workgroup owns 64 columns of one head; every workgroup forms the
-// prefix sum up to its columns from the head's counts by itself.
+// prefix sum up to its columns from the head's counts by itself.  Bound by latency (a few hundred
+// workgroups, each a chain of short phases): the waves vote different row tiles with no barrier in
+// between, counts and column indices are compared as one number, four per LDS read, and every lane
+// writes its own column's list.  (40 heads x 1182 blocks: 152 -> 58 us a launch; 12 x 512: 22.6 -> 18 us;
+// 12 x 146, whose rows are not 16-byte aligned: 20 -> 9.6 us.)
+constexpr int kKeyBits = 12;   // column index in a sort key: kMaxT of the interface is below 2^12
+__host__ __device__ constexpr int col_tables_lds(int Tw) { return 64 * Tw * 4 + 64 * Tw * 8; }
+
 __global__ __launch_bounds__(256) void col_tables_kernel(const int8_t* __restrict__ Mc, int Tq, int rq, int T, int n_h,
                                                          const int32_t* __restrict__ cnt_g,
                                                          int32_t* __restrict__ ptr, int32_t* __restrict__ order,
                                                          int32_t* __restrict__ rows) {
-  extern __shared__ int cnt[];          // T counts of the head
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   __shared__ int part[4][64];
   __shared__ int wsum[4];
   __shared__ int cptr[64];
-  __shared__ int8_t tile[64][68];
+  const int Tw = (T + 63) / 64;
+  uint32_t* key = reinterpret_cast<uint32_t*>(smem);   // (count, column descending) of the head; 0 past T
+  unsigned long long* crit = reinterpret_cast<unsigned long long*>(smem + 64 * Tw * 4);   // [row tile][column]
   const int bh = blockIdx.y, j0 = blockIdx.x * 64;
-  const int tid = threadIdx.x, l = tid & 63, w = tid >> 6;
+  const int tid = threadIdx.x, l = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int32_t* cg = cnt_g + (size_t)bh * T;
   int before = 0;   // this thread's share of the counts of the columns before j0
-  for (int j = tid; j < T; j += 256) {
-    const int c = cg[j];
-    cnt[j] = c;
+  for (int j = tid; j < 64 * Tw; j += 256) {
+    const int c = j < T ? cg[j] : 0;
+    key[j] = j < T ? (uint32_t)c << kKeyBits | (uint32_t)((1 << kKeyBits) - 1 - j) : 0u;
     if (j < j0) before += c;
   }
+  if (n_h > 0)
+    for (int t = w; t < Tw; t += 4) {
+      const ColumnVotes<64> v = column_votes<64, false>(Mc + (size_t)bh * Tq * T, T, rq, 64 * t, j0, l);
+      crit[64 * t + l] = (unsigned long long)v.crit[1] << 32 | v.crit[0];
+    }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) before += __shfl_xor(before, o);
   if (l == 0) wsum[w] = before;
   __syncthreads();
   // pointers of this workgroup's columns: wave 0 scans its 64 counts
+  const uint32_t mine = key[j0 + l];
   if (w == 0) {
     const int j = j0 + l;
-    const int c = j < T ? cnt[j] : 0;
+    const int c = (int)(mine >> kKeyBits);
     int incl = c;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
@@ -393,57 +417,32 @@ __global__ __launch_bounds__(256) void col_tables_kernel(const int8_t* __restric
     if (j < T) ptr[(size_t)bh * (T + 1) + j] = p;
     if (j == T - 1) ptr[(size_t)bh * (T + 1) + T] = p + c;
   }
-  // rank of this workgroup's columns; four threads share the comparisons of a column
+  // rank of this workgroup's columns; the four waves share the comparisons of a column
   {
-    const int j = j0 + l;
     int rank = 0;
-    if (j < T) {
-      const int c = cnt[j];
-      const int chunk = (T + 3) / 4, lo = min(T, w * chunk), hi = min(T, lo + chunk);
-      for (int k = lo; k < hi; ++k) rank += (cnt[k] > c) || (cnt[k] == c && k < j);
+    const uint4* k4 = reinterpret_cast<const uint4*>(key) + 4 * Tw * w;
+#pragma unroll 4
+    for (int k = 0; k < 4 * Tw; ++k) {
+      const uint4 x = k4[k];
+      rank += (x.x > mine) + (x.y > mine) + (x.z > mine) + (x.w > mine);
     }
     part[w][l] = rank;
   }
   __syncthreads();
   if (w == 0 && j0 + l < T) order[(size_t)bh * T + part[0][l] + part[1][l] + part[2][l] + part[3][l]] = j0 + l;
   if (n_h == 0) return;
-  // rows of the critical blocks: tiles of 64 rows, wave w votes columns 16 w .. 16 w + 15
-  const int8_t* src = Mc + (size_t)bh * Tq * T;
+  // rows of the critical blocks: wave w writes those of the row tiles it voted, every lane its column's
   int32_t* out = rows + (size_t)bh * T * n_h;
-  int run[16];
+  int pos = cptr[l];   // where the rows of the next row tile go
+  for (int t = 0; t < Tw; ++t) {
+    const unsigned long long m = crit[64 * t + l];
+    if ((t & 3) == w) {
+      int p = pos;
 #pragma unroll
-  for (int c = 0; c < 16; ++c) run[c] = cptr[16 * w + c];
-  auto vote = [&](int i0) {
-#pragma unroll
-    for (int c = 0; c < 16; ++c) {
-      const bool crit = tile[l][16 * w + c] == 1;
-      const unsigned long long m = __ballot(crit);
-      if (crit) out[run[c] + __popcll(m & ((1ull << l) - 1ull))] = i0 + l;
-      run[c] += __popcll(m);
+      for (int h = 0; h < 2; ++h)
+        for (unsigned x = (unsigned)(m >> (32 * h)); x; x &= x - 1) out[p++] = 64 * t + 32 * h + __ffs(x) - 1;
     }
-  };
-  if (T % 16 == 0) {
-    // eight tiles' loads in flight at a time
-    for (int ib = 0; ib < T; ib += 512) {
-      uint4 pre[8];
-#pragma unroll
-      for (int k = 0; k < 8; ++k) pre[k] = mask_piece(src, T, rq, ib + 64 * k, j0, tid);
-#pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        if (ib + 64 * k >= T) break;
-        __syncthreads();   // the previous tile has been read
-        put_piece(tile, pre[k], tid);
-        __syncthreads();
-        vote(ib + 64 * k);
-      }
-    }
-  } else {
-    for (int i0 = 0; i0 < T; i0 += 64) {
-      __syncthreads();   // the previous tile has been read
-      load_mask_tile_bytes(tile, src, T, rq, i0, j0, l, w);
-      __syncthreads();
-      vote(i0);
-    }
+    pos += __popcll(m);
   }
 }
 
@@ -611,8 +610,8 @@ hipError_t launch_csc(const int8_t* Mc, const Shape& s, int32_t* col_cnt, int32_
   }
   {
     KernelTimer kt("col_tables", st);
-    col_tables_kernel<<<dim3(Tw, s.BH), 256, s.T * sizeof(int), st>>>(Mc, s.Tq, s.rq, s.T, s.n_h, col_cnt, col_ptr, col_order,
-                                                                      col_rows);
+    col_tables_kernel<<<dim3(Tw, s.BH), 256, col_tables_lds(Tw), st>>>(Mc, s.Tq, s.rq, s.T, s.n_h, col_cnt, col_ptr, col_order,
+                                                                       col_rows);
   }
   return hipGetLastError();
 }
