@@ -192,11 +192,6 @@ __global__ __launch_bounds__(256 * QT, QT == 1 ? 2 : 1) void fwd_mfma_kernel(
   const int q0 = i * kBlk, rows = max(0, min(kBlk, N - q0));
   const int qrow = qh * 32 + ln;                  // this lane's query inside the block
   const bool qok = qrow < rows;
-  const size_t qoff = lay.head(bh) + (size_t)(q0 + qrow) * lay.ts;
-  bf16x8 qf[KT];
-#pragma unroll
-  for (int t = 0; t < KT; ++t)
-    qf[t] = qok ? *reinterpret_cast<const bf16x8*>(Q + qoff + 16 * t + 8 * g) : zero_bf16x8();
   f32x16 oT[NT];
 #pragma unroll
   for (int et = 0; et < NT; ++et) oT[et] = zero_f32x16();
@@ -211,6 +206,15 @@ __global__ __launch_bounds__(256 * QT, QT == 1 ? 2 : 1) void fwd_mfma_kernel(
   constexpr int IPW = RunLoader<D, NW>::IPW;
   const BufDesc descK = head_rsrc<D>(K + lay.head(bh), N, 2 * lay.ts);
   const BufDesc descV = head_rsrc<D>(V + lay.head(bh), N, 2 * lay.ts);
+  // Q_i comes in as a tile too (whole rows per load, zeros past the end of the sequence) and is
+  // picked up in operand layout: a row per lane straight from memory touches every cache line four
+  // times, and the compiler would wait for those loads by draining the tiles requested behind them
+  constexpr int QSLOT = 3 * Lds::TILE;   // V_1's slot, which is filled once Q_i has been picked up
+  {
+    TileLoader<D> tq;
+    tq.init(lds_base(smem) + grp * Lds::BYTES, w, l, 2 * lay.ts);
+    tq.load(head_rsrc<D>(Q + lay.head(bh), N, 2 * lay.ts), ic, QSLOT);
+  }
   // a d x d bf16 matrix (aggregated state H_i, prepared projection matrix) goes global -> LDS like
   // the tiles: rows 0..63 into the slot at off0, the rest into the one at off1
   auto issue_matrix = [&](const bf16* M, int off0, int off1) {
@@ -218,21 +222,27 @@ __global__ __launch_bounds__(256 * QT, QT == 1 ? 2 : 1) void fwd_mfma_kernel(
     tm.load(dm, 0, off0);
     if (D > kBlk) tm.load(dm, 1, off1);
   };
-  // H_i together with Z_i (one dword per lane of the first D / 64 waves, global -> LDS like the tiles:
+  // Slots at the end of the loop, with p the parity of the last step: H_i is requested as if it were
+  // the key block behind the last one, its rows 0..63 as K_{n_h} and the rest as V_{n_h}, so that
+  // it has landed when the loop ends; the exchange areas go to the other two slots (K_last, V_last)
+  // once the loop is over.  (With this and Q_i as a tile: 12 heads x 512 query blocks of 26 key blocks,
+  // d = 128: 547 -> 535 us a launch; 40 x 1182 of 59: 7514 -> 7400 us; 12 x 146 of 7: 81 -> 78 us.)
+  const int pl = n_h > 0 ? (n_h - 1) & 1 : 0;
+  const int h0 = (2 - 2 * pl) * Lds::TILE, h1 = (3 - 2 * pl) * Lds::TILE;
+  const int x0 = 2 * pl * Lds::TILE, x1 = (2 * pl + 1) * Lds::TILE;
+  const int nk = n_0 > 0 ? n_h + 1 : n_h;   // tiles requested in the K stream
+  const int nh1 = n_0 > 0 ? n_h + 1 : 0;    // n_h + 1 where H_i is among them
+  // Z_i comes with the second half (one dword per lane of the first D / 64 waves, global -> LDS like the tiles:
   // a load the compiler sees would be waited for behind the projection matrix's loads, which
   // are requested before it is used)
-  auto issue_state = [&](int off0, int off1) {
-    issue_matrix(H16 + ((size_t)bh * Tn + ic) * (D * D), off0, off1);
+  const BufDesc descH = tile_rsrc(H16 + ((size_t)bh * Tn + ic) * (D * D), D * D * 2);
+  auto issue_state0 = [&]() __attribute__((always_inline)) { tm.load(descH, 0, h0); };
+  auto issue_state1 = [&]() __attribute__((always_inline)) {
+    if (D > kBlk) tm.load(descH, 1, h1);
     if (w < D / 64)
       load_to_lds4(tile_rsrc(Zs + ((size_t)bh * Tn + ic) * D, D * 4), (w * 64 + l) * 4,
                    lds_base(smem) + grp * Lds::BYTES + Lds::ZOFF + w * 256);
   };
-  // Slots at the end of the loop, with p the parity of the last step: H_i goes to the slots of
-  // K_{last+1} (never filled) and V_last, both free from the last step's second barrier on, the
-  // exchange areas to the other two once the loop is over.
-  const int pl = n_h > 0 ? (n_h - 1) & 1 : 0;
-  const int h0 = (2 - 2 * pl) * Lds::TILE, h1 = (2 * pl + 1) * Lds::TILE;
-  const int x0 = 2 * pl * Lds::TILE, x1 = (3 - 2 * pl) * Lds::TILE;
   float* ml = reinterpret_cast<float*>(gsm + Lds::STAT);   // [par][qh][32][2]
   // byte offsets (inside a head) of the key blocks of steps s .. s + 3; the table entry behind the
   // fourth is fetched a step before the load that needs it
@@ -244,20 +254,14 @@ __global__ __launch_bounds__(256 * QT, QT == 1 ? 2 : 1) void fwd_mfma_kernel(
     kb3 = lut[min(3, n_h - 1)] * tl.tile_step;
     tl.template load<0>(descK, kb0);
     tl.template load<Lds::TILE>(descV, kb0);
-    if (n_h > 1) {
-      tl.template load<2 * Lds::TILE>(descK, kb1);
-      tl.template load<3 * Lds::TILE>(descV, kb1);
-    }
-  } else if (n_0 > 0) {
-    issue_state(h0, h1);
+    if (n_h > 1) tl.template load<2 * Lds::TILE>(descK, kb1);
+    else if (n_0 > 0) issue_state0();
   }
   unsigned lo = 16;                                  // byte offset of the next table entry to fetch
   const unsigned lomax = 4u * (unsigned)max(n_h - 1, 0);
   // a sequence whose last key block is partial: its offset and its number of keys
   const int off_tail = (N % kBlk) ? (Tn - 1) * tl.tile_step : -1;
   const int tail_cols = N - (N / kBlk) * kBlk;
-#pragma unroll
-  for (int t = 0; t < KT; ++t) pin_loaded(qf[t]);
   // per-lane LDS offsets of this wave's operand reads inside a tile (rows 32 par .. of both tiles)
   int kaddr[KT], vaddr[2][NT];
   {
@@ -281,18 +285,35 @@ __global__ __launch_bounds__(256 * QT, QT == 1 ? 2 : 1) void fwd_mfma_kernel(
   // one accumulator, during which the wave could issue nothing else) run under the exponentials
   // of the current step: S_0 here, S_{s+1} inside step s.
   f32x16 sT = zero_f32x16();
-  if (n_h > 0) {
-    if (n_h > 1) wait_vm<3 * IPW>();   // K_0 has landed; V_0, K_1 and V_1 may stay in flight
-    else wait_vm<IPW>();
-    __syncthreads();
-    bf16x8 k0[KT];
+  bf16x8 qf[KT], k0[KT];
+  if (nk > 1) wait_vm<2 * IPW>();      // Q_i and K_0 have landed; V_0 and K_1 may stay in flight
+  else wait_vm0();
+  __syncthreads();
+  {
+    TileAddr<D> qa;
+    qa.init(32 * qh, l);
 #pragma unroll
-    for (int t = 0; t < KT; ++t) k0[t] = lds_row(smem, kaddr[t]);
-    __syncthreads();                   // every wave holds its rows of K_0: the slot takes K_2
+    for (int t = 0; t < KT; ++t) qf[t] = lds_row(gsm, qa.row(t) + QSLOT);
+#pragma unroll
+    for (int t = 0; t < KT; ++t) k0[t] = lds_row(smem, kaddr[t]);   // (with n_h = 0: not used)
+  }
+#pragma unroll
+  for (int t = 0; t < KT; ++t) pin_loaded(qf[t]);
+#pragma unroll
+  for (int t = 0; t < KT; ++t) pin_loaded(k0[t]);
+  __syncthreads();                     // every wave holds its rows of both: the slots take V_1 and K_2
+  if (n_h > 1) {
+    tl.template load<3 * Lds::TILE>(descV, kb1);
     if (n_h > 2) tl.template load<0>(descK, kb2);
+    else if (n_0 > 0) issue_state0();
+  } else if (n_0 > 0) {
+    if (n_h == 0) issue_state0();
+    issue_state1();
+  }
+  if (n_h > 0) {
 #pragma unroll
     for (int t = 0; t < KT; ++t) sT = mfma32(k0[t], qf[t], sT);
-    if (n_h > 2) wait_vm<2 * IPW>();   // V_0 and K_1 have landed
+    if (nk > 2) wait_vm<2 * IPW>();    // V_0 and K_1 have landed
     else wait_vm0();
     __syncthreads();
   }
@@ -341,8 +362,9 @@ __global__ __launch_bounds__(256 * QT, QT == 1 ? 2 : 1) void fwd_mfma_kernel(
     const float moff = m == -INFINITY ? 0.0f : -m * c2;   // a half with no valid key yet
     __syncthreads();   // every wave holds its operands of this step: both slots are refilled
     if (s + 3 < n_h) tl.template load<KN>(descK, kb3);
+    else if (s + 4 == nh1) issue_state0();
     if (s + 2 < n_h) tl.template load<VS>(descV, kb2);
-    else if (s + 1 == n_h && n_0 > 0) issue_state(h0, h1);   // arrives under the last step
+    else if (s + 3 == nh1) issue_state1();
     const int jn = *reinterpret_cast<const int32_t*>(reinterpret_cast<const char*>(lut) + min(lo, lomax));
     lo += 4;
     sched_fence();
@@ -372,11 +394,14 @@ __global__ __launch_bounds__(256 * QT, QT == 1 ? 2 : 1) void fwd_mfma_kernel(
     kb2 = kb3;
     kb3 = jn * tl.tile_step;
     sched_fence();     // (the matrix products above are issued before this wait)
-    // K_{s+2} and V_{s+1}, requested a step ago, have landed; the two tiles requested in this
-    // step may stay in flight (near the end fewer were requested: everything is waited for)
-    if (s + 4 < n_h) wait_vm<2 * IPW>();
-    else wait_vm0();
-    __syncthreads();
+    // K_{s+2} and V_{s+1}, requested a step ago, have landed; the two tiles requested in this step
+    // (one of them near the end) may stay in flight.  Behind the last step there is nothing to wait for.
+    if (s + 1 < n_h) {
+      if (s + 3 < nk) wait_vm<2 * IPW>();
+      else if (s + 2 < (D > kBlk ? nk : n_h)) wait_vm<IPW>();
+      else wait_vm0();
+      __syncthreads();
+    }
   };
   {
     const std::integral_constant<int, 0> p0;
