@@ -452,7 +452,13 @@ __global__ __launch_bounds__(256) void col_tables_kernel(const int8_t* __restric
 // that size each of the four kernels above is a few microseconds of work behind as many
 // microseconds of launch.  Same arithmetic, same tables.  With `given` the scores are read
 // instead of computed (classification of given scores).
-__global__ __launch_bounds__(256) void mask_small_kernel(
+// Bound by latency: one workgroup per head, a chain of short phases, so the workgroup is as wide as
+// it can be (a row of M_c per wave at 16 blocks) and forms only the scores of a T x T corner: TT x TT
+// per thread, 32 TT >= T.  (256 heads of 16 blocks, d = 64:
+// 14.5 -> 8.5 us a launch with the gap before it; 2 of 18, d = 128: 19 -> 10.3 us.)
+constexpr int kSmallWaves = 16;
+template <int TT>
+__global__ __launch_bounds__(64 * kSmallWaves) void mask_small_kernel(
     const float* __restrict__ qbar, const float* __restrict__ kbar, const float* __restrict__ given, int Tq, int rq,
     int T, int d, float scale, int n_h, int n_l, float* __restrict__ s_out, int8_t* __restrict__ Mc,
     int32_t* __restrict__ row_idx, unsigned long long* __restrict__ ind, unsigned long long* __restrict__ indT,
@@ -466,16 +472,50 @@ __global__ __launch_bounds__(256) void mask_small_kernel(
   const unsigned long long below = (1ull << lane) - 1ull;
   if (given) {
     const float* g = given + (size_t)bh * Tq * T;
-    for (int e = tid; e < Tq * T; e += 256) sc[e / T][e % T] = g[e];
+    for (int e = tid; e < Tq * T; e += 64 * kSmallWaves) sc[e / T][e % T] = g[e];
   } else {
-    float acc[4][4];
-    score_tile(qbar + (size_t)bh * Tq * d, kbar + (size_t)bh * T * d, Tq, T, d, 0, 0, qs, ks, acc);
-    const int ty = tid >> 4, tx = tid & 15;
+    // thread (ty, tx): rows ty + 32 a, columns tx + 32 b; one fused multiply-add chain per score in
+    // ascending feature order, as in score_tile
+    const float* qb = qbar + (size_t)bh * Tq * d;
+    const float* kb = kbar + (size_t)bh * T * d;
+    const int ty = tid >> 5, tx = tid & 31, lr = tid >> 4, lc = 4 * (tid & 15);
+    float acc[TT][TT];
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+    for (int a = 0; a < TT; ++a)
 #pragma unroll
-      for (int b = 0; b < 4; ++b) {
-        const int i = ty + 16 * a, j = tx + 16 * b;
+      for (int b = 0; b < TT; ++b) acc[a][b] = 0.0f;
+    for (int k0 = 0; k0 < d; k0 += 64) {
+      const float4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+      *reinterpret_cast<float4*>(&qs[lr][lc]) = lr < Tq ? *reinterpret_cast<const float4*>(qb + (size_t)lr * d + k0 + lc) : zero;
+      *reinterpret_cast<float4*>(&ks[lr][lc]) = lr < T ? *reinterpret_cast<const float4*>(kb + (size_t)lr * d + k0 + lc) : zero;
+      __syncthreads();
+#pragma unroll 4
+      for (int k = 0; k < 64; k += 4) {
+        float4 av[TT], bv[TT];
+#pragma unroll
+        for (int a = 0; a < TT; ++a) {
+          av[a] = *reinterpret_cast<const float4*>(&qs[ty + 32 * a][k]);
+          bv[a] = *reinterpret_cast<const float4*>(&ks[tx + 32 * a][k]);
+        }
+#pragma unroll
+        for (int a = 0; a < TT; ++a)
+#pragma unroll
+          for (int b = 0; b < TT; ++b) {
+            float x = acc[a][b];
+            x = __fmaf_rn(av[a].x, bv[b].x, x);
+            x = __fmaf_rn(av[a].y, bv[b].y, x);
+            x = __fmaf_rn(av[a].z, bv[b].z, x);
+            x = __fmaf_rn(av[a].w, bv[b].w, x);
+            acc[a][b] = x;
+          }
+      }
+      __syncthreads();
+    }
+#pragma unroll
+    for (int a = 0; a < TT; ++a)
+#pragma unroll
+      for (int b = 0; b < TT; ++b) {
+        const int i = ty + 32 * a, j = tx + 32 * b;
         if (i < Tq && j < T) {
           const float v = __fmul_rn(acc[a][b], scale);
           sc[i][j] = v;
@@ -485,7 +525,7 @@ __global__ __launch_bounds__(256) void mask_small_kernel(
   }
   __syncthreads();
   // classification: a wave per row of M_c, the row in one register per lane
-  for (int i = wave; i < Tq; i += 4) {
+  for (int i = wave; i < Tq; i += kSmallWaves) {
     uint32_t key[1];
     int8_t lb[1];
     key[0] = lane < T ? order_key(sc[i][lane]) : 0u;
@@ -504,7 +544,7 @@ __global__ __launch_bounds__(256) void mask_small_kernel(
   }
   __syncthreads();
   // bit masks and column counts over query tiles: tile r has the labels of row r / rq
-  for (int r = wave; r < 64; r += 4) {
+  for (int r = wave; r < 64; r += kSmallWaves) {
     const int8_t rv = (r < T) ? lab[r / rq][lane] : (int8_t)2;                 // row r, column = lane
     const int8_t cv = (r < T && lane < T) ? lab[lane / rq][r] : (int8_t)2;     // column r, query tile = lane
     const unsigned long long rowbits = __ballot(rv == 0), colbits = __ballot(cv == 0);
@@ -537,7 +577,7 @@ __global__ __launch_bounds__(256) void mask_small_kernel(
   }
   __syncthreads();
   if (n_h == 0) return;
-  for (int j = wave; j < T; j += 4) {   // the critical query tiles of column j, ascending
+  for (int j = wave; j < T; j += kSmallWaves) {   // the critical query tiles of column j, ascending
     const bool crit = lane < T && lab[lane / rq][j] == 1;
     const unsigned long long m = __ballot(crit);
     if (crit) col_rows[(size_t)bh * T * n_h + cptr[j] + __popcll(m & below)] = lane;
@@ -620,8 +660,9 @@ hipError_t launch_mask_small(const float* qbar, const float* kbar, const float* 
                              int8_t* Mc, int32_t* row_idx, unsigned long long* ind, unsigned long long* indT,
                              int32_t* col_ptr, int32_t* col_order, int32_t* col_rows, hipStream_t st) {
   KernelTimer kt("mask_small", st);
-  mask_small_kernel<<<s.BH, 256, 0, st>>>(qbar, kbar, given, s.Tq, s.rq, s.T, s.d, s.scale, s.n_h, s.n_l, scores, Mc,
-                                          row_idx, ind, indT, col_ptr, col_order, col_rows);
+  auto kern = s.T <= 32 ? mask_small_kernel<1> : mask_small_kernel<2>;
+  kern<<<s.BH, 64 * kSmallWaves, 0, st>>>(qbar, kbar, given, s.Tq, s.rq, s.T, s.d, s.scale, s.n_h, s.n_l, scores, Mc, row_idx,
+                                          ind, indT, col_ptr, col_order, col_rows);
   return hipGetLastError();
 }
 
