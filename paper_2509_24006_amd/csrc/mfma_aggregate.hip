@@ -188,9 +188,14 @@ __global__ __launch_bounds__(256, 2) void aggregate_mfma_kernel(const bf16* __re
 
 // Short sequences (T <= 64: one k-step, one indicator word per row): a workgroup's four waves
 // take four column tiles of the same 32 MT output rows, each wave with a stage of its own, so
-// that no wave waits for another; the rows of the stage past T are fetched as zeros.
+// that no wave waits for another; the rows of the stage past T are fetched as zeros.  Each wave
+// waits for its loads once and stores once, so what hides that is other workgroups: a stage has
+// room for 32 MT rows only, which lets four workgroups share a CU up to 32 blocks.  (256 heads of
+// 16 blocks, d = 64: 16.2 -> 15.5 us a launch with the gap before it.)
 template <int MT>
-__global__ __launch_bounds__(256, 2) void aggregate_short_kernel(const bf16* __restrict__ in,
+constexpr int kShortStage = 32 * MT * 256 > kOutStage ? 32 * MT * 256 : kOutStage;
+template <int MT>
+__global__ __launch_bounds__(256, MT == 1 ? 4 : 2) void aggregate_short_kernel(const bf16* __restrict__ in,
                                                                  const unsigned long long* __restrict__ ind,
                                                                  int T, int row_len, int dd,
                                                                  bf16* __restrict__ outH, float* __restrict__ outZ) {
@@ -205,8 +210,8 @@ __global__ __launch_bounds__(256, 2) void aggregate_short_kernel(const bf16* __r
   const BufDesc rsrc = tile_rsrc(inb, T * row_len * 2);
   const int pitch = row_len * 2;
   const int wu = wave_uniform(w);
-  unsigned char* stage = smem + wu * kStage;
-  const unsigned lds0 = lds_base(smem) + wu * kStage;
+  unsigned char* stage = smem + wu * kShortStage<MT>;
+  const unsigned lds0 = lds_base(smem) + wu * kShortStage<MT>;
   const int nu = (T + 15) / 16;   // 16-row groups that hold valid rows
   for (int k = 0; k < 4 * nu; ++k) {
     const int row = 4 * k + (l >> 4), pc = l & 15;
@@ -284,10 +289,11 @@ hipError_t mfma_aggregate(const void* in, const unsigned long long* ind, const S
   const int ntile = dd / 128 + 1;
   if (s.T <= 64) {
     auto kern = s.T <= 32 ? aggregate_short_kernel<1> : aggregate_short_kernel<2>;
-    e = ensure_dyn_lds(kern, kAggLds);
+    const int lds = 4 * (s.T <= 32 ? kShortStage<1> : kShortStage<2>);
+    e = ensure_dyn_lds(kern, lds);
     if (e != hipSuccess) return e;
     KernelTimer kt("aggregate", st);
-    kern<<<dim3((ntile + 3) / 4, s.BH), 256, kAggLds, st>>>((const bf16*)in, ind, s.T, row_len, dd, (bf16*)outH, outZ);
+    kern<<<dim3((ntile + 3) / 4, s.BH), 256, lds, st>>>((const bf16*)in, ind, s.T, row_len, dd, (bf16*)outH, outZ);
     return hipGetLastError();
   }
   {
