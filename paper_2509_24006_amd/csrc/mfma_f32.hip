@@ -36,18 +36,26 @@ struct FTile {
 // Direct loads of 64-row tiles whose rows lie tsB bytes apart, behind a descriptor that spans the
 // whole head (rows past its end read as zeros: the part of an offset that may pass the end rides on
 // the per-lane offset, which the range check covers; the tile's own offset is always inside).
+// N tsB is below 2^31, so offsets of rows past the end of a sequence of 62 rows and more stay below
+// 2^32.  Shorter ones (a single tile) with rows 64 MB and more apart would come back into range:
+// their rows past the end get an offset that is out of range in any case.
 template <int D>
 struct FLoader {
   using T = FTile<D>;
+  static constexpr int kFar = 1 << 26;   // 64 rows of this pitch: 2^32 bytes
   int voff[2];    // this lane's byte offset for even and odd loads (the swizzle has period 16 rows)
+  int kend;       // this lane's loads from kend on are of rows past the end (only where rows are far apart)
   int kstep, tile_step;
   unsigned lds0;
-  __device__ __forceinline__ void init(unsigned lds_base_addr, int w, int l, int tsB) {
+  // N: rows of the head (a packed matrix needs none: its rows are near)
+  __device__ __forceinline__ void init(unsigned lds_base_addr, int w, int l, int tsB, int N = 0) {
+    const int r0 = T::RPI * w + l / T::CPR;
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
-      const int r0 = T::RPI * w + l / T::CPR, row = r0 + 4 * T::RPI * k;
+      const int row = r0 + 4 * T::RPI * k;
       voff[k] = r0 * tsB + (((l % T::CPR) ^ (row & 15)) << 4);
     }
+    kend = tsB < kFar ? T::IPW : (N - r0 + 4 * T::RPI - 1) / (4 * T::RPI);
     kstep = 4 * T::RPI * tsB;
     tile_step = kBlk * tsB;
     lds0 = lds_base_addr + wave_uniform(w) * 1024;
@@ -56,7 +64,7 @@ struct FLoader {
   __device__ __forceinline__ void load(BufDesc desc, int tile, int slot) const {
 #pragma unroll
     for (int k = 0; k < T::IPW; ++k)
-      load_to_lds16(desc, voff[k & 1] + k * kstep, tile * tile_step, lds0 + slot + 4096 * k);
+      load_to_lds16(desc, k < kend ? voff[k & 1] + k * kstep : 0x7ffffff0, tile * tile_step, lds0 + slot + 4096 * k);
   }
 };
 
@@ -255,7 +263,7 @@ __global__ __launch_bounds__(256, 2) void f32_states_kernel(const float* __restr
   const int n0 = j * kBlk, cnt = min(kBlk, N - n0), row = 16 * w + n;
   const float* Kh = K + lay.head(bh);
   FLoader<D> ld;
-  ld.init(lds_base(smem), w, l, 4 * lay.ts);
+  ld.init(lds_base(smem), w, l, 4 * lay.ts, N);
   ld.load(head_rsrc_f32<D>(V + lay.head(bh), N, 4 * lay.ts), j, TB);
   f32x4 x[NT], y[NT];
   load_frag<NT>(Kh + (size_t)(n0 + row) * lay.ts, row < cnt, g, x);
@@ -385,7 +393,7 @@ __global__ __launch_bounds__(256, 2) void f32_forward_kernel(
   const size_t qb = ((size_t)bh * N + q0 + row) * D;                       // in the library's packed tensors
   const size_t uq = lay.head(bh) + (size_t)(q0 + row) * lay.ts;            // in the caller's tensors
   FLoader<D> ld, lm;   // the caller's tensors; packed D x D matrices
-  ld.init(lds_base(smem), w, l, 4 * lay.ts);
+  ld.init(lds_base(smem), w, l, 4 * lay.ts, N);
   lm.init(lds_base(smem), w, l, 4 * D);
   const BufDesc dK = head_rsrc_f32<D>(K + lay.head(bh), N, 4 * lay.ts);
   const BufDesc dV = head_rsrc_f32<D>(V + lay.head(bh), N, 4 * lay.ts);
@@ -519,7 +527,7 @@ __global__ __launch_bounds__(256, 2) void f32_bwd_query_kernel(
   const size_t qi = (size_t)bh * N + q0 + row;
   const size_t uq = lay.head(bh) + (size_t)(q0 + row) * lay.ts;
   FLoader<D> ld, lm;
-  ld.init(lds_base(smem), w, l, 4 * lay.ts);
+  ld.init(lds_base(smem), w, l, 4 * lay.ts, N);
   lm.init(lds_base(smem), w, l, 4 * D);
   FAddr<D> ad;
   ad.init(l);
@@ -701,7 +709,7 @@ __global__ __launch_bounds__(256, 2) void f32_bwd_key_kernel(
 #pragma unroll
   for (int t = 0; t < NT; ++t) dk[t] = dv[t] = zero4();
   FLoader<D> ld;
-  ld.init(lds_base(smem), w, l, 4 * lay.ts);
+  ld.init(lds_base(smem), w, l, 4 * lay.ts, N);
   FAddr<D> ad;
   ad.init(l);
   const BufDesc dQd = head_rsrc_f32<D>(Q + lay.head(bh), N, 4 * lay.ts);
@@ -863,7 +871,7 @@ __global__ __launch_bounds__(256, 2) void f32_dw_kernel(const float* __restrict_
   const int tid = threadIdx.x, w = wave_uniform(tid >> 6), l = tid & 63;
   FLoader<D> lo, lg;
   lo.init(lds_base(smem), w, l, 4 * D);
-  lg.init(lds_base(smem), w, l, 4 * lay.ts);
+  lg.init(lds_base(smem), w, l, 4 * lay.ts, N);
   FAddr<D> ad;
   ad.init(l);
   f32x4 acc[D / 64][NT];
