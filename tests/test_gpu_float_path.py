@@ -40,6 +40,25 @@ def test_a_state_that_is_not_finite_reaches_only_the_rows_that_add_it(oracle, T)
     assert np.abs(r["Hi"][fin] - f["Hi"][fin]).max() <= 1e-5 * np.abs(f["Hi"][fin]).max()
 
 
+@pytest.mark.parametrize("T,d,k_h", [(1, 64, 0.0), (1, 128, 0.0), (2, 64, 0.0), (3, 128, 0.3), (4, 64, 0.2), (4, 128, 0.0),
+                                     (5, 64, 0.2), (5, 128, 0.0)])
+def test_sums_of_the_states_of_a_few_blocks(oracle, T, d, k_h):
+    # up to four blocks one thread holds its columns of every state, from five on the matrix form;
+    # every row marginal or some, a ragged last block, more heads than one
+    x = _inputs(64 * T - 9, d, H=3)
+    _full_case(oracle, x, "fp32", k_h, 0.2, floor_rms=0.05 if T < 4 else 0.0)
+    if T == 1:
+        return
+    x["V"][0, 1, 5, 7] = np.inf
+    x["V"][0, 2, 64 * (T - 1), 9] = np.nan
+    Mc = oracle.build_mask(x["Q"], x["K"], k_h, 0.2)
+    f = oracle.forward(x["Q"], x["K"], x["V"], x["Proj"], Mc)
+    r = run_gpu(x, "fp32", k_h, 0.2, backward=False)
+    fin = np.isfinite(f["Hi"])
+    assert not fin.all() and np.array_equal(np.isfinite(r["Hi"]), fin)
+    assert np.abs(r["Hi"][fin] - f["Hi"][fin]).max() <= 1e-5 * np.abs(f["Hi"][fin]).max()
+
+
 @pytest.mark.parametrize("d,k_h", [(64, 1.0), (64, 0.0), (128, 1.0), (128, 0.0)])
 def test_rows_far_apart_read_nothing_between_them(d, k_h):
     # three tokens 512 MB + 4 KB apart, NaN everywhere else: the offsets of the 61 rows that the
