@@ -164,8 +164,11 @@ __global__ __launch_bounds__(256, 4) void states_mfma_kernel(const bf16* __restr
 // The step loop is written for few instructions (a wave issues one every five to eight cycles
 // whatever its kind, and a SIMD has two waves): tile slots fixed per step parity (two copies of
 // the step, every LDS offset an immediate), per-lane LDS addresses held in registers, one M0 value
-// per tile (RunLoader), the key block table read one entry per step through a running offset, the
-// few conditions as branches of the whole wave.
+// per tile (RunLoader), the key block table read one entry per step through a running offset, no
+// conditions but in the copy of the step that the last four steps run (with conditions on every step,
+// before -> now: d = 64, 1 head x 157 query blocks of 157 key blocks 93.2 -> 83.1 us a launch, 12 x
+// 512 of 102 828 -> 812; d = 128, 1 x 157 of 39 39.3 -> 37.1, 12 x 512 of 102 1502 -> 1476, of 26
+// 516 -> 510 us).
 template <int D>
 struct FwdLds {
   // Slot 2p holds the K tile and slot 2p + 1 the V tile of the steps of parity p.  The scores S_s
@@ -339,9 +342,11 @@ __global__ __launch_bounds__(256 * QT, QT == 1 ? 2 : 1) void fwd_mfma_kernel(
   // One step; P = parity of s.  On entry K_{s+1} and V_s are in their slots for every wave, sT
   // holds S_s; sN receives S_{s+1}.  The wave copies its operands of the step to registers first;
   // a second barrier then frees both slots for K_{s+3} and V_{s+2}, two steps before they are
-  // needed.  The few conditions are wave-uniform branches (two scalar instructions each).
-  auto step = [&](auto Pc, int s, f32x16& sT, f32x16& sN) __attribute__((always_inline)) {
+  // needed.  The conditions are wave-uniform branches (two scalar instructions each); MID: s + 3 < n_h,
+  // where each of them holds.
+  auto step = [&](auto Pc, auto Mid, int s, f32x16& sT, f32x16& sN) __attribute__((always_inline)) {
     constexpr int P = decltype(Pc)::value;
+    constexpr bool MID = decltype(Mid)::value;
     constexpr int VS = (2 * P + 1) * Lds::TILE;    // V_s, then V_{s+2}
     constexpr int KN = 2 * (1 - P) * Lds::TILE;    // K_{s+1}, then K_{s+3}
     bf16x8 ka[KT], va[2][NT];
@@ -380,9 +385,9 @@ __global__ __launch_bounds__(256 * QT, QT == 1 ? 2 : 1) void fwd_mfma_kernel(
     }
     const float moff = m == -INFINITY ? 0.0f : -m * c2;   // a half with no valid key yet
     __syncthreads();   // every wave holds its operands of this step: both slots are refilled
-    if (s + 3 < n_h) tl.template load<KN>(descK, kb3);
+    if (MID || s + 3 < n_h) tl.template load<KN>(descK, kb3);
     else if (s + 4 == nh1) issue_state0();
-    if (s + 2 < n_h) tl.template load<VS>(descV, kb2);
+    if (MID || s + 2 < n_h) tl.template load<VS>(descV, kb2);
     else if (s + 3 == nh1) issue_state1();
     const int jn = *reinterpret_cast<const int32_t*>(reinterpret_cast<const char*>(lut) + min(lo, lomax));
     lo += 4;
@@ -415,8 +420,8 @@ __global__ __launch_bounds__(256 * QT, QT == 1 ? 2 : 1) void fwd_mfma_kernel(
     sched_fence();     // (the matrix products above are issued before this wait)
     // K_{s+2} and V_{s+1}, requested a step ago, have landed; the two tiles requested in this step
     // (one of them near the end) may stay in flight.  Behind the last step there is nothing to wait for.
-    if (s + 1 < n_h) {
-      if (s + 3 < nk) wait_vm<2 * IPW>();
+    if (MID || s + 1 < n_h) {
+      if (MID || s + 3 < nk) wait_vm<2 * IPW>();
       else if (s + 2 < (D > kBlk ? nk : n_h)) wait_vm<IPW>();
       else wait_vm0();
       __syncthreads();
@@ -425,10 +430,17 @@ __global__ __launch_bounds__(256 * QT, QT == 1 ? 2 : 1) void fwd_mfma_kernel(
   {
     const std::integral_constant<int, 0> p0;
     const std::integral_constant<int, 1> p1;
+    const std::integral_constant<bool, true> mid;
+    const std::integral_constant<bool, false> any;
     f32x16 sU = zero_f32x16();
-    for (int s = 0; s < n_h; s += 2) {
-      step(p0, s, sT, sU);
-      if (s + 1 < n_h) step(p1, s + 1, sU, sT);
+    int s = 0;
+    for (; s + 4 < n_h; s += 2) {
+      step(p0, mid, s, sT, sU);
+      step(p1, mid, s + 1, sU, sT);
+    }
+    for (; s < n_h; s += 2) {
+      step(p0, any, s, sT, sU);
+      if (s + 1 < n_h) step(p1, any, s + 1, sU, sT);
     }
   }
   // ---- merge the two key-tile streams (par 0 / par 1) of each query half

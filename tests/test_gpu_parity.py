@@ -154,6 +154,22 @@ def test_short_sequences(oracle, N):
     _full_case(oracle, x, "fp32", 0.34, 0.34, floor_rms=0.05)
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n_h", range(9))
+def test_every_beginning_and_end_of_the_forward_loop(oracle, wide_tiles, n_h, d):
+    # the forward kernel requests tiles two steps ahead, the aggregated state as the tile behind the
+    # last one, and runs all but its last steps without conditions: every number of critical blocks
+    # from none to beyond that, with marginal blocks and without, a ragged last block, query blocks of
+    # one tile and of two (four-wave and eight-wave kernels)
+    T = 13
+    N = 64 * T - 9
+    rng = np.random.default_rng(100 * n_h + d)
+    x = {k: wl.round_to_bf16(rng.standard_normal((1, 2, N, d)).astype(np.float32)) for k in ("Q", "K", "V", "dO")}
+    x["Proj"] = wl.round_to_bf16((rng.standard_normal((d, d)) * 0.05).astype(np.float32))
+    for bq, k_l in ((64, 0.1), (64, 1.0), (128, 0.1), (128, 1.0)):
+        _full_case(oracle, x, "bf16", n_h / T, k_l, bq=bq, backward=False)
+
+
 @pytest.mark.parametrize("N,d", [(2565, 128), (4096, 64), (2048, 128)])
 def test_bf16_mid_length_sequences(oracle, N, d):
     # 33..64 blocks: the short-sequence state aggregation with two row tiles, a ragged tail and
