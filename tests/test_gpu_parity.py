@@ -170,6 +170,20 @@ def test_every_beginning_and_end_of_the_forward_loop(oracle, wide_tiles, n_h, d)
         _full_case(oracle, x, "bf16", n_h / T, k_l, bq=bq, backward=False)
 
 
+@pytest.mark.parametrize("T,bq,H", [(1, 64, 11), (3, 64, 8), (7, 64, 1), (8, 64, 11), (9, 64, 11), (15, 128, 9),
+                                    (16, 128, 11), (17, 128, 3)])
+def test_heads_of_a_few_tiles(oracle, wide_tiles, T, bq, H):
+    # up to eight workgroups a head stays on one XCD, eight heads to a row of the grid: numbers of
+    # heads that are no multiple of eight, both sides of the line for four-wave workgroups (8, 9
+    # tiles) and for eight-wave ones (16, 17 tiles of query blocks of two)
+    N, d = 64 * T - 9, 64
+    rng = np.random.default_rng(T + H)
+    x = {k: wl.round_to_bf16(rng.standard_normal((1, H, N, d)).astype(np.float32)) for k in ("Q", "K", "V", "dO")}
+    x["Proj"] = wl.round_to_bf16((rng.standard_normal((d, d)) * 0.05).astype(np.float32))
+    for k_h, k_l in ((0.3, 0.3), (1.0, 0.0), (0.0, 0.0)):
+        _full_case(oracle, x, "bf16", k_h, k_l, bq=bq, backward=False)
+
+
 @pytest.mark.parametrize("N,d", [(2565, 128), (4096, 64), (2048, 128)])
 def test_bf16_mid_length_sequences(oracle, N, d):
     # 33..64 blocks: the short-sequence state aggregation with two row tiles, a ragged tail and
