@@ -366,9 +366,15 @@ __global__ __launch_bounds__(256) void indicator_kernel(const int8_t* __restrict
 // every column, ascending).  A workgroup owns 64 columns of one head; every workgroup forms the
 // prefix sum up to its columns from the head's counts by itself.  Bound by latency (a few hundred
 // workgroups, each a chain of short phases): the waves vote different row tiles with no barrier in
-// between, counts and column indices are compared as one number, four per LDS read, and every lane
-// writes its own column's list.  (40 heads x 1182 blocks: 152 -> 58 us a launch; 12 x 512: 22.6 -> 18 us;
-// 12 x 146, whose rows are not 16-byte aligned: 20 -> 9.6 us.)
+// between, counts and column indices are compared as one number, four per LDS read, and the rows of
+// a tile are written the cheaper of two ways: short lists by a lane per column (a store touches 64
+// lists, so the longest one counts), long ones by the whole wave, column by column (a store is one
+// piece of a list, and every column costs the same).  (5 % critical, 40 heads x 1182 blocks: 152 -> 58
+// us a launch; 12 x 146, whose rows are not 16-byte aligned: 20 -> 9.6 us.  A lane per column alone,
+// both: 40 x 512 with 10 % critical in few columns 35 -> 22.9, with 20 % 51 -> 23.9, with all 92 ->
+// 24.8 us; 4096 x 65, all 160 -> 59.)
+constexpr int kLongList = 12;   // rows of a column's list in a tile from which the wave writes it
+constexpr int kManyLong = 24;   // such columns in a tile from which it writes all 64 without a choice
 constexpr int kKeyBits = 12;   // column index in a sort key: kMaxT of the interface is below 2^12
 __host__ __device__ constexpr int col_tables_lds(int Tw) { return 64 * Tw * 4 + 64 * Tw * 8; }
 
@@ -431,21 +437,35 @@ __global__ __launch_bounds__(256) void col_tables_kernel(const int8_t* __restric
   __syncthreads();
   if (w == 0 && j0 + l < T) order[(size_t)bh * T + part[0][l] + part[1][l] + part[2][l] + part[3][l]] = j0 + l;
   if (n_h == 0) return;
-  // rows of the critical blocks: wave w writes those of the row tiles it voted, every lane its column's
+  // rows of the critical blocks: wave w writes those of the row tiles it voted
   int32_t* out = rows + (size_t)bh * T * n_h;
   int pos = cptr[l];   // where the rows of the next row tile go
   for (int t = 0; t < Tw; ++t) {
     const unsigned long long m = crit[64 * t + l];
     if ((t & 3) == w) {
-      int p = pos;
+      const unsigned mlo = (unsigned)m, mhi = (unsigned)(m >> 32);
+      auto column = [&](int c) {   // the wave writes column c's rows
+        const unsigned lo = __builtin_amdgcn_readlane(mlo, c), hi = __builtin_amdgcn_readlane(mhi, c);
+        const unsigned p = __builtin_amdgcn_readlane(pos, c) + __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0));
+        if (__builtin_amdgcn_inverse_ballot_w64((unsigned long long)hi << 32 | lo)) out[p] = 64 * t + l;
+      };
+      unsigned long long longs = __ballot(__popcll(m) > kLongList);
+      if (__popcll(longs) >= kManyLong) {
+#pragma unroll 8
+        for (int c = 0; c < 64; ++c) column(c);
+      } else {
+        if (__popcll(m) <= kLongList) {
+          unsigned p = pos;
 #pragma unroll
-      for (int h = 0; h < 2; ++h)
-        for (unsigned x = (unsigned)(m >> (32 * h)); x; x &= x - 1) out[p++] = 64 * t + 32 * h + __ffs(x) - 1;
+          for (int h = 0; h < 2; ++h)
+            for (unsigned x = h ? mhi : mlo; x; x &= x - 1) out[p++] = 64 * t + 32 * h + __ffs(x) - 1;
+        }
+        for (; longs; longs &= longs - 1) column(__ffsll(longs) - 1);
+      }
     }
     pos += __popcll(m);
   }
 }
-
 
 // ---------------------------------------------------------------- short sequences
 // At most 64 key blocks: scores, classification and all tables of a head in one workgroup.  At

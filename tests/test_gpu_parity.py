@@ -331,6 +331,28 @@ def test_classification_and_tables_at_the_edges_of_the_row_lengths(oracle, T, bq
                v["col_order"])
 
 
+@pytest.mark.parametrize("T,bq,hot,k_h", [(65, 64, 23, 0.4), (130, 64, 24, 0.24), (130, 64, 22, 0.24), (130, 64, 10, 0.2),
+                                          (130, 64, 0, 0.19), (200, 128, 12, 0.14), (193, 192, 30, 0.25), (130, 64, 0, 1.0)])
+def test_column_lists_short_and_long_in_one_tile(oracle, T, bq, hot, k_h):
+    # lists of up to 12 rows of a 64-row tile are written by a lane each, longer ones by the wave, all
+    # 64 by the wave where 24 columns and more are long: `hot` columns that every row selects (22, 23,
+    # 24 in a tile), the rest of a row's n_h at random (without hot ones: about 12 rows a list)
+    from paper_2509_24006_amd import binding as sla
+    rng = np.random.default_rng(T + hot)
+    p = sla.make_params(1, 2, T * 64, 64, k_h, 0.0, torch.bfloat16, bq=bq)
+    z = sla.sla_sizes(p)
+    s = rng.standard_normal((1, 2, z.Tq, z.T)).astype(np.float32)
+    s[..., 3:3 + hot] += 8.0
+    nh, nl = oracle.counts(z.T, k_h, 0.0)
+    ref = oracle.classify(s, nh, nl)
+    Mc, luts = sla.sla_classify_scores(p, torch.from_numpy(s).cuda())
+    torch.cuda.synchronize()
+    assert np.array_equal(Mc.cpu().numpy(), ref)
+    v = {k: t.cpu().numpy() for k, t in sla.lut_views(p, luts).items()}
+    check_luts(per_tile(ref, bq // 64, z.T), v["row_idx"], v["col_ptr"], v["col_rows"], v["ind"], v["ind_t"],
+               v["col_order"])
+
+
 @pytest.mark.parametrize("bq,N", [(128, 130 * 64), (192, 130 * 64 - 40), (256, 33 * 64)])
 def test_classify_given_scores_with_ties_and_larger_query_blocks(oracle, bq, N):
     # rectangular score matrices (one row per block of bq queries), heavy ties; N is chosen so that
