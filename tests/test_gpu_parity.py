@@ -307,9 +307,9 @@ def test_classify_given_scores_with_ties(oracle):
 
 
 @pytest.mark.parametrize("T,bq", [(65, 64), (128, 64), (129, 64), (192, 128), (193, 192), (256, 64), (257, 64),
-                                  (384, 128), (385, 64), (513, 192), (641, 256), (832, 64), (833, 128), (1025, 256),
-                                  (1216, 128), (1217, 256), (1409, 256), (1728, 256), (1729, 256), (2049, 256),
-                                  (3072, 256)])
+                                  (384, 128), (385, 64), (512, 64), (513, 192), (640, 256), (641, 256), (832, 64),
+                                  (833, 128), (1024, 256), (1025, 256), (1216, 128), (1217, 256), (1408, 256),
+                                  (1409, 256), (1728, 256), (1729, 256), (2048, 256), (2049, 256), (3072, 256)])
 def test_classification_and_tables_at_the_edges_of_the_row_lengths(oracle, T, bq):
     # whole numbers, so the comparison is exact: one row of ties only, one of two values, one of
     # small integers, the rest distinct (where the threshold search ends early)
