@@ -244,7 +244,6 @@ int sla_forward(const sla_params* p, const void* Q, const void* K, const void* V
   const char* l = (const char*)luts;
   FwdArgs a;
   a.Q = Q; a.K = K; a.V = V; a.W = W;
-  a.Mc = Mc;
   a.row_idx = (const int32_t*)(l + z.lut_row_idx);
   a.ind = (const unsigned long long*)(l + z.lut_ind);
   a.O = O;
@@ -278,7 +277,6 @@ int sla_backward(const sla_params* p, const void* Q, const void* K, const void* 
   const char* l = (const char*)luts;
   BwdArgs a;
   a.Q = Q; a.K = K; a.V = V; a.W = W; a.dO = dO;
-  a.Mc = Mc;
   a.row_idx = (const int32_t*)(l + z.lut_row_idx);
   a.col_ptr = (const int32_t*)(l + z.lut_col_ptr);
   a.col_rows = (const int32_t*)(l + z.lut_col_rows);

@@ -718,6 +718,7 @@ __global__ __launch_bounds__(256, 2) void f32_bwd_key_kernel(
     const int32_t* __restrict__ col_ptr, const int32_t* __restrict__ col_rows, const int32_t* __restrict__ col_order,
     const float* __restrict__ dHZcol, int N, int Tn, Lay lay, int n_h, int n_0, int phi, float scale,
     float* __restrict__ dK, float* __restrict__ dV) {
+  static_assert(QW == 2 || QW == 4, "waves that share a group of 16 keys");
   constexpr int NT = D / 16, TB = FTile<D>::BYTES, NQ = 4 / QW, NO = NT / QW;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const unsigned char* stat = smem + 2 * TB;
@@ -792,13 +793,7 @@ __global__ __launch_bounds__(256, 2) void f32_bwd_key_kernel(
   }
   // wave wq of the QW that share a key group gets the feature tiles wq, wq + QW, ...
   f32x4 ok_[NO], ov[NO];
-  if (QW == 1) {
-#pragma unroll
-    for (int m = 0; m < NO; ++m) {
-      ok_[m] = dk[m];
-      ov[m] = dv[m];
-    }
-  } else {
+  {
     f32x4* x = reinterpret_cast<f32x4*>(smem);      // [wave][dK, dV][tile][lane]
 #pragma unroll
     for (int f = 0; f < NT; ++f) {
@@ -862,13 +857,11 @@ __global__ __launch_bounds__(256, 2) void f32_bwd_key_kernel(
     }
     if (phi == 0) {
       float dot = dot_frag<NO>(gk, yo);
-      if (QW > 1) {
-        if (g == 0) dots[16 * w + n] = dot;
-        __syncthreads();
-        dot = 0.0f;
+      if (g == 0) dots[16 * w + n] = dot;
+      __syncthreads();
+      dot = 0.0f;
 #pragma unroll
-        for (int q = 0; q < QW; ++q) dot += dots[16 * (wk * QW + q) + n];
-      }
+      for (int q = 0; q < QW; ++q) dot += dots[16 * (wk * QW + q) + n];
 #pragma unroll
       for (int m = 0; m < NO; ++m)
 #pragma unroll
@@ -914,6 +907,26 @@ __global__ __launch_bounds__(256, 2) void f32_dw_kernel(const float* __restrict_
     __syncthreads();
   }
   store_outer<D>(part + (size_t)blockIdx.x * D * D, acc, w, l);   // rows c of O^l along the lanes
+}
+
+// out[i] = sum over k with bit k of ind[i] set of the state rows in[k]
+hipError_t f32_aggregate(const float* in, const unsigned long long* ind, const Shape& s, float* out, hipStream_t st) {
+  const int row_len = s.state_row(), Tw = (s.T + 63) / 64;
+  const int gx = (row_len / 32 + 3) / 4;
+  KernelTimer kt("aggregate", st);
+  // From five blocks on the matrix form takes the same or less with few heads (eight blocks, d = 64,
+  // 16 heads: 7.2 us against 8.2 with the short one) and no more than one thread per column and row
+  // did with many (five blocks, 256 heads, d = 128, two marginal: 104 against 110 us).
+  if (s.T <= kFew) {
+    f32_aggregate_few_kernel<<<dim3((row_len / 4 + 255) / 256, s.BH), 256, 0, st>>>(in, ind, s.T, row_len, out);
+    return hipGetLastError();
+  }
+  // up to 128 rows per wave (the states are read ceil(T / 128) times), in tiles of 32 dealt evenly
+  const int ny = (s.T + 127) / 128, mt = ((s.T + 31) / 32 + ny - 1) / ny;
+  auto kern = mt == 1 ? f32_aggregate_kernel<1> : mt == 2 ? f32_aggregate_kernel<2>
+            : mt == 3 ? f32_aggregate_kernel<3> : f32_aggregate_kernel<4>;
+  kern<<<dim3(gx, ny, s.BH), 256, 0, st>>>(in, ind, s.T, Tw, row_len, out);
+  return hipGetLastError();
 }
 
 template <int D>
@@ -978,25 +991,6 @@ hipError_t backward_impl(const Shape& s, const BwdArgs& a, float* Ds, float* dHZ
 }
 
 }  // namespace
-
-hipError_t f32_aggregate(const float* in, const unsigned long long* ind, const Shape& s, float* out, hipStream_t st) {
-  const int row_len = s.state_row(), Tw = (s.T + 63) / 64;
-  const int gx = (row_len / 32 + 3) / 4;
-  KernelTimer kt("aggregate", st);
-  // From five blocks on the matrix form takes the same or less with few heads (eight blocks, d = 64,
-  // 16 heads: 7.2 us against 8.2 with the short one) and no more than one thread per column and row
-  // did with many (five blocks, 256 heads, d = 128, two marginal: 104 against 110 us).
-  if (s.T <= kFew) {
-    f32_aggregate_few_kernel<<<dim3((row_len / 4 + 255) / 256, s.BH), 256, 0, st>>>(in, ind, s.T, row_len, out);
-    return hipGetLastError();
-  }
-  // up to 128 rows per wave (the states are read ceil(T / 128) times), in tiles of 32 dealt evenly
-  const int ny = (s.T + 127) / 128, mt = ((s.T + 31) / 32 + ny - 1) / ny;
-  auto kern = mt == 1 ? f32_aggregate_kernel<1> : mt == 2 ? f32_aggregate_kernel<2>
-            : mt == 3 ? f32_aggregate_kernel<3> : f32_aggregate_kernel<4>;
-  kern<<<dim3(gx, ny, s.BH), 256, 0, st>>>(in, ind, s.T, Tw, row_len, out);
-  return hipGetLastError();
-}
 
 hipError_t f32_backward(const Shape& s, const BwdArgs& a, float* Ds, float* dHZ, float* dHZcol, float* dWpart,
                         int nparts, hipStream_t st) {

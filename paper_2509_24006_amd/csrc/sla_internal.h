@@ -39,8 +39,6 @@ struct Shape {
 
 __device__ __forceinline__ float to_f32(float x) { return x; }
 __device__ __forceinline__ float to_f32(__hip_bfloat16 x) { return __bfloat162float(x); }
-__device__ __forceinline__ void from_f32(float& dst, float x) { dst = x; }
-__device__ __forceinline__ void from_f32(__hip_bfloat16& dst, float x) { dst = __float2bfloat16(x); }
 
 // ---- mask step (mask_kernels.hip)
 hipError_t launch_pool(const void* Q, const void* K, const Shape& s, float* qbar, float* kbar, hipStream_t st);
@@ -64,7 +62,6 @@ hipError_t launch_fill_zero(float* p, size_t n, hipStream_t st);
 // ---- float path (mfma_f32.hip)
 struct FwdArgs {
   const void *Q, *K, *V, *W;
-  const int8_t* Mc;
   const unsigned long long* ind;   // marginal indicator bit masks
   const int32_t* row_idx;
   void* O;
@@ -74,12 +71,9 @@ struct FwdArgs {
   float* hz;       // [BH,T] state rows of the key blocks (workspace)
 };
 hipError_t f32_forward(const Shape& s, const FwdArgs& a, hipStream_t st);
-// out[i] = sum over k with bit k of ind[i] set of the float state rows in[k]
-hipError_t f32_aggregate(const float* in, const unsigned long long* ind, const Shape& s, float* out, hipStream_t st);
 
 struct BwdArgs {
   const void *Q, *K, *V, *W, *dO;
-  const int8_t* Mc;
   const unsigned long long* indT;  // marginal indicator bit masks, transposed
   const int32_t *row_idx, *col_ptr, *col_rows, *col_order;
   const void *Os, *Ol;
