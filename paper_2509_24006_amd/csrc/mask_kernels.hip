@@ -642,11 +642,11 @@ hipError_t launch_classify(const float* scores, const Shape& s, int8_t* Mc, int3
   {
     KernelTimer kt("classify", st);
     const dim3 grid((rows + 3) / 4);
-    // slots per lane as the row needs them (the kernel's time goes with the slots), in steps that
-    // keep the number of instances small
+    // slots per lane as the row needs them (the kernel's time goes with the slots): the fewest
+    // instances with which no row pays for more than a fifth more slots than it needs
     const int slots = (s.T + 63) / 64;
     if (slots <= 32) {
-      auto kern = slots <= 1 ? classify_reg_kernel<1> : slots <= 2 ? classify_reg_kernel<2>
+      auto kern = slots <= 2 ? classify_reg_kernel<2>
                 : slots <= 3 ? classify_reg_kernel<3> : slots <= 4 ? classify_reg_kernel<4>
                 : slots <= 6 ? classify_reg_kernel<6> : slots <= 8 ? classify_reg_kernel<8>
                 : slots <= 10 ? classify_reg_kernel<10> : slots <= 13 ? classify_reg_kernel<13>
