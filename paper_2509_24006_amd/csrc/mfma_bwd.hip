@@ -100,7 +100,7 @@ __global__ __launch_bounds__(256, 2) void bwd_dkdv_mfma_kernel(
   const int beg = ptr[j], cnt = ptr[j + 1] - beg;
   const float sl2 = scale * kLog2e, rscale = 1.0f / scale;
   TileLoader<D> tl;   // tiles of the caller's tensors (ldv, lds0 below: the library's packed ones)
-  tl.init(lds_base(smem), w, l, 2 * lay.ts);
+  tl.init(lds_base(smem), w, l, 2 * lay.ts, N);
   const BufDesc descQ = head_rsrc<D>(Q + lay.head(bh), N, 2 * lay.ts);
   const BufDesc descG = head_rsrc<D>(dO + lay.head(bh), N, 2 * lay.ts);
   const float* Lb = L + (size_t)bh * N;
@@ -116,14 +116,18 @@ __global__ __launch_bounds__(256, 2) void bwd_dkdv_mfma_kernel(
     tl.load(descQ, ii, off);
     tl.load(descG, ii, off + Lds::TILE);
   };
+  auto issue_first = [&](int ii) __attribute__((always_inline)) {
+    tl.load_first(descQ, ii, 0);
+    tl.load_first(descG, ii, Lds::TILE);
+  };
   // K_j and V_j come in as tiles (whole rows per load, zeros past the end of the sequence) and are
   // picked up from LDS in operand layout.  With a linear branch, the aggregated dH^T of this key
   // block (d x d, stored [b][a]) comes in with them, through the second pair buffer (rows 0..63
   // in the Q slot, the rest in the dO slot), K_j and V_j through the first, which is handed to the
   // first pair's tiles as soon as the operands are in registers; dZ_j goes to registers directly.
   const int kvoff = dHcol ? 0 : Lds::BUF;
-  tl.load(head_rsrc<D>(K + lay.head(bh), N, 2 * lay.ts), j, kvoff);
-  tl.load(head_rsrc<D>(V + lay.head(bh), N, 2 * lay.ts), j, kvoff + Lds::TILE);
+  tl.load_first(head_rsrc<D>(K + lay.head(bh), N, 2 * lay.ts), j, kvoff);
+  tl.load_first(head_rsrc<D>(V + lay.head(bh), N, 2 * lay.ts), j, kvoff + Lds::TILE);
   f32x4 z4[HT][4];
   if (dHcol) {
     const bf16* M = dHcol + ((size_t)bh * Tn + j) * (D * D);
@@ -135,7 +139,7 @@ __global__ __launch_bounds__(256, 2) void bwd_dkdv_mfma_kernel(
 #pragma unroll
       for (int r4 = 0; r4 < 4; ++r4) z4[dt][r4] = *reinterpret_cast<const f32x4*>(dZ + 32 * (xh * HT + dt) + 8 * r4 + 4 * g);
   } else if (cnt > 0) {
-    issue(icur, 0);
+    issue_first(icur);
   }
   wait_vm0_known();
   if (dHcol) {   // (tell the compiler too, or it waits for dZ later, with the first pair's loads in flight)
@@ -179,7 +183,7 @@ __global__ __launch_bounds__(256, 2) void bwd_dkdv_mfma_kernel(
 #pragma unroll
       for (int r4 = 0; r4 < 4; ++r4) pin_loaded(kc[dt][r4]);
     __syncthreads();   // K_j and V_j are in registers everywhere: their buffer takes the first pair
-    if (cnt > 0) issue(icur, 0);
+    if (cnt > 0) issue_first(icur);
     float kmx, kinv;
     TileAddr<D> ma;
     ma.init(0, l);

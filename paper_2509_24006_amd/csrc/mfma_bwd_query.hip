@@ -63,11 +63,11 @@ __device__ __forceinline__ void pre_body(
   const unsigned lds0 = lds_base(smem) + wu * 1024;
   const bf16* Hrow = H16 + ((size_t)bh * Tn + i) * (D * D);   // stored [b][c] = H_i[c][b]
   TileLoader<D> tl;   // tiles of the caller's dO and Q (base: the library's own packed tensors)
-  tl.init(lds_base(smem), w, l, 2 * lay.ts);
-  tl.load(head_rsrc<D>(dO + lay.head(bh), N, 2 * lay.ts), i, S0);
+  tl.init(lds_base(smem), w, l, 2 * lay.ts, N);
+  tl.load_first(head_rsrc<D>(dO + lay.head(bh), N, 2 * lay.ts), i, S0);
   issue_tile_load<D>(Os + base, rows, lds0, S1, ldv);
   if (n_0 > 0) issue_tile_load<D>(Ol + base, rows, lds0, S2, ldv);
-  if (n_0 > 0 || FUSED) tl.load(head_rsrc<D>(Q + lay.head(bh), N, 2 * lay.ts), i, S3);
+  if (n_0 > 0 || FUSED) tl.load_first(head_rsrc<D>(Q + lay.head(bh), N, 2 * lay.ts), i, S3);
   // rows of W for this wave's dO^l tiles, and Z_i, requested together with the tiles
   bf16x8 wfr[HT][KT];
   if (n_0 > 0) {
@@ -382,8 +382,8 @@ __global__ __launch_bounds__(256 * QT, QT == 1 ? (D == 64 ? 3 : 2) : 1) void bwd
   }
   TileLoader<D, NW> tl;   // K_j, V_j: all waves of the workgroup
   TileLoader<D> tq;       // Q_i, dO_i: the four waves of a group, into the group's area
-  tl.init(lds_base(smem), wall, l, 2 * lay.ts);
-  tq.init(lds_base(smem) + (grp ? Lds::BYTES - Lds::BUF : 0), w, l, 2 * lay.ts);
+  tl.init(lds_base(smem), wall, l, 2 * lay.ts, N);
+  tq.init(lds_base(smem) + (grp ? Lds::BYTES - Lds::BUF : 0), w, l, 2 * lay.ts, N);
   const BufDesc descK = head_rsrc<D>(K + lay.head(bh), N, 2 * lay.ts);
   const BufDesc descV = head_rsrc<D>(V + lay.head(bh), N, 2 * lay.ts);
   // key block indices of steps s, s + 1, s + 2, fetched a step before the loads that need them
@@ -396,14 +396,15 @@ __global__ __launch_bounds__(256 * QT, QT == 1 ? (D == 64 ? 3 : 2) : 1) void bwd
   // the end of the sequence) and are picked up from there in operand layout
   {
     const int it = min(i, Tn - 1);
-    tq.load(head_rsrc<D>(Q + lay.head(bh), N, 2 * lay.ts), it, Lds::BUF);
-    tq.load(head_rsrc<D>(dO + lay.head(bh), N, 2 * lay.ts), it, Lds::BUF + Lds::TILE);
+    tq.load_first(head_rsrc<D>(Q + lay.head(bh), N, 2 * lay.ts), it, Lds::BUF);
+    tq.load_first(head_rsrc<D>(dO + lay.head(bh), N, 2 * lay.ts), it, Lds::BUF + Lds::TILE);
   }
   if (n_h > 0) {
     j0 = lut[0];
     j1 = lut[min(1, n_h - 1)];
     j2 = lut[min(2, n_h - 1)];
-    issue(j0, 0);
+    tl.load_first(descK, j0, 0);
+    tl.load_first(descV, j0, Lds::TILE);
   }
   const float Lq = qok ? L[(size_t)bh * N + q0 + qrow] * kLog2e : INFINITY;
   float nDq;
@@ -573,7 +574,7 @@ __global__ __launch_bounds__(256, 2) void dw_mfma_kernel(const bf16* __restrict_
   const int ldv = tile_lane_offset<D>(w, l);
   const unsigned lds0 = lds_base(smem) + wave_uniform(w) * 1024;
   TileLoader<D> tl;   // tiles of the caller's dO
-  tl.init(lds_base(smem), w, l, 2 * lay.ts);
+  tl.init(lds_base(smem), w, l, 2 * lay.ts, N);
   f32x16 acc[NT];
 #pragma unroll
   for (int et = 0; et < NT; ++et) acc[et] = zero_f32x16();
@@ -583,7 +584,7 @@ __global__ __launch_bounds__(256, 2) void dw_mfma_kernel(const bf16* __restrict_
     const int rows = min(kBlk, N - i * kBlk);
     const size_t base = ((size_t)bh * N + (size_t)i * kBlk) * D;
     issue_tile_load<D>(Ol + base, rows, lds0, buf * BUF, ldv);
-    tl.load(head_rsrc<D>(dO + lay.head(bh), N, 2 * lay.ts), i, buf * BUF + T::BYTES);
+    tl.load_first(head_rsrc<D>(dO + lay.head(bh), N, 2 * lay.ts), i, buf * BUF + T::BYTES);
   };
   TileAddr<D> ad;
   ad.init(0, l);

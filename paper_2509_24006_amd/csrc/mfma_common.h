@@ -319,19 +319,30 @@ template <int D>
 __device__ __forceinline__ BufDesc head_rsrc(const bf16* head_base, int N, int tsB) {
   return tile_rsrc(head_base, (N - 1) * tsB + 2 * D);
 }
+// The N rows of a head take less than 2^31 bytes, so offsets of rows past the end of a sequence of 62
+// rows and more stay below 2^32.  Those of a shorter one, a single tile, can pass it where rows lie 64 MB and
+// more apart, and would come back into range.  Every tile that can be the only one of its head
+// therefore comes in by load_first or RunLoader: a lane's first row is never taken past row N, whose offset is
+// out of range already, and the offsets of its further rows stop below 2^31.  The steps are bounded so that
+// no sum of offsets reaches 2^32, in load either: what it requests behind the only tile is not used, but in range.
+constexpr unsigned kPastEnd = 0x7ffffff0u;   // past the last byte of any head
+constexpr int kMaxStep = 0x7ff00000;         // this and the offset of row N add up to less than 2^32
+
 template <int D, int NW = 4>
 struct TileLoader {
   using T = SwzTile<D>;
   static constexpr int IPW = kBlk / T::RPI / NW;   // loads per wave (NW waves share a tile)
   int ldv;        // this lane's byte offset inside a tile's memory image
   int kstep;      // bytes between the rows of two consecutive loads of a wave
+  int fstep;      // the same in load_first
   unsigned ldsw;  // LDS address of this wave's first KB of the tile at LDS offset 0
   int tile_step;  // bytes between consecutive 64-row tiles
-  // w: this wave's index among the NW waves that fill a tile together
-  __device__ __forceinline__ void init(unsigned lds_base_addr, int w, int l, int tsB) {
+  // w: this wave's index among the NW waves that fill a tile together; N: rows of the head
+  __device__ __forceinline__ void init(unsigned lds_base_addr, int w, int l, int tsB, int N = kBlk) {
     const int row = T::RPI * w + l / T::CPR;
-    ldv = row * tsB + (((l % T::CPR) ^ swz<D>(row)) << 4);
-    kstep = NW * T::RPI * tsB;
+    ldv = min(row, N) * tsB + (((l % T::CPR) ^ swz<D>(row)) << 4);
+    kstep = NW * T::RPI * min(tsB, kMaxStep / kBlk);   // (exact for every head of more than one tile)
+    fstep = NW * T::RPI * min(tsB, kMaxStep / (NW * T::RPI));
     tile_step = kBlk * tsB;
     ldsw = lds_base_addr + __builtin_amdgcn_readfirstlane(w) * 1024;
   }
@@ -340,6 +351,15 @@ struct TileLoader {
 #pragma unroll
     for (int k = 0; k < IPW; ++k)
       load_to_lds16(desc, ldv, tile * tile_step + k * kstep, ldsw + lds_tile + 1024 * NW * k);
+  }
+  // the same where the tile may be the only one of its head
+  __device__ __forceinline__ void load_first(BufDesc desc, int tile, int lds_tile) const {
+    unsigned off = (unsigned)ldv;
+#pragma unroll
+    for (int k = 0; k < IPW; ++k) {
+      load_to_lds16(desc, (int)off, tile * tile_step, ldsw + lds_tile + 1024 * NW * k);
+      off = min(off + (unsigned)fstep, kPastEnd);
+    }
   }
 };
 
@@ -358,11 +378,12 @@ struct RunLoader {
   int voff[IPW];
   unsigned ldsw;  // LDS address of this wave's run of the tile at LDS offset 0
   int tile_step;  // bytes between consecutive 64-row tiles in memory
-  __device__ __forceinline__ void init(unsigned lds_base_addr, int w, int l, int tsB) {
+  // N: rows of the head
+  __device__ __forceinline__ void init(unsigned lds_base_addr, int w, int l, int tsB, int N) {
 #pragma unroll
     for (int k = 0; k < IPW; ++k) {
       const int row = T::RPI * (IPW * w + k) + l / T::CPR;
-      voff[k] = row * tsB + (((l % T::CPR) ^ swz<D>(row)) << 4) - 1024 * k;
+      voff[k] = min(row, N) * tsB + (((l % T::CPR) ^ swz<D>(row)) << 4) - 1024 * k;
     }
     tile_step = __builtin_amdgcn_readfirstlane(kBlk * tsB);
     ldsw = lds_base_addr + __builtin_amdgcn_readfirstlane(w) * (1024 * IPW);

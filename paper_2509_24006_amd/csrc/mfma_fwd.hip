@@ -71,9 +71,9 @@ __global__ __launch_bounds__(256, 4) void states_mfma_kernel(const bf16* __restr
   const int wu = wave_uniform(w);
   {
     TileLoader<D> tl;
-    tl.init(lds_base(smem), w, l, 2 * lay.ts);
-    tl.load(head_rsrc<D>(K + lay.head(bh), N, 2 * lay.ts), j, 0);
-    tl.load(head_rsrc<D>(V + lay.head(bh), N, 2 * lay.ts), j, T::BYTES);
+    tl.init(lds_base(smem), w, l, 2 * lay.ts, N);
+    tl.load_first(head_rsrc<D>(K + lay.head(bh), N, 2 * lay.ts), j, 0);
+    tl.load_first(head_rsrc<D>(V + lay.head(bh), N, 2 * lay.ts), j, T::BYTES);
   }
   wait_vm0();
   __syncthreads();
@@ -227,7 +227,7 @@ __global__ __launch_bounds__(256 * QT, QT == 1 ? 2 : 1) void fwd_mfma_kernel(
   using T = SwzTile<D>;
   RunLoader<D, NW> tl;    // tiles of the caller's K and V: all waves of the workgroup, into the slots
   TileLoader<D> tm;       // packed d x d matrices: the four waves of a group, into the group's area
-  tl.init(lds_base(smem), wall, l, 2 * lay.ts);
+  tl.init(lds_base(smem), wall, l, 2 * lay.ts, N);
   tm.init(lds_base(smem) + grp * Lds::BYTES, w, l, 2 * D);
   constexpr int IPW = RunLoader<D, NW>::IPW;
   const BufDesc descK = head_rsrc<D>(K + lay.head(bh), N, 2 * lay.ts);
@@ -238,8 +238,8 @@ __global__ __launch_bounds__(256 * QT, QT == 1 ? 2 : 1) void fwd_mfma_kernel(
   constexpr int QSLOT = 3 * Lds::TILE;   // V_1's slot, which is filled once Q_i has been picked up
   {
     TileLoader<D> tq;
-    tq.init(lds_base(smem) + grp * Lds::BYTES, w, l, 2 * lay.ts);
-    tq.load(head_rsrc<D>(Q + lay.head(bh), N, 2 * lay.ts), ic, QSLOT);
+    tq.init(lds_base(smem) + grp * Lds::BYTES, w, l, 2 * lay.ts, N);
+    tq.load_first(head_rsrc<D>(Q + lay.head(bh), N, 2 * lay.ts), ic, QSLOT);
   }
   // a d x d bf16 matrix (aggregated state H_i, prepared projection matrix) goes global -> LDS like
   // the tiles: rows 0..63 into the slot at off0, the rest into the one at off1

@@ -1,9 +1,7 @@
 """GPU parity of the float path at the edges of its tiles, against the CPU oracle."""
 import numpy as np
 import pytest
-import torch
 
-from paper_2509_24006_amd import binding as sla
 from tests.gpu_util import run_gpu
 from tests.test_gpu_parity import _full_case
 
@@ -69,29 +67,3 @@ def test_sums_of_the_states_of_a_few_blocks(oracle, T, d, k_h):
     fin = np.isfinite(f["Hi"])
     assert not fin.all() and np.array_equal(np.isfinite(r["Hi"]), fin)
     assert np.abs(r["Hi"][fin] - f["Hi"][fin]).max() <= 1e-5 * np.abs(f["Hi"][fin]).max()
-
-
-@pytest.mark.parametrize("d,k_h", [(64, 1.0), (64, 0.0), (128, 1.0), (128, 0.0)])
-def test_rows_far_apart_read_nothing_between_them(d, k_h):
-    # three tokens 512 MB + 4 KB apart, NaN everywhere else: the offsets of the 61 rows that the
-    # block does not have pass 2^32 and come back into the range of the tensor, 32 KB and more behind
-    # a row of it.  Results equal the packed call's bit for bit (same arithmetic, another row pitch)
-    N, step = 3, (1 << 27) + 1024
-    rng = np.random.default_rng(d)
-    x = {k: rng.standard_normal((1, 1, N, d)).astype(np.float32) for k in ("Q", "K", "V", "dO")}
-    x["Proj"] = (rng.standard_normal((d, d)) * 0.05).astype(np.float32)
-    ref = run_gpu(x, "fp32", k_h, 0.0)
-    buf = torch.full(((N - 1) * step + 8 * d,), float("nan"), device="cuda")
-    view = lambda i: buf.as_strided((1, 1, N, d), (step, step, step, 1), i * d)
-    Q, K, V, dO, O, dQ, dK, dV = (view(i) for i in range(8))
-    for t, k in ((Q, "Q"), (K, "K"), (V, "V"), (dO, "dO")):
-        t.copy_(torch.from_numpy(x[k]))
-    p = sla.make_params(1, 1, N, d, k_h, 0.0, torch.float32, layout=sla.SLA_STRIDED, strides=(step, step, step))
-    W = torch.from_numpy(x["Proj"]).cuda()
-    Mc, luts, _ = sla.sla_build_mask(p, Q, K)
-    _, saved = sla.sla_forward(p, Q, K, V, W, Mc, luts, O=O)
-    dW = torch.empty((d, d), dtype=torch.float32, device="cuda")
-    sla.sla_backward(p, Q, K, V, W, Mc, luts, saved, dO, out=(dQ, dK, dV, dW))
-    torch.cuda.synchronize()
-    for k, got in (("O", O), ("dQ", dQ), ("dK", dK), ("dV", dV), ("dW", dW)):
-        assert np.array_equal(got.double().cpu().numpy(), ref[k]), f"{k} differs from the packed call"

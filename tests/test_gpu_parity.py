@@ -288,6 +288,36 @@ def test_slices_of_a_fused_projection(oracle, name):
         assert np.array_equal(f64(got), ref[k]), f"{k} differs from the packed call"
 
 
+@pytest.mark.parametrize("k_h", [1.0, 0.0])
+@pytest.mark.parametrize("dtype,d", [("fp32", 64), ("fp32", 128), ("bf16", 64), ("bf16", 128)])
+def test_rows_far_apart_read_nothing_between_them(wide_tiles, dtype, d, k_h):
+    # tokens 512 MB + 4 KB apart, NaN everywhere else: the offsets of the rows that the block does not
+    # have pass 2^32 and come back into the range of the tensor, 32 KB and more behind a row of it.
+    # Results equal the packed call's bit for bit (same arithmetic, another row pitch)
+    from paper_2509_24006_amd import binding as sla
+    tdt, esz = (torch.float32, 4) if dtype == "fp32" else (torch.bfloat16, 2)
+    N, step = 3, ((1 << 29) + 4096) // esz
+    rng = np.random.default_rng(d)
+    x = {k: wl.round_to_bf16(rng.standard_normal((1, 1, N, d)).astype(np.float32)) for k in ("Q", "K", "V", "dO")}
+    x["Proj"] = wl.round_to_bf16((rng.standard_normal((d, d)) * 0.05).astype(np.float32))
+    buf = torch.full(((N - 1) * step + 8 * d,), float("nan"), device="cuda", dtype=tdt)
+    view = lambda i: buf.as_strided((1, 1, N, d), (step, step, step, 1), i * d)
+    Q, K, V, dO, O, dQ, dK, dV = (view(i) for i in range(8))
+    for t, k in ((Q, "Q"), (K, "K"), (V, "V"), (dO, "dO")):
+        t.copy_(torch.from_numpy(x[k]))
+    W = torch.from_numpy(x["Proj"]).cuda().to(tdt)
+    dW = torch.empty((d, d), dtype=torch.float32, device="cuda")
+    for bq in (64, 128):
+        ref = run_gpu(x, dtype, k_h, 0.0, bq=bq)
+        p = sla.make_params(1, 1, N, d, k_h, 0.0, tdt, bq=bq, layout=sla.SLA_STRIDED, strides=(step, step, step))
+        Mc, luts, _ = sla.sla_build_mask(p, Q, K)
+        _, saved = sla.sla_forward(p, Q, K, V, W, Mc, luts, O=O)
+        sla.sla_backward(p, Q, K, V, W, Mc, luts, saved, dO, out=(dQ, dK, dV, dW))
+        torch.cuda.synchronize()
+        for k, got in (("O", O), ("dQ", dQ), ("dK", dK), ("dV", dV), ("dW", dW)):
+            assert np.array_equal(got.double().cpu().numpy(), ref[k]), f"{k} differs from the packed call (bq = {bq})"
+
+
 def test_classify_given_scores_with_ties(oracle):
     from paper_2509_24006_amd import binding as sla
     rng = np.random.default_rng(0)
