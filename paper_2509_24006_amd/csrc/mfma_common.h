@@ -663,6 +663,33 @@ __device__ __forceinline__ void phi_fragments(const bf16x8 (&xf)[KT], int phi, b
   phi_fragments<KT>(xf, phi, out, mx, inv);
 }
 
+// phi without the softmax map's normaliser (the exponentials relative to the token's maximum): enough
+// where phi enters numerator and denominator of the same quotient.
+template <int KT>
+__device__ __forceinline__ void phi_fragments_raw(const bf16x8 (&xf)[KT], int phi, bf16x8 (&out)[KT]) {
+  if (phi != 0) {
+    float mx, inv;
+    phi_fragments<KT>(xf, phi, out, mx, inv);
+    return;
+  }
+  float mx = -INFINITY;
+#pragma unroll
+  for (int t = 0; t < KT; ++t)
+#pragma unroll
+    for (int s = 0; s < 8; ++s) mx = fmaxf(mx, (float)xf[t][s]);
+  mx = half_max(mx);
+  if (__any(!(fabsf(mx) <= 1e38f))) {   // (the product below would overflow)
+    float inv;
+    phi_fragments<KT>(xf, phi, out, mx, inv);
+    return;
+  }
+  const float off = -mx * kLog2e;
+#pragma unroll
+  for (int t = 0; t < KT; ++t)
+#pragma unroll
+    for (int s = 0; s < 8; ++s) out[t][s] = (__bf16)fast_exp2(fmaf((float)xf[t][s], kLog2e, off));
+}
+
 __device__ __forceinline__ float phi_val(float x, int phi, float mx, float inv) {
   return phi == 0 ? fast_exp2((x - mx) * kLog2e) * inv : (x > 0.0f ? x + 1.0f : fast_exp2(x * kLog2e));
 }

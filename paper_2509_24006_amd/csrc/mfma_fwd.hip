@@ -179,11 +179,10 @@ struct FwdLds {
   // After the loop the slots hold the exchange between the two key streams, H_i and the
   // projection matrix; the softmax statistics have a KB of their own behind the slots.
   static constexpr int TILE = SwzTile<D>::BYTES;
-  static constexpr int XCH_HALF = (D / 2) * 64 * 4;       // C registers of one query half
-  static_assert(XCH_HALF <= TILE, "exchange areas are laid over tile slots");
   static constexpr int STAT = 4 * TILE;                  // softmax statistics of the four waves (1 KB)
   static constexpr int ZOFF = STAT + 1024;               // Z_i (D floats)
-  static constexpr int BYTES = ZOFF + D * 4;
+  static constexpr int DEN = ZOFF + D * 4;               // halves of the denominator of O^l (512 bytes)
+  static constexpr int BYTES = DEN + 512;
 };
 // Query blocks of 128 (or 256) tokens: QT = 2 adjacent 64-query tiles, which have the same list of
 // critical key blocks, share one workgroup of eight waves.  K_j and V_j are then fetched into LDS
@@ -199,7 +198,7 @@ __global__ __launch_bounds__(256 * QT, QT == 1 ? 2 : 1) void fwd_mfma_kernel(
     int BH, int N, int Tn, Lay lay, int n_h, int n_0, int phi, float scale_log2e, bf16* __restrict__ O,
     bf16* __restrict__ Os, bf16* __restrict__ Ol, float* __restrict__ L) {
   using Lds = FwdLds<D>;
-  constexpr int NT = D / 32, KT = D / 16;
+  constexpr int NT = D / 32, KT = D / 16, HT = NT / 2;
   constexpr int NW = 4 * QT;   // waves that fill a K or V tile together
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int tid = threadIdx.x, wall = tid >> 6, l = tid & 63, g = l >> 5, ln = l & 31;
@@ -288,7 +287,10 @@ __global__ __launch_bounds__(256 * QT, QT == 1 ? 2 : 1) void fwd_mfma_kernel(
   // a sequence whose last key block is partial: its offset and its number of keys
   const int off_tail = (N % kBlk) ? (Tn - 1) * tl.tile_step : -1;
   const int tail_cols = N - (N / kBlk) * kBlk;
-  // per-lane LDS offsets of this wave's operand reads inside a tile (rows 32 par .. of both tiles)
+  // per-lane LDS offsets of this wave's operand reads inside a tile (rows 32 par .. of both tiles).
+  // Accumulator tile et holds feature tile et ^ rot: the half of the features that the wave
+  // finishes by itself comes first, in both waves of a query half.
+  const int rot = wave_uniform(par) * HT;
   int kaddr[KT], vaddr[2][NT];
   {
     TileAddr<D> ad;
@@ -302,7 +304,7 @@ __global__ __launch_bounds__(256 * QT, QT == 1 ? 2 : 1) void fwd_mfma_kernel(
     for (int h = 0; h < 2; ++h)
 #pragma unroll
       for (int et = 0; et < NT; ++et) {
-        vaddr[h][et] = ad.tr(h, et);
+        vaddr[h][et] = ad.tr(h, et ^ rot);
         asm volatile("" : "+v"(vaddr[h][et]));
       }
   }
@@ -447,7 +449,15 @@ __global__ __launch_bounds__(256 * QT, QT == 1 ? 2 : 1) void fwd_mfma_kernel(
       if (s + 1 < n_h) step(p1, any, s + 1, sU, sT);
     }
   }
-  // ---- merge the two key-tile streams (par 0 / par 1) of each query half
+  // ---- closing lines.  The two waves of a query half hold sums over different keys of all features;
+  // each finishes half of the features of the output.  It sends the other half of its O^s to its partner,
+  // forms the numerators of O^l of its queries whole (as its partner does: products are cheaper here
+  // than another exchange) and their product with W for its features; the projection matrix lands
+  // under phi(Q) and the first product.  Bound by instructions (a wave issues one in five cycles or more),
+  // so phi stays without its normaliser, which cancels in O^l, and the two waves sum half of the
+  // denominator each.  (Before: two exchanges, phi normalised, the matrix requested behind the first exchange.  256
+  // heads x 16 query blocks of 2, d = 64: 57.2 -> 53.2 us a launch, 12 x 146 of 7, d = 128: 82.1 -> 80.0; 12 x 512
+  // of 26 even to 1 % less, there the loop counts.)
   lsum = half_sum(lsum);
   if (g == 0) {
     ml[((par * 2 + qh) * 32 + ln) * 2 + 0] = m;
@@ -455,6 +465,7 @@ __global__ __launch_bounds__(256 * QT, QT == 1 ? 2 : 1) void fwd_mfma_kernel(
   }
   wait_vm0();        // this wave's share of H_i has landed
   __syncthreads();   // also: all waves are done with the K / V tiles
+  if (n_0 > 0) issue_matrix(WTp, x0, x1);
   const float m_o = ml[(((par ^ 1) * 2 + qh) * 32 + ln) * 2 + 0];
   const float l_o = ml[(((par ^ 1) * 2 + qh) * 32 + ln) * 2 + 1];
   float cw = 0.0f, Lval = -INFINITY;
@@ -465,119 +476,98 @@ __global__ __launch_bounds__(256 * QT, QT == 1 ? 2 : 1) void fwd_mfma_kernel(
     cw = a_me / ltot;
     Lval = mstar * c2 * kLn2 + logf(ltot);
   }
+  if (L && par == 0 && g == 0 && qok) L[(size_t)bh * N + q0 + qrow] = Lval;
 #pragma unroll
   for (int et = 0; et < NT; ++et)
 #pragma unroll
     for (int r = 0; r < 16; ++r) oT[et][r] *= cw;
-  float* myx = reinterpret_cast<float*>(gsm + (qh ? x1 : x0));   // exchange, then this query half's staging
-  unsigned char* mystage = reinterpret_cast<unsigned char*>(myx);
-  if (par == 1) {
-#pragma unroll
-    for (int et = 0; et < NT; ++et)
-#pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4)
-        *reinterpret_cast<f32x4*>(myx + ((et * 4 + r4) * 64 + l) * 4) =
-            f32x4{oT[et][4 * r4], oT[et][4 * r4 + 1], oT[et][4 * r4 + 2], oT[et][4 * r4 + 3]};
-  }
-  __syncthreads();
-  const size_t orow0 = ((size_t)bh * N + q0 + 32 * qh) * D;   // first query of this wave
-  const int wrows = rows - 32 * qh;                           // valid ones among its 32
-  if (par == 0) {
-#pragma unroll
-    for (int et = 0; et < NT; ++et)
-#pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4) {
-        const f32x4 xv = *reinterpret_cast<const f32x4*>(myx + ((et * 4 + r4) * 64 + l) * 4);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) oT[et][4 * r4 + r] += xv[r];
-      }
-    if (L && g == 0 && qok) L[(size_t)bh * N + q0 + qrow] = Lval;
-    if (Os) store_rows_bf16<NT>(mystage, oT, Os + orow0, D, wrows, l);
-  }
-  // ---- linear branch: wave par computes O^l for features [par D/2, (par+1) D/2) of its queries
-  // (both waves accumulate their share of O^l W into oT; par 1 starts again from zero)
-  if (par == 1) {
-#pragma unroll
-    for (int et = 0; et < NT; ++et) oT[et] = zero_f32x16();
-  }
+  float* const dl = reinterpret_cast<float*>(gsm + Lds::DEN);   // [par][qh][32]
+  constexpr int RB = 16 * T::ROW_BYTES;
+  TileAddr<D> ma;                // rows 32 (et % 2) + ln of a 64-row tile: + 2 RB per odd tile
+  ma.init(0, l);
+  bf16x8 olf[NT][2];             // numerators of O^l, tile et ^ rot in place et, as operands of the product with W
+  f32x16 own[HT];                // the first half of them, unrounded
   if (n_0 > 0) {
-    __syncthreads();   // the exchange area is free: the projection matrix goes there
-    issue_matrix(WTp, x0, x1);
     // phi(Q) of this lane's query: the lane holds features 16 t + 8 g + s, its partner the rest
     const float* Z = reinterpret_cast<const float*>(gsm + Lds::ZOFF);
     bf16x8 qp[KT];
-    phi_fragments<KT>(qf, phi, qp);
+    phi_fragments_raw<KT>(qf, phi, qp);
     float den = 0.0f;
 #pragma unroll
-    for (int t = 0; t < KT; ++t) {
-      const f32x4 z0 = *reinterpret_cast<const f32x4*>(Z + 16 * t + 8 * g);
-      const f32x4 z1 = *reinterpret_cast<const f32x4*>(Z + 16 * t + 8 * g + 4);
+    for (int k = 0; k < KT / 2; ++k) {
+      const float* zk = Z + 16 * (k + (KT / 2) * (rot / HT)) + 8 * g;
+      const f32x4 z0 = *reinterpret_cast<const f32x4*>(zk), z1 = *reinterpret_cast<const f32x4*>(zk + 4);
+      const bf16x8 x = rot ? qp[KT / 2 + k] : qp[k];
 #pragma unroll
-      for (int s2 = 0; s2 < 8; ++s2) den = fmaf((float)qp[t][s2], s2 < 4 ? z0[s2] : z1[s2 - 4], den);
+      for (int s2 = 0; s2 < 8; ++s2) den = fmaf((float)x[s2], s2 < 4 ? z0[s2] : z1[s2 - 4], den);
     }
     den = half_sum(den);
-    const float dinv = 1.0f / den;
-    constexpr int HT = NT / 2;     // e-tiles per wave
-    TileAddr<D> ma;                // rows 32 (et % 2) + ln of a 64-row tile: + 2 RB per odd tile
-    ma.init(0, l);
-    constexpr int RB = 16 * T::ROW_BYTES;
-    f32x16 ol[HT];
+    if (g == 0) dl[(par * 2 + qh) * 32 + ln] = den;
 #pragma unroll
-    for (int h2 = 0; h2 < HT; ++h2) {
-      const int et = par * HT + h2;
-      ol[h2] = zero_f32x16();
+    for (int et = 0; et < NT; ++et) {
+      const int er = et ^ rot, base = (er / 2 ? h1 : h0) + (er % 2) * 2 * RB;
+      f32x16 ol = zero_f32x16();
 #pragma unroll
-      for (int t = 0; t < KT; ++t)
-        ol[h2] = mfma32(lds_row(gsm, ma.row(t) + (et / 2 ? h1 : h0) + (et % 2) * 2 * RB), qp[t], ol[h2]);
+      for (int t = 0; t < KT; ++t) ol = mfma32(lds_row(gsm, ma.row(t) + base), qp[t], ol);
 #pragma unroll
-      for (int r = 0; r < 16; ++r) ol[h2][r] *= dinv;
+      for (int u = 0; u < 2; ++u) olf[et][u] = c_to_operand(ol, u);
+      if (et < HT) own[et] = ol;
     }
     wait_vm0();
-    __syncthreads();   // the projection matrix has landed; H_i is no longer needed
-    // O^T[e'][q] += sum_{e in this wave's tiles} W[e][e'] O^l[q][e]
+    __syncthreads();   // the projection matrix has landed; H_i is no longer needed: the exchange goes there
+  }
+  float* const xch = reinterpret_cast<float*>(gsm + (qh ? h1 : h0));
+#pragma unroll
+  for (int h2 = 0; h2 < HT; ++h2)
+#pragma unroll
+    for (int r4 = 0; r4 < 4; ++r4)
+      *reinterpret_cast<f32x4*>(xch + par * (Lds::TILE / 8) + ((h2 * 4 + r4) * 64 + l) * 4) =
+          f32x4{oT[HT + h2][4 * r4], oT[HT + h2][4 * r4 + 1], oT[HT + h2][4 * r4 + 2], oT[HT + h2][4 * r4 + 3]};
+  f32x16 lin[HT];
+  if (n_0 > 0) {
+    // lin[e'][q] = sum_e W[e][e'] numerator[q][e], tiles e in the order of olf
 #pragma unroll
     for (int h2 = 0; h2 < HT; ++h2) {
-      const int et = par * HT + h2;
+      const int ep = h2 ^ rot, base = (ep / 2 ? x1 : x0) + (ep % 2) * 2 * RB;
+      lin[h2] = zero_f32x16();
 #pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const bf16x8 b = c_to_operand(ol[h2], u);
-#pragma unroll
-        for (int ep = 0; ep < NT; ++ep)
-          oT[ep] = mfma32(lds_row(gsm, ma.row(2 * et + u) + (ep / 2 ? x1 : x0) + (ep % 2) * 2 * RB), b, oT[ep]);
-      }
-    }
-    if (Ol)
-      store_rows_bf16<HT>(gsm + (w < 2 ? h0 : h1) + (w & 1) * (32 * (64 * HT + 16)), ol, Ol + orow0 + par * (D / 2), D,
-                          wrows, l);
-    __syncthreads();   // everyone is done with the projection matrix
-    if (par == 1) {
-#pragma unroll
-      for (int et = 0; et < NT; ++et)
-#pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4)
-          *reinterpret_cast<f32x4*>(myx + ((et * 4 + r4) * 64 + l) * 4) =
-              f32x4{oT[et][4 * r4], oT[et][4 * r4 + 1], oT[et][4 * r4 + 2], oT[et][4 * r4 + 3]};
-    }
-    __syncthreads();
-    if (par == 0) {
-#pragma unroll
-      for (int et = 0; et < NT; ++et)
-#pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4) {
-          const f32x4 xv = *reinterpret_cast<const f32x4*>(myx + ((et * 4 + r4) * 64 + l) * 4);
-#pragma unroll
-          for (int r = 0; r < 4; ++r) oT[et][4 * r4 + r] += xv[r];
-        }
+      for (int t = 0; t < KT; ++t) lin[h2] = mfma32(lds_row(gsm, ma.row(t ^ (2 * rot)) + base), olf[t / 2][t % 2], lin[h2]);
     }
   }
-  if (par == 0) {
-    store_rows_bf16<NT>(mystage, oT, O + lay.head(bh) + (size_t)(q0 + 32 * qh) * lay.ts, lay.ts, wrows, l);
-    if (n_0 == 0 && Ol) {   // no marginal block: O^l is identically zero
+  __syncthreads();     // the exchange is there; everyone is done with the projection matrix: staging goes there
 #pragma unroll
-      for (int et = 0; et < NT; ++et) oT[et] = zero_f32x16();
-      store_rows_bf16<NT>(mystage, oT, Ol + orow0, D, wrows, l);
+  for (int h2 = 0; h2 < HT; ++h2)
+#pragma unroll
+    for (int r4 = 0; r4 < 4; ++r4) {
+      const f32x4 xv = *reinterpret_cast<const f32x4*>(xch + (par ^ 1) * (Lds::TILE / 8) + ((h2 * 4 + r4) * 64 + l) * 4);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) oT[h2][4 * r4 + r] += xv[r];
     }
+  f32x16 (&o)[HT] = *reinterpret_cast<f32x16 (*)[HT]>(&oT[0]);
+  static_assert(32 * (64 * HT + 16) <= Lds::TILE / 2, "staging of two waves fits in a tile slot");
+  unsigned char* const stage = gsm + (qh ? x1 : x0) + par * (Lds::TILE / 2);
+  const size_t orow0 = ((size_t)bh * N + q0 + 32 * qh) * D + par * (D / 2);   // first query of this wave
+  const int wrows = rows - 32 * qh;                                           // valid ones among its 32
+  if (Os) store_rows_bf16<HT>(stage, o, Os + orow0, D, wrows, l);
+  if (n_0 > 0) {
+    const float dinv = 1.0f / (dl[qh * 32 + ln] + dl[(2 + qh) * 32 + ln]);
+#pragma unroll
+    for (int h2 = 0; h2 < HT; ++h2)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[h2][r] = fmaf(lin[h2][r], dinv, o[h2][r]);
+    if (Ol) {
+#pragma unroll
+      for (int h2 = 0; h2 < HT; ++h2)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) own[h2][r] *= dinv;
+      store_rows_bf16<HT>(stage, own, Ol + orow0, D, wrows, l);
+    }
+  } else if (Ol) {   // no marginal block: O^l is identically zero
+#pragma unroll
+    for (int h2 = 0; h2 < HT; ++h2) own[h2] = zero_f32x16();
+    store_rows_bf16<HT>(stage, own, Ol + orow0, D, wrows, l);
   }
+  store_rows_bf16<HT>(stage, o, O + lay.head(bh) + (size_t)(q0 + 32 * qh) * lay.ts + par * (D / 2), lay.ts, wrows, l);
 }
 
 __global__ void fill_zero_f32_kernel(float* __restrict__ p, size_t n) {
