@@ -104,3 +104,22 @@ def test_autograd_casts_a_float_projection_weight():
     assert W32.grad.dtype == torch.float32 and torch.equal(W32.grad.to(torch.bfloat16), W16.grad)
     with pytest.raises(sla.SLAError, match="W"):
         sla.sla_forward(mask[0], Q.detach(), K.detach(), V.detach(), W32.detach(), mask[1], mask[2])
+
+
+@pytest.mark.parametrize("kh, kl", [(0.12, 0.15), (0.0, 0.1), (0.5, 0.5)])   # (no critical, no marginal block)
+def test_attention_without_gradients_gives_the_same_output(kh, kl):
+    # no tensor needs a gradient, or gradients are switched off: no tensors are saved, O is the same
+    from paper_2509_24006_amd.autograd import sla_attention
+    for name in ("small_fp32", "small_bf16_d64", "small_bf16"):
+        w = wl.WORKLOADS[name]
+        x = wl.make_inputs(w)
+        tdt = torch.float32 if w.dtype == "fp32" else torch.bfloat16
+        Q, K, V, W = (torch.from_numpy(x[k]).cuda().to(tdt) for k in ("Q", "K", "V", "Proj"))
+        plain = sla_attention(Q, K, V, W, kh, kl)
+        Qg = Q.clone().requires_grad_(True)
+        O = sla_attention(Qg, K, V, W, kh, kl)
+        with torch.no_grad():
+            off = sla_attention(Qg, K, V, W, kh, kl)
+        assert O.requires_grad and not off.requires_grad and not plain.requires_grad
+        assert torch.equal(O, plain) and torch.equal(O, off)
+        assert torch.autograd.grad(O.float().sum(), Qg)[0].shape == Q.shape
