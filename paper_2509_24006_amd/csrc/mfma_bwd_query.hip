@@ -24,26 +24,36 @@ namespace {
 template <int D>
 struct PreLds {
   static constexpr int TILE = SwzTile<D>::BYTES;
-  // slots: 0 dO, then dO^l | 1 O^s, then a, then rows 64.. of H_i | 2 O^l, then rows 0..63 of H_i | 3 Q
-  // (a fifth slot for H_i would let all of it arrive early, but 5 tiles + 1 KB is just over half a CU's LDS)
+  // slots: 0 dO, then dO^l | 1 O^s, then rows 0..63 of H_i, then a | 2 O^l, then rows 64.. of H_i, then dO
+  // for the loop that follows | 3 Q.  Behind the last product 0 and 1 take the first K, V pair of that
+  // loop, 2, 3 and what lies behind them the output staging.
   static constexpr int F_OFF = 4 * TILE;
-  static constexpr int BYTES = F_OFF + 4 * kBlk * 4 + D * 4;   // D^l partial [par][q], dot partial [par][q], Z_i
-  static constexpr int STG = 32 * (64 * (D / 32) + 16);   // staging of one wave, laid over slots 1..3
-  static_assert(4 * STG <= 3 * TILE, "output staging fits over three slots");
+  static constexpr int F_BYTES = 4 * kBlk * 4 + D * 4;   // D^l partial [par][q], dot partial [par][q], Z_i
+  static constexpr int STG = 32 * (64 * (D / 32) + 16);  // staging of one of the D / 32 waves that store dH_i
+  static constexpr int TAIL = (D / 32) * STG - 2 * TILE;
+  static constexpr int BYTES = F_OFF + (F_BYTES > TAIL ? F_BYTES : TAIL);
 };
 
 // FUSED: the body runs as the prologue of the row-wise dQ kernel (below) for the same query block.
 // It then leaves the block's Q and dO operand fragments (qf, gf), every lane's D^s (ds_lane) and the
 // linear-branch part of dQ (lin: this wave's half of the features, in the register layout of the
-// dQ^T accumulators) in registers instead of writing that part to memory.
-template <int D, bool FUSED>
+// dQ^T accumulators) in registers instead of writing that part to memory, and calls first_pair once
+// slots 0 and 1 are free, to request the loop's first tiles.
+// Bound by latency (a chain of short phases, two or three workgroups per CU), hence the order: dQ^phi
+// before dH_i, so that H_i comes into slots that are free early and lands under dO^l and phi(Q), dO
+// comes back under the dH_i product and the first K, V pair under the stores.  (dH_i first, the
+// second half of H_i requested behind it and Q, dO, K, V behind the stores, each waited for at once, and
+// the feature map chosen at run time -> now: 256 heads x 16 query blocks, d = 64, 84.3 -> 78.4 us a launch;
+// 12 x 146, d = 128, 131 -> 121; 2 x 18 21.2 -> 19.3; 12 x 512 705 either way, there the loop counts.)
+template <int D, bool FUSED, int PHI, class First>
 __device__ __forceinline__ void pre_body(
     unsigned char* smem, const int i, const int bh,
     const bf16* __restrict__ Q, const bf16* __restrict__ dO, const bf16* __restrict__ W,
     const bf16* __restrict__ Os, const bf16* __restrict__ Ol, const bf16* __restrict__ H16,
     const float* __restrict__ Zs, int N,
-    int Tn, Lay lay, int n_0, int phi, float* __restrict__ Ds, bf16* __restrict__ dHZ,
-    bf16* __restrict__ dQlin, bf16x8 (&qf)[D / 16], bf16x8 (&gf)[D / 16], float& ds_lane, f32x16 (&lin)[D / 64]) {
+    int Tn, Lay lay, int n_0, float* __restrict__ Ds, bf16* __restrict__ dHZ,
+    bf16* __restrict__ dQlin, bf16x8 (&qf)[D / 16], bf16x8 (&gf)[D / 16], float& ds_lane, f32x16 (&lin)[D / 64],
+    First&& first_pair) {
   using Lds = PreLds<D>;
   using T = SwzTile<D>;
   constexpr int NT = D / 32, KT = D / 16, HT = NT / 2;
@@ -99,16 +109,24 @@ __device__ __forceinline__ void pre_body(
     if (par == 0 && g == 0 && qok) Ds[(size_t)bh * N + q0 + qrow] = ds;
     ds_lane = ds;
   }
-  if (n_0 > 0 || FUSED) {
-#pragma unroll
-    for (int t = 0; t < KT; ++t) qf[t] = lds_row(smem, qa.row(t) + S3);
-  }
   if (n_0 == 0) {   // no linear branch: nothing else to do (uniform over the grid)
 #pragma unroll
     for (int h2 = 0; h2 < HT; ++h2) lin[h2] = zero_f32x16();
+    if (FUSED) {
+#pragma unroll
+      for (int t = 0; t < KT; ++t) qf[t] = lds_row(smem, qa.row(t) + S3);
+      __syncthreads();   // the tiles are consumed
+      first_pair();
+    }
     return;
   }
-  __syncthreads();   // dO and O^s are consumed: their slots take dO^l and a
+  // Q in operand layout, k-step t ^ rot in place t: the features of which the wave forms a come first
+  const int rot = wave_uniform(par) * (KT / 2);
+  bf16x8 qx[KT];
+#pragma unroll
+  for (int t = 0; t < KT; ++t) qx[t] = lds_row(smem, qa.row(t ^ rot) + S3);
+  __syncthreads();   // dO and O^s are consumed: their slots take dO^l and the first half of H_i
+  issue_tile_load<D>(Hrow, min(kBlk, D), lds0, S1, ldv);
   const int rowb = qrow * T::ROW_BYTES, rsw = swz<D>(qrow);
   // dO^l^T[b][q] = sum_e W[b][e] dO[q][e]; this wave: b-tiles par*HT .. par*HT+HT-1
   float dl = 0.0f;
@@ -137,62 +155,96 @@ __device__ __forceinline__ void pre_body(
   }
   dl = half_sum(dl);
   if (g == 0) dlp[par * kBlk + qrow] = dl;
-  // phi(Q), its normaliser, and a = phi(Q) / den as a row-major tile (this wave: half of the features)
-  float qmx = 0.0f, qinv = 1.0f;
-  float den = 0.0f;
-  float yq[KT][8];
-  if (phi == 0) {   // softmax over the features: the exponentials are formed once
-    qmx = -INFINITY;
-#pragma unroll
-    for (int t = 0; t < KT; ++t)
-#pragma unroll
-      for (int s = 0; s < 8; ++s) qmx = fmaxf(qmx, (float)qf[t][s]);
-    qmx = half_max(qmx);
-    float sum = 0.0f;
-#pragma unroll
-    for (int t = 0; t < KT; ++t)
-#pragma unroll
-      for (int s = 0; s < 8; ++s) {
-        yq[t][s] = fast_exp2(((float)qf[t][s] - qmx) * kLog2e);
-        sum += yq[t][s];
-      }
-    sum = half_sum(sum);
-    qinv = 1.0f / sum;
-  }
+  __syncthreads();   // dO^l is complete; O^l is consumed: its slot takes the rest of H_i
+  if (D > kBlk) issue_tile_load<D>(Hrow + (size_t)kBlk * D, D - kBlk, lds0, S2, ldv);
+  const float Dl = dlp[qrow] + dlp[kBlk + qrow];
+  // phi(Q), its normaliser, and this wave's half of the features of a = phi(Q) / den
+  float qmx, qinv, den = 0.0f;
+  bf16x8 qp[KT], av[KT / 2];
+  phi_fragments<KT>(qx, PHI, qp, qmx, qinv);
 #pragma unroll
   for (int t = 0; t < KT; ++t) {
-    const f32x4 z0 = *reinterpret_cast<const f32x4*>(zl + 16 * t + 8 * g);
-    const f32x4 z1 = *reinterpret_cast<const f32x4*>(zl + 16 * t + 8 * g + 4);
+    const float* zt = zl + 16 * (t ^ rot) + 8 * g;
+    const f32x4 z0 = *reinterpret_cast<const f32x4*>(zt), z1 = *reinterpret_cast<const f32x4*>(zt + 4);
 #pragma unroll
-    for (int s = 0; s < 8; ++s) {
-      const float x = (float)qf[t][s];
-      const float y = (float)(__bf16)(phi == 0 ? yq[t][s] * qinv : (x > 0.0f ? x + 1.0f : fast_exp2(x * kLog2e)));
-      yq[t][s] = y;
-      den = fmaf(y, s < 4 ? z0[s] : z1[s - 4], den);
-    }
+    for (int s = 0; s < 8; ++s) den = fmaf((float)qp[t][s], s < 4 ? z0[s] : z1[s - 4], den);
   }
   den = half_sum(den);
   const float dinv = qok ? 1.0f / den : 0.0f;
 #pragma unroll
-  for (int t = 0; t < KT; ++t) {
-    if ((t >= KT / 2) != (par == 1)) continue;
-    bf16x8 av;
+  for (int t = 0; t < KT / 2; ++t)
 #pragma unroll
-    for (int s = 0; s < 8; ++s) av[s] = (__bf16)(yq[t][s] * dinv);
-    *reinterpret_cast<bf16x8*>(smem + S1 + rowb + (((2 * t + g) ^ rsw) << 4)) = av;
+    for (int s = 0; s < 8; ++s) av[t][s] = (__bf16)((float)qp[t][s] * dinv);
+  wait_vm0();
+  __syncthreads();   // H_i has landed
+  // dQ^phi^T[c][q] = (sum_b H[c][b] dO^l[q][b] - D^l_q Z[c]) / den_q; this wave: c-tiles of par.  H^T is
+  // read with the transposing read, whose k order is the one a C tile hands over, so dO^l is picked
+  // up in that order too (two 8-byte pieces per k-step: features 16 t + 4 g .. and 16 t + 8 + 4 g ..)
+  TileAddr<D> ad;
+  ad.init(0, l);
+  f32x16 dq[HT];
+  float dot = 0.0f;
+  float yc[HT][16];
+#pragma unroll
+  for (int h2 = 0; h2 < HT; ++h2) dq[h2] = zero_f32x16();
+#pragma unroll
+  for (int t = 0; t < KT; ++t) {
+    const bf16x4 v0 = *reinterpret_cast<const bf16x4*>(smem + S0 + rowb + (((2 * t) ^ rsw) << 4) + 8 * g);
+    const bf16x4 v1 = *reinterpret_cast<const bf16x4*>(smem + S0 + rowb + (((2 * t + 1) ^ rsw) << 4) + 8 * g);
+    bf16x8 gb;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      gb[e] = v0[e];
+      gb[4 + e] = v1[e];
+    }
+    const int mbase = (t / 4 ? S2 : S1) + (t % 4) * RB;   // rows b = 16 t .. of the stored matrix
+#pragma unroll
+    for (int h2 = 0; h2 < HT; ++h2) {
+      const int ct = par * HT + h2;
+      dq[h2] = mfma32(lds_tr<D>(smem, ad.tr(0, ct) + mbase, ad.tr(1, ct) + mbase), gb, dq[h2]);
+    }
   }
-  __syncthreads();   // dO^l and a are complete; O^l is consumed: its slot takes rows 0..63 of H_i
-  issue_tile_load<D>(Hrow, min(kBlk, D), lds0, S2, ldv);
-  const float Dl = dlp[qrow] + dlp[kBlk + qrow];
-  bf16* out = dHZ + ((size_t)bh * Tn + i) * (D * D + D);
+#pragma unroll
+  for (int h2 = 0; h2 < HT; ++h2) {
+    const int ct = par * HT + h2;
+#pragma unroll
+    for (int r4 = 0; r4 < 4; ++r4) {
+      const int c0 = 32 * ct + 8 * r4 + 4 * g;
+      const f32x4 z4 = *reinterpret_cast<const f32x4*>(zl + c0);
+      const bf16x4 q4 = *reinterpret_cast<const bf16x4*>(smem + S3 + rowb + (((c0 >> 3) ^ rsw) << 4) + (c0 & 7) * 2);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float v = (dq[h2][4 * r4 + r] - Dl * z4[r]) * dinv;
+        const float x = (float)q4[r];
+        const float y = PHI == 0 ? phi_val(x, 0, qmx, qinv) : (x > 0.0f ? 1.0f : fast_exp2(x * kLog2e));
+        dq[h2][4 * r4 + r] = v;
+        yc[h2][4 * r4 + r] = y;
+        dot = fmaf(v, y, dot);
+      }
+    }
+  }
+  dot = half_sum(dot);
+  if (g == 0) dotp[par * kBlk + qrow] = dot;
+  __syncthreads();   // H_i is consumed: its slots take a and dO
+#pragma unroll
+  for (int t = 0; t < KT / 2; ++t)
+    *reinterpret_cast<bf16x8*>(smem + S1 + rowb + (((2 * (t ^ rot) + g) ^ rsw) << 4)) = av[t];
+  if (FUSED) tl.load_first(head_rsrc<D>(dO + lay.head(bh), N, 2 * lay.ts), i, S2);
+  {
+    const float dtot = PHI == 0 ? dotp[qrow] + dotp[kBlk + qrow] : 0.0f;
+#pragma unroll
+    for (int h2 = 0; h2 < HT; ++h2)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) lin[h2][r] = yc[h2][r] * (dq[h2][r] - dtot);
+  }
+  __syncthreads();   // a is complete
   // dH_i^T[b][c] = sum_q dO^l[q][b] a[q][c]: both operands contracted over tile rows; formed with b
   // along the lanes (C tile rows = c), so that a lane holds consecutive c of one stored row.
   // Wave w owns b-tile w.  dZ_i[c] = - sum_q a[q][c] D^l_q rides along as one more column: the wave
   // multiplies its own c-tile of a^T by D^l (in the k order of the transposing read).
   static_assert(NT <= 4, "one b-tile per wave");
-  TileAddr<D> ad;
-  ad.init(0, l);
   f32x16 acc[NT];
+  bf16x4 zpk[4];
 #pragma unroll
   for (int ct = 0; ct < NT; ++ct) acc[ct] = zero_f32x16();
   if (w < NT) {
@@ -217,94 +269,60 @@ __device__ __forceinline__ void pre_body(
         if (ct == w) zacc = mfma32(ao, dlc, mfma32(ao, dlb, zacc));   // every column of this tile: sum_q a[q][c] D^l_q
       }
     }
+#pragma unroll
+    for (int r4 = 0; r4 < 4; ++r4)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) zpk[r4][r] = (__bf16)(-zacc[4 * r4 + r]);
+  }
+  if (FUSED) wait_vm0();   // dO is back
+  __syncthreads();         // dO^l and a are consumed
+  if (FUSED) {
+    first_pair();
+#pragma unroll
+    for (int t = 0; t < KT; ++t) {
+      qf[t] = lds_row(smem, qa.row(t) + S3);
+      gf[t] = lds_row(smem, qa.row(t) + S2);
+    }
+#pragma unroll
+    for (int t = 0; t < KT; ++t) {
+      pin_loaded(qf[t]);
+      pin_loaded(gf[t]);
+    }
+    __syncthreads();       // Q and dO are in registers: slots 2 and 3 become the output staging
+  }
+  bf16* out = dHZ + ((size_t)bh * Tn + i) * (D * D + D);
+  unsigned char* stage = smem + S2 + wu * Lds::STG;
+  if (w < NT) {
+    store_rows_bf16<NT>(stage, acc, out + (size_t)(32 * w) * D, D, 32, l);
     if (ln == 0) {
 #pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4) {
-        bf16x4 pk;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) pk[r] = (__bf16)(-zacc[4 * r4 + r]);
-        *reinterpret_cast<bf16x4*>(out + (size_t)D * D + 32 * w + 8 * r4 + 4 * g) = pk;
-      }
+      for (int r4 = 0; r4 < 4; ++r4) *reinterpret_cast<bf16x4*>(out + (size_t)D * D + 32 * w + 8 * r4 + 4 * g) = zpk[r4];
     }
   }
-  __syncthreads();   // a is consumed: its slot takes the other rows of H_i
-  if (D > kBlk) issue_tile_load<D>(Hrow + (size_t)kBlk * D, D - kBlk, lds0, S1, ldv);
-  wait_vm0();
-  __syncthreads();
-  // dQ^phi^T[c][q] = (sum_b H[c][b] dO^l[q][b] - D^l_q Z[c]) / den_q; this wave: c-tiles of par.  H^T is
-  // read with the transposing read, whose k order is the one a C tile hands over, so dO^l is picked
-  // up in that order too (two 8-byte pieces per k-step: features 16 t + 4 g .. and 16 t + 8 + 4 g ..)
-  f32x16 dq[HT];
-  float dot = 0.0f;
-  float yc[HT][16];
-#pragma unroll
-  for (int h2 = 0; h2 < HT; ++h2) dq[h2] = zero_f32x16();
-#pragma unroll
-  for (int t = 0; t < KT; ++t) {
-    const bf16x4 v0 = *reinterpret_cast<const bf16x4*>(smem + S0 + rowb + (((2 * t) ^ rsw) << 4) + 8 * g);
-    const bf16x4 v1 = *reinterpret_cast<const bf16x4*>(smem + S0 + rowb + (((2 * t + 1) ^ rsw) << 4) + 8 * g);
-    bf16x8 gb;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      gb[e] = v0[e];
-      gb[4 + e] = v1[e];
-    }
-    const int mbase = (t / 4 ? S1 : S2) + (t % 4) * RB;   // rows b = 16 t .. of the stored matrix
-#pragma unroll
-    for (int h2 = 0; h2 < HT; ++h2) {
-      const int ct = par * HT + h2;
-      dq[h2] = mfma32(lds_tr<D>(smem, ad.tr(0, ct) + mbase, ad.tr(1, ct) + mbase), gb, dq[h2]);
-    }
-  }
-#pragma unroll
-  for (int h2 = 0; h2 < HT; ++h2) {
-    const int ct = par * HT + h2;
-#pragma unroll
-    for (int r4 = 0; r4 < 4; ++r4) {
-      const int c0 = 32 * ct + 8 * r4 + 4 * g;
-      const f32x4 z4 = *reinterpret_cast<const f32x4*>(zl + c0);
-      const bf16x4 q4 = *reinterpret_cast<const bf16x4*>(smem + S3 + rowb + (((c0 >> 3) ^ rsw) << 4) + (c0 & 7) * 2);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float v = (dq[h2][4 * r4 + r] - Dl * z4[r]) * dinv;
-        const float x = (float)q4[r];
-        const float y = phi == 0 ? phi_val(x, 0, qmx, qinv) : (x > 0.0f ? 1.0f : fast_exp2(x * kLog2e));
-        dq[h2][4 * r4 + r] = v;
-        yc[h2][4 * r4 + r] = y;
-        dot = fmaf(v, y, dot);
-      }
-    }
-  }
-  dot = half_sum(dot);
-  if (g == 0) dotp[par * kBlk + qrow] = dot;
-  __syncthreads();   // also: every wave is done with the tiles, slots 1..3 become the output staging
-  const float dtot = phi == 0 ? dotp[qrow] + dotp[kBlk + qrow] : 0.0f;
-  unsigned char* stage = smem + S1 + wu * Lds::STG;
-  if (w < NT) store_rows_bf16<NT>(stage, acc, out + (size_t)(32 * w) * D, D, 32, l);
-#pragma unroll
-  for (int h2 = 0; h2 < HT; ++h2)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) lin[h2][r] = yc[h2][r] * (dq[h2][r] - dtot);
   // (bf16: the row-wise kernel adds this part to its float sum and rounds once more; a float
   // round trip would move 2 x 4 bytes per element instead of 2 x 2)
-  if (!FUSED) store_rows_bf16<HT>(stage, lin, dQlin + base + (size_t)(32 * qh) * D + par * (D / 2), D, rows - 32 * qh, l);
+  if (!FUSED) {
+    __syncthreads();   // (four waves' staging areas need not lie where the D / 32 above did)
+    store_rows_bf16<HT>(smem + S1 + wu * (32 * (64 * HT + 16)), lin,
+                        dQlin + base + (size_t)(32 * qh) * D + par * (D / 2), D, rows - 32 * qh, l);
+  }
 }
 
 // The query side on its own (query blocks of several tiles, whose dQ kernel shares a workgroup
 // between two tiles): one workgroup per 64-token tile.
-template <int D>
+template <int D, int PHI>
 __global__ __launch_bounds__(256, 2) void bwd_pre_mfma_kernel(
     const bf16* __restrict__ Q, const bf16* __restrict__ dO, const bf16* __restrict__ W,
     const bf16* __restrict__ Os, const bf16* __restrict__ Ol, const bf16* __restrict__ H16,
     const float* __restrict__ Zs, int N,
-    int Tn, Lay lay, int n_0, int phi, float* __restrict__ Ds, bf16* __restrict__ dHZ,
+    int Tn, Lay lay, int n_0, float* __restrict__ Ds, bf16* __restrict__ dHZ,
     bf16* __restrict__ dQlin) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   bf16x8 qf[D / 16], gf[D / 16];
   f32x16 lin[D / 64];
   float ds;
-  pre_body<D, false>(smem, blockIdx.x, blockIdx.y, Q, dO, W, Os, Ol, H16, Zs, N, Tn, lay, n_0, phi, Ds, dHZ, dQlin, qf,
-                     gf, ds, lin);
+  pre_body<D, false, PHI>(smem, blockIdx.x, blockIdx.y, Q, dO, W, Os, Ol, H16, Zs, N, Tn, lay, n_0, Ds, dHZ, dQlin, qf,
+                          gf, ds, lin, [] {});
 }
 
 // LDS of the row-wise dQ kernel: two pair buffers (K_j and V_j of the step in use and of the next
@@ -336,11 +354,12 @@ struct PairLds {
 struct PreArgs {
   const bf16 *W, *Os, *Ol, *H16;
   const float* Zs;
-  int n_0, phi;
+  int n_0;
   float* Ds_out;
   bf16* dHZ;
 };
-template <int D, int QT, bool FUSED>
+// PHI: the feature map, 0 softmax over the features, 1 elu + 1 (used by the first part).
+template <int D, int QT, bool FUSED, int PHI>
 __global__ __launch_bounds__(256 * QT, QT == 1 ? (D == 64 ? 3 : 2) : 1) void bwd_dq_mfma_kernel(
     const bf16* __restrict__ Q, const bf16* __restrict__ K, const bf16* __restrict__ V,
     const bf16* __restrict__ dO, const float* __restrict__ L, const float* __restrict__ Ds,
@@ -370,48 +389,35 @@ __global__ __launch_bounds__(256 * QT, QT == 1 ? (D == 64 ? 3 : 2) : 1) void bwd
   const float sl2 = scale * kLog2e;
   bf16x8 qf[KT], gf[KT];
   f32x16 lin[NT / 2];
-  float ds_pre = 0.0f;
-  if constexpr (FUSED) {
-    // (the first part's own copies of the Q and dO fragments are not kept: holding them across it
-    // costs more registers than the loop below leaves, and the tiles come back from the L2 together
-    // with the first K, V pair)
-    bf16x8 qf0[KT], gf0[KT];
-    pre_body<D, true>(smem, i, bh, Q, dO, pa.W, pa.Os, pa.Ol, pa.H16, pa.Zs, N, Tn, lay, pa.n_0, pa.phi, pa.Ds_out,
-                      pa.dHZ, nullptr, qf0, gf0, ds_pre, lin);
-    __syncthreads();   // every wave is done with the first part's tiles and staging areas
-  }
   TileLoader<D, NW> tl;   // K_j, V_j: all waves of the workgroup
-  TileLoader<D> tq;       // Q_i, dO_i: the four waves of a group, into the group's area
   tl.init(lds_base(smem), wall, l, 2 * lay.ts, N);
-  tq.init(lds_base(smem) + (grp ? Lds::BYTES - Lds::BUF : 0), w, l, 2 * lay.ts, N);
   const BufDesc descK = head_rsrc<D>(K + lay.head(bh), N, 2 * lay.ts);
   const BufDesc descV = head_rsrc<D>(V + lay.head(bh), N, 2 * lay.ts);
   // key block indices of steps s, s + 1, s + 2, fetched a step before the loads that need them
   int j0 = 0, j1 = 0, j2 = 0;
-  auto issue = [&](int jj, const int bufi) __attribute__((always_inline)) {
-    tl.load(descK, jj, bufi * Lds::BUF);
-    tl.load(descV, jj, bufi * Lds::BUF + Lds::TILE);
-  };
-  // Q_i and dO_i come in as tiles through the second pair buffer (whole rows per load, zeros past
-  // the end of the sequence) and are picked up from there in operand layout
-  {
-    const int it = min(i, Tn - 1);
-    tq.load_first(head_rsrc<D>(Q + lay.head(bh), N, 2 * lay.ts), it, Lds::BUF);
-    tq.load_first(head_rsrc<D>(dO + lay.head(bh), N, 2 * lay.ts), it, Lds::BUF + Lds::TILE);
-  }
   if (n_h > 0) {
     j0 = lut[0];
     j1 = lut[min(1, n_h - 1)];
     j2 = lut[min(2, n_h - 1)];
-    tl.load_first(descK, j0, 0);
-    tl.load_first(descV, j0, Lds::TILE);
   }
-  const float Lq = qok ? L[(size_t)bh * N + q0 + qrow] * kLog2e : INFINITY;
+  auto issue = [&](int jj, const int bufi) __attribute__((always_inline)) {
+    tl.load(descK, jj, bufi * Lds::BUF);
+    tl.load(descV, jj, bufi * Lds::BUF + Lds::TILE);
+  };
+  auto issue_first = [&]() __attribute__((always_inline)) {
+    if (n_h > 0) {
+      tl.load_first(descK, j0, 0);
+      tl.load_first(descV, j0, Lds::TILE);
+    }
+  };
+  float Lq = qok ? L[(size_t)bh * N + q0 + qrow] * kLog2e : INFINITY;
   float nDq;
   f32x16 dqT[NT];
-#pragma unroll
-  for (int t = 0; t < NT; ++t) dqT[t] = zero_f32x16();
   if constexpr (FUSED) {
+    float ds_pre;
+    pre_body<D, true, PHI>(smem, i, bh, Q, dO, pa.W, pa.Os, pa.Ol, pa.H16, pa.Zs, N, Tn, lay, pa.n_0, pa.Ds_out, pa.dHZ,
+                           nullptr, qf, gf, ds_pre, lin, issue_first);
+    sched_fence();   // (the accumulators below are not formed while the stored sums take up registers)
     nDq = qok ? -ds_pre : 0.0f;
     // the linear part of dQ, this wave's half of the features, as the start value of those
     // accumulators (the sum is multiplied by 1/sqrt(d) at the end)
@@ -423,11 +429,19 @@ __global__ __launch_bounds__(256 * QT, QT == 1 ? (D == 64 ? 3 : 2) : 1) void bwd
       for (int r = 0; r < 16; ++r) dqT[dt][r] = mine ? lin[dt % (NT / 2)][r] * rscale : 0.0f;
     }
   } else {
+    // Q_i and dO_i come in as tiles through the second pair buffer (whole rows per load, zeros past
+    // the end of the sequence) and are picked up from there in operand layout
+    TileLoader<D> tq;       // the four waves of a group, into the group's area
+    tq.init(lds_base(smem) + (grp ? Lds::BYTES - Lds::BUF : 0), w, l, 2 * lay.ts, N);
+    const int it = min(i, Tn - 1);
+    tq.load_first(head_rsrc<D>(Q + lay.head(bh), N, 2 * lay.ts), it, Lds::BUF);
+    tq.load_first(head_rsrc<D>(dO + lay.head(bh), N, 2 * lay.ts), it, Lds::BUF + Lds::TILE);
+    issue_first();
     nDq = qok ? -Ds[(size_t)bh * N + q0 + qrow] : 0.0f;
-  }
-  wait_vm0();
-  __syncthreads();
-  {
+#pragma unroll
+    for (int t = 0; t < NT; ++t) dqT[t] = zero_f32x16();
+    wait_vm0();
+    __syncthreads();
     TileAddr<D> qa;
     qa.init(32 * qh, l);
 #pragma unroll
@@ -435,11 +449,11 @@ __global__ __launch_bounds__(256 * QT, QT == 1 ? (D == 64 ? 3 : 2) : 1) void bwd
       qf[t] = lds_row(gsm, qa.row(t) + Lds::BUF);
       gf[t] = lds_row(gsm, qa.row(t) + Lds::BUF + Lds::TILE);
     }
-  }
 #pragma unroll
-  for (int t = 0; t < KT; ++t) {
-    pin_loaded(qf[t]);
-    pin_loaded(gf[t]);
+    for (int t = 0; t < KT; ++t) {
+      pin_loaded(qf[t]);
+      pin_loaded(gf[t]);
+    }
   }
   // (the first step's barrier orders these reads before the loads that reuse the buffer)
   TileAddr<D> ad;   // this wave reads rows 32 kh .. of K_j and V_j
@@ -632,27 +646,29 @@ hipError_t dw_impl(const Shape& s, const BwdArgs& a, float* dWpart, int nparts, 
 template <int D>
 hipError_t query_impl(const Shape& s, const BwdArgs& a, float* Ds, bf16* dHZ, bf16* dQlin, hipStream_t st) {
   const float* Zs = (const float*)((const char*)a.HZ + state_z_offset(s));
-  const PreArgs pa{(const bf16*)a.W, (const bf16*)a.Os, (const bf16*)a.Ol, (const bf16*)a.HZ, Zs, s.n_0, s.phi, Ds, dHZ};
+  const PreArgs pa{(const bf16*)a.W, (const bf16*)a.Os, (const bf16*)a.Ol, (const bf16*)a.HZ, Zs, s.n_0, Ds, dHZ};
   constexpr int lds_q = PairLds<D>::BYTES, lds_p = PreLds<D>::BYTES;
   if (s.rq % 2 == 0 && wide_query_tiles()) {
-    SLA_TRY(ensure_dyn_lds(bwd_pre_mfma_kernel<D>, lds_p));
+    auto pre = s.phi == 0 ? bwd_pre_mfma_kernel<D, 0> : bwd_pre_mfma_kernel<D, 1>;
+    SLA_TRY(ensure_dyn_lds(pre, lds_p));
     {
       KernelTimer kt("bwd_pre", st);
-      bwd_pre_mfma_kernel<D><<<dim3(s.T, s.BH), 256, lds_p, st>>>(
-          (const bf16*)a.Q, (const bf16*)a.dO, pa.W, pa.Os, pa.Ol, pa.H16, Zs, s.N, s.T, s.lay(), s.n_0, s.phi, Ds, dHZ,
+      pre<<<dim3(s.T, s.BH), 256, lds_p, st>>>(
+          (const bf16*)a.Q, (const bf16*)a.dO, pa.W, pa.Os, pa.Ol, pa.H16, Zs, s.N, s.T, s.lay(), s.n_0, Ds, dHZ,
           dQlin);
     }
     const int bytes = lds_q + PairLds<D>::GROUP;
-    SLA_TRY(ensure_dyn_lds(bwd_dq_mfma_kernel<D, 2, false>, bytes));
+    SLA_TRY(ensure_dyn_lds(bwd_dq_mfma_kernel<D, 2, false, 0>, bytes));
     KernelTimer kt("bwd_sparse_q", st);
-    bwd_dq_mfma_kernel<D, 2, false><<<dim3(xcd_grid((s.T + 1) / 2), s.BH), 512, bytes, st>>>(
+    bwd_dq_mfma_kernel<D, 2, false, 0><<<dim3(xcd_grid((s.T + 1) / 2), s.BH), 512, bytes, st>>>(
         (const bf16*)a.Q, (const bf16*)a.K, (const bf16*)a.V, (const bf16*)a.dO, a.L, Ds, a.row_idx,
         s.n_0 > 0 ? dQlin : nullptr, s.N, s.T, s.lay(), s.n_h, s.scale, (bf16*)a.dQ, pa);
   } else {
     constexpr int bytes = lds_q > lds_p ? lds_q : lds_p;
-    SLA_TRY(ensure_dyn_lds(bwd_dq_mfma_kernel<D, 1, true>, bytes));
+    auto kern = s.phi == 0 ? bwd_dq_mfma_kernel<D, 1, true, 0> : bwd_dq_mfma_kernel<D, 1, true, 1>;
+    SLA_TRY(ensure_dyn_lds(kern, bytes));
     KernelTimer kt("bwd_query", st);
-    bwd_dq_mfma_kernel<D, 1, true><<<dim3(xcd_grid(s.T), s.BH), 256, bytes, st>>>(
+    kern<<<dim3(xcd_grid(s.T), s.BH), 256, bytes, st>>>(
         (const bf16*)a.Q, (const bf16*)a.K, (const bf16*)a.V, (const bf16*)a.dO, a.L, nullptr, a.row_idx, nullptr, s.N,
         s.T, s.lay(), s.n_h, s.scale, (bf16*)a.dQ, pa);
   }
