@@ -434,6 +434,26 @@ def test_accumulation_line_by_every_method(oracle, T, d, k_h, k_l, bq):
         _compare("Z", Zm.double().cpu().numpy(), ref[..., d * d:], 1e-4 if method == sla.SLA_AGG_PREAGG else 1e-5)
 
 
+@pytest.mark.parametrize("T", [64, 65, 96, 127, 128, 129, 256, 257, 385])
+@pytest.mark.parametrize("d", [64, 128])
+def test_state_sums_at_the_edges_of_the_row_tiles(T, d):
+    # 32 or 64 output rows a wave, 64-column tiles in runs per XCD, several heads (the runs are rotated);
+    # bound: the sums are float (T additions), the matrix part is rounded to bf16 once
+    from paper_2509_24006_amd import binding as sla
+    H = 3
+    p = sla.make_params(1, H, T * 64, d, 0.1, 0.2, torch.bfloat16)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(T)
+    sc = torch.randn(1, H, T, T, generator=g, device="cuda")
+    h = torch.randn(1, H, T, d * d + d, generator=g, device="cuda").bfloat16()
+    Mc, luts = sla.sla_classify_scores(p, sc)
+    Hm, Zm = sla.sla_aggregate_states(p, sla.SLA_AGG_GEMM, luts, h)
+    ref = torch.matmul((Mc == 0).double(), h.double())
+    mag = torch.matmul((Mc == 0).double(), h.double().abs()) * T * 2.0 ** -24
+    assert bool(((Hm.double() - ref[..., :d * d]).abs() <= ref[..., :d * d].abs() * 2.0 ** -8 + mag[..., :d * d]).all())
+    assert bool(((Zm.double() - ref[..., d * d:]).abs() <= mag[..., d * d:]).all())
+
+
 def test_forward_without_saved_matches(oracle):
     from paper_2509_24006_amd import binding as sla
     from tests.gpu_util import to_dev, f64
