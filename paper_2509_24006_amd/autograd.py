@@ -22,7 +22,9 @@ class _SLAFunction(torch.autograd.Function):
         # the library reads W in the storage type of Q, K, V (a float parameter next to bf16
         # activations is cast here; its gradient goes back in the parameter's own type)
         ctx.w_dtype = W.dtype
-        W = W.detach().to(Q.dtype).contiguous()
+        W = W.detach()
+        if W.dtype != Q.dtype or not W.is_contiguous():
+            W = W.to(Q.dtype).contiguous()
         # without a backward pass to come (grad false) O^s, O^l, L stay on the chip and H, Z in the
         # workspace: two thirds of the forward kernel's stores (16 x 16 heads x 1024 tokens, d = 64: 53 -> 46 us)
         O, saved = sla.sla_forward(p, Q, K, V, W, Mc, luts, need_saved=grad)
@@ -49,7 +51,7 @@ def build_mask(Q: torch.Tensor, K: torch.Tensor, k_h: float, k_l: float,
         B, H, N, d = Q.shape
     p = sla.make_params(B, H, N, d, k_h, k_l, Q.dtype, phi=phi, bq=bq,
                         layout=sla.SLA_BNHD if token_major else sla.SLA_BHND)
-    Mc, luts, _ = sla.sla_build_mask(p, Q.detach(), K.detach())
+    Mc, luts, _ = sla.sla_build_mask(p, Q, K)   # (only the tensors' memory is handed on: no part of a graph)
     return p, Mc, luts
 
 

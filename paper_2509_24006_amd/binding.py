@@ -81,6 +81,25 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
+_host = None
+
+
+def _host_calls():
+    """The compiled host part of the three per-pass calls (csrc/host_calls.cpp): checks, allocations and
+    the library call in one go.  What it does not take as it stands it returns None for, and the Python
+    code below, which does the same step by step, raises the error."""
+    global _host
+    if _host is None:
+        lib()
+        try:
+            from . import _sla_host
+        except ImportError as e:
+            raise SLAError(f"{_HERE}/_sla_host.so is missing or does not load ({e}): build it with "
+                           "paper_2509_24006_amd/build.py") from e
+        _host = _sla_host
+    return _host
+
+
 def _check(rc: int, what: str) -> None:
     if rc != 0:
         raise SLAError(f"{what} failed: {lib().sla_strerror(rc).decode()} (code {rc})")
@@ -102,10 +121,8 @@ def sla_sizes(p: sla_params) -> sla_sizes_t:
     return z
 
 
-# Small calls are bound by the host (2 heads x 1110 tokens, d = 128, one training step: 237 us before the
-# kernels of short sequences and the two lines below, 195 us now): addresses go to ctypes as plain
-# integers (the argument types make pointers of them), and the stream of the current device is asked
-# for by its handle -- 0.2 us a call, a torch.cuda.Stream object built for it 2.9 us.
+# Addresses go to ctypes as plain integers (the argument types make pointers of them), and the stream of
+# the current device is asked for by its handle: 0.2 us a call, a torch.cuda.Stream object built for it 2.9.
 
 def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     return None if t is None else t.data_ptr()
@@ -168,6 +185,11 @@ def sla_build_mask(p: sla_params, Q: torch.Tensor, K: torch.Tensor,
                    luts: Optional[torch.Tensor] = None
                    ) -> Tuple[torch.Tensor, torch.Tensor, torch.Tensor]:
     """Returns (Mc int8 [B,H,Tq,T], luts, workspace); the workspace keeps pool(Q), pool(K), s."""
+    r = _host_calls().build_mask(ctypes.addressof(p), Q, K, workspace, Mc, luts)
+    if type(r) is tuple:
+        return r
+    if r is not None:
+        _check(r, "sla_build_mask")
     z = sla_sizes(p)
     _dense(Q, p, "Q"); _dense(K, p, "K")
     if Mc is None:
@@ -208,6 +230,11 @@ def sla_forward(p: sla_params, Q, K, V, W, Mc, luts, O: Optional[torch.Tensor] =
                 saved: Optional[torch.Tensor] = None, workspace: Optional[torch.Tensor] = None,
                 need_saved: bool = True) -> Tuple[torch.Tensor, Optional[torch.Tensor]]:
     """Returns (O, saved).  saved is None when need_saved is False (inference)."""
+    r = _host_calls().forward(ctypes.addressof(p), Q, K, V, W, Mc, luts, O, saved, workspace, need_saved)
+    if type(r) is tuple:
+        return r
+    if r is not None:
+        _check(r, "sla_forward")
     z = sla_sizes(p)
     for n, t in (("Q", Q), ("K", K), ("V", V)):
         _dense(t, p, n)
@@ -231,6 +258,12 @@ def sla_forward(p: sla_params, Q, K, V, W, Mc, luts, O: Optional[torch.Tensor] =
 def sla_backward(p: sla_params, Q, K, V, W, Mc, luts, saved, dO,
                  workspace: Optional[torch.Tensor] = None, out=None):
     """Returns (dQ, dK, dV, dW); dW is float32 [d, d]."""
+    r = _host_calls().backward(ctypes.addressof(p), Q, K, V, W, Mc, luts, saved, dO, workspace,
+                               *((None,) * 4 if out is None else out))
+    if type(r) is tuple:
+        return r
+    if r is not None:
+        _check(r, "sla_backward")
     z = sla_sizes(p)
     for n, t in (("Q", Q), ("K", K), ("V", V), ("dO", dO)):
         _dense(t, p, n)

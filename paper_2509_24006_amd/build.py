@@ -1,14 +1,17 @@
-"""Builds libsla_hip.so (hand-written HIP for gfx950) in-tree with hipcc."""
+"""Builds libsla_hip.so (hand-written HIP for gfx950) and _sla_host.so (the host part of its calls as
+a CPython module) in-tree."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsla_hip.so")
+HOST = os.path.join(HERE, "_sla_host.so")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wno-unused-command-line-argument", "-Wno-unknown-attributes"]
@@ -47,7 +50,29 @@ def build(verbose: bool = False, force: bool = True) -> str:
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"link failed:\n{r.stdout}\n{r.stderr}")
+    build_host(verbose, force)
     return LIB
+
+
+def build_host(verbose: bool = False, force: bool = True) -> str:
+    """csrc/host_calls.cpp against torch's headers, linked to the library next to it."""
+    import torch
+    from torch.utils import cpp_extension
+    src = os.path.join(CSRC, "host_calls.cpp")
+    hdr = os.path.join(HERE, "..", "include", "sla.h")
+    if not force and os.path.exists(HOST) and os.path.getmtime(HOST) > max(os.path.getmtime(f) for f in (src, hdr)):
+        return HOST
+    inc = [f"-I{d}" for d in cpp_extension.include_paths() + [sysconfig.get_paths()["include"]]]
+    lib = [f"-L{d}" for d in cpp_extension.library_paths()]
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-w",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *inc, src, "-o", HOST, *lib,
+           "-lc10", "-ltorch_cpu", "-ltorch_python", f"-L{HERE}", "-l:libsla_hip.so", "-Wl,-rpath,$ORIGIN"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"{cmd[0]} failed on {src}:\n{r.stdout}\n{r.stderr}")
+    return HOST
 
 
 if __name__ == "__main__":

@@ -1,0 +1,112 @@
+"""The compiled host part of the calls against the binding's own Python code: the same outputs for every
+layout and every choice of buffers passed in, the same errors for what does not fit."""
+import pytest
+import torch
+
+from paper_2509_24006_amd import binding as sla
+
+pytestmark = pytest.mark.gpu
+
+
+class _HandsEverythingBack:
+    build_mask = forward = backward = staticmethod(lambda *a: None)
+
+
+def _tensors(layout, dtype, B=2, H=3, N=333, d=64):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    new = lambda *s: torch.randn(*s, generator=g, device="cuda").to(dtype)
+    W = new(d, d) * 0.02
+    if layout == sla.SLA_STRIDED:
+        x = [new(B, N, 3, H, d)[:, :, i].transpose(1, 2) for i in range(3)] + [new(B, N, 3, H, d)[:, :, 0].transpose(1, 2)]
+        return sla.make_params(B, H, N, d, 0.2, 0.2, dtype, layout=layout, strides=x[0].stride()[:3]), x, W
+    shape = (B, N, H, d) if layout == sla.SLA_BNHD else (B, H, N, d)
+    return sla.make_params(B, H, N, d, 0.2, 0.2, dtype, layout=layout), [new(*shape) for _ in range(4)], W
+
+
+def _all(p, x, W, given):
+    z, dev = sla.sla_sizes(p), "cuda"
+    u8 = lambda n: torch.empty(n + 64, dtype=torch.uint8, device=dev)
+    like = lambda t: torch.empty_strided(t.shape, t.stride(), dtype=t.dtype, device=dev)
+    kw = [{}, {}, {}]
+    if given:
+        kw = [dict(workspace=u8(z.ws_mask_bytes), Mc=torch.empty((p.B, p.H, z.Tq, z.T), dtype=torch.int8, device=dev),
+                   luts=u8(z.luts_bytes)),
+              dict(O=like(x[0]), saved=u8(z.saved_bytes), workspace=u8(z.ws_forward_bytes), need_saved=False),
+              dict(workspace=u8(z.ws_backward_bytes),
+                   out=(like(x[0]), like(x[1]), like(x[2]), torch.empty(p.d, p.d, device=dev)))]
+    Mc, luts, ws = sla.sla_build_mask(p, x[0], x[1], **kw[0])
+    O, saved = sla.sla_forward(p, x[0], x[1], x[2], W, Mc, luts, **kw[1])
+    grads = sla.sla_backward(p, x[0], x[1], x[2], W, Mc, luts, saved, x[3], **kw[2])
+    if given:
+        assert Mc is kw[0]["Mc"] and luts is kw[0]["luts"] and ws is kw[0]["workspace"]
+        assert O is kw[1]["O"] and saved is kw[1]["saved"]
+        assert all(a is b for a, b in zip(grads, kw[2]["out"]))
+    assert sla.sla_forward(p, x[0], x[1], x[2], W, Mc, luts, need_saved=False)[1] is None
+    return (Mc, O) + tuple(grads)
+
+
+@pytest.mark.parametrize("given", [False, True])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("layout", [sla.SLA_BHND, sla.SLA_BNHD, sla.SLA_STRIDED])
+def test_same_results_as_the_calls_step_by_step(monkeypatch, layout, dtype, given):
+    p, x, W = _tensors(layout, dtype)
+    got = _all(p, x, W, given)
+    monkeypatch.setattr(sla, "_host_calls", lambda: _HandsEverythingBack)
+    ref = _all(p, x, W, given)
+    for a, b in zip(got, ref):
+        assert a.stride() == b.stride() and a.dtype == b.dtype and a.device == b.device
+        assert torch.equal(a, b)
+
+
+def test_same_errors_as_the_calls_step_by_step(monkeypatch):
+    p, x, W = _tensors(sla.SLA_BHND, torch.bfloat16)
+    Q, K, V, dO = x
+    Mc, luts, _ = sla.sla_build_mask(p, Q, K)
+    O, saved = sla.sla_forward(p, Q, K, V, W, Mc, luts)
+    bad_p = sla.make_params(2, 3, 333, 64, 0.2, 0.2, torch.bfloat16, bkv=128)
+    small = torch.empty(8, dtype=torch.uint8, device="cuda")
+    calls = [
+        lambda: sla.sla_build_mask(bad_p, Q, K),
+        lambda: sla.sla_build_mask(p, Q.float(), K),
+        lambda: sla.sla_build_mask(p, Q[:, :, :300], K),
+        lambda: sla.sla_build_mask(p, Q.transpose(1, 2).contiguous().transpose(1, 2), K),
+        lambda: sla.sla_build_mask(p, Q.cpu(), K),
+        lambda: sla.sla_build_mask(p, Q, K, workspace=small),
+        lambda: sla.sla_build_mask(p, Q, K, luts=small),
+        lambda: sla.sla_forward(p, Q, K, V, W.float(), Mc, luts),
+        lambda: sla.sla_forward(p, Q, K, V, W.t(), Mc, luts),
+        lambda: sla.sla_forward(p, Q, K, V, W, Mc[:, :, :2], luts),
+        lambda: sla.sla_forward(p, Q, K, V, W, Mc, luts, O=O.float()),
+        lambda: sla.sla_forward(p, Q, K, V, W, Mc, luts, saved=small),
+        lambda: sla.sla_forward(p, Q, K, None, W, Mc, luts),
+        lambda: sla.sla_backward(p, Q, K, V, W, Mc, luts, small, dO),
+        lambda: sla.sla_backward(p, Q, K, V, W, Mc, luts, saved, dO, out=(Q, K, V, W)),
+        lambda: sla.sla_backward(p, Q, K, V, W, Mc, luts, saved, dO, out=(Q, K, V)),
+        lambda: sla.sla_backward(p, Q, K, V, W, Mc, luts, saved, None),
+        # a workspace that is not 16-byte aligned: refused by the library itself
+        lambda: sla.sla_forward(p, Q, K, V, W, Mc, luts,
+                                workspace=torch.empty(sla.sla_sizes(p).ws_forward_bytes + 1, dtype=torch.uint8, device="cuda")[1:]),
+    ]
+
+    def errors():
+        out = []
+        for f in calls:
+            with pytest.raises((sla.SLAError, ValueError, AttributeError, TypeError)) as e:
+                f()
+            out.append((type(e.value), str(e.value)))
+        return out
+
+    got = errors()
+    monkeypatch.setattr(sla, "_host_calls", lambda: _HandsEverythingBack)
+    assert got == errors()
+
+
+def test_subclasses_take_the_python_path():
+    class Plain(torch.Tensor):
+        pass
+
+    p, x, W = _tensors(sla.SLA_BHND, torch.bfloat16)
+    ref = sla.sla_build_mask(p, x[0], x[1])[0]
+    got = sla.sla_build_mask(p, x[0].as_subclass(Plain), x[1])[0]
+    assert torch.equal(ref, got)
