@@ -150,6 +150,12 @@ int sla_backward(const sla_params* p, const void* Q, const void* K, const void* 
                  void* dK, void* dV, float* dW, void* workspace, size_t workspace_bytes,
                  void* stream);
 
+/* The same with dW in a chosen type: dW_dtype SLA_F32, or SLA_BF16 (the float sums rounded to nearest even). */
+int sla_backward_typed(const sla_params* p, const void* Q, const void* K, const void* V, const void* W,
+                       const int8_t* Mc, const void* luts, const void* saved, const void* dO, void* dQ,
+                       void* dK, void* dV, void* dW, int dW_dtype, void* workspace, size_t workspace_bytes,
+                       void* stream);
+
 /* Alg. 1's accumulation line on its own, by a chosen method:
  *   H_i = sum of h_j over the marginal key blocks j of query tile i,  Z_i likewise from z_j.
  * SLA_AGG_GEMM is what sla_forward and sla_backward use (a product with the 0/1 marginal

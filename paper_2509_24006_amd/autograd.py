@@ -36,7 +36,8 @@ class _SLAFunction(torch.autograd.Function):
     @staticmethod
     def backward(ctx, dO):
         Q, K, V, W, Mc, luts, saved = ctx.saved_tensors
-        dQ, dK, dV, dW = sla.sla_backward(ctx.p, Q, K, V, W, Mc, luts, saved, dO.contiguous())
+        dt = torch.bfloat16 if ctx.w_dtype == torch.bfloat16 else torch.float32
+        dQ, dK, dV, dW = sla._backward(ctx.p, Q, K, V, W, Mc, luts, saved, dO.contiguous(), None, None, dt)
         return dQ, dK, dV, dW.to(ctx.w_dtype), None, None, None, None
 
 

@@ -21,7 +21,7 @@ SLA_PHI_SOFTMAX, SLA_PHI_ELU1 = 0, 1
 SLA_BHND, SLA_BNHD, SLA_STRIDED = 0, 1, 2
 SLA_AGG_GEMM, SLA_AGG_ADD, SLA_AGG_PREAGG, SLA_AGG_FOUR_RUSSIANS = 0, 1, 2, 3
 SLA_STATIC_WS_BYTES = 32 << 20
-EXPORTS = ("sla_sizes", "sla_build_mask", "sla_build_mask_static", "sla_classify_scores", "sla_forward", "sla_backward",
+EXPORTS = ("sla_sizes", "sla_build_mask", "sla_build_mask_static", "sla_classify_scores", "sla_forward", "sla_backward", "sla_backward_typed",
            "sla_aggregate_ws_bytes", "sla_aggregate_states", "sla_wide_query_tiles",
            "sla_profile_enable", "sla_profile_read", "sla_profile_mfma_peak", "sla_profile_dq_atomics", "sla_strerror")
 
@@ -66,6 +66,7 @@ def lib() -> ctypes.CDLL:
         L.sla_classify_scores.argtypes = [pp, vp, vp, vp, vp]
         L.sla_forward.argtypes = [pp] + [vp] * 9 + [sz, vp]
         L.sla_backward.argtypes = [pp] + [vp] * 13 + [sz, vp]
+        L.sla_backward_typed.argtypes = [pp] + [vp] * 12 + [ctypes.c_int, vp, sz, vp]
         L.sla_aggregate_ws_bytes.argtypes = [pp, ctypes.c_int, ctypes.POINTER(ctypes.c_uint64)]
         L.sla_aggregate_states.argtypes = [pp, ctypes.c_int, vp, vp, vp, vp, vp, sz, vp]
         L.sla_profile_enable.argtypes = [ctypes.c_int]
@@ -258,8 +259,13 @@ def sla_forward(p: sla_params, Q, K, V, W, Mc, luts, O: Optional[torch.Tensor] =
 def sla_backward(p: sla_params, Q, K, V, W, Mc, luts, saved, dO,
                  workspace: Optional[torch.Tensor] = None, out=None):
     """Returns (dQ, dK, dV, dW); dW is float32 [d, d]."""
+    return _backward(p, Q, K, V, W, Mc, luts, saved, dO, workspace, out, torch.float32)
+
+
+def _backward(p, Q, K, V, W, Mc, luts, saved, dO, workspace, out, w_dtype):
+    """sla_backward with dW in w_dtype, float32 or bfloat16"""
     r = _host_calls().backward(ctypes.addressof(p), Q, K, V, W, Mc, luts, saved, dO, workspace,
-                               *((None,) * 4 if out is None else out))
+                               *((None,) * 4 if out is None else out), w_dtype == torch.bfloat16)
     if type(r) is tuple:
         return r
     if r is not None:
@@ -269,20 +275,21 @@ def sla_backward(p: sla_params, Q, K, V, W, Mc, luts, saved, dO,
         _dense(t, p, n)
     if out is None:
         dQ, dK, dV = _like(Q, p), _like(K, p), _like(V, p)
-        dW = torch.empty((p.d, p.d), dtype=torch.float32, device=Q.device)
+        dW = torch.empty((p.d, p.d), dtype=w_dtype, device=Q.device)
     else:
         dQ, dK, dV, dW = out
     ws = workspace if workspace is not None else _buf(z.ws_backward_bytes, Q.device)
     for n, t in (("dQ", dQ), ("dK", dK), ("dV", dV)):
         _dense(t, p, n)
     _packed(W, (p.d, p.d), _tdtype(p), "W")
-    _packed(dW, (p.d, p.d), torch.float32, "dW")
+    _packed(dW, (p.d, p.d), w_dtype, "dW")
     _packed(Mc, (p.B, p.H, z.Tq, z.T), torch.int8, "Mc")
     _bytes(luts, z.luts_bytes, "luts"); _bytes(saved, z.saved_bytes, "saved")
     _bytes(ws, z.ws_backward_bytes, "workspace")
-    _check(lib().sla_backward(ctypes.byref(p), _ptr(Q), _ptr(K), _ptr(V), _ptr(W), _ptr(Mc),
+    _check(lib().sla_backward_typed(ctypes.byref(p), _ptr(Q), _ptr(K), _ptr(V), _ptr(W), _ptr(Mc),
                               _ptr(luts), _ptr(saved), _ptr(dO), _ptr(dQ), _ptr(dK), _ptr(dV),
-                              _ptr(dW), _ptr(ws), ws.numel(), _stream()), "sla_backward")
+                              _ptr(dW), SLA_BF16 if w_dtype == torch.bfloat16 else SLA_F32, _ptr(ws), ws.numel(),
+                              _stream()), "sla_backward")
     return dQ, dK, dV, dW
 
 

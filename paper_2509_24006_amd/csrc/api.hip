@@ -261,9 +261,17 @@ int sla_backward(const sla_params* p, const void* Q, const void* K, const void* 
                  const int8_t* Mc, const void* luts, const void* saved, const void* dO, void* dQ,
                  void* dK, void* dV, float* dW, void* workspace, size_t workspace_bytes,
                  void* stream) {
+  return sla_backward_typed(p, Q, K, V, W, Mc, luts, saved, dO, dQ, dK, dV, dW, SLA_F32, workspace, workspace_bytes, stream);
+}
+
+int sla_backward_typed(const sla_params* p, const void* Q, const void* K, const void* V, const void* W,
+                       const int8_t* Mc, const void* luts, const void* saved, const void* dO, void* dQ,
+                       void* dK, void* dV, void* dW, int dW_dtype, void* workspace, size_t workspace_bytes,
+                       void* stream) {
   Shape s;
   const int rc = make_shape(p, &s);
   if (rc != SLA_OK) return rc;
+  if (dW_dtype != SLA_F32 && dW_dtype != SLA_BF16) return SLA_EUNSUPPORTED;
   if (!Q || !K || !V || !W || !Mc || !luts || !saved || !dO || !dQ || !dK || !dV || !dW || !workspace)
     return SLA_EINVAL;
   if (misaligned(Q) || misaligned(K) || misaligned(V) || misaligned(W) || misaligned(dO) ||
@@ -288,6 +296,7 @@ int sla_backward(const sla_params* p, const void* Q, const void* K, const void* 
   a.HZ = (const float*)(sv + z.saved_HZ);
   a.dQ = dQ; a.dK = dK; a.dV = dV;
   a.dW = dW;
+  a.dW16 = dW_dtype == SLA_BF16;
   a.ws = (char*)workspace;
   return hip_status(backward(s, a, (hipStream_t)stream));
 }

@@ -185,18 +185,21 @@ PyObject* forward(PyObject*, PyObject* const* a, Py_ssize_t n) {
   END_HANDLE_TH_ERRORS
 }
 
-// backward(params address, Q, K, V, W, Mc, luts, saved, dO, workspace, dQ, dK, dV, dW) -> (dQ, dK, dV, dW)
+// backward(params address, Q, K, V, W, Mc, luts, saved, dO, workspace, dQ, dK, dV, dW, dW in bf16) -> (dQ, dK, dV, dW)
 PyObject* backward(PyObject*, PyObject* const* a, Py_ssize_t n) {
   HANDLE_TH_ERRORS
   Call c;
-  if (n != 14 || !open_call(a[0], c)) Py_RETURN_NONE;
+  if (n != 15 || !open_call(a[0], c)) Py_RETURN_NONE;
   const at::Tensor *Q = plain(a[1]), *K = plain(a[2]), *V = plain(a[3]), *W = plain(a[4]), *Mc = plain(a[5]),
                    *luts = plain(a[6]), *saved = plain(a[7]), *dO = plain(a[8]);
   Slot ws(a[9]), dQ(a[10]), dK(a[11]), dV(a[12]), dW(a[13]);
+  const int w16 = PyObject_IsTrue(a[14]);
+  if (w16 < 0) return nullptr;
+  const at::ScalarType wt = w16 ? at::kBFloat16 : at::kFloat;
   const auto fits = [&](auto t) { return dense(t, c); };
   if (!dense(Q, c) || !dense(K, c) || !dense(V, c) || !dense(dO, c) || !packed(W, {c.p->d, c.p->d}, c.dt) ||
       !mask(Mc, c) || !bytes(luts, c.z.luts_bytes) || !bytes(saved, c.z.saved_bytes) || !dQ.ok(fits) || !dK.ok(fits) ||
-      !dV.ok(fits) || !dW.ok([&](auto t) { return packed(t, {c.p->d, c.p->d}, at::kFloat); }) ||
+      !dV.ok(fits) || !dW.ok([&](auto t) { return packed(t, {c.p->d, c.p->d}, wt); }) ||
       !ws.ok([&](auto t) { return bytes(t, c.z.ws_backward_bytes); }))
     Py_RETURN_NONE;
   void* st;
@@ -207,11 +210,11 @@ PyObject* backward(PyObject*, PyObject* const* a, Py_ssize_t n) {
     dQ.fill([&] { return new_like(*Q, c); });
     dK.fill([&] { return new_like(*K, c); });
     dV.fill([&] { return new_like(*V, c); });
-    dW.fill([&] { return at::empty({c.p->d, c.p->d}, Q->options().dtype(at::kFloat).requires_grad(false)); });
+    dW.fill([&] { return at::empty({c.p->d, c.p->d}, Q->options().dtype(wt).requires_grad(false)); });
     ws.fill([&] { return new_bytes(c.z.ws_backward_bytes, *Q); });
-    rc = sla_backward(c.p, Q->data_ptr(), K->data_ptr(), V->data_ptr(), W->data_ptr(), (const int8_t*)Mc->data_ptr(),
-                      luts->data_ptr(), saved->data_ptr(), dO->data_ptr(), dQ.ptr(), dK.ptr(), dV.ptr(), (float*)dW.ptr(),
-                      ws.ptr(), ws.size(), st);
+    rc = sla_backward_typed(c.p, Q->data_ptr(), K->data_ptr(), V->data_ptr(), W->data_ptr(), (const int8_t*)Mc->data_ptr(),
+                      luts->data_ptr(), saved->data_ptr(), dO->data_ptr(), dQ.ptr(), dK.ptr(), dV.ptr(), dW.ptr(),
+                            w16 ? SLA_BF16 : SLA_F32, ws.ptr(), ws.size(), st);
   }
   if (rc != SLA_OK) return PyLong_FromLong(rc);
   return pack({dQ.object(), dK.object(), dV.object(), dW.object()});

@@ -44,14 +44,18 @@ __global__ __launch_bounds__(256, 2) void bwd_dkdv_mfma_kernel(
     const bf16* __restrict__ dO, const float* __restrict__ L, const float* __restrict__ Ds,
     const int32_t* __restrict__ col_ptr, const int32_t* __restrict__ col_rows,
     const int32_t* __restrict__ col_order, const bf16* __restrict__ dHcol,
-    const float* __restrict__ dZcol, int N, int Tn, Lay lay, int n_h, float scale,
-    bf16* __restrict__ dK, bf16* __restrict__ dV) {
+    const float* __restrict__ dZcol, int BH, int N, int Tn, Lay lay, int n_h, float scale,
+    bf16* __restrict__ dK, bf16* __restrict__ dV, DwSum dw) {
   using Lds = KvLds<D>;
   using T = SwzTile<D>;
   constexpr int NT = D / 32, KT = D / 16, HT = NT / 2;
   constexpr int RB = 16 * T::ROW_BYTES;
   constexpr int phi = PHI;   // feature map: 0 softmax over the features, 1 elu + 1
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  if ((int)blockIdx.x >= Tn * BH) {   // the last workgroups: dW
+    dw_sum(dw, blockIdx.x - Tn * BH, smem);
+    return;
+  }
   const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, g = l >> 5, ln = l & 31;
   const int kh = w & 1, xh = w >> 1;
   // Longest column lists first, across all heads: the r-th heaviest key block of every head
@@ -63,7 +67,6 @@ __global__ __launch_bounds__(256, 2) void bwd_dkdv_mfma_kernel(
   // Within that order the heads are dealt to the XCDs (workgroups go to them round robin) in
   // halves -- the even or the odd ranks of a head -- so that an XCD's L2 serves the Q and dO tiles
   // of few heads at a time; most tile loads of this kernel miss the L2.
-  const int BH = gridDim.x / Tn;
   int bh, rank;
   if (BH % 8 == 0 && BH >= 32 && Tn >= 128) {
     // Many long heads: every XCD takes its BH / 8 heads one after the other, each heaviest list first.
@@ -378,14 +381,16 @@ __global__ __launch_bounds__(256, 2) void bwd_dkdv_mfma_kernel(
 }
 
 template <int D>
-hipError_t sparse_impl(const Shape& s, const BwdArgs& a, const float* Ds, const void* dHZcol, hipStream_t st) {
+hipError_t sparse_impl(const Shape& s, const BwdArgs& a, const float* Ds, const void* dHZcol, const DwSum& dw,
+                       hipStream_t st) {
   const float* dZcol = dHZcol ? reinterpret_cast<const float*>((const char*)dHZcol + state_z_offset(s)) : nullptr;
   auto launch_kv = [&](auto kern) -> hipError_t {
     SLA_TRY(ensure_dyn_lds(kern, KvLds<D>::BYTES));
     KernelTimer kt("bwd_sparse_kv", st);
-    kern<<<dim3(s.T * s.BH), 256, KvLds<D>::BYTES, st>>>(
+    kern<<<dim3(s.T * s.BH + dw.dd / kDwPiece), 256, KvLds<D>::BYTES, st>>>(
         (const bf16*)a.Q, (const bf16*)a.K, (const bf16*)a.V, (const bf16*)a.dO, a.L, Ds, a.col_ptr, a.col_rows,
-        a.col_order, (const bf16*)dHZcol, dZcol, s.N, s.T, s.lay(), s.n_h, s.scale, (bf16*)a.dK, (bf16*)a.dV);
+        a.col_order, (const bf16*)dHZcol, dZcol, s.BH, s.N, s.T, s.lay(), s.n_h, s.scale, (bf16*)a.dK, (bf16*)a.dV,
+        dw);
     return hipSuccess;
   };
   SLA_TRY(s.phi == 0 ? launch_kv(bwd_dkdv_mfma_kernel<D, 0>) : launch_kv(bwd_dkdv_mfma_kernel<D, 1>));
@@ -394,8 +399,9 @@ hipError_t sparse_impl(const Shape& s, const BwdArgs& a, const float* Ds, const 
 
 }  // namespace
 
-hipError_t mfma_backward_sparse(const Shape& s, const BwdArgs& a, const float* Ds, const void* dHZcol, hipStream_t st) {
-  return s.d == 64 ? sparse_impl<64>(s, a, Ds, dHZcol, st) : sparse_impl<128>(s, a, Ds, dHZcol, st);
+hipError_t mfma_backward_sparse(const Shape& s, const BwdArgs& a, const float* Ds, const void* dHZcol, const DwSum& dw,
+                                hipStream_t st) {
+  return s.d == 64 ? sparse_impl<64>(s, a, Ds, dHZcol, dw, st) : sparse_impl<128>(s, a, Ds, dHZcol, dw, st);
 }
 
 }  // namespace sla

@@ -593,6 +593,45 @@ __device__ __forceinline__ void wait_vm() {
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
+// dW = sum of the partial d x d sums, elements [32 block, +32).  Bound by the latency of its loads (64
+// partials of 16 KB and up, 512 of them in a large call), so a workgroup of 256 owns only 32 consecutive
+// elements (128 bytes) and deals the partials to 32 groups of eight lanes with eight loads of a
+// thread in flight.  The groups meet by shuffles and in LDS (512 bytes at smem), in an order fixed by
+// nparts alone.  The workgroups are the last of the key-side kernel's launch, where CUs run out of
+// lists; a launch of their own took 4.8 us at d = 64 and 7 us at d = 128, and another kernel 4.4 us for
+// a bf16 copy of the result.
+constexpr int kDwPiece = 32;
+__device__ __forceinline__ void dw_sum(const DwSum& a, int block, unsigned char* smem) {
+  float* red = reinterpret_cast<float*>(smem);   // [wave][32]
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63, q = threadIdx.x & 7;
+  const float* src = a.part + block * kDwPiece + 4 * q;   // (dd is a multiple of 32)
+  f32x4 s = {0.0f, 0.0f, 0.0f, 0.0f};
+  for (int p0 = threadIdx.x >> 3; p0 < a.nparts; p0 += 256) {
+    f32x4 x[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k)   // (past the end: the last partial again, not added)
+      x[k] = *reinterpret_cast<const f32x4*>(src + (size_t)min(p0 + 32 * k, a.nparts - 1) * a.dd);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      if (p0 + 32 * k >= a.nparts) break;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s[e] += x[k][e];
+    }
+  }
+#pragma unroll
+  for (int o = 8; o < 64; o <<= 1)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) s[e] += __shfl_xor(s[e], o);
+  if (l < 8) *reinterpret_cast<f32x4*>(red + 32 * w + 4 * q) = s;
+  __syncthreads();
+  if (threadIdx.x < kDwPiece) {
+    const float t = (red[threadIdx.x] + red[32 + threadIdx.x]) + (red[64 + threadIdx.x] + red[96 + threadIdx.x]);
+    const int at = block * kDwPiece + threadIdx.x;
+    if (a.bf16) reinterpret_cast<__bf16*>(a.dW)[at] = (__bf16)t;
+    else reinterpret_cast<float*>(a.dW)[at] = t;
+  }
+}
+
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 

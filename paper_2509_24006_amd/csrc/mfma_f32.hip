@@ -717,10 +717,15 @@ __global__ __launch_bounds__(256, 2) void f32_bwd_key_kernel(
     const float* __restrict__ dO, const float* __restrict__ L, const float* __restrict__ Ds,
     const int32_t* __restrict__ col_ptr, const int32_t* __restrict__ col_rows, const int32_t* __restrict__ col_order,
     const float* __restrict__ dHZcol, int N, int Tn, Lay lay, int n_h, int n_0, int phi, float scale,
-    float* __restrict__ dK, float* __restrict__ dV) {
+    float* __restrict__ dK, float* __restrict__ dV, DwSum dw) {
   static_assert(QW == 2 || QW == 4, "waves that share a group of 16 keys");
   constexpr int NT = D / 16, TB = FTile<D>::BYTES, NQ = 4 / QW, NO = NT / QW;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  if ((int)blockIdx.y >= Tn * QW) {   // the last rows of the grid: dW
+    const int block = ((int)blockIdx.y - Tn * QW) * gridDim.x + blockIdx.x;
+    if (block < dw.dd / kDwPiece) dw_sum(dw, block, smem);
+    return;
+  }
   const unsigned char* stat = smem + 2 * TB;
   float* dots = reinterpret_cast<float*>(smem + 2 * TB + 512);
   const int tid = threadIdx.x, w = wave_uniform(tid >> 6), l = tid & 63, g = l >> 4, n = l & 15;
@@ -883,7 +888,7 @@ __global__ __launch_bounds__(256, 2) void f32_bwd_key_kernel(
 }
 
 // dW = sum over tokens of (O^l)^T dO: each workgroup sums a strided set of 64-token tiles into its
-// own partial d x d matrix; dw_reduce adds the partials.
+// own partial d x d matrix; dw_sum adds the partials.
 template <int D>
 __global__ __launch_bounds__(256, 2) void f32_dw_kernel(const float* __restrict__ Ol, const float* __restrict__ dO,
                                                         int BH, int N, int Tn, Lay lay, float* __restrict__ part) {
@@ -954,12 +959,13 @@ hipError_t forward_impl(const Shape& s, const FwdArgs& a, hipStream_t st) {
 }
 
 template <int D, int QW>
-hipError_t launch_key(const Shape& s, const BwdArgs& a, const float* Ds, const float* dHZcol, hipStream_t st) {
+hipError_t launch_key(const Shape& s, const BwdArgs& a, const float* Ds, const float* dHZcol, const DwSum& dw,
+                      hipStream_t st) {
   SLA_TRY(ensure_dyn_lds(f32_bwd_key_kernel<D, QW>, f32_bwd_key_lds<D>()));
   KernelTimer kt("bwd_sparse_kv", st);
-  f32_bwd_key_kernel<D, QW><<<dim3(s.BH, s.T * QW), 256, f32_bwd_key_lds<D>(), st>>>(
+  f32_bwd_key_kernel<D, QW><<<dim3(s.BH, s.T * QW + (dw.dd / kDwPiece + s.BH - 1) / s.BH), 256, f32_bwd_key_lds<D>(), st>>>(
       (const float*)a.Q, (const float*)a.K, (const float*)a.V, (const float*)a.dO, a.L, Ds, a.col_ptr, a.col_rows,
-      a.col_order, dHZcol, s.N, s.T, s.lay(), s.n_h, s.n_0, s.phi, s.scale, (float*)a.dK, (float*)a.dV);
+      a.col_order, dHZcol, s.N, s.T, s.lay(), s.n_h, s.n_0, s.phi, s.scale, (float*)a.dK, (float*)a.dV, dw);
   return hipGetLastError();
 }
 
@@ -980,14 +986,14 @@ hipError_t backward_impl(const Shape& s, const BwdArgs& a, float* Ds, float* dHZ
     KernelTimer kt("dw_partial", st);
     f32_dw_kernel<D><<<nparts, 256, tiles, st>>>((const float*)a.Ol, (const float*)a.dO, s.BH, s.N, s.T, s.lay(), dWpart);
   }
-  SLA_TRY(launch_dw_reduce(dWpart, nparts, D * D, a.dW, st));
+  const DwSum dw{dWpart, nparts, D * D, a.dW, a.dW16};
   if (s.n_0 > 0) SLA_TRY(f32_aggregate(dHZ, a.indT, s, dHZcol, st));
   // A quarter of the keys per workgroup balances the uneven lists (clip, 4 heads x 122 blocks: 189 us,
   // 273 with halves, 444 with whole key blocks); with enough workgroups the tiles that they fetch
   // cost more than the balance gives (16 heads x 63 blocks: 347 against 297 us with halves; 12 x
   // 157 at 20 %: 2191 against 2010, 2039 with whole blocks).
-  if (s.BH * s.T < 768) return launch_key<D, 4>(s, a, Ds, dHZcol, st);
-  return launch_key<D, 2>(s, a, Ds, dHZcol, st);
+  if (s.BH * s.T < 768) return launch_key<D, 4>(s, a, Ds, dHZcol, dw, st);
+  return launch_key<D, 2>(s, a, Ds, dHZcol, dw, st);
 }
 
 }  // namespace

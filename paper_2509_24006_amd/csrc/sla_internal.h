@@ -79,16 +79,24 @@ struct BwdArgs {
   const void *Os, *Ol;
   const float *L, *HZ;
   void *dQ, *dK, *dV;
-  float* dW;
+  void* dW;    // float, or bf16 with dW16
+  bool dW16;
   char* ws;  // workspace, ws_backward_bytes
 };
 size_t backward_ws_bytes(const Shape& s);   // (backward.hip)
-hipError_t launch_dw_reduce(const float* part, int nparts, int dd, float* dW, hipStream_t st);
+// The sum of dW's partial d x d sums, done by extra workgroups of the key-side kernel's launch.
+struct DwSum {
+  const float* part;
+  int nparts, dd;
+  void* dW;
+  bool bf16;
+};
 // critical-block gradients on the matrix cores (mfma_bwd.hip).  dQlin: linear-branch part of dQ.
 // dHZcol: dH and dZ summed over the marginal blocks of each key block (bf16 matrices, then float
 // vectors at state_z_offset); the dK/dV kernel turns them into the linear-branch parts of dK and
 // dV itself.  Both may be null (no marginal block).
-hipError_t mfma_backward_sparse(const Shape& s, const BwdArgs& a, const float* Ds, const void* dHZcol, hipStream_t st);
+hipError_t mfma_backward_sparse(const Shape& s, const BwdArgs& a, const float* Ds, const void* dHZcol, const DwSum& dw,
+                                hipStream_t st);
 // the float path's backward pass; the workspace pieces are carved by backward()
 hipError_t f32_backward(const Shape& s, const BwdArgs& a, float* Ds, float* dHZ, float* dHZcol, float* dWpart,
                         int nparts, hipStream_t st);
