@@ -33,8 +33,7 @@ BwdWs carve_bwd(const Shape& s, char* ws) {
 hipError_t backward_bf16(const Shape& s, const BwdArgs& a, hipStream_t st) {
   const BwdWs w = carve_bwd(s, a.ws);
   const bool lin = s.n_0 > 0;
-  SLA_TRY(mfma_backward_query(s, a, w.Ds, w.dHZ, w.dQlin, st));   // dHZ holds bf16 rows
-  SLA_TRY(mfma_backward_dw(s, a, w.dWpart, w.nparts, st));
+  SLA_TRY(mfma_backward_query(s, a, w.Ds, w.dHZ, w.dQlin, w.dWpart, w.nparts, st));   // dHZ holds bf16 rows
   if (lin) {
     SLA_TRY(mfma_aggregate(w.dHZ, a.indT, s, w.dHZcol,
                            reinterpret_cast<float*>(reinterpret_cast<char*>(w.dHZcol) + state_z_offset(s)), st));

@@ -5,7 +5,7 @@
 //   bwd_dq_mfma     one workgroup per query block i, walking the row table:
 //                   dQ_i += dS K_j / sqrt(d)   (S, dP are recomputed; no atomics, one owner);
 //                   with query blocks of one tile it runs pre_body first, in the same launch
-//   dw_mfma         dW = sum_n (O^l_n)^T dO_n, per-workgroup partial sums
+//   dw_part         dW = sum_n (O^l_n)^T dO_n, partial sums by the last workgroups of the launch
 // One lane owns one token (query or key) in every product whose result is per token, so the
 // row-wise quantities (softmax statistics of phi, D^l, the normaliser phi(Q) Z) are per-lane scalars.
 #include "mfma_common.h"
@@ -308,20 +308,93 @@ __device__ __forceinline__ void pre_body(
   }
 }
 
+// ------------------------------------------------------------------ dW partial sums
+// dW = sum over tokens of O^l^T dO (gradient of Proj, Eq. 6).  Part g of G sums over token tiles
+// g, g + G, ...; the two tiles of a step come in as LDS tiles, double-buffered, and both operands
+// are contracted over tile rows (transposing reads).  Wave w owns rows c in [32 w, 32 w + 32) of dW.
+// It needs nothing that the query side forms: the parts are the last workgroups of that launch and run
+// where its last round leaves CUs idle.  (Query side and a launch of its own behind it -> now: 256 heads x 16
+// blocks, d = 64, 79.8 + 15.0 -> 81.0 us; 12 x 146, d = 128, 123.3 + 17.0 -> 123.2; 12 x 512 720 + 46 -> 733;
+// 2 x 18 19.3 + 6.6 -> 19.2.)
+struct DwArgs {
+  const bf16 *Ol, *dO;
+  float* part;
+  int parts;   // G
+};
+template <int D>
+constexpr int kDwLds = 4 * SwzTile<D>::BYTES;
+template <int D>
+__device__ __forceinline__ void dw_part(unsigned char* smem, const DwArgs& a, int p, int BH, int N, int Tn, Lay lay) {
+  using T = SwzTile<D>;
+  constexpr int NT = D / 32;
+  constexpr int BUF = 2 * T::BYTES;
+  constexpr int RB = 16 * T::ROW_BYTES;
+  static_assert(2 * BUF == kDwLds<D>, "two pairs of tiles");
+  const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, g = l >> 5, ln = l & 31;
+  const int ldv = tile_lane_offset<D>(w, l);
+  const unsigned lds0 = lds_base(smem) + wave_uniform(w) * 1024;
+  TileLoader<D> tl;   // tiles of the caller's dO
+  tl.init(lds_base(smem), w, l, 2 * lay.ts, N);
+  f32x16 acc[NT];
+#pragma unroll
+  for (int et = 0; et < NT; ++et) acc[et] = zero_f32x16();
+  const int total = BH * Tn;
+  auto issue = [&](int t, int buf) {
+    const int bh = t / Tn, i = t - bh * Tn;
+    const int rows = min(kBlk, N - i * kBlk);
+    const size_t base = ((size_t)bh * N + (size_t)i * kBlk) * D;
+    issue_tile_load<D>(a.Ol + base, rows, lds0, buf * BUF, ldv);
+    tl.load_first(head_rsrc<D>(a.dO + lay.head(bh), N, 2 * lay.ts), i, buf * BUF + T::BYTES);
+  };
+  TileAddr<D> ad;
+  ad.init(0, l);
+  if (p < total) issue(p, 0);
+  int buf = 0;
+  for (int t = p; t < total; t += a.parts) {
+    wait_vm0();
+    __syncthreads();   // this step's tiles have landed; the other buffer is fully consumed
+    if (t + a.parts < total) issue(t + a.parts, buf ^ 1);
+    const int off = buf * BUF;
+    buf ^= 1;
+    if (w < NT) {
+#pragma unroll
+      for (int u = 0; u < kBlk / 16; ++u) {
+        const bf16x8 x = lds_tr<D>(smem, ad.tr(0, w) + off + u * RB, ad.tr(1, w) + off + u * RB);   // O^l^T rows c
+#pragma unroll
+        for (int et = 0; et < NT; ++et) {
+          const bf16x8 b = lds_tr<D>(smem, ad.tr(0, et) + off + T::BYTES + u * RB, ad.tr(1, et) + off + T::BYTES + u * RB);
+          acc[et] = mfma32(x, b, acc[et]);
+        }
+      }
+    }
+  }
+  if (w < NT) {
+    float* out = a.part + (size_t)p * D * D;
+#pragma unroll
+    for (int et = 0; et < NT; ++et)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) out[(size_t)(32 * w + c_row(r, g)) * D + 32 * et + ln] = acc[et][r];
+  }
+}
+
 // The query side on its own (query blocks of several tiles, whose dQ kernel shares a workgroup
-// between two tiles): one workgroup per 64-token tile.
+// between two tiles): one workgroup per 64-token tile, then the parts of dW.
 template <int D, int PHI>
 __global__ __launch_bounds__(256, 2) void bwd_pre_mfma_kernel(
     const bf16* __restrict__ Q, const bf16* __restrict__ dO, const bf16* __restrict__ W,
     const bf16* __restrict__ Os, const bf16* __restrict__ Ol, const bf16* __restrict__ H16,
-    const float* __restrict__ Zs, int N,
+    const float* __restrict__ Zs, int BH, int N,
     int Tn, Lay lay, int n_0, float* __restrict__ Ds, bf16* __restrict__ dHZ,
-    bf16* __restrict__ dQlin) {
+    bf16* __restrict__ dQlin, DwArgs dw) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  if ((int)blockIdx.x >= Tn * BH) {
+    dw_part<D>(smem, dw, blockIdx.x - Tn * BH, BH, N, Tn, lay);
+    return;
+  }
   bf16x8 qf[D / 16], gf[D / 16];
   f32x16 lin[D / 64];
   float ds;
-  pre_body<D, false, PHI>(smem, blockIdx.x, blockIdx.y, Q, dO, W, Os, Ol, H16, Zs, N, Tn, lay, n_0, Ds, dHZ, dQlin, qf,
+  pre_body<D, false, PHI>(smem, blockIdx.x % Tn, blockIdx.x / Tn, Q, dO, W, Os, Ol, H16, Zs, N, Tn, lay, n_0, Ds, dHZ, dQlin, qf,
                           gf, ds, lin, [] {});
 }
 
@@ -363,8 +436,8 @@ template <int D, int QT, bool FUSED, int PHI>
 __global__ __launch_bounds__(256 * QT, QT == 1 ? (D == 64 ? 3 : 2) : 1) void bwd_dq_mfma_kernel(
     const bf16* __restrict__ Q, const bf16* __restrict__ K, const bf16* __restrict__ V,
     const bf16* __restrict__ dO, const float* __restrict__ L, const float* __restrict__ Ds,
-    const int32_t* __restrict__ row_idx, const bf16* __restrict__ dQlin, int N, int Tn, Lay lay, int n_h,
-    float scale, bf16* __restrict__ dQ, PreArgs pa) {
+    const int32_t* __restrict__ row_idx, const bf16* __restrict__ dQlin, int BH, int N, int Tn, Lay lay, int n_h,
+    float scale, bf16* __restrict__ dQ, PreArgs pa, DwArgs dw) {
   static_assert(!FUSED || QT == 1, "the fused form has one query tile per workgroup");
   using Lds = PairLds<D>;
   using T = SwzTile<D>;
@@ -375,7 +448,12 @@ __global__ __launch_bounds__(256 * QT, QT == 1 ? (D == 64 ? 3 : 2) : 1) void bwd
   const int wall = threadIdx.x >> 6, l = threadIdx.x & 63, g = l >> 5, ln = l & 31;
   const int grp = QT == 1 ? 0 : wave_uniform(wall >> 2), w = wall & 3, tid = threadIdx.x & 255;
   const int qh = w & 1, kh = w >> 1;
-  const int ib = xcd_local_block(blockIdx.x, (Tn + QT - 1) / QT), bh = blockIdx.y;
+  const int nb = (Tn + QT - 1) / QT, per_head = xcd_grid(nb), bh = blockIdx.x / per_head;
+  if (FUSED && bh >= BH) {   // the last workgroups
+    dw_part<D>(smem, dw, blockIdx.x - per_head * BH, BH, N, Tn, lay);
+    return;
+  }
+  const int ib = xcd_local_block(blockIdx.x % per_head, nb);
   if (ib < 0) return;
   // (a last block of a single tile: the second group runs along with no valid query and stores nothing)
   const int i = QT * ib + grp;
@@ -571,121 +649,53 @@ __global__ __launch_bounds__(256 * QT, QT == 1 ? (D == 64 ? 3 : 2) : 1) void bwd
   }
 }
 
-// ------------------------------------------------------------------ dW partial sums
-// dW = sum over tokens of O^l^T dO (gradient of Proj, Eq. 6).  Workgroup g sums over token tiles
-// g, g + G, ...; the two tiles of a step come in as LDS tiles, double-buffered, and both operands
-// are contracted over tile rows (transposing reads).  Wave w owns rows c in [32 w, 32 w + 32) of dW.
-template <int D>
-__global__ __launch_bounds__(256, 2) void dw_mfma_kernel(const bf16* __restrict__ Ol,
-                                                         const bf16* __restrict__ dO, int BH, int N,
-                                                         int Tn, Lay lay, float* __restrict__ part) {
-  using T = SwzTile<D>;
-  constexpr int NT = D / 32;
-  constexpr int BUF = 2 * T::BYTES;
-  constexpr int RB = 16 * T::ROW_BYTES;
-  __shared__ __attribute__((aligned(16))) unsigned char smem[2 * BUF];
-  const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, g = l >> 5, ln = l & 31;
-  const int ldv = tile_lane_offset<D>(w, l);
-  const unsigned lds0 = lds_base(smem) + wave_uniform(w) * 1024;
-  TileLoader<D> tl;   // tiles of the caller's dO
-  tl.init(lds_base(smem), w, l, 2 * lay.ts, N);
-  f32x16 acc[NT];
-#pragma unroll
-  for (int et = 0; et < NT; ++et) acc[et] = zero_f32x16();
-  const int total = BH * Tn;
-  auto issue = [&](int t, int buf) {
-    const int bh = t / Tn, i = t - bh * Tn;
-    const int rows = min(kBlk, N - i * kBlk);
-    const size_t base = ((size_t)bh * N + (size_t)i * kBlk) * D;
-    issue_tile_load<D>(Ol + base, rows, lds0, buf * BUF, ldv);
-    tl.load_first(head_rsrc<D>(dO + lay.head(bh), N, 2 * lay.ts), i, buf * BUF + T::BYTES);
-  };
-  TileAddr<D> ad;
-  ad.init(0, l);
-  if ((int)blockIdx.x < total) issue(blockIdx.x, 0);
-  int buf = 0;
-  for (int t = blockIdx.x; t < total; t += gridDim.x) {
-    wait_vm0();
-    __syncthreads();   // this step's tiles have landed; the other buffer is fully consumed
-    if (t + (int)gridDim.x < total) issue(t + gridDim.x, buf ^ 1);
-    const int off = buf * BUF;
-    buf ^= 1;
-    if (w < NT) {
-#pragma unroll
-      for (int u = 0; u < kBlk / 16; ++u) {
-        const bf16x8 a = lds_tr<D>(smem, ad.tr(0, w) + off + u * RB, ad.tr(1, w) + off + u * RB);   // O^l^T rows c
-#pragma unroll
-        for (int et = 0; et < NT; ++et) {
-          const bf16x8 b = lds_tr<D>(smem, ad.tr(0, et) + off + T::BYTES + u * RB, ad.tr(1, et) + off + T::BYTES + u * RB);
-          acc[et] = mfma32(a, b, acc[et]);
-        }
-      }
-    }
-  }
-  if (w < NT) {
-    float* out = part + (size_t)blockIdx.x * D * D;
-#pragma unroll
-    for (int et = 0; et < NT; ++et)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) out[(size_t)(32 * w + c_row(r, g)) * D + 32 * et + ln] = acc[et][r];
-  }
-}
-
-// dW partial sums of the whole call (launched between the query side and the column sums)
-template <int D>
-hipError_t dw_impl(const Shape& s, const BwdArgs& a, float* dWpart, int nparts, hipStream_t st) {
-  KernelTimer kt("dw_partial", st);
-  dw_mfma_kernel<D><<<nparts, 256, 0, st>>>((const bf16*)a.Ol, (const bf16*)a.dO, s.BH, s.N, s.T, s.lay(), dWpart);
-  return hipGetLastError();
-}
-
 // Query side of the backward pass: the linear branch's first loop and the row-wise dQ kernel.  With
 // query blocks of one tile (or an odd number of tiles) both run in one launch; with two tiles per
 // workgroup in the dQ kernel the linear part runs as a kernel of its own and hands its part of dQ
 // over in memory.
 template <int D>
-hipError_t query_impl(const Shape& s, const BwdArgs& a, float* Ds, bf16* dHZ, bf16* dQlin, hipStream_t st) {
+hipError_t query_impl(const Shape& s, const BwdArgs& a, float* Ds, bf16* dHZ, bf16* dQlin, float* dWpart, int nparts,
+                      hipStream_t st) {
   const float* Zs = (const float*)((const char*)a.HZ + state_z_offset(s));
   const PreArgs pa{(const bf16*)a.W, (const bf16*)a.Os, (const bf16*)a.Ol, (const bf16*)a.HZ, Zs, s.n_0, Ds, dHZ};
+  const DwArgs dw{(const bf16*)a.Ol, (const bf16*)a.dO, dWpart, nparts};
   constexpr int lds_q = PairLds<D>::BYTES, lds_p = PreLds<D>::BYTES;
+  static_assert(lds_p >= kDwLds<D>, "the parts of dW find room");
   if (s.rq % 2 == 0 && wide_query_tiles()) {
     auto pre = s.phi == 0 ? bwd_pre_mfma_kernel<D, 0> : bwd_pre_mfma_kernel<D, 1>;
     SLA_TRY(ensure_dyn_lds(pre, lds_p));
     {
       KernelTimer kt("bwd_pre", st);
-      pre<<<dim3(s.T, s.BH), 256, lds_p, st>>>(
-          (const bf16*)a.Q, (const bf16*)a.dO, pa.W, pa.Os, pa.Ol, pa.H16, Zs, s.N, s.T, s.lay(), s.n_0, Ds, dHZ,
-          dQlin);
+      pre<<<s.T * s.BH + nparts, 256, lds_p, st>>>(
+          (const bf16*)a.Q, (const bf16*)a.dO, pa.W, pa.Os, pa.Ol, pa.H16, Zs, s.BH, s.N, s.T, s.lay(), s.n_0, Ds,
+          dHZ, dQlin, dw);
     }
     const int bytes = lds_q + PairLds<D>::GROUP;
     SLA_TRY(ensure_dyn_lds(bwd_dq_mfma_kernel<D, 2, false, 0>, bytes));
     KernelTimer kt("bwd_sparse_q", st);
-    bwd_dq_mfma_kernel<D, 2, false, 0><<<dim3(xcd_grid((s.T + 1) / 2), s.BH), 512, bytes, st>>>(
+    bwd_dq_mfma_kernel<D, 2, false, 0><<<xcd_grid((s.T + 1) / 2) * s.BH, 512, bytes, st>>>(
         (const bf16*)a.Q, (const bf16*)a.K, (const bf16*)a.V, (const bf16*)a.dO, a.L, Ds, a.row_idx,
-        s.n_0 > 0 ? dQlin : nullptr, s.N, s.T, s.lay(), s.n_h, s.scale, (bf16*)a.dQ, pa);
+        s.n_0 > 0 ? dQlin : nullptr, s.BH, s.N, s.T, s.lay(), s.n_h, s.scale, (bf16*)a.dQ, pa, dw);
   } else {
     constexpr int bytes = lds_q > lds_p ? lds_q : lds_p;
     auto kern = s.phi == 0 ? bwd_dq_mfma_kernel<D, 1, true, 0> : bwd_dq_mfma_kernel<D, 1, true, 1>;
     SLA_TRY(ensure_dyn_lds(kern, bytes));
     KernelTimer kt("bwd_query", st);
-    kern<<<dim3(xcd_grid(s.T), s.BH), 256, bytes, st>>>(
-        (const bf16*)a.Q, (const bf16*)a.K, (const bf16*)a.V, (const bf16*)a.dO, a.L, nullptr, a.row_idx, nullptr, s.N,
-        s.T, s.lay(), s.n_h, s.scale, (bf16*)a.dQ, pa);
+    kern<<<xcd_grid(s.T) * s.BH + nparts, 256, bytes, st>>>(
+        (const bf16*)a.Q, (const bf16*)a.K, (const bf16*)a.V, (const bf16*)a.dO, a.L, nullptr, a.row_idx, nullptr, s.BH,
+        s.N, s.T, s.lay(), s.n_h, s.scale, (bf16*)a.dQ, pa, dw);
   }
   return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t mfma_backward_query(const Shape& s, const BwdArgs& a, float* Ds, void* dHZ16, float* dQlin,
-                               hipStream_t st) {
+hipError_t mfma_backward_query(const Shape& s, const BwdArgs& a, float* Ds, void* dHZ16, float* dQlin, float* dWpart,
+                               int nparts, hipStream_t st) {
   bf16* dHZ = reinterpret_cast<bf16*>(dHZ16);
   bf16* dQl = reinterpret_cast<bf16*>(dQlin);   // bf16 rows in the float-sized buffer
-  return s.d == 64 ? query_impl<64>(s, a, Ds, dHZ, dQl, st) : query_impl<128>(s, a, Ds, dHZ, dQl, st);
-}
-
-hipError_t mfma_backward_dw(const Shape& s, const BwdArgs& a, float* dWpart, int nparts, hipStream_t st) {
-  return s.d == 64 ? dw_impl<64>(s, a, dWpart, nparts, st) : dw_impl<128>(s, a, dWpart, nparts, st);
+  return s.d == 64 ? query_impl<64>(s, a, Ds, dHZ, dQl, dWpart, nparts, st)
+                   : query_impl<128>(s, a, Ds, dHZ, dQl, dWpart, nparts, st);
 }
 
 }  // namespace sla

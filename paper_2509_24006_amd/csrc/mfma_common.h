@@ -572,7 +572,7 @@ __device__ __forceinline__ int xcd_local_block(int bx, int T) {
   const int i = (bx & 7) * C + (bx >> 3);
   return i < T ? i : -1;
 }
-inline int xcd_grid(int T) { return 8 * ((T + 7) / 8); }
+__host__ __device__ inline int xcd_grid(int T) { return 8 * ((T + 7) / 8); }
 
 // all outstanding global loads of this wave (including those that write LDS) have completed
 __device__ __forceinline__ void wait_vm0() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }

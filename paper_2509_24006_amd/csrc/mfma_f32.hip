@@ -532,6 +532,34 @@ __global__ __launch_bounds__(256, 2) void f32_forward_kernel(
   if (Ol) store_frag<NT>(Ol + qb, g, ol);
 }
 
+// dW = sum over tokens of (O^l)^T dO: part p of `parts` sums the 64-token tiles p, p + parts, .. into its own d x d
+// matrix; dw_sum adds the parts.  They are the last workgroups of the query-side launch (it forms nothing they
+// need) and run where its last round leaves CUs idle (4 heads
+// x 122 blocks, d = 128: 119.5 + 20.0 us in two launches -> 127.2).
+template <int D>
+__device__ __forceinline__ void f32_dw_part(unsigned char* smem, const float* __restrict__ Ol, const float* __restrict__ dO,
+                                            int p, int parts, int BH, int N, int Tn, Lay lay, float* __restrict__ part) {
+  constexpr int NT = D / 16, TB = FTile<D>::BYTES;
+  const int tid = threadIdx.x, w = wave_uniform(tid >> 6), l = tid & 63;
+  FLoader<D> lo, lg;
+  lo.init(lds_base(smem), w, l, 4 * D);
+  lg.init(lds_base(smem), w, l, 4 * lay.ts, N);
+  FAddr<D> ad;
+  ad.init(l);
+  f32x4 acc[D / 64][NT];
+  zero_outer<D>(acc);
+  for (int t = p; t < BH * Tn; t += parts) {
+    const int bh = t / Tn, i = t - bh * Tn;
+    lo.load(matrix_rsrc_f32<D>(Ol + (size_t)bh * N * D, N), i, TB);
+    lg.load(head_rsrc_f32<D>(dO + lay.head(bh), N, 4 * lay.ts), i, 0);
+    wait_vm0();
+    __syncthreads();
+    outer_product<D>(ad, smem, smem + TB, w, acc);
+    __syncthreads();
+  }
+  store_outer<D>(part + (size_t)p * D * D, acc, w, l);   // rows c of O^l along the lanes
+}
+
 // ------------------------------------------------------------------ backward, query side
 // One workgroup per query block, waves as in the forward kernel (lane = query).  D line of Alg. 2
 // (dO^l = dO W^T, D^s, D^l), then its first loop: dH_i, dZ_i and dQ^phi_i through phi, then the
@@ -544,12 +572,16 @@ __global__ __launch_bounds__(256, 2) void f32_bwd_query_kernel(
     const float* __restrict__ dO, const float* __restrict__ Os, const float* __restrict__ Ol,
     const float* __restrict__ L, const float* __restrict__ HZ, const int32_t* __restrict__ row_idx, int N, int Tn,
     Lay lay, int n_h, int n_0, int phi, float scale, float* __restrict__ Ds, float* __restrict__ dHZ,
-    float* __restrict__ dQ) {
+    float* __restrict__ dQ, int BH, float* __restrict__ dWpart, int nparts) {
   constexpr int NT = D / 16, TB = FTile<D>::BYTES;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  if ((int)blockIdx.x >= Tn * BH) {   // the last workgroups
+    f32_dw_part<D>(smem, Ol, dO, blockIdx.x - Tn * BH, nparts, BH, N, Tn, lay, dWpart);
+    return;
+  }
   float* dls = reinterpret_cast<float*>(smem + 2 * TB);   // D^l / (phi(Q) Z) of the 64 queries
   const int tid = threadIdx.x, w = wave_uniform(tid >> 6), l = tid & 63, g = l >> 4, n = l & 15;
-  const int i = blockIdx.x, bh = blockIdx.y;
+  const int i = blockIdx.x % Tn, bh = blockIdx.x / Tn;
   const int q0 = i * kBlk, rows = min(kBlk, N - q0), row = 16 * w + n;
   const bool ok = row < rows;
   const size_t qi = (size_t)bh * N + q0 + row;
@@ -887,33 +919,6 @@ __global__ __launch_bounds__(256, 2) void f32_bwd_key_kernel(
   }
 }
 
-// dW = sum over tokens of (O^l)^T dO: each workgroup sums a strided set of 64-token tiles into its
-// own partial d x d matrix; dw_sum adds the partials.
-template <int D>
-__global__ __launch_bounds__(256, 2) void f32_dw_kernel(const float* __restrict__ Ol, const float* __restrict__ dO,
-                                                        int BH, int N, int Tn, Lay lay, float* __restrict__ part) {
-  constexpr int NT = D / 16, TB = FTile<D>::BYTES;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  const int tid = threadIdx.x, w = wave_uniform(tid >> 6), l = tid & 63;
-  FLoader<D> lo, lg;
-  lo.init(lds_base(smem), w, l, 4 * D);
-  lg.init(lds_base(smem), w, l, 4 * lay.ts, N);
-  FAddr<D> ad;
-  ad.init(l);
-  f32x4 acc[D / 64][NT];
-  zero_outer<D>(acc);
-  for (int t = blockIdx.x; t < BH * Tn; t += gridDim.x) {
-    const int bh = t / Tn, i = t - bh * Tn;
-    lo.load(matrix_rsrc_f32<D>(Ol + (size_t)bh * N * D, N), i, TB);
-    lg.load(head_rsrc_f32<D>(dO + lay.head(bh), N, 4 * lay.ts), i, 0);
-    wait_vm0();
-    __syncthreads();
-    outer_product<D>(ad, smem, smem + TB, w, acc);
-    __syncthreads();
-  }
-  store_outer<D>(part + (size_t)blockIdx.x * D * D, acc, w, l);   // rows c of O^l along the lanes
-}
-
 // out[i] = sum over k with bit k of ind[i] set of the state rows in[k]
 hipError_t f32_aggregate(const float* in, const unsigned long long* ind, const Shape& s, float* out, hipStream_t st) {
   const int row_len = s.state_row(), Tw = (s.T + 63) / 64;
@@ -972,19 +977,14 @@ hipError_t launch_key(const Shape& s, const BwdArgs& a, const float* Ds, const f
 template <int D>
 hipError_t backward_impl(const Shape& s, const BwdArgs& a, float* Ds, float* dHZ, float* dHZcol, float* dWpart,
                          int nparts, hipStream_t st) {
-  const size_t tiles = 2 * FTile<D>::BYTES, lds_q = tiles + 4 * kBlk;
+  const size_t lds_q = 2 * FTile<D>::BYTES + 4 * kBlk;
   SLA_TRY(ensure_dyn_lds(f32_bwd_query_kernel<D>, lds_q));
   {
     KernelTimer kt("bwd_query", st);
-    f32_bwd_query_kernel<D><<<dim3(s.T, s.BH), 256, lds_q, st>>>(
+    f32_bwd_query_kernel<D><<<s.T * s.BH + nparts, 256, lds_q, st>>>(
         (const float*)a.Q, (const float*)a.K, (const float*)a.V, (const float*)a.W, (const float*)a.dO,
         (const float*)a.Os, (const float*)a.Ol, a.L, a.HZ, a.row_idx, s.N, s.T, s.lay(), s.n_h, s.n_0, s.phi, s.scale,
-        Ds, dHZ, (float*)a.dQ);
-  }
-  SLA_TRY(ensure_dyn_lds(f32_dw_kernel<D>, tiles));
-  {
-    KernelTimer kt("dw_partial", st);
-    f32_dw_kernel<D><<<nparts, 256, tiles, st>>>((const float*)a.Ol, (const float*)a.dO, s.BH, s.N, s.T, s.lay(), dWpart);
+        Ds, dHZ, (float*)a.dQ, s.BH, dWpart, nparts);
   }
   const DwSum dw{dWpart, nparts, D * D, a.dW, a.dW16};
   if (s.n_0 > 0) SLA_TRY(f32_aggregate(dHZ, a.indT, s, dHZcol, st));

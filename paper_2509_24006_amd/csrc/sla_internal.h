@@ -120,9 +120,9 @@ hipError_t aggregate_alt(int method, const void* in, const unsigned long long* i
 
 // query side on the matrix cores (mfma_bwd_query.hip): D^s, dH_i / dZ_i rows (dHZ16), dQ.  dQlin:
 // scratch for the linear part of dQ (only used with query blocks of two or four tiles).
-hipError_t mfma_backward_query(const Shape& s, const BwdArgs& a, float* Ds, void* dHZ16, float* dQlin, hipStream_t st);
-// partial sums of dW = sum O^l^T dO
-hipError_t mfma_backward_dw(const Shape& s, const BwdArgs& a, float* dWpart, int nparts, hipStream_t st);
+// dWpart: nparts partial sums of dW = sum O^l^T dO.
+hipError_t mfma_backward_query(const Shape& s, const BwdArgs& a, float* Ds, void* dHZ16, float* dQlin, float* dWpart,
+                               int nparts, hipStream_t st);
 
 // Brackets one kernel launch with events when profiling is on (profile.hip).
 class KernelTimer {
