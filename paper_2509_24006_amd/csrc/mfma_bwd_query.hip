@@ -448,12 +448,14 @@ __global__ __launch_bounds__(256 * QT, QT == 1 ? (D == 64 ? 3 : 2) : 1) void bwd
   const int wall = threadIdx.x >> 6, l = threadIdx.x & 63, g = l >> 5, ln = l & 31;
   const int grp = QT == 1 ? 0 : wave_uniform(wall >> 2), w = wall & 3, tid = threadIdx.x & 255;
   const int qh = w & 1, kh = w >> 1;
-  const int nb = (Tn + QT - 1) / QT, per_head = xcd_grid(nb), bh = blockIdx.x / per_head;
-  if (FUSED && bh >= BH) {   // the last workgroups
-    dw_part<D>(smem, dw, blockIdx.x - per_head * BH, BH, N, Tn, lay);
+  const int nb = (Tn + QT - 1) / QT, per_row = block_row(nb), tiles = per_row * block_rows(BH, nb);
+  if (FUSED && (int)blockIdx.x >= tiles) {   // the last workgroups
+    dw_part<D>(smem, dw, blockIdx.x - tiles, BH, N, Tn, lay);
     return;
   }
-  const int ib = xcd_local_block(blockIdx.x % per_head, nb);
+  const int block_y = blockIdx.x / per_row;
+  const BlockOf own_block = block_of(block_y, blockIdx.x - block_y * per_row, BH, nb);
+  const int bh = own_block.bh, ib = own_block.i;
   if (ib < 0) return;
   // (a last block of a single tile: the second group runs along with no valid query and stores nothing)
   const int i = QT * ib + grp;
@@ -673,7 +675,7 @@ hipError_t query_impl(const Shape& s, const BwdArgs& a, float* Ds, bf16* dHZ, bf
     const int bytes = lds_q + PairLds<D>::GROUP;
     SLA_TRY(ensure_dyn_lds(bwd_dq_mfma_kernel<D, 2, false, 0>, bytes));
     KernelTimer kt("bwd_sparse_q", st);
-    bwd_dq_mfma_kernel<D, 2, false, 0><<<xcd_grid((s.T + 1) / 2) * s.BH, 512, bytes, st>>>(
+    bwd_dq_mfma_kernel<D, 2, false, 0><<<block_row((s.T + 1) / 2) * block_rows(s.BH, (s.T + 1) / 2), 512, bytes, st>>>(
         (const bf16*)a.Q, (const bf16*)a.K, (const bf16*)a.V, (const bf16*)a.dO, a.L, Ds, a.row_idx,
         s.n_0 > 0 ? dQlin : nullptr, s.BH, s.N, s.T, s.lay(), s.n_h, s.scale, (bf16*)a.dQ, pa, dw);
   } else {
@@ -681,7 +683,7 @@ hipError_t query_impl(const Shape& s, const BwdArgs& a, float* Ds, bf16* dHZ, bf
     auto kern = s.phi == 0 ? bwd_dq_mfma_kernel<D, 1, true, 0> : bwd_dq_mfma_kernel<D, 1, true, 1>;
     SLA_TRY(ensure_dyn_lds(kern, bytes));
     KernelTimer kt("bwd_query", st);
-    kern<<<xcd_grid(s.T) * s.BH + nparts, 256, bytes, st>>>(
+    kern<<<block_row(s.T) * block_rows(s.BH, s.T) + nparts, 256, bytes, st>>>(
         (const bf16*)a.Q, (const bf16*)a.K, (const bf16*)a.V, (const bf16*)a.dO, a.L, nullptr, a.row_idx, nullptr, s.BH,
         s.N, s.T, s.lay(), s.n_h, s.scale, (bf16*)a.dQ, pa, dw);
   }

@@ -562,17 +562,32 @@ __device__ __forceinline__ void store_rows_f32(unsigned char* stage, const f32x1
   }
 }
 
-// Workgroups are dealt to the 8 XCDs (each with its own L2) round-robin by linear index.  With a
-// grid of 8 * ceil(T / 8) workgroups per head, XCD x gets the contiguous blocks
-// [x ceil(T/8), (x+1) ceil(T/8)) in ascending order, so that neighbouring query blocks -- which
-// share many of their critical key blocks -- run on the same L2 at about the same time.
-// Returns the block index, or -1 for a padding workgroup.
-__device__ __forceinline__ int xcd_local_block(int bx, int T) {
-  const int C = (T + 7) >> 3;
-  const int i = (bx & 7) * C + (bx >> 3);
-  return i < T ? i : -1;
+// Which query block a workgroup of a launch over nb blocks per head owns.  Workgroups are dealt to the 8
+// XCDs (each with its own L2) round-robin by index.  Within a head XCD x gets a contiguous range of
+// ceil(nb / 8) blocks in ascending order, so that neighbouring query blocks -- which share many of their
+// critical key blocks -- run on the same L2 at about the same time.  The last ranges are shorter where nb is
+// no multiple of eight; the ranges rotate from head to head, so that no XCD gets them all (12 heads x
+// 146 blocks of 7, d = 128, forward 86.1 -> 82.1 us; 256 x 17 of 2, d = 64, 72 -> 62, query side 113 -> 98).
+// A head of up to eight blocks stays on one XCD whole: a workgroup per XCD would fetch every K_j, V_j into
+// as many L2s, and the XCDs from the head's length on would get nothing.  (Forward, d = 128, one
+// workgroup per XCD -> one head: 2048 heads x 7 blocks, all critical 624 -> 354 us, x 8 662 -> 436; 4096 x 1
+// 451 -> 67; 9 x 8, two critical 11.5 either way.  Query side with the parts of dW, d = 64: 4096 x 1 213 -> 48,
+// 2048 x 5 of 2 293 -> 212, 1024 x 8 172.6 -> 169.5.)
+// i < 0: a padding workgroup.
+struct BlockOf {
+  int bh, i;
+};
+// The launch has block_rows rows (a head, or eight short ones) of block_row workgroups, a multiple of eight.
+__device__ __forceinline__ BlockOf block_of(int row, int r, int BH, int nb) {
+  if (nb <= 8) {
+    const int bh = 8 * row + (r & 7);
+    return BlockOf{bh, bh < BH ? r >> 3 : -1};
+  }
+  const int i = ((r + row) & 7) * ((nb + 7) >> 3) + (r >> 3);
+  return BlockOf{row, i < nb ? i : -1};
 }
-__host__ __device__ inline int xcd_grid(int T) { return 8 * ((T + 7) / 8); }
+__host__ __device__ inline int block_row(int nb) { return nb <= 8 ? 8 * nb : 8 * ((nb + 7) / 8); }
+__host__ __device__ inline int block_rows(int BH, int nb) { return nb <= 8 ? (BH + 7) / 8 : BH; }
 
 // all outstanding global loads of this wave (including those that write LDS) have completed
 __device__ __forceinline__ void wait_vm0() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }

@@ -205,10 +205,8 @@ __global__ __launch_bounds__(256 * QT, QT == 1 ? 2 : 1) void fwd_mfma_kernel(
   const int grp = QT == 1 ? 0 : wave_uniform(wall >> 2), w = wall & 3;   // tile of the workgroup, wave of the tile
   const int qh = w & 1, par = w >> 1;
   const int nb = (Tn + QT - 1) / QT;
-  // heads of up to eight workgroups: one head per XCD, eight heads per row of the grid
-  const bool whole = nb <= 8;
-  const int bh = whole ? 8 * blockIdx.y + (blockIdx.x & 7) : blockIdx.y;
-  const int ib = whole ? (bh < BH ? (int)(blockIdx.x >> 3) : -1) : xcd_local_block(blockIdx.x, nb);
+  const BlockOf own_block = block_of(blockIdx.y, blockIdx.x, BH, nb);
+  const int bh = own_block.bh, ib = own_block.i;
   if (ib < 0) return;
   // a last block of a single tile: the second group runs along (it shares the tile loads and the
   // barriers) on the last tile's tables with no valid query, and stores nothing
@@ -592,13 +590,8 @@ hipError_t forward_impl(const Shape& s, const FwdArgs& a, bf16* hz16, bf16* WTp,
   auto launch = [&](auto kern, int qt) -> hipError_t {
     SLA_TRY(ensure_dyn_lds(kern, qt * lds));
     KernelTimer kt("fwd_sparse", st);
-    // Workgroups go to the XCDs round-robin.  A head of up to eight stays on one of them: a workgroup
-    // per XCD would fetch every K_j, V_j into as many L2s, and the XCDs from the head's length on
-    // would get nothing.  (d = 128, one workgroup per XCD -> one head: 2048 heads x 7 tiles, all
-    // critical 624 -> 354 us, x 8 662 -> 436; 4096 x 1 451 -> 67; 9 x 8, two critical 11.5 either way.)
     const int nb = (s.T + qt - 1) / qt;
-    const dim3 grid = nb <= 8 ? dim3(8 * nb, (s.BH + 7) / 8) : dim3(xcd_grid(nb), s.BH);
-    kern<<<grid, 256 * qt, qt * lds, st>>>(
+    kern<<<dim3(block_row(nb), block_rows(s.BH, nb)), 256 * qt, qt * lds, st>>>(
         (const bf16*)a.Q, (const bf16*)a.K, (const bf16*)a.V, WTp, a.row_idx, (const bf16*)a.HZ, Zs, s.BH, s.N, s.T,
         s.lay(), s.n_h, s.n_0, s.phi, s.scale * kLog2e, (bf16*)a.O, (bf16*)a.Os, (bf16*)a.Ol, a.L);
     return hipSuccess;
