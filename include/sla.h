@@ -141,6 +141,13 @@ int sla_forward(const sla_params* p, const void* Q, const void* K, const void* V
                 const int8_t* Mc, const void* luts, void* O, void* saved, void* workspace,
                 size_t workspace_bytes, void* stream);
 
+/* sla_build_mask and sla_forward in one call, for a caller that has no use for the mask before the forward
+ * pass: the same results in fewer launches.  mask_workspace: as for sla_build_mask, workspace: as for
+ * sla_forward; Mc and luts are outputs. */
+int sla_mask_forward(const sla_params* p, const void* Q, const void* K, const void* V, const void* W, int8_t* Mc,
+                     void* luts, void* mask_workspace, size_t mask_workspace_bytes, void* O, void* saved,
+                     void* workspace, size_t workspace_bytes, void* stream);
+
 /* Algorithm 2, with dQ, dK scaled by 1/sqrt(d), dV accumulated over both branches, and the
  * chain rule through phi and W.  dO, dQ, dK, dV: dtype [B,H,N,d] (or [B,N,H,d]); dW: float [d,d] (out,
  * summed over batch, heads and tokens).  saved: as written by sla_forward with the same

@@ -21,7 +21,7 @@ SLA_PHI_SOFTMAX, SLA_PHI_ELU1 = 0, 1
 SLA_BHND, SLA_BNHD, SLA_STRIDED = 0, 1, 2
 SLA_AGG_GEMM, SLA_AGG_ADD, SLA_AGG_PREAGG, SLA_AGG_FOUR_RUSSIANS = 0, 1, 2, 3
 SLA_STATIC_WS_BYTES = 32 << 20
-EXPORTS = ("sla_sizes", "sla_build_mask", "sla_build_mask_static", "sla_classify_scores", "sla_forward", "sla_backward", "sla_backward_typed",
+EXPORTS = ("sla_sizes", "sla_build_mask", "sla_build_mask_static", "sla_classify_scores", "sla_forward", "sla_mask_forward", "sla_backward", "sla_backward_typed",
            "sla_aggregate_ws_bytes", "sla_aggregate_states", "sla_wide_query_tiles",
            "sla_profile_enable", "sla_profile_read", "sla_profile_mfma_peak", "sla_profile_dq_atomics", "sla_strerror")
 
@@ -65,6 +65,7 @@ def lib() -> ctypes.CDLL:
         L.sla_build_mask_static.argtypes = [pp, vp, vp, vp, vp, vp]
         L.sla_classify_scores.argtypes = [pp, vp, vp, vp, vp]
         L.sla_forward.argtypes = [pp] + [vp] * 9 + [sz, vp]
+        L.sla_mask_forward.argtypes = [pp] + [vp] * 7 + [sz] + [vp] * 3 + [sz, vp]
         L.sla_backward.argtypes = [pp] + [vp] * 13 + [sz, vp]
         L.sla_backward_typed.argtypes = [pp] + [vp] * 12 + [ctypes.c_int, vp, sz, vp]
         L.sla_aggregate_ws_bytes.argtypes = [pp, ctypes.c_int, ctypes.POINTER(ctypes.c_uint64)]
@@ -254,6 +255,18 @@ def sla_forward(p: sla_params, Q, K, V, W, Mc, luts, O: Optional[torch.Tensor] =
                              _ptr(luts), _ptr(O), _ptr(saved), _ptr(ws), ws.numel(), _stream()),
            "sla_forward")
     return O, saved
+
+
+def sla_mask_forward(p: sla_params, Q, K, V, W, need_saved: bool = True
+                     ) -> Tuple[torch.Tensor, torch.Tensor, torch.Tensor, Optional[torch.Tensor]]:
+    """sla_build_mask and sla_forward in one call (fewer launches): (Mc, luts, O, saved)."""
+    r = _host_calls().mask_forward(ctypes.addressof(p), Q, K, V, W, need_saved)
+    if type(r) is tuple:
+        return r
+    if r is not None:
+        _check(r, "sla_mask_forward")
+    Mc, luts, _ = sla_build_mask(p, Q, K)
+    return (Mc, luts) + sla_forward(p, Q, K, V, W, Mc, luts, need_saved=need_saved)
 
 
 def sla_backward(p: sla_params, Q, K, V, W, Mc, luts, saved, dO,

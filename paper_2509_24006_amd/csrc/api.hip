@@ -145,6 +145,109 @@ hipError_t scratch_of_current_device(void** out) {
 
 int hip_status(hipError_t e) { return e == hipSuccess ? SLA_OK : SLA_EHIP; }
 
+// The mask and its lookup tables, as pointers into the caller's buffers.
+struct Tables {
+  int8_t* Mc;
+  int32_t *row_idx, *col_cnt;
+  unsigned long long *ind, *ind_t;
+  ColArgs col;
+};
+Tables tables(const Shape& s, const sla_sizes_t& z, int8_t* Mc, void* luts) {
+  char* l = (char*)luts;
+  Tables t;
+  t.Mc = Mc;
+  t.row_idx = (int32_t*)(l + z.lut_row_idx);
+  t.col_cnt = (int32_t*)(l + z.luts_bytes - align_up((size_t)s.BH * s.T * 4));
+  t.ind = (unsigned long long*)(l + z.lut_ind);
+  t.ind_t = (unsigned long long*)(l + z.lut_ind_t);
+  t.col = ColArgs{Mc, s.Tq, s.rq, s.T, s.n_h, t.col_cnt, (int32_t*)(l + z.lut_col_ptr), (int32_t*)(l + z.lut_col_order),
+                  (int32_t*)(l + z.lut_col_rows)};
+  return t;
+}
+
+// at most 64 key blocks: everything behind the pooling (or behind given scores) in one launch
+hipError_t mask_small(const Shape& s, const float* qbar, const float* kbar, const float* given, float* scores,
+                      const Tables& t, hipStream_t st) {
+  return launch_mask_small(qbar, kbar, given, s, scores, t.Mc, t.row_idx, t.ind, t.ind_t, t.col.ptr, t.col.order, t.col.rows,
+                           st);
+}
+// more of them: labels, row table, bit masks and column counts of given scores
+hipError_t classify(const Shape& s, const float* scores, const Tables& t, hipStream_t st) {
+  const hipError_t e = launch_classify(scores, s, t.Mc, t.row_idx, t.col_cnt, st);
+  return e == hipSuccess ? launch_indicator(t.Mc, s, t.col_cnt, t.ind, t.ind_t, st) : e;
+}
+
+// One mask step: checked arguments, the workspace's pieces, and what follows the pooling but for the
+// column tables of longer sequences.
+struct MaskCall {
+  Shape s;
+  sla_sizes_t z;
+  float *qbar, *kbar, *scores;
+  PoolArgs pool;
+  Tables t;
+  int open(const sla_params* p, const void* Q, const void* K, int8_t* Mc, void* luts, void* workspace,
+           size_t workspace_bytes) {
+    const int rc = make_shape(p, &s);
+    if (rc != SLA_OK) return rc;
+    if (!Q || !K || !Mc || !luts || !workspace) return SLA_EINVAL;
+    if (misaligned(Q) || misaligned(K) || misaligned(luts) || misaligned(workspace)) return SLA_EINVAL;
+    fill_sizes(s, &z);
+    if (workspace_bytes < z.ws_mask_bytes) return SLA_ENOSPACE;
+    char* ws = (char*)workspace;
+    qbar = (float*)(ws + z.ws_mask_qbar);
+    kbar = (float*)(ws + z.ws_mask_kbar);
+    scores = (float*)(ws + z.ws_mask_scores);
+    pool = pool_args(Q, K, s, qbar, kbar);
+    t = tables(s, z, Mc, luts);
+    return SLA_OK;
+  }
+  hipError_t behind_pool(hipStream_t st) const {
+    if (s.T <= kBlk) return mask_small(s, qbar, kbar, nullptr, scores, t, st);
+    const hipError_t e = launch_scores(qbar, kbar, s, scores, st);
+    return e == hipSuccess ? classify(s, scores, t, st) : e;
+  }
+};
+
+// One forward pass: checked arguments, the kernels' view of them, and its two parts.
+struct FwdCall {
+  Shape s;
+  FwdArgs a;
+  char* states;   // bf16: the workspace's part for the key-block states and the projection matrix
+  int open(const sla_params* p, const void* Q, const void* K, const void* V, const void* W, const int8_t* Mc,
+           const void* luts, void* O, void* saved, void* workspace, size_t workspace_bytes) {
+    const int rc = make_shape(p, &s);
+    if (rc != SLA_OK) return rc;
+    if (!Q || !K || !V || !W || !Mc || !luts || !O || !workspace) return SLA_EINVAL;
+    if (misaligned(Q) || misaligned(K) || misaligned(V) || misaligned(W) || misaligned(O) ||
+        misaligned(luts) || misaligned(saved) || misaligned(workspace))
+      return SLA_EINVAL;
+    sla_sizes_t z;
+    fill_sizes(s, &z);
+    if (workspace_bytes < z.ws_forward_bytes) return SLA_ENOSPACE;
+    char* ws = (char*)workspace;
+    char* sv = (char*)saved;
+    const char* l = (const char*)luts;
+    a.Q = Q; a.K = K; a.V = V; a.W = W;
+    a.row_idx = (const int32_t*)(l + z.lut_row_idx);
+    a.ind = (const unsigned long long*)(l + z.lut_ind);
+    a.O = O;
+    a.Os = sv ? sv + z.saved_Os : nullptr;
+    a.Ol = sv ? sv + z.saved_Ol : nullptr;
+    a.L = sv ? (float*)(sv + z.saved_L) : nullptr;
+    const size_t state = z.saved_bytes - z.saved_HZ;
+    states = ws + state;
+    a.hz = (float*)states;
+    a.HZ = sv ? (float*)(sv + z.saved_HZ) : (float*)ws;
+    return SLA_OK;
+  }
+  hipError_t key_states(const Beside& b, hipStream_t st) const {   // (only with marginal blocks)
+    return s.dtype == SLA_BF16 ? mfma_states(s, a, states, b, st) : f32_states(s, a, b, st);
+  }
+  hipError_t behind_states(hipStream_t st) const {
+    return s.dtype == SLA_BF16 ? mfma_forward(s, a, states, st) : f32_forward(s, a, st);
+  }
+};
+
 }  // namespace
 
 extern "C" {
@@ -167,47 +270,22 @@ int sla_classify_scores(const sla_params* p, const float* scores, int8_t* Mc, vo
   sla_sizes_t z;
   fill_sizes(s, &z);
   hipStream_t st = (hipStream_t)stream;
-  char* l = (char*)luts;
-  if (s.T <= kBlk)
-    return hip_status(launch_mask_small(nullptr, nullptr, scores, s, nullptr, Mc, (int32_t*)(l + z.lut_row_idx),
-                                        (unsigned long long*)(l + z.lut_ind), (unsigned long long*)(l + z.lut_ind_t),
-                                        (int32_t*)(l + z.lut_col_ptr), (int32_t*)(l + z.lut_col_order),
-                                        (int32_t*)(l + z.lut_col_rows), st));
-  int32_t* col_cnt = (int32_t*)(l + z.luts_bytes - align_up((size_t)s.BH * s.T * 4));
-  hipError_t e = launch_classify(scores, s, Mc, (int32_t*)(l + z.lut_row_idx), col_cnt, st);
-  if (e == hipSuccess)
-    e = launch_csc(Mc, s, col_cnt, (int32_t*)(l + z.lut_col_ptr), (int32_t*)(l + z.lut_col_rows),
-                   (unsigned long long*)(l + z.lut_ind), (unsigned long long*)(l + z.lut_ind_t),
-                   (int32_t*)(l + z.lut_col_order), st);
+  const Tables t = tables(s, z, Mc, luts);
+  hipError_t e = s.T <= kBlk ? mask_small(s, nullptr, nullptr, scores, nullptr, t, st) : classify(s, scores, t, st);
+  if (e == hipSuccess && s.T > kBlk) e = launch_col_tables(t.col, s, st);
   return hip_status(e);
 }
 
 int sla_build_mask(const sla_params* p, const void* Q, const void* K, int8_t* Mc, void* luts,
                    void* workspace, size_t workspace_bytes, void* stream) {
-  Shape s;
-  const int rc = make_shape(p, &s);
+  MaskCall m;
+  const int rc = m.open(p, Q, K, Mc, luts, workspace, workspace_bytes);
   if (rc != SLA_OK) return rc;
-  if (!Q || !K || !Mc || !luts || !workspace) return SLA_EINVAL;
-  if (misaligned(Q) || misaligned(K) || misaligned(luts) || misaligned(workspace)) return SLA_EINVAL;
-  sla_sizes_t z;
-  fill_sizes(s, &z);
-  if (workspace_bytes < z.ws_mask_bytes) return SLA_ENOSPACE;
   hipStream_t st = (hipStream_t)stream;
-  char* ws = (char*)workspace;
-  float* qbar = (float*)(ws + z.ws_mask_qbar);
-  float* kbar = (float*)(ws + z.ws_mask_kbar);
-  float* sc = (float*)(ws + z.ws_mask_scores);
-  hipError_t e = launch_pool(Q, K, s, qbar, kbar, st);
-  if (e == hipSuccess && s.T <= kBlk) {
-    char* l = (char*)luts;
-    return hip_status(launch_mask_small(qbar, kbar, nullptr, s, sc, Mc, (int32_t*)(l + z.lut_row_idx),
-                                        (unsigned long long*)(l + z.lut_ind), (unsigned long long*)(l + z.lut_ind_t),
-                                        (int32_t*)(l + z.lut_col_ptr), (int32_t*)(l + z.lut_col_order),
-                                        (int32_t*)(l + z.lut_col_rows), st));
-  }
-  if (e == hipSuccess) e = launch_scores(qbar, kbar, s, sc, st);
-  if (e != hipSuccess) return SLA_EHIP;
-  return sla_classify_scores(p, sc, Mc, luts, stream);
+  hipError_t e = launch_pool(m.pool, m.s, st);
+  if (e == hipSuccess) e = m.behind_pool(st);
+  if (e == hipSuccess && m.s.T > kBlk) e = launch_col_tables(m.t.col, m.s, st);
+  return hip_status(e);
 }
 
 int sla_build_mask_static(const sla_params* p, const void* Q, const void* K, int8_t* Mc, void* luts,
@@ -229,32 +307,35 @@ int sla_build_mask_static(const sla_params* p, const void* Q, const void* K, int
 int sla_forward(const sla_params* p, const void* Q, const void* K, const void* V, const void* W,
                 const int8_t* Mc, const void* luts, void* O, void* saved, void* workspace,
                 size_t workspace_bytes, void* stream) {
-  Shape s;
-  const int rc = make_shape(p, &s);
+  FwdCall f;
+  const int rc = f.open(p, Q, K, V, W, Mc, luts, O, saved, workspace, workspace_bytes);
   if (rc != SLA_OK) return rc;
-  if (!Q || !K || !V || !W || !Mc || !luts || !O || !workspace) return SLA_EINVAL;
-  if (misaligned(Q) || misaligned(K) || misaligned(V) || misaligned(W) || misaligned(O) ||
-      misaligned(luts) || misaligned(saved) || misaligned(workspace))
-    return SLA_EINVAL;
-  sla_sizes_t z;
-  fill_sizes(s, &z);
-  if (workspace_bytes < z.ws_forward_bytes) return SLA_ENOSPACE;
-  char* ws = (char*)workspace;
-  char* sv = (char*)saved;
-  const char* l = (const char*)luts;
-  FwdArgs a;
-  a.Q = Q; a.K = K; a.V = V; a.W = W;
-  a.row_idx = (const int32_t*)(l + z.lut_row_idx);
-  a.ind = (const unsigned long long*)(l + z.lut_ind);
-  a.O = O;
-  a.Os = sv ? sv + z.saved_Os : nullptr;
-  a.Ol = sv ? sv + z.saved_Ol : nullptr;
-  a.L = sv ? (float*)(sv + z.saved_L) : nullptr;
-  const size_t state = z.saved_bytes - z.saved_HZ;
-  a.hz = (float*)(ws + state);
-  a.HZ = sv ? (float*)(sv + z.saved_HZ) : (float*)ws;
-  if (s.dtype == SLA_BF16) return hip_status(mfma_forward(s, a, ws + state, (hipStream_t)stream));
-  return hip_status(f32_forward(s, a, (hipStream_t)stream));
+  hipStream_t st = (hipStream_t)stream;
+  hipError_t e = f.s.n_0 > 0 ? f.key_states(Beside{}, st) : hipSuccess;
+  if (e == hipSuccess) e = f.behind_states(st);
+  return hip_status(e);
+}
+
+int sla_mask_forward(const sla_params* p, const void* Q, const void* K, const void* V, const void* W, int8_t* Mc,
+                     void* luts, void* mask_workspace, size_t mask_workspace_bytes, void* O, void* saved,
+                     void* workspace, size_t workspace_bytes, void* stream) {
+  MaskCall m;
+  int rc = m.open(p, Q, K, Mc, luts, mask_workspace, mask_workspace_bytes);
+  if (rc != SLA_OK) return rc;
+  FwdCall f;
+  rc = f.open(p, Q, K, V, W, Mc, luts, O, saved, workspace, workspace_bytes);
+  if (rc != SLA_OK) return rc;
+  hipStream_t st = (hipStream_t)stream;
+  const bool small = f.s.T <= kBlk, lin = f.s.n_0 > 0;
+  // The key-block states need no mask.  Their launch takes in the pooling of a short sequence, and the column
+  // tables, which only the backward pass reads, of a longer one.
+  hipError_t e;
+  if (small && lin) e = f.key_states(Beside{&m.pool, nullptr}, st);
+  else e = launch_pool(m.pool, m.s, st);
+  if (e == hipSuccess) e = m.behind_pool(st);
+  if (e == hipSuccess && !small) e = lin ? f.key_states(Beside{nullptr, &m.t.col}, st) : launch_col_tables(m.t.col, m.s, st);
+  if (e == hipSuccess) e = f.behind_states(st);
+  return hip_status(e);
 }
 
 int sla_backward(const sla_params* p, const void* Q, const void* K, const void* V, const void* W,

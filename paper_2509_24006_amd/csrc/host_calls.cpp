@@ -185,6 +185,36 @@ PyObject* forward(PyObject*, PyObject* const* a, Py_ssize_t n) {
   END_HANDLE_TH_ERRORS
 }
 
+// mask_forward(params address, Q, K, V, W, need_saved) -> (Mc, luts, O, saved or None)
+PyObject* mask_forward(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  HANDLE_TH_ERRORS
+  Call c;
+  if (n != 6 || !open_call(a[0], c)) Py_RETURN_NONE;
+  const at::Tensor *Q = plain(a[1]), *K = plain(a[2]), *V = plain(a[3]), *W = plain(a[4]);
+  if (!dense(Q, c) || !dense(K, c) || !dense(V, c) || !packed(W, {c.p->d, c.p->d}, c.dt)) Py_RETURN_NONE;
+  const int save = PyObject_IsTrue(a[5]);
+  if (save < 0) return nullptr;
+  void* st;
+  if (!current_stream(&st)) return nullptr;
+  at::Tensor Mc, luts, O, saved;
+  int rc;
+  {
+    NoGil free;
+    Mc = at::empty({c.p->B, c.p->H, c.z.Tq, c.z.T}, Q->options().dtype(at::kChar).requires_grad(false));
+    luts = new_bytes(c.z.luts_bytes, *Q);
+    O = new_like(*Q, c);
+    if (save) saved = new_bytes(c.z.saved_bytes, *Q);
+    const at::Tensor wm = new_bytes(c.z.ws_mask_bytes, *Q), wf = new_bytes(c.z.ws_forward_bytes, *Q);
+    rc = sla_mask_forward(c.p, Q->data_ptr(), K->data_ptr(), V->data_ptr(), W->data_ptr(), (int8_t*)Mc.data_ptr(),
+                          luts.data_ptr(), wm.data_ptr(), (size_t)wm.numel(), O.data_ptr(), save ? saved.data_ptr() : nullptr,
+                          wf.data_ptr(), (size_t)wf.numel(), st);
+  }
+  if (rc != SLA_OK) return PyLong_FromLong(rc);
+  if (!save) Py_INCREF(Py_None);
+  return pack({THPVariable_Wrap(Mc), THPVariable_Wrap(luts), THPVariable_Wrap(O), save ? THPVariable_Wrap(saved) : Py_None});
+  END_HANDLE_TH_ERRORS
+}
+
 // backward(params address, Q, K, V, W, Mc, luts, saved, dO, workspace, dQ, dK, dV, dW, dW in bf16) -> (dQ, dK, dV, dW)
 PyObject* backward(PyObject*, PyObject* const* a, Py_ssize_t n) {
   HANDLE_TH_ERRORS
@@ -224,6 +254,7 @@ PyObject* backward(PyObject*, PyObject* const* a, Py_ssize_t n) {
 PyMethodDef g_methods[] = {
     {"build_mask", (PyCFunction)(void (*)(void))build_mask, METH_FASTCALL, nullptr},
     {"forward", (PyCFunction)(void (*)(void))forward, METH_FASTCALL, nullptr},
+    {"mask_forward", (PyCFunction)(void (*)(void))mask_forward, METH_FASTCALL, nullptr},
     {"backward", (PyCFunction)(void (*)(void))backward, METH_FASTCALL, nullptr},
     {nullptr, nullptr, 0, nullptr},
 };

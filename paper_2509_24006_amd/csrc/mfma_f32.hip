@@ -14,6 +14,7 @@
 // chunk c of row r sits at chunk position c ^ (r % 16).  Both reads are then free of bank
 // conflicts: 16 rows at one chunk (operand read by rows) hit 16 different positions, and 4 rows of
 // 16 adjacent floats (operand contracted over tile rows) hit four different 64-byte pieces.
+#include "mask_parts.h"
 #include "mfma_common.h"
 
 namespace sla {
@@ -253,13 +254,27 @@ __device__ __forceinline__ float tile_elem(const unsigned char* tile, int r, int
 // ------------------------------------------------------------------ key-block states
 // Alg. 1 precompute line: h_j = phi(K_j)^T V_j, z_j = rowsum(phi(K_j)^T), one workgroup per key
 // block; stored as a state row (h transposed, then z).
-template <int D>
+// BESIDE: what the first workgroups do, as in the bf16 path: pool Q and K (1), form the column tables (2).
+// (4 heads x 122 blocks, d = 128: tables and states 11.1 + 23.1 -> 23.3 us; 2 x 16, d = 64: pooling 6.1 + 7.5 -> 7.5.)
+template <int D, int BESIDE>
 __global__ __launch_bounds__(256, 2) void f32_states_kernel(const float* __restrict__ K, const float* __restrict__ V,
-                                                            int N, int Tn, Lay lay, int phi, float* __restrict__ hz) {
+                                                            int N, int Tn, Lay lay, int phi, float* __restrict__ hz,
+                                                            PoolArgs pool, ColArgs col) {
   constexpr int NT = D / 16, TB = FTile<D>::BYTES;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int tid = threadIdx.x, w = wave_uniform(tid >> 6), l = tid & 63, g = l >> 4, n = l & 15;
-  const int j = blockIdx.x, bh = blockIdx.y;
+  int j = blockIdx.x, bh = blockIdx.y;
+  if constexpr (BESIDE != 0) {   // (one row of workgroups, those beside the states first)
+    const int Tw = (Tn + 63) / 64, first = BESIDE == 1 ? 2 * pool.wgs : Tw * pool.BH;
+    if (j < first) {
+      if constexpr (BESIDE == 1) pool_part<float, D>(pool, j);
+      else col_tables_part(smem, col, j % Tw, j / Tw);
+      return;
+    }
+    j -= first;
+    bh = j / Tn;
+    j -= bh * Tn;
+  }
   const int n0 = j * kBlk, cnt = min(kBlk, N - n0), row = 16 * w + n;
   const float* Kh = K + lay.head(bh);
   FLoader<D> ld;
@@ -940,15 +955,28 @@ hipError_t f32_aggregate(const float* in, const unsigned long long* ind, const S
 }
 
 template <int D>
+hipError_t states_impl(const Shape& s, const FwdArgs& a, const Beside& b, hipStream_t st) {
+  const int Tw = (s.T + 63) / 64;
+  constexpr int tiles = 2 * FTile<D>::BYTES;
+  const int lds = b.col ? max(tiles, col_tables_lds(Tw)) : tiles;
+  const int first = b.pool ? 2 * b.pool->wgs : b.col ? Tw * s.BH : 0;
+  PoolArgs pool = {};
+  if (b.pool) pool = *b.pool;
+  pool.BH = s.BH;
+  auto kern = b.pool ? f32_states_kernel<D, 1> : b.col ? f32_states_kernel<D, 2> : f32_states_kernel<D, 0>;
+  SLA_TRY(ensure_dyn_lds(kern, lds));
+  KernelTimer kt(b.pool ? "states_pool" : b.col ? "states_cols" : "states", st);
+  const dim3 grid = first ? dim3(first + s.T * s.BH) : dim3(s.T, s.BH);
+  kern<<<grid, 256, lds, st>>>((const float*)a.K, (const float*)a.V, s.N, s.T, s.lay(), s.phi, a.hz, pool,
+                               b.col ? *b.col : ColArgs{});
+  return hipGetLastError();
+}
+
+template <int D>
 hipError_t forward_impl(const Shape& s, const FwdArgs& a, hipStream_t st) {
   const dim3 grid(s.T, s.BH);
   const size_t lds = 2 * FTile<D>::BYTES;
   if (s.n_0 > 0) {
-    SLA_TRY(ensure_dyn_lds(f32_states_kernel<D>, lds));
-    {
-      KernelTimer kt("states", st);
-      f32_states_kernel<D><<<grid, 256, lds, st>>>((const float*)a.K, (const float*)a.V, s.N, s.T, s.lay(), s.phi, a.hz);
-    }
     SLA_TRY(f32_aggregate(a.hz, a.ind, s, a.HZ, st));
   } else {
     SLA_TRY(launch_fill_zero(a.HZ, (size_t)s.BH * s.T * s.state_row(), st));
@@ -1002,6 +1030,10 @@ hipError_t f32_backward(const Shape& s, const BwdArgs& a, float* Ds, float* dHZ,
                         int nparts, hipStream_t st) {
   return s.d == 64 ? backward_impl<64>(s, a, Ds, dHZ, dHZcol, dWpart, nparts, st)
                    : backward_impl<128>(s, a, Ds, dHZ, dHZcol, dWpart, nparts, st);
+}
+
+hipError_t f32_states(const Shape& s, const FwdArgs& a, const Beside& b, hipStream_t st) {
+  return s.d == 64 ? states_impl<64>(s, a, b, st) : states_impl<128>(s, a, b, st);
 }
 
 hipError_t f32_forward(const Shape& s, const FwdArgs& a, hipStream_t st) {

@@ -6,6 +6,7 @@
 //                   the closing line (O^s, L, O^l) and O = O^s + O^l W
 // All contractions run on v_mfma_f32_32x32x16_bf16 with float accumulation.
 #include <type_traits>
+#include "mask_parts.h"
 #include "mfma_common.h"
 
 namespace sla {
@@ -52,17 +53,38 @@ __device__ __forceinline__ void prep_w(const bf16* __restrict__ W, bf16* __restr
 // transposing LDS read; the product is formed with e along the lanes so that the rows of h^T leave
 // whole.  Wave w owns rows e in [32 w, 32 w + 32).
 template <int D>
+constexpr int states_lds() {
+  constexpr int rows = D / 32 * 32 * (2 * D + 16);   // store_rows_bf16 areas of the waves that store
+  return 2 * SwzTile<D>::BYTES > rows ? 2 * SwzTile<D>::BYTES : rows;
+}
+// BESIDE: in a call that also builds the mask, the first workgroups pool Q and K (1) or form the column tables
+// (2).  Neither needs the states or is needed by them; the tables are a chain of short phases that leaves
+// the memory idle, and the pooling of a short sequence a launch of a few workgroups.  (Two launches -> one, us:
+// pooling, 256 heads x 16 blocks, d = 64, 21.8 + 20.6 -> 36.4, 2 x 18, d = 128, 7.8 + 8.3 -> 8.8; column tables,
+// 12 x 146 11.6 + 25.8 -> 28.0, 12 x 512 20.0 + 67.4 -> 69.9.)
+template <int D, int BESIDE>
 __global__ __launch_bounds__(256, 4) void states_mfma_kernel(const bf16* __restrict__ K,
                                                              const bf16* __restrict__ V, int N, int Tn, Lay lay,
                                                              int phi, bf16* __restrict__ hz,
-                                                             const bf16* __restrict__ W, bf16* __restrict__ WTp) {
+                                                             const bf16* __restrict__ W, bf16* __restrict__ WTp,
+                                                             PoolArgs pool, ColArgs col) {
   using T = SwzTile<D>;
   constexpr int NT = D / 32;
   constexpr int STG = 32 * (64 * NT + 16);           // store_rows_bf16<NT> area of one wave
-  constexpr int LDSB = 2 * T::BYTES > NT * STG ? 2 * T::BYTES : NT * STG;
-  __shared__ __attribute__((aligned(16))) unsigned char smem[LDSB];
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, g = l >> 5;
-  const int j = blockIdx.x, bh = blockIdx.y;
+  int j = blockIdx.x, bh = blockIdx.y;
+  if constexpr (BESIDE != 0) {   // (one row of workgroups, those beside the states first)
+    const int Tw = (Tn + 63) / 64, first = BESIDE == 1 ? 2 * pool.wgs : Tw * (pool.BH);
+    if (j < first) {
+      if constexpr (BESIDE == 1) pool_part<bf16, D>(pool, j);
+      else col_tables_part(smem, col, j % Tw, j / Tw);
+      return;
+    }
+    j -= first;
+    bh = j / (Tn + 1);
+    j -= bh * (Tn + 1);
+  }
   if (j == Tn) {   // the extra column of the grid: head 0's workgroup prepares the projection matrix
     if (bh == 0) prep_w<D>(W, WTp, tid);
     return;
@@ -574,14 +596,24 @@ __global__ void fill_zero_f32_kernel(float* __restrict__ p, size_t n) {
 }
 
 template <int D>
+hipError_t states_impl(const Shape& s, const FwdArgs& a, bf16* hz16, bf16* WTp, const Beside& b, hipStream_t st) {
+  const int Tw = (s.T + 63) / 64, lds = b.col ? max(states_lds<D>(), col_tables_lds(Tw)) : states_lds<D>();
+  const int first = b.pool ? 2 * b.pool->wgs : b.col ? Tw * s.BH : 0;
+  PoolArgs pool = {};
+  if (b.pool) pool = *b.pool;
+  pool.BH = s.BH;
+  KernelTimer kt(b.pool ? "states_pool" : b.col ? "states_cols" : "states", st);
+  auto kern = b.pool ? states_mfma_kernel<D, 1> : b.col ? states_mfma_kernel<D, 2> : states_mfma_kernel<D, 0>;
+  const dim3 grid = first ? dim3(first + (s.T + 1) * s.BH) : dim3(s.T + 1, s.BH);
+  kern<<<grid, 256, lds, st>>>((const bf16*)a.K, (const bf16*)a.V, s.N, s.T, s.lay(), s.phi, hz16, (const bf16*)a.W, WTp,
+                               pool, b.col ? *b.col : ColArgs{});
+  return hipGetLastError();
+}
+
+template <int D>
 hipError_t forward_impl(const Shape& s, const FwdArgs& a, bf16* hz16, bf16* WTp, hipStream_t st) {
   float* Zs = reinterpret_cast<float*>(reinterpret_cast<char*>(a.HZ) + state_z_offset(s));
   if (s.n_0 > 0) {
-    {
-      KernelTimer kt("states", st);
-      states_mfma_kernel<D><<<dim3(s.T + 1, s.BH), 256, 0, st>>>((const bf16*)a.K, (const bf16*)a.V, s.N, s.T,
-                                                               s.lay(), s.phi, hz16, (const bf16*)a.W, WTp);
-    }
     SLA_TRY(mfma_aggregate(hz16, a.ind, s, a.HZ, Zs, st));
   } else if (a.Os) {   // saved states must read as zero
     SLA_TRY(launch_fill_zero(a.HZ, (size_t)s.BH * s.T * s.state_row(), st));
@@ -613,6 +645,12 @@ hipError_t launch_fill_zero(float* p, size_t n, hipStream_t st) {
 
 size_t mfma_forward_ws_bytes(const Shape& s) {
   return align_up((size_t)s.BH * s.T * s.state_row() * 2) + align_up((size_t)s.d * s.d * 2);
+}
+
+hipError_t mfma_states(const Shape& s, const FwdArgs& a, char* ws, const Beside& b, hipStream_t st) {
+  bf16* hz16 = reinterpret_cast<bf16*>(ws);
+  bf16* WTp = reinterpret_cast<bf16*>(ws + align_up((size_t)s.BH * s.T * s.state_row() * 2));
+  return s.d == 64 ? states_impl<64>(s, a, hz16, WTp, b, st) : states_impl<128>(s, a, hz16, WTp, b, st);
 }
 
 hipError_t mfma_forward(const Shape& s, const FwdArgs& a, char* ws, hipStream_t st) {

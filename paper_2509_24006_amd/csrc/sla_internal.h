@@ -41,14 +41,35 @@ __device__ __forceinline__ float to_f32(float x) { return x; }
 __device__ __forceinline__ float to_f32(__hip_bfloat16 x) { return __bfloat162float(x); }
 
 // ---- mask step (mask_kernels.hip)
-hipError_t launch_pool(const void* Q, const void* K, const Shape& s, float* qbar, float* kbar, hipStream_t st);
+// block means of X0 = Q (blocks of 64 rq tokens) and X1 = K (64) -> out0 (float [BH][Tq][d]), out1 (float [BH][T][d])
+struct PoolArgs {
+  const void *X0, *X1;
+  int BH, N, Tn0, len0, Tn1, len1;
+  int wgs;   // workgroups per tensor
+  Lay lay;
+  float *out0, *out1;
+};
+PoolArgs pool_args(const void* Q, const void* K, const Shape& s, float* qbar, float* kbar);
+hipError_t launch_pool(const PoolArgs& a, const Shape& s, hipStream_t st);
 hipError_t launch_scores(const float* qbar, const float* kbar, const Shape& s, float* scores,
                          hipStream_t st);
 // col_cnt: [BH][T] ints of scratch: cleared by the classification, filled by the table build
 hipError_t launch_classify(const float* scores, const Shape& s, int8_t* Mc, int32_t* row_idx,
                            int32_t* col_cnt, hipStream_t st);
-hipError_t launch_csc(const int8_t* Mc, const Shape& s, int32_t* col_cnt, int32_t* col_ptr, int32_t* col_rows,
-                      unsigned long long* ind, unsigned long long* indT, int32_t* col_order, hipStream_t st);
+hipError_t launch_indicator(const int8_t* Mc, const Shape& s, int32_t* col_cnt, unsigned long long* ind,
+                            unsigned long long* indT, hipStream_t st);
+struct ColArgs {
+  const int8_t* Mc;
+  int Tq, rq, T, n_h;
+  const int32_t* cnt;            // critical blocks per column
+  int32_t *ptr, *order, *rows;
+};
+hipError_t launch_col_tables(const ColArgs& a, const Shape& s, hipStream_t st);
+// What the state kernel's launch does besides the states: nothing, the pooling, or the column tables.
+struct Beside {
+  const PoolArgs* pool = nullptr;
+  const ColArgs* col = nullptr;
+};
 
 // T <= 64: scores (computed from qbar, kbar and written to `scores`, or read from `given`),
 // classification and all tables in one launch
@@ -70,7 +91,8 @@ struct FwdArgs {
   float* HZ;       // [BH,T] state rows (saved or workspace)
   float* hz;       // [BH,T] state rows of the key blocks (workspace)
 };
-hipError_t f32_forward(const Shape& s, const FwdArgs& a, hipStream_t st);
+hipError_t f32_states(const Shape& s, const FwdArgs& a, const Beside& b, hipStream_t st);   // (only with marginal blocks)
+hipError_t f32_forward(const Shape& s, const FwdArgs& a, hipStream_t st);                  // what follows the states
 
 struct BwdArgs {
   const void *Q, *K, *V, *W, *dO;
@@ -104,6 +126,7 @@ hipError_t backward(const Shape& s, const BwdArgs& a, hipStream_t st);
 
 // ---- bf16 matrix-core path (mfma_fwd.hip)
 size_t mfma_forward_ws_bytes(const Shape& s);
+hipError_t mfma_states(const Shape& s, const FwdArgs& a, char* ws, const Beside& b, hipStream_t st);
 hipError_t mfma_forward(const Shape& s, const FwdArgs& a, char* ws, hipStream_t st);
 // out[i] = sum over k with bit k of ind[i] set of the bf16 state rows in[k] (mfma_aggregate.hip)
 hipError_t mfma_aggregate(const void* in, const unsigned long long* ind, const Shape& s, void* outH, float* outZ,

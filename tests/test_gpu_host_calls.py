@@ -9,7 +9,7 @@ pytestmark = pytest.mark.gpu
 
 
 class _HandsEverythingBack:
-    build_mask = forward = backward = staticmethod(lambda *a: None)
+    build_mask = forward = mask_forward = backward = staticmethod(lambda *a: None)
 
 
 def _tensors(layout, dtype, B=2, H=3, N=333, d=64):
@@ -110,3 +110,30 @@ def test_subclasses_take_the_python_path():
     ref = sla.sla_build_mask(p, x[0], x[1])[0]
     got = sla.sla_build_mask(p, x[0].as_subclass(Plain), x[1])[0]
     assert torch.equal(ref, got)
+
+
+@pytest.mark.parametrize("saved", [True, False])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("T,H,d,bq,k_h,k_l", [(1, 3, 64, 64, 1.0, 0.0), (5, 2, 128, 64, 0.2, 0.2), (64, 1, 64, 128, 0.1, 0.1),
+                                               (65, 2, 128, 64, 0.1, 0.1), (130, 1, 64, 256, 0.05, 0.2),
+                                               (70, 3, 64, 64, 0.3, 0.7), (70, 1, 128, 64, 0.0, 0.1)])
+def test_mask_and_forward_in_one_call(monkeypatch, T, H, d, bq, k_h, k_l, dtype, saved):
+    # pooling or column tables beside the states; no marginal block (no states at all); no critical block
+    g = torch.Generator(device="cuda")
+    g.manual_seed(T)
+    N = T * 64 - (7 if T > 1 else 0)
+    Q, K, V, dO = (torch.randn(2, H, N, d, generator=g, device="cuda").to(dtype) for _ in range(4))
+    W = (0.02 * torch.randn(d, d, generator=g, device="cuda")).to(dtype)
+    p = sla.make_params(2, H, N, d, k_h, k_l, dtype, bq=bq)
+    got = sla.sla_mask_forward(p, Q, K, V, W, need_saved=saved)
+    with monkeypatch.context() as m:
+        m.setattr(sla, "_host_calls", lambda: _HandsEverythingBack)
+        ref = sla.sla_mask_forward(p, Q, K, V, W, need_saved=saved)
+    names = lambda luts: sla.lut_views(p, luts)
+    assert torch.equal(got[0], ref[0]) and torch.equal(got[2], ref[2])
+    for (k, a), b in zip(names(got[1]).items(), names(ref[1]).values()):
+        assert torch.equal(a, b), k
+    assert (got[3] is None) == (not saved)
+    if saved:
+        a, b = (sla.sla_backward(p, Q, K, V, W, x[0], x[1], x[3], dO) for x in (got, ref))
+        assert all(torch.equal(x, y) for x, y in zip(a, b))
