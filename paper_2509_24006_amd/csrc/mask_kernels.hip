@@ -16,23 +16,24 @@ __global__ __launch_bounds__(256) void pool_kernel(PoolArgs a) {
 }
 
 // ---------------------------------------------------------------- scores
-// 64x64 output tile per workgroup, 4x4 outputs per thread, features staged through LDS in
+// 16 R x 16 R output tile per workgroup, R x R outputs per thread, features staged through LDS in
 // chunks of 64 and read four at a time; each output keeps one fused multiply-add chain in
 // ascending feature order.
 // acc[a][b] = sum over features (ascending, one fused multiply-add chain) of
 // qb[i0 + ty + 16 a][.] kb[j0 + tx + 16 b][.]; rows past Tq / T count as zeros.
+template <int R>
 __device__ __forceinline__ void score_tile(const float* __restrict__ qb, const float* __restrict__ kb, int Tq, int T,
                                            int d, int i0, int j0, float (*qs)[68], float (*ks)[68],
-                                           float (&acc)[4][4]) {
+                                           float (&acc)[R][R]) {
   const int tid = threadIdx.x, ty = tid >> 4, tx = tid & 15;
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
+  for (int a = 0; a < R; ++a)
 #pragma unroll
-    for (int b = 0; b < 4; ++b) acc[a][b] = 0.0f;
+    for (int b = 0; b < R; ++b) acc[a][b] = 0.0f;
   for (int k0 = 0; k0 < d; k0 += 64) {
     // thread t brings 16 bytes: piece t % 16 of rows t / 16 + 16 q (d is a multiple of 64)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
+    for (int q = 0; q < R; ++q) {
       const int r = (tid >> 4) + 16 * q, c = 4 * (tid & 15);
       const float4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
       *reinterpret_cast<float4*>(&qs[r][c]) =
@@ -43,15 +44,15 @@ __device__ __forceinline__ void score_tile(const float* __restrict__ qb, const f
     __syncthreads();
 #pragma unroll 4
     for (int k = 0; k < 64; k += 4) {
-      float4 av[4], bv[4];
+      float4 av[R], bv[R];
 #pragma unroll
-      for (int a = 0; a < 4; ++a) av[a] = *reinterpret_cast<const float4*>(&qs[ty + 16 * a][k]);
+      for (int a = 0; a < R; ++a) av[a] = *reinterpret_cast<const float4*>(&qs[ty + 16 * a][k]);
 #pragma unroll
-      for (int b = 0; b < 4; ++b) bv[b] = *reinterpret_cast<const float4*>(&ks[tx + 16 * b][k]);
+      for (int b = 0; b < R; ++b) bv[b] = *reinterpret_cast<const float4*>(&ks[tx + 16 * b][k]);
 #pragma unroll
-      for (int a = 0; a < 4; ++a)
+      for (int a = 0; a < R; ++a)
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
+        for (int b = 0; b < R; ++b) {
           float x = acc[a][b];
           x = __fmaf_rn(av[a].x, bv[b].x, x);
           x = __fmaf_rn(av[a].y, bv[b].y, x);
@@ -64,21 +65,22 @@ __device__ __forceinline__ void score_tile(const float* __restrict__ qb, const f
   }
 }
 
+template <int R>
 __global__ __launch_bounds__(256) void score_kernel(const float* __restrict__ qbar,
                                                     const float* __restrict__ kbar, int Tq, int T, int d,
                                                     float scale, float* __restrict__ s) {
-  __shared__ __attribute__((aligned(16))) float qs[64][68];
-  __shared__ __attribute__((aligned(16))) float ks[64][68];
+  __shared__ __attribute__((aligned(16))) float qs[16 * R][68];
+  __shared__ __attribute__((aligned(16))) float ks[16 * R][68];
   const int tid = threadIdx.x, ty = tid >> 4, tx = tid & 15;
-  const int bh = blockIdx.z, i0 = blockIdx.y * 64, j0 = blockIdx.x * 64;
-  float acc[4][4];
-  score_tile(qbar + (size_t)bh * Tq * d, kbar + (size_t)bh * T * d, Tq, T, d, i0, j0, qs, ks, acc);
+  const int bh = blockIdx.z, i0 = blockIdx.y * 16 * R, j0 = blockIdx.x * 16 * R;
+  float acc[R][R];
+  score_tile<R>(qbar + (size_t)bh * Tq * d, kbar + (size_t)bh * T * d, Tq, T, d, i0, j0, qs, ks, acc);
 #pragma unroll
-  for (int a = 0; a < 4; ++a) {
+  for (int a = 0; a < R; ++a) {
     const int i = i0 + ty + 16 * a;
     if (i >= Tq) continue;
 #pragma unroll
-    for (int b = 0; b < 4; ++b) {
+    for (int b = 0; b < R; ++b) {
       const int j = j0 + tx + 16 * b;
       if (j < T) s[((size_t)bh * Tq + i) * T + j] = __fmul_rn(acc[a][b], scale);
     }
@@ -434,11 +436,15 @@ hipError_t launch_pool(const PoolArgs& a, const Shape& s, hipStream_t st) {
 
 hipError_t launch_scores(const float* qbar, const float* kbar, const Shape& s, float* scores,
                          hipStream_t st) {
-  const int nt = (s.T + 63) / 64;
-  {
-    KernelTimer kt("score", st);
-    score_kernel<<<dim3(nt, (s.Tq + 63) / 64, s.BH), 256, 0, st>>>(qbar, kbar, s.Tq, s.T, s.d, s.scale, scores);
-  }
+  // Tiles of 64 x 64 scores read half as much from LDS per product as those of 32 x 32, but up to two of them
+  // per CU leave most of the chip idle.  (Tiles of 64 -> 32, us: 12 heads x 73 x 146 scores, 72 tiles of 64,
+  // 13.6 -> 8.4; 4 x 122 x 122, 16 tiles, 13.3 -> 8.3; 24 x 250 x 250, d = 64, 384 tiles, 11.1 -> 10.6;
+  // 12 x 512 x 512, 768 tiles, 20.2 -> 22.9; 40 x 1182 x 1182 235 -> 297.)
+  const bool wide = (s.T + 63) / 64 * ((s.Tq + 63) / 64) * s.BH > 512;
+  const int t = wide ? 64 : 32;
+  auto kern = wide ? score_kernel<4> : score_kernel<2>;
+  KernelTimer kt("score", st);
+  kern<<<dim3((s.T + t - 1) / t, (s.Tq + t - 1) / t, s.BH), 256, 0, st>>>(qbar, kbar, s.Tq, s.T, s.d, s.scale, scores);
   return hipGetLastError();
 }
 

@@ -454,6 +454,22 @@ def test_state_sums_at_the_edges_of_the_row_tiles(T, d):
     assert bool(((Zm.double() - ref[..., d * d:]).abs() <= mag[..., d * d:]).all())
 
 
+@pytest.mark.parametrize("T,H,bq", [(65, 140, 64), (97, 129, 64), (130, 100, 128)])
+def test_scores_are_the_same_with_tiles_of_either_size(T, H, bq):
+    # many heads in one call take tiles of 64 x 64 scores, a few of them tiles of 32 x 32: the same bits
+    from paper_2509_24006_amd import binding as sla
+    g = torch.Generator(device="cuda")
+    g.manual_seed(T)
+    Q, K = (torch.randn(1, H, T * 64 - 9, 64, generator=g, device="cuda").bfloat16() for _ in range(2))
+    mk = lambda h: sla.make_params(1, h, T * 64 - 9, 64, 0.1, 0.1, torch.bfloat16, bq=bq)
+    Mc, _, ws = sla.sla_build_mask(mk(H), Q, K)
+    scores = sla.mask_ws_views(mk(H), ws)["scores"]
+    for h in (0, H // 2, H - 1):
+        m1, _, w1 = sla.sla_build_mask(mk(1), Q[:, h:h + 1].contiguous(), K[:, h:h + 1].contiguous())
+        assert torch.equal(sla.mask_ws_views(mk(1), w1)["scores"][0, 0], scores[0, h])
+        assert torch.equal(m1[0, 0], Mc[0, h])
+
+
 def test_forward_without_saved_matches(oracle):
     from paper_2509_24006_amd import binding as sla
     from tests.gpu_util import to_dev, f64
