@@ -37,15 +37,9 @@ __device__ __forceinline__ unsigned bits2bf(unsigned x, int s) {
   return (((y << 15) | y) & 0x00010001u) * 0x3f80u;
 }
 
-// The main kernel's form, half the instructions: bits K and K + 16 of x -> the same dword.  It keeps
-// the rows of a stage in the order that makes neighbours of rows 16 apart (stage_row), so that the
-// two bits of a dword already lie 16 apart in the indicator word.  (40 heads x 1182 blocks, d = 128:
-// 1751 -> 1633 us a launch; 12 x 512: 107 us either way, there the traffic is the bound.)
-template <int K>
-__device__ __forceinline__ unsigned bits16bf(unsigned x) {
-  static_assert(K <= 7, "the factor keeps every bit of 0x3f80");
-  return (x & (0x00010001u << K)) * (0x3f80u >> K);
-}
+// (The main kernel keeps the rows of a stage in the order that makes neighbours of rows 16 apart, stage_row, for
+// bits16bf's half the instructions: 40 heads x 1182 blocks, d = 128, 1751 -> 1633 us a launch; 12 x 512 107 us either
+// way, there the traffic is the bound.)
 // which of a k-step's 64 state rows is row r of the stage
 __device__ __forceinline__ int stage_row(int r) { return (r & 32) | ((r >> 1) & 15) | ((r & 1) << 4); }
 

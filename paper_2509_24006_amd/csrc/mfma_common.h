@@ -55,6 +55,13 @@ __device__ __forceinline__ f32x16 zero_f32x16() {
   return z;
 }
 
+// indicator bits K and K + 16 of x -> a dword holding two bf16 (1.0 or 0.0), two instructions
+template <int K>
+__device__ __forceinline__ unsigned bits16bf(unsigned x) {
+  static_assert(K <= 7, "the factor keeps every bit of 0x3f80");
+  return (x & (0x00010001u << K)) * (0x3f80u >> K);
+}
+
 // eight consecutive floats -> bf16x8 (round to nearest even)
 __device__ __forceinline__ bf16x8 cvt8(const float* p) {
   const f32x4 a = *reinterpret_cast<const f32x4*>(p);

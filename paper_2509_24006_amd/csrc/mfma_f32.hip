@@ -304,13 +304,18 @@ __global__ __launch_bounds__(256, 2) void f32_states_kernel(const float* __restr
 }
 
 // ------------------------------------------------------------------ aggregation
-// out[i] = sum of the state rows in[k] over the k whose bit is set in ind[i] (ascending k): the
-// indicator (1 or 0) times the states on v_mfma_f32_32x32x2_f32, whose products with 1 and 0 are
-// exact.  A wave owns 32 columns and 32 MT rows i and reads every state once, straight into the B
-// operand (lane = column, 128 contiguous bytes per half wave), so no LDS and no barriers.  A state
-// that is not finite would reach every row through its product with 0: such values are taken out
-// of the product and added only to the rows that hold the bit.  (122 blocks x 4 heads, d = 128:
-// 39 us, matrix cores busy half of it; one thread per column and row took 1070 us.)
+// out[i] = sum of the state rows in[k] over the k whose bit is set in ind[i]: the indicator (1 or 0)
+// times the states on the matrix cores.  A float is the sum of three bf16 values exactly (24 bits in pieces of
+// eight) and their products with 1 and 0 are exact, so three v_mfma_f32_32x32x16_bf16 do in 96 cycles, with the
+// same float accumulation, what eight v_mfma_f32_32x32x2_f32 do in 512: that was the bound (122 blocks x 4
+// heads, d = 128: 37.6 -> 17.9 us a launch, 12 x 100 77 -> 33, 64 x 8, d = 64, 12.5 -> 9.3).  The sums are closer to
+// those in 64 bits than before (relative error 2.4e-7 -> 1.9e-7, 1.9e-7 -> 1.7e-7, 1.65e-7 -> 1.62e-7): the
+// accumulators are rounded less often.  A wave owns 32 columns and 32 MT rows i and reads every state
+// once, straight into the B operand (lane = column, 128 contiguous bytes per half wave), so no LDS and
+// no barriers.  The k-index runs over rows such that the two of a dword lie 16 apart, as their indicator
+// bits then do in the dword's place (bits16bf).  A state that is not finite would reach every row
+// through its product with 0: such values are taken out of the product and added only to the rows that
+// hold the bit.
 constexpr float kMaxFinite = 3.402823466e38f;
 
 template <int MT>
@@ -326,15 +331,16 @@ __global__ __launch_bounds__(256) void f32_aggregate_kernel(const float* __restr
       const_cast<float*>(in + (size_t)bh * T * row_len), 0, T * row_len * 4, 0x00020000);
   const __amdgpu_buffer_rsrc_t orsrc =
       __builtin_amdgcn_make_buffer_rsrc(out + (size_t)bh * T * row_len, 0, T * row_len * 4, 0x00020000);
-  const int pitch = row_len * 4, voff = g * pitch + (c0 + n) * 4;
-  constexpr int CH = 16;       // k-pairs per chunk of loads
+  const int pitch = row_len * 4, voff = 4 * g * pitch + (c0 + n) * 4;
+  constexpr int CH = 16;       // values of a chunk of 32 states: slots (u, p, h) = state 8 u + 4 g + p + 16 h
   f32x16 acc[MT];
 #pragma unroll
   for (int m = 0; m < MT; ++m) acc[m] = zero_f32x16();
   auto fetch = [&](int k0, float (&x)[CH]) {
 #pragma unroll
     for (int q = 0; q < CH; ++q)   // (rows past T read as zeros)
-      x[q] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, voff + (k0 + 2 * q) * pitch, 0, 0));
+      x[q] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+          rsrc, voff + (k0 + 8 * (q >> 3) + ((q >> 1) & 3) + 16 * (q & 1)) * pitch, 0, 0));
   };
   float x[CH], nx[CH];
   bool bad = false;
@@ -347,26 +353,46 @@ __global__ __launch_bounds__(256) void f32_aggregate_kernel(const float* __restr
     if ((k0 & 63) == 0) {
 #pragma unroll
       for (int m = 0; m < MT; ++m) {
-        wb[m] = nwb[m] >> g;
+        wb[m] = nwb[m];
         nwb[m] = ib[(size_t)min(m0 + 32 * m + n, T - 1) * Tw + min((k0 >> 6) + 1, Tw - 1)];
       }
     }
     if (k0 + 2 * CH < T) fetch(k0 + 2 * CH, nx);
+    unsigned part[3][CH / 2];   // [piece][dword]: the pieces of two states, most significant first
 #pragma unroll
-    for (int q = 0; q < CH; ++q) {
-      const bool fin = fabsf(x[q]) <= kMaxFinite;
-      bad |= !fin;
-      x[q] = fin ? x[q] : 0.0f;
+    for (int q = 0; q < CH; q += 2) {
+      unsigned y[2][3];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const bool fin = fabsf(x[q + h]) <= kMaxFinite;
+        bad |= !fin;
+        float v = fin ? x[q + h] : 0.0f;
+#pragma unroll
+        for (int e = 0; e < 3; ++e) {   // the top 16 bits are a bf16, and what is left of v is exact
+          y[h][e] = __float_as_uint(v) & 0xffff0000u;
+          v -= __uint_as_float(y[h][e]);
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < 3; ++e) part[e][q / 2] = y[1][e] | y[0][e] >> 16;
     }
-    const int sh = k0 & 32;
 #pragma unroll
-    for (int q = 0; q < CH; ++q)
+    for (int u = 0; u < 2; ++u) {
+      bf16x8 b[3];
+#pragma unroll
+      for (int e = 0; e < 3; ++e) {
+        const u32x4 t = {part[e][4 * u], part[e][4 * u + 1], part[e][4 * u + 2], part[e][4 * u + 3]};
+        b[e] = __builtin_bit_cast(bf16x8, t);
+      }
 #pragma unroll
       for (int m = 0; m < MT; ++m) {
-        const unsigned bits = (unsigned)(wb[m] >> sh);
-        const float a = ((bits >> (2 * q)) & 1u) ? 1.0f : 0.0f;
-        acc[m] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, x[q], acc[m], 0, 0, 0);
+        const unsigned bits = (unsigned)(wb[m] >> (k0 & 32)) >> (8 * u + 4 * g);
+        const u32x4 t = {bits16bf<0>(bits), bits16bf<1>(bits), bits16bf<2>(bits), bits16bf<3>(bits)};
+        const bf16x8 a = __builtin_bit_cast(bf16x8, t);
+#pragma unroll
+        for (int e = 2; e >= 0; --e) acc[m] = mfma32(a, b[e], acc[m]);
       }
+    }
 #pragma unroll
     for (int q = 0; q < CH; ++q) x[q] = nx[q];
   }
@@ -391,8 +417,7 @@ __global__ __launch_bounds__(256) void f32_aggregate_kernel(const float* __restr
 // padding: a thread owns four columns, holds them of every state and writes the sums of every row, so
 // that the states are read once and nothing but the traffic is left.  (One block, d = 64: 256 heads
 // 31.9 -> 6.6 us a launch, 4096 heads 396 -> 24.6; four blocks, 256 heads, d = 128: 103 -> 23.)
-constexpr int kFew = 4;
-
+template <int kFew>
 __global__ __launch_bounds__(256) void f32_aggregate_few_kernel(const float* __restrict__ in,
                                                                 const unsigned long long* __restrict__ ind, int T,
                                                                 int row_len, float* __restrict__ out) {
@@ -939,11 +964,12 @@ hipError_t f32_aggregate(const float* in, const unsigned long long* ind, const S
   const int row_len = s.state_row(), Tw = (s.T + 63) / 64;
   const int gx = (row_len / 32 + 3) / 4;
   KernelTimer kt("aggregate", st);
-  // From five blocks on the matrix form takes the same or less with few heads (eight blocks, d = 64,
-  // 16 heads: 7.2 us against 8.2 with the short one) and no more than one thread per column and row
-  // did with many (five blocks, 256 heads, d = 128, two marginal: 104 against 110 us).
-  if (s.T <= kFew) {
-    f32_aggregate_few_kernel<<<dim3((row_len / 4 + 255) / 256, s.BH), 256, 0, st>>>(in, ind, s.T, row_len, out);
+  // From five blocks on the matrix form takes less with few heads (eight blocks, d = 64, 16 heads: 6.4 us against
+  // 8.0 with the short form); with many, up to eight blocks, the short form runs at the memory's rate (five
+  // blocks, 256 heads, d = 128: 63 against 28 us; eight, 512 heads, d = 64: 39 against 23).
+  if (s.T <= 4 || (s.T <= 8 && s.BH >= 128)) {
+    auto few = s.T <= 4 ? f32_aggregate_few_kernel<4> : f32_aggregate_few_kernel<8>;
+    few<<<dim3((row_len / 4 + 255) / 256, s.BH), 256, 0, st>>>(in, ind, s.T, row_len, out);
     return hipGetLastError();
   }
   // up to 128 rows per wave (the states are read ceil(T / 128) times), in tiles of 32 dealt evenly

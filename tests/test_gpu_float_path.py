@@ -67,3 +67,31 @@ def test_sums_of_the_states_of_a_few_blocks(oracle, T, d, k_h):
     fin = np.isfinite(f["Hi"])
     assert not fin.all() and np.array_equal(np.isfinite(r["Hi"]), fin)
     assert np.abs(r["Hi"][fin] - f["Hi"][fin]).max() <= 1e-5 * np.abs(f["Hi"][fin]).max()
+
+
+@pytest.mark.parametrize("T,d", [(5, 64), (7, 128), (8, 64), (8, 128), (9, 64)])
+def test_state_sums_of_many_short_heads(T, d):
+    # up to eight blocks many heads take another form of the sums than a few: bound for sums of T floats each
+    import torch
+    from paper_2509_24006_amd import binding as sla
+    g = torch.Generator(device="cuda")
+    g.manual_seed(T)
+    H, N = 130, T * 64 - 9
+    Q, K, V = (torch.randn(1, H, N, d, generator=g, device="cuda") for _ in range(3))
+    V[0, 3, 70, 5] = float("inf")
+    W = torch.zeros(d, d, device="cuda")
+
+    def states(q, k, v):
+        p = sla.make_params(1, q.shape[1], N, d, 0.2, 0.2, torch.float32)
+        Mc, luts, _ = sla.sla_build_mask(p, q, k)
+        _, saved = sla.sla_forward(p, q, k, v, W, Mc, luts)
+        return sla.saved_views(p, saved)
+
+    many = states(Q, K, V)
+    cut = lambda t: t[:, 2:5].contiguous()
+    few, mag = states(cut(Q), cut(K), cut(V)), states(cut(Q), cut(K), cut(V).abs())
+    for n in ("Hi", "Zi"):
+        a, b, m = many[n][:, 2:5].double(), few[n].double(), mag[n].double()
+        fin = torch.isfinite(b)
+        assert torch.equal(torch.isfinite(a), fin) and (n == "Zi" or not bool(fin.all()))
+        assert bool(((a - b).abs()[fin] <= 2 * T * 2.0 ** -24 * m[fin]).all())
