@@ -5,6 +5,7 @@ namespace sla {
 namespace {
 
 struct BwdWs {
+  KvSplit kv;
   float *Ds, *dHZ, *dHZcol, *dQlin, *dWpart;
   int nparts;
   size_t bytes;
@@ -26,6 +27,9 @@ BwdWs carve_bwd(const Shape& s, char* ws) {
   w.dHZcol = take(st);
   w.dQlin = take(s.dtype == 0 ? 0 : nd);   // (bf16 with query blocks of several tiles)
   w.dWpart = take((size_t)w.nparts * s.d * s.d);
+  w.kv = kv_split(s);
+  w.kv.units = reinterpret_cast<int4*>(take((size_t)s.BH * (2 * w.kv.ecap + s.T) * 4));
+  w.kv.part = take((size_t)s.BH * 2 * w.kv.ecap * 2 * kBlk * s.d);
   w.bytes = off;
   return w;
 }
@@ -33,22 +37,41 @@ BwdWs carve_bwd(const Shape& s, char* ws) {
 hipError_t backward_bf16(const Shape& s, const BwdArgs& a, hipStream_t st) {
   const BwdWs w = carve_bwd(s, a.ws);
   const bool lin = s.n_0 > 0;
-  SLA_TRY(mfma_backward_query(s, a, w.Ds, w.dHZ, w.dQlin, w.dWpart, w.nparts, st));   // dHZ holds bf16 rows
+  SLA_TRY(mfma_backward_query(s, a, w.Ds, w.dHZ, w.dQlin, w.dWpart, w.nparts, w.kv, st));   // dHZ holds bf16 rows
   if (lin) {
     SLA_TRY(mfma_aggregate(w.dHZ, a.indT, s, w.dHZcol,
                            reinterpret_cast<float*>(reinterpret_cast<char*>(w.dHZcol) + state_z_offset(s)), st));
   }
-  return mfma_backward_sparse(s, a, w.Ds, lin ? w.dHZcol : nullptr, DwSum{w.dWpart, w.nparts, s.d * s.d, a.dW, a.dW16}, st);
+  return mfma_backward_sparse(s, a, w.Ds, lin ? w.dHZcol : nullptr, DwSum{w.dWpart, w.nparts, s.d * s.d, a.dW, a.dW16}, w.kv, st);
 }
 
 }  // namespace
+
+// Whether and into what the column lists are cut.  They are very uneven (on video-like inputs the longest holds
+// four to thirty times the average), and where a workgroup slot of the chip has few entries the launch lasts as
+// long as the longest list.  A cut list costs float sums out and back and a launch that adds them.  So a
+// piece lasts about as long as a slot's share of everything (a key block's fixed cost is that of four entries;
+// with floats, where an entry takes several times as long, it does not count), and nothing is cut where a third of the longest list there can be, T, is shorter than a piece: at 12 heads x 512
+// blocks of 26 entries (piece 360) the launch is balanced as it is.  (Key side with the adding launch, whole ->
+// cut, us: 12 x 146 of 7, d = 128, 139 -> 113; 14 x 68 of 2 80 -> 51; 8 x 254 of 10, d = 64, 107 -> 78; 8 x 42 of 7
+// 42 -> 30; where the lists happen to be short, 16 x 58 of 2, d = 128, at most 21: 41 -> 48.  Floats: 4 x 122 of 6,
+// d = 128, 175 -> 157; 2 x 122 of 12 201 -> 152; 8 x 122 of 6, d = 64, 228 -> 139; 16 x 63 of 5 157 -> 125.)
+KvSplit kv_split(const Shape& s) {
+  const bool f32 = s.dtype == 0;
+  const long long slots = s.d == 64 && !f32 ? 768 : 512;
+  const long long cols = (long long)s.BH * s.T * (!f32 ? 1 : f32_key_quarters(s) ? 4 : 2);
+  long long piece = (cols * s.n_h + slots - 1) / slots + (f32 ? 0 : 4 * cols / slots);
+  piece = piece < 12 ? 12 : piece;
+  if (s.n_h == 0 || 3 * piece > s.T) return KvSplit{0x7fffffff, 0, nullptr, nullptr};
+  return KvSplit{(int)piece, (int)((long long)s.T * s.n_h / piece), nullptr, nullptr};
+}
 
 size_t backward_ws_bytes(const Shape& s) { return carve_bwd(s, nullptr).bytes; }
 
 hipError_t backward(const Shape& s, const BwdArgs& a, hipStream_t st) {
   if (s.dtype != 0) return backward_bf16(s, a, st);
   const BwdWs w = carve_bwd(s, a.ws);
-  return f32_backward(s, a, w.Ds, w.dHZ, w.dHZcol, w.dWpart, w.nparts, st);
+  return f32_backward(s, a, w.Ds, w.dHZ, w.dHZcol, w.dWpart, w.nparts, w.kv, st);
 }
 
 }  // namespace sla

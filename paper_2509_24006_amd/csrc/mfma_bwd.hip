@@ -38,13 +38,30 @@ struct KvLds {
   static constexpr int STG = 32 * (64 * (D / 64) + 16);  // output staging of one wave, laid over the tiles
 };
 
+// this lane's place in a slot of kv.part: per wave 8 HT pieces of 16 bytes a lane, dV^T then dK^T
+template <int D>
+__device__ __forceinline__ f32x4* kv_slot(const KvSplit& kv, int bh, int slot, int w, int l) {
+  return reinterpret_cast<f32x4*>(kv.part + ((size_t)bh * 2 * kv.ecap + slot) * (2 * kBlk * D)) + w * (D / 8 * 64) + l;
+}
+// this wave's quarter of dK_j, dV_j (accumulators as the loop leaves them) leaves as whole rows
+template <int D>
+__device__ __forceinline__ void store_kv(unsigned char* stage, const f32x16 (&dvT)[D / 64], f32x16 (&dkT)[D / 64], float scale,
+                                         bf16* dV, bf16* dK, size_t o0, int ts, int rows, int l) {
+  store_rows_bf16<D / 64>(stage, dvT, dV + o0, ts, rows, l);
+#pragma unroll
+  for (int dt = 0; dt < D / 64; ++dt)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) dkT[dt][r] *= scale;
+  store_rows_bf16<D / 64>(stage, dkT, dK + o0, ts, rows, l);
+}
+
 template <int D, int PHI>
 __global__ __launch_bounds__(256, 2) void bwd_dkdv_mfma_kernel(
     const bf16* __restrict__ Q, const bf16* __restrict__ K, const bf16* __restrict__ V,
     const bf16* __restrict__ dO, const float* __restrict__ L, const float* __restrict__ Ds,
     const int32_t* __restrict__ col_ptr, const int32_t* __restrict__ col_rows,
-    const int32_t* __restrict__ col_order, const bf16* __restrict__ dHcol,
-    const float* __restrict__ dZcol, int BH, int N, int Tn, Lay lay, int n_h, float scale,
+    const int32_t* __restrict__ col_order, const bf16* __restrict__ dHcol_all,
+    const float* __restrict__ dZcol, KvSplit kv, int BH, int N, int Tn, Lay lay, int n_h, float scale,
     bf16* __restrict__ dK, bf16* __restrict__ dV, DwSum dw) {
   using Lds = KvLds<D>;
   using T = SwzTile<D>;
@@ -52,8 +69,10 @@ __global__ __launch_bounds__(256, 2) void bwd_dkdv_mfma_kernel(
   constexpr int RB = 16 * T::ROW_BYTES;
   constexpr int phi = PHI;   // feature map: 0 softmax over the features, 1 elu + 1
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  if ((int)blockIdx.x >= Tn * BH) {   // the last workgroups: dW
-    dw_sum(dw, blockIdx.x - Tn * BH, smem);
+  const int extras = (BH * kv.ecap + 7) & ~7;   // workgroups for them, first in the launch
+  int index = (int)blockIdx.x - extras;
+  if (index >= Tn * BH) {   // the last workgroups: dW
+    dw_sum(dw, index - Tn * BH, smem);
     return;
   }
   const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, g = l >> 5, ln = l & 31;
@@ -67,27 +86,46 @@ __global__ __launch_bounds__(256, 2) void bwd_dkdv_mfma_kernel(
   // Within that order the heads are dealt to the XCDs (workgroups go to them round robin) in
   // halves -- the even or the odd ranks of a head -- so that an XCD's L2 serves the Q and dO tiles
   // of few heads at a time; most tile loads of this kernel miss the L2.
-  int bh, rank;
-  if (BH % 8 == 0 && BH >= 32 && Tn >= 128) {
+  int bh, place;   // head, place among its units
+  if (index < 0) {
+    // pieces of long lists: all of the same length, and the longest units there are
+    bh = blockIdx.x % BH;
+    place = blockIdx.x / BH;
+    if (place >= kv.ecap) return;
+  } else if (BH % 8 == 0 && BH >= 32 && Tn >= 128) {
     // Many long heads: every XCD takes its BH / 8 heads one after the other, each heaviest list first.
     // Its workgroups then share one head's Q and dO tiles and, being neighbours in rank, walk
     // their lists at about the same pace; a head is a small part of the launch, so the late start
     // of the last head's heavy lists costs little.
     const int hp = BH / 8;
-    const int x = blockIdx.x & 7, m = blockIdx.x >> 3;
+    const int x = index & 7, m = index >> 3;
     bh = hp * x + m / Tn;
-    rank = m % Tn;
+    place = kv.ecap + m % Tn;
   } else if ((2 * BH) % 8 == 0 && Tn % 2 == 0) {
     const int upx = 2 * BH / 8;   // half-heads per XCD
-    const int x = blockIdx.x & 7, m = blockIdx.x >> 3;
+    const int x = index & 7, m = index >> 3;
     const int u = upx * x + m % upx;
     bh = u >> 1;
-    rank = 2 * (m / upx) + (u & 1);
+    place = kv.ecap + 2 * (m / upx) + (u & 1);
   } else {
-    bh = blockIdx.x % BH;
-    rank = blockIdx.x / BH;
+    bh = index % BH;
+    place = kv.ecap + index / BH;
   }
-  const int j = col_order[(size_t)bh * Tn + rank];
+  int j, beg, cnt, slot = -1;
+  if (kv.ecap > 0) {
+    const int4 unit = kv.units[(size_t)bh * (2 * kv.ecap + Tn) + place];
+    j = unit.x;
+    beg = unit.y;
+    cnt = unit.z;
+    slot = unit.w;
+  } else {
+    const int32_t* ptr = col_ptr + (size_t)bh * (Tn + 1);
+    j = col_order[(size_t)bh * Tn + place];
+    beg = ptr[j];
+    cnt = ptr[j + 1] - beg;
+  }
+  if (index < 0 && cnt == 0) return;
+  const bf16* dHcol = index < 0 ? nullptr : dHcol_all;   // (the linear branch goes with the rest of a list)
   const int k0 = j * kBlk, cols = min(kBlk, N - k0);
   const int krow = kh * 32 + ln;
   const bool kok = krow < cols;
@@ -98,9 +136,7 @@ __global__ __launch_bounds__(256, 2) void bwd_dkdv_mfma_kernel(
     dvT[t] = zero_f32x16();
     dkT[t] = zero_f32x16();
   }
-  const int32_t* ptr = col_ptr + (size_t)bh * (Tn + 1);
   const int32_t* list = col_rows + (size_t)bh * Tn * n_h;
-  const int beg = ptr[j], cnt = ptr[j + 1] - beg;
   const float sl2 = scale * kLog2e, rscale = 1.0f / scale;
   TileLoader<D> tl;   // tiles of the caller's tensors (ldv, lds0 below: the library's packed ones)
   tl.init(lds_base(smem), w, l, 2 * lay.ts, N);
@@ -369,39 +405,94 @@ __global__ __launch_bounds__(256, 2) void bwd_dkdv_mfma_kernel(
   // ---- each wave owns keys 32 kh .., features (D / 2) x .. of dK_j and dV_j: whole-row stores
   // through its own staging area
   wait_vm0_known();        // the last step's surplus request has landed
+  if (slot >= 0) {   // part of a cut list: the sums as they lie in the registers
+    f32x4* o = kv_slot<D>(kv, bh, slot, w, l);
+#pragma unroll
+    for (int dt = 0; dt < HT; ++dt)
+#pragma unroll
+      for (int r4 = 0; r4 < 4; ++r4) {
+        o[(4 * dt + r4) * 64] = f32x4{dvT[dt][4 * r4], dvT[dt][4 * r4 + 1], dvT[dt][4 * r4 + 2], dvT[dt][4 * r4 + 3]};
+        o[(4 * (HT + dt) + r4) * 64] = f32x4{dkT[dt][4 * r4], dkT[dt][4 * r4 + 1], dkT[dt][4 * r4 + 2], dkT[dt][4 * r4 + 3]};
+      }
+    return;
+  }
   __syncthreads();   // every wave is done with the tiles
-  unsigned char* stage = smem + wu * Lds::STG;
-  const size_t o0 = lay.head(bh) + (size_t)(k0 + 32 * kh) * lay.ts + (D / 2) * xh;
-  store_rows_bf16<HT>(stage, dvT, dV + o0, lay.ts, cols - 32 * kh, l);
+  store_kv<D>(smem + wu * Lds::STG, dvT, dkT, scale, dV, dK,
+              lay.head(bh) + (size_t)(k0 + 32 * kh) * lay.ts + (D / 2) * xh, lay.ts, cols - 32 * kh, l);
+}
+
+// dK_j, dV_j of the key blocks whose lists were cut: the sums of the rest and of the extras, in that order.
+// Bound by its traffic (64 KB a slot at d = 128) and the launch.
+template <int D>
+__global__ __launch_bounds__(256) void kv_merge_kernel(KvSplit kv, int BH, int N, int Tn, Lay lay, float scale,
+                                                       bf16* __restrict__ dK, bf16* __restrict__ dV) {
+  constexpr int HT = D / 64;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int bh = blockIdx.x % BH, m = blockIdx.x / BH;
+  const int4 unit = kv.units[(size_t)bh * (2 * kv.ecap + Tn) + kv.ecap + Tn + m];
+  const int j = unit.x, first = unit.z, extras = unit.w;
+  if (extras == 0) return;
+  const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, kh = w & 1, xh = w >> 1;
+  constexpr int NQ = 2 * HT * 4;
+  f32x4 s[NQ];
+  const f32x4* p = kv_slot<D>(kv, bh, unit.y, w, l);
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) s[q] = p[q * 64];
+  for (int e = 0; e < extras; e += 2) {   // (two in flight; past the end: the last again, not added)
+    f32x4 x[2][NQ];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const f32x4* y = kv_slot<D>(kv, bh, first + min(e + k, extras - 1), w, l);
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) x[k][q] = y[q * 64];
+    }
+    const bool two = e + 1 < extras;
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      s[q] += x[0][q];
+      if (two) s[q] += x[1][q];
+    }
+  }
+  f32x16 dvT[HT], dkT[HT];
 #pragma unroll
   for (int dt = 0; dt < HT; ++dt)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) dkT[dt][r] *= scale;
-  store_rows_bf16<HT>(stage, dkT, dK + o0, lay.ts, cols - 32 * kh, l);
+    for (int r = 0; r < 16; ++r) {
+      dvT[dt][r] = s[4 * dt + r / 4][r % 4];
+      dkT[dt][r] = s[4 * (HT + dt) + r / 4][r % 4];
+    }
+  const int k0 = j * kBlk, cols = min(kBlk, N - k0);
+  store_kv<D>(smem + wave_uniform(w) * KvLds<D>::STG, dvT, dkT, scale, dV, dK,
+              lay.head(bh) + (size_t)(k0 + 32 * kh) * lay.ts + (D / 2) * xh, lay.ts, cols - 32 * kh, l);
 }
 
 template <int D>
 hipError_t sparse_impl(const Shape& s, const BwdArgs& a, const float* Ds, const void* dHZcol, const DwSum& dw,
-                       hipStream_t st) {
+                       const KvSplit& kv, hipStream_t st) {
   const float* dZcol = dHZcol ? reinterpret_cast<const float*>((const char*)dHZcol + state_z_offset(s)) : nullptr;
   auto launch_kv = [&](auto kern) -> hipError_t {
     SLA_TRY(ensure_dyn_lds(kern, KvLds<D>::BYTES));
     KernelTimer kt("bwd_sparse_kv", st);
-    kern<<<dim3(s.T * s.BH + dw.dd / kDwPiece), 256, KvLds<D>::BYTES, st>>>(
+    kern<<<dim3(((s.BH * kv.ecap + 7) & ~7) + s.T * s.BH + dw.dd / kDwPiece), 256, KvLds<D>::BYTES, st>>>(
         (const bf16*)a.Q, (const bf16*)a.K, (const bf16*)a.V, (const bf16*)a.dO, a.L, Ds, a.col_ptr, a.col_rows,
-        a.col_order, (const bf16*)dHZcol, dZcol, s.BH, s.N, s.T, s.lay(), s.n_h, s.scale, (bf16*)a.dK, (bf16*)a.dV,
+        a.col_order, (const bf16*)dHZcol, dZcol, kv, s.BH, s.N, s.T, s.lay(), s.n_h, s.scale, (bf16*)a.dK, (bf16*)a.dV,
         dw);
     return hipSuccess;
   };
   SLA_TRY(s.phi == 0 ? launch_kv(bwd_dkdv_mfma_kernel<D, 0>) : launch_kv(bwd_dkdv_mfma_kernel<D, 1>));
+  if (kv.ecap > 0) {
+    KernelTimer kt("kv_merge", st);
+    kv_merge_kernel<D><<<s.BH * kv.ecap, 256, 4 * KvLds<D>::STG, st>>>(kv, s.BH, s.N, s.T, s.lay(), s.scale, (bf16*)a.dK,
+                                                                      (bf16*)a.dV);
+  }
   return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t mfma_backward_sparse(const Shape& s, const BwdArgs& a, const float* Ds, const void* dHZcol, const DwSum& dw,
-                                hipStream_t st) {
-  return s.d == 64 ? sparse_impl<64>(s, a, Ds, dHZcol, dw, st) : sparse_impl<128>(s, a, Ds, dHZcol, dw, st);
+                                const KvSplit& kv, hipStream_t st) {
+  return s.d == 64 ? sparse_impl<64>(s, a, Ds, dHZcol, dw, kv, st) : sparse_impl<128>(s, a, Ds, dHZcol, dw, kv, st);
 }
 
 }  // namespace sla

@@ -377,6 +377,19 @@ __device__ __forceinline__ void dw_part(unsigned char* smem, const DwArgs& a, in
   }
 }
 
+// The workgroups behind the query blocks': the units of the key-side kernel, a wave per head, then the parts of dW.
+template <int D>
+__device__ __forceinline__ void last_part(unsigned char* smem, const DwArgs& dw, const KvPlanArgs& plan, int p, int BH,
+                                          int N, int Tn, Lay lay) {
+  const int plans = kv_plan_wgs(plan.split, BH);
+  if (p < plans) {
+    const int bh = 4 * p + (threadIdx.x >> 6);
+    if (bh < BH) kv_plan(plan, Tn, bh);
+  } else {
+    dw_part<D>(smem, dw, p - plans, BH, N, Tn, lay);
+  }
+}
+
 // The query side on its own (query blocks of several tiles, whose dQ kernel shares a workgroup
 // between two tiles): one workgroup per 64-token tile, then the parts of dW.
 template <int D, int PHI>
@@ -385,10 +398,10 @@ __global__ __launch_bounds__(256, 2) void bwd_pre_mfma_kernel(
     const bf16* __restrict__ Os, const bf16* __restrict__ Ol, const bf16* __restrict__ H16,
     const float* __restrict__ Zs, int BH, int N,
     int Tn, Lay lay, int n_0, float* __restrict__ Ds, bf16* __restrict__ dHZ,
-    bf16* __restrict__ dQlin, DwArgs dw) {
+    bf16* __restrict__ dQlin, DwArgs dw, KvPlanArgs plan) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   if ((int)blockIdx.x >= Tn * BH) {
-    dw_part<D>(smem, dw, blockIdx.x - Tn * BH, BH, N, Tn, lay);
+    last_part<D>(smem, dw, plan, blockIdx.x - Tn * BH, BH, N, Tn, lay);
     return;
   }
   bf16x8 qf[D / 16], gf[D / 16];
@@ -437,7 +450,7 @@ __global__ __launch_bounds__(256 * QT, QT == 1 ? (D == 64 ? 3 : 2) : 1) void bwd
     const bf16* __restrict__ Q, const bf16* __restrict__ K, const bf16* __restrict__ V,
     const bf16* __restrict__ dO, const float* __restrict__ L, const float* __restrict__ Ds,
     const int32_t* __restrict__ row_idx, const bf16* __restrict__ dQlin, int BH, int N, int Tn, Lay lay, int n_h,
-    float scale, bf16* __restrict__ dQ, PreArgs pa, DwArgs dw) {
+    float scale, bf16* __restrict__ dQ, PreArgs pa, DwArgs dw, KvPlanArgs plan) {
   static_assert(!FUSED || QT == 1, "the fused form has one query tile per workgroup");
   using Lds = PairLds<D>;
   using T = SwzTile<D>;
@@ -450,7 +463,7 @@ __global__ __launch_bounds__(256 * QT, QT == 1 ? (D == 64 ? 3 : 2) : 1) void bwd
   const int qh = w & 1, kh = w >> 1;
   const int nb = (Tn + QT - 1) / QT, per_row = block_row(nb), tiles = per_row * block_rows(BH, nb);
   if (FUSED && (int)blockIdx.x >= tiles) {   // the last workgroups
-    dw_part<D>(smem, dw, blockIdx.x - tiles, BH, N, Tn, lay);
+    last_part<D>(smem, dw, plan, blockIdx.x - tiles, BH, N, Tn, lay);
     return;
   }
   const int block_y = blockIdx.x / per_row;
@@ -657,10 +670,12 @@ __global__ __launch_bounds__(256 * QT, QT == 1 ? (D == 64 ? 3 : 2) : 1) void bwd
 // over in memory.
 template <int D>
 hipError_t query_impl(const Shape& s, const BwdArgs& a, float* Ds, bf16* dHZ, bf16* dQlin, float* dWpart, int nparts,
-                      hipStream_t st) {
+                      const KvSplit& kv, hipStream_t st) {
   const float* Zs = (const float*)((const char*)a.HZ + state_z_offset(s));
   const PreArgs pa{(const bf16*)a.W, (const bf16*)a.Os, (const bf16*)a.Ol, (const bf16*)a.HZ, Zs, s.n_0, Ds, dHZ};
   const DwArgs dw{(const bf16*)a.Ol, (const bf16*)a.dO, dWpart, nparts};
+  const KvPlanArgs plan{kv, a.col_ptr, a.col_order};
+  const int last = kv_plan_wgs(kv, s.BH) + nparts;
   constexpr int lds_q = PairLds<D>::BYTES, lds_p = PreLds<D>::BYTES;
   static_assert(lds_p >= kDwLds<D>, "the parts of dW find room");
   if (s.rq % 2 == 0 && wide_query_tiles()) {
@@ -668,24 +683,24 @@ hipError_t query_impl(const Shape& s, const BwdArgs& a, float* Ds, bf16* dHZ, bf
     SLA_TRY(ensure_dyn_lds(pre, lds_p));
     {
       KernelTimer kt("bwd_pre", st);
-      pre<<<s.T * s.BH + nparts, 256, lds_p, st>>>(
+      pre<<<s.T * s.BH + last, 256, lds_p, st>>>(
           (const bf16*)a.Q, (const bf16*)a.dO, pa.W, pa.Os, pa.Ol, pa.H16, Zs, s.BH, s.N, s.T, s.lay(), s.n_0, Ds,
-          dHZ, dQlin, dw);
+          dHZ, dQlin, dw, plan);
     }
     const int bytes = lds_q + PairLds<D>::GROUP;
     SLA_TRY(ensure_dyn_lds(bwd_dq_mfma_kernel<D, 2, false, 0>, bytes));
     KernelTimer kt("bwd_sparse_q", st);
     bwd_dq_mfma_kernel<D, 2, false, 0><<<block_row((s.T + 1) / 2) * block_rows(s.BH, (s.T + 1) / 2), 512, bytes, st>>>(
         (const bf16*)a.Q, (const bf16*)a.K, (const bf16*)a.V, (const bf16*)a.dO, a.L, Ds, a.row_idx,
-        s.n_0 > 0 ? dQlin : nullptr, s.BH, s.N, s.T, s.lay(), s.n_h, s.scale, (bf16*)a.dQ, pa, dw);
+        s.n_0 > 0 ? dQlin : nullptr, s.BH, s.N, s.T, s.lay(), s.n_h, s.scale, (bf16*)a.dQ, pa, dw, plan);
   } else {
     constexpr int bytes = lds_q > lds_p ? lds_q : lds_p;
     auto kern = s.phi == 0 ? bwd_dq_mfma_kernel<D, 1, true, 0> : bwd_dq_mfma_kernel<D, 1, true, 1>;
     SLA_TRY(ensure_dyn_lds(kern, bytes));
     KernelTimer kt("bwd_query", st);
-    kern<<<block_row(s.T) * block_rows(s.BH, s.T) + nparts, 256, bytes, st>>>(
+    kern<<<block_row(s.T) * block_rows(s.BH, s.T) + last, 256, bytes, st>>>(
         (const bf16*)a.Q, (const bf16*)a.K, (const bf16*)a.V, (const bf16*)a.dO, a.L, nullptr, a.row_idx, nullptr, s.BH,
-        s.N, s.T, s.lay(), s.n_h, s.scale, (bf16*)a.dQ, pa, dw);
+        s.N, s.T, s.lay(), s.n_h, s.scale, (bf16*)a.dQ, pa, dw, plan);
   }
   return hipGetLastError();
 }
@@ -693,11 +708,11 @@ hipError_t query_impl(const Shape& s, const BwdArgs& a, float* Ds, bf16* dHZ, bf
 }  // namespace
 
 hipError_t mfma_backward_query(const Shape& s, const BwdArgs& a, float* Ds, void* dHZ16, float* dQlin, float* dWpart,
-                               int nparts, hipStream_t st) {
+                               int nparts, const KvSplit& kv, hipStream_t st) {
   bf16* dHZ = reinterpret_cast<bf16*>(dHZ16);
   bf16* dQl = reinterpret_cast<bf16*>(dQlin);   // bf16 rows in the float-sized buffer
-  return s.d == 64 ? query_impl<64>(s, a, Ds, dHZ, dQl, dWpart, nparts, st)
-                   : query_impl<128>(s, a, Ds, dHZ, dQl, dWpart, nparts, st);
+  return s.d == 64 ? query_impl<64>(s, a, Ds, dHZ, dQl, dWpart, nparts, kv, st)
+                   : query_impl<128>(s, a, Ds, dHZ, dQl, dWpart, nparts, kv, st);
 }
 
 }  // namespace sla

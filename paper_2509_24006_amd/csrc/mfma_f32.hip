@@ -612,11 +612,13 @@ __global__ __launch_bounds__(256, 2) void f32_bwd_query_kernel(
     const float* __restrict__ dO, const float* __restrict__ Os, const float* __restrict__ Ol,
     const float* __restrict__ L, const float* __restrict__ HZ, const int32_t* __restrict__ row_idx, int N, int Tn,
     Lay lay, int n_h, int n_0, int phi, float scale, float* __restrict__ Ds, float* __restrict__ dHZ,
-    float* __restrict__ dQ, int BH, float* __restrict__ dWpart, int nparts) {
+    float* __restrict__ dQ, int BH, float* __restrict__ dWpart, int nparts, KvPlanArgs plan) {
   constexpr int NT = D / 16, TB = FTile<D>::BYTES;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  if ((int)blockIdx.x >= Tn * BH) {   // the last workgroups
-    f32_dw_part<D>(smem, Ol, dO, blockIdx.x - Tn * BH, nparts, BH, N, Tn, lay, dWpart);
+  if ((int)blockIdx.x >= Tn * BH) {   // the last workgroups: units of the key side, then the parts of dW
+    const int p = blockIdx.x - Tn * BH, plans = kv_plan_wgs(plan.split, BH);
+    if (p >= plans) f32_dw_part<D>(smem, Ol, dO, p - plans, nparts, BH, N, Tn, lay, dWpart);
+    else if (4 * p + (int)(threadIdx.x >> 6) < BH) kv_plan(plan, Tn, 4 * p + (threadIdx.x >> 6));
     return;
   }
   float* dls = reinterpret_cast<float*>(smem + 2 * TB);   // D^l / (phi(Q) Z) of the 64 queries
@@ -766,7 +768,9 @@ __global__ __launch_bounds__(256, 2) void f32_bwd_query_kernel(
 // share 16 of them (lane = key) split the 64 queries of every step in QW parts, and the
 // workgroups start with the longest lists of all heads.  The partial sums of the QW waves meet in
 // LDS once, after the loop; each then finishes its share of the features.  Q and dO go through
-// one slot each; every load lands under a product that reads the other one.
+// one slot each; every load lands under a product that reads the other one.  Lists that would still outlast
+// the rest are cut: the first workgroups walk pieces of them and leave their sums as rows of a slot, which
+// f32_kv_merge_kernel adds to what the rest of the list gave.
 template <int QW, int M>
 __device__ __forceinline__ void pick_tiles(const f32x4* x, int wq, f32x4 (&y)[M]) {
   // y[m] = x[wq + QW m] with wq uniform, without indexing registers
@@ -780,6 +784,32 @@ __device__ __forceinline__ void pick_tiles(const f32x4* x, int wq, f32x4 (&y)[M]
   }
 }
 
+// a slot: the 64 rows of dK, then those of dV
+template <int D>
+__device__ __forceinline__ float* f32_kv_slot(const KvSplit& kv, int bh, int slot) {
+  return kv.part + ((size_t)bh * 2 * kv.ecap + slot) * (2 * kBlk * D);
+}
+// dK_j, dV_j of the key blocks whose lists were cut += the sums of the extras, in order; a workgroup per
+// 16 rows of the two
+template <int D>
+__global__ __launch_bounds__(256) void f32_kv_merge_kernel(KvSplit kv, int BH, int N, int Tn, Lay lay,
+                                                           float* __restrict__ dK, float* __restrict__ dV) {
+  const int bh = blockIdx.x % BH, m = blockIdx.x / BH;
+  const int4 unit = kv.units[(size_t)bh * (2 * kv.ecap + Tn) + kv.ecap + Tn + m];
+  if (unit.w == 0) return;
+  constexpr int C = D / 4;   // 16-byte pieces of a row
+  for (int i = blockIdx.y * 16 * C + threadIdx.x; i < (blockIdx.y + 1) * 16 * C; i += 256) {
+    const int row = i / C, c = 4 * (i % C), key = unit.x * kBlk + row % kBlk;
+    if (key >= N) continue;
+    float* o = (row < kBlk ? dK : dV) + lay.head(bh) + (size_t)key * lay.ts + c;
+    f32x4 s = *reinterpret_cast<const f32x4*>(o);
+#pragma unroll 4
+    for (int e = 0; e < unit.w; ++e)
+      s += *reinterpret_cast<const f32x4*>(f32_kv_slot<D>(kv, bh, unit.z + e) + (size_t)row * D + c);
+    *reinterpret_cast<f32x4*>(o) = s;
+  }
+}
+
 template <int D>
 constexpr int f32_bwd_key_lds() { return 2 * FTile<D>::BYTES + 512 + 256; }   // + L, D^s of 64 queries + dot products
 
@@ -789,12 +819,13 @@ __global__ __launch_bounds__(256, 2) void f32_bwd_key_kernel(
     const float* __restrict__ dO, const float* __restrict__ L, const float* __restrict__ Ds,
     const int32_t* __restrict__ col_ptr, const int32_t* __restrict__ col_rows, const int32_t* __restrict__ col_order,
     const float* __restrict__ dHZcol, int N, int Tn, Lay lay, int n_h, int n_0, int phi, float scale,
-    float* __restrict__ dK, float* __restrict__ dV, DwSum dw) {
+    float* __restrict__ dK, float* __restrict__ dV, DwSum dw, KvSplit kv) {
   static_assert(QW == 2 || QW == 4, "waves that share a group of 16 keys");
   constexpr int NT = D / 16, TB = FTile<D>::BYTES, NQ = 4 / QW, NO = NT / QW;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  if ((int)blockIdx.y >= Tn * QW) {   // the last rows of the grid: dW
-    const int block = ((int)blockIdx.y - Tn * QW) * gridDim.x + blockIdx.x;
+  const int y = (int)blockIdx.y - kv.ecap * QW;   // below zero: extras
+  if (y >= Tn * QW) {   // the last rows of the grid: dW
+    const int block = (y - Tn * QW) * gridDim.x + blockIdx.x;
     if (block < dw.dd / kDwPiece) dw_sum(dw, block, smem);
     return;
   }
@@ -803,7 +834,22 @@ __global__ __launch_bounds__(256, 2) void f32_bwd_key_kernel(
   const int tid = threadIdx.x, w = wave_uniform(tid >> 6), l = tid & 63, g = l >> 4, n = l & 15;
   const int wk = w / QW, wq = w % QW;
   const int bh = blockIdx.x, kg = blockIdx.y % QW;
-  const int j = col_order[(size_t)bh * Tn + blockIdx.y / QW];
+  int j, t0 = 0, t1 = 0, slot = 0;
+  if (kv.ecap > 0) {
+    const int4 unit = kv.units[(size_t)bh * (2 * kv.ecap + Tn) + blockIdx.y / QW];
+    j = unit.x;
+    t0 = unit.y;
+    t1 = t0 + unit.z;
+    slot = unit.w;
+    if (y < 0 && unit.z == 0) return;
+  } else {
+    j = col_order[(size_t)bh * Tn + blockIdx.y / QW];
+    const int32_t* ptr = col_ptr + (size_t)bh * (Tn + 1);
+    if (n_h > 0) {
+      t0 = ptr[j];
+      t1 = ptr[j + 1];
+    }
+  }
   const int k0 = j * kBlk + kg * (kBlk / QW);      // first key of this workgroup
   if (k0 >= N) return;
   const int key = k0 + 16 * wk + n;
@@ -826,9 +872,7 @@ __global__ __launch_bounds__(256, 2) void f32_bwd_key_kernel(
     ld.load(dQd, i, 0);
     if (w < 2) load_to_lds4(dSt, (i * kBlk + l) * 4, lds_base(smem) + 2 * TB + 256 * w);
   };
-  const int32_t* ptr = col_ptr + (size_t)bh * (Tn + 1);
   const int32_t* list = col_rows + (size_t)bh * Tn * n_h;
-  const int t0 = n_h > 0 ? ptr[j] : 0, t1 = n_h > 0 ? ptr[j + 1] : 0;
   if (t0 < t1) {
     int i = list[t0];
     ld.load(dOd, i, TB);
@@ -898,6 +942,15 @@ __global__ __launch_bounds__(256, 2) void f32_bwd_key_kernel(
   for (int m = 0; m < NO; ++m)
 #pragma unroll
     for (int r = 0; r < 4; ++r) ok_[m][r] *= scale;
+  if (y < 0) {
+    float* o = f32_kv_slot<D>(kv, bh, slot) + (size_t)(key - j * kBlk) * D;
+#pragma unroll
+    for (int m = 0; m < NO; ++m) {
+      *reinterpret_cast<f32x4*>(o + 16 * (wq + QW * m) + 4 * g) = ok_[m];
+      *reinterpret_cast<f32x4*>(o + kBlk * D + 16 * (wq + QW * m) + 4 * g) = ov[m];
+    }
+    return;
+  }
   if (n_0 > 0) {
     // last line of Alg. 2: dK^phi = V dH^T + dZ (then through phi), dV += phi(K) dH, with dH, dZ
     // the sums over the marginal query blocks of this key block; LDS holds dH^T (rows e)
@@ -1019,43 +1072,45 @@ hipError_t forward_impl(const Shape& s, const FwdArgs& a, hipStream_t st) {
 
 template <int D, int QW>
 hipError_t launch_key(const Shape& s, const BwdArgs& a, const float* Ds, const float* dHZcol, const DwSum& dw,
-                      hipStream_t st) {
+                      const KvSplit& kv, hipStream_t st) {
   SLA_TRY(ensure_dyn_lds(f32_bwd_key_kernel<D, QW>, f32_bwd_key_lds<D>()));
-  KernelTimer kt("bwd_sparse_kv", st);
-  f32_bwd_key_kernel<D, QW><<<dim3(s.BH, s.T * QW + (dw.dd / kDwPiece + s.BH - 1) / s.BH), 256, f32_bwd_key_lds<D>(), st>>>(
-      (const float*)a.Q, (const float*)a.K, (const float*)a.V, (const float*)a.dO, a.L, Ds, a.col_ptr, a.col_rows,
-      a.col_order, dHZcol, s.N, s.T, s.lay(), s.n_h, s.n_0, s.phi, s.scale, (float*)a.dK, (float*)a.dV, dw);
+  {
+    KernelTimer kt("bwd_sparse_kv", st);
+    f32_bwd_key_kernel<D, QW><<<dim3(s.BH, (kv.ecap + s.T) * QW + (dw.dd / kDwPiece + s.BH - 1) / s.BH), 256, f32_bwd_key_lds<D>(), st>>>(
+        (const float*)a.Q, (const float*)a.K, (const float*)a.V, (const float*)a.dO, a.L, Ds, a.col_ptr, a.col_rows,
+        a.col_order, dHZcol, s.N, s.T, s.lay(), s.n_h, s.n_0, s.phi, s.scale, (float*)a.dK, (float*)a.dV, dw, kv);
+  }
+  if (kv.ecap > 0) {
+    KernelTimer kt("kv_merge", st);
+    f32_kv_merge_kernel<D><<<dim3(s.BH * kv.ecap, 8), 256, 0, st>>>(kv, s.BH, s.N, s.T, s.lay(), (float*)a.dK, (float*)a.dV);
+  }
   return hipGetLastError();
 }
 
 template <int D>
 hipError_t backward_impl(const Shape& s, const BwdArgs& a, float* Ds, float* dHZ, float* dHZcol, float* dWpart,
-                         int nparts, hipStream_t st) {
+                         int nparts, const KvSplit& kv, hipStream_t st) {
   const size_t lds_q = 2 * FTile<D>::BYTES + 4 * kBlk;
   SLA_TRY(ensure_dyn_lds(f32_bwd_query_kernel<D>, lds_q));
   {
     KernelTimer kt("bwd_query", st);
-    f32_bwd_query_kernel<D><<<s.T * s.BH + nparts, 256, lds_q, st>>>(
+    f32_bwd_query_kernel<D><<<s.T * s.BH + kv_plan_wgs(kv, s.BH) + nparts, 256, lds_q, st>>>(
         (const float*)a.Q, (const float*)a.K, (const float*)a.V, (const float*)a.W, (const float*)a.dO,
         (const float*)a.Os, (const float*)a.Ol, a.L, a.HZ, a.row_idx, s.N, s.T, s.lay(), s.n_h, s.n_0, s.phi, s.scale,
-        Ds, dHZ, (float*)a.dQ, s.BH, dWpart, nparts);
+        Ds, dHZ, (float*)a.dQ, s.BH, dWpart, nparts, KvPlanArgs{kv, a.col_ptr, a.col_order});
   }
   const DwSum dw{dWpart, nparts, D * D, a.dW, a.dW16};
   if (s.n_0 > 0) SLA_TRY(f32_aggregate(dHZ, a.indT, s, dHZcol, st));
-  // A quarter of the keys per workgroup balances the uneven lists (clip, 4 heads x 122 blocks: 189 us,
-  // 273 with halves, 444 with whole key blocks); with enough workgroups the tiles that they fetch
-  // cost more than the balance gives (16 heads x 63 blocks: 347 against 297 us with halves; 12 x
-  // 157 at 20 %: 2191 against 2010, 2039 with whole blocks).
-  if (s.BH * s.T < 768) return launch_key<D, 4>(s, a, Ds, dHZcol, dw, st);
-  return launch_key<D, 2>(s, a, Ds, dHZcol, dw, st);
+  if (f32_key_quarters(s)) return launch_key<D, 4>(s, a, Ds, dHZcol, dw, kv, st);
+  return launch_key<D, 2>(s, a, Ds, dHZcol, dw, kv, st);
 }
 
 }  // namespace
 
 hipError_t f32_backward(const Shape& s, const BwdArgs& a, float* Ds, float* dHZ, float* dHZcol, float* dWpart,
-                        int nparts, hipStream_t st) {
-  return s.d == 64 ? backward_impl<64>(s, a, Ds, dHZ, dHZcol, dWpart, nparts, st)
-                   : backward_impl<128>(s, a, Ds, dHZ, dHZcol, dWpart, nparts, st);
+                        int nparts, const KvSplit& kv, hipStream_t st) {
+  return s.d == 64 ? backward_impl<64>(s, a, Ds, dHZ, dHZcol, dWpart, nparts, kv, st)
+                   : backward_impl<128>(s, a, Ds, dHZ, dHZcol, dWpart, nparts, kv, st);
 }
 
 hipError_t f32_states(const Shape& s, const FwdArgs& a, const Beside& b, hipStream_t st) {

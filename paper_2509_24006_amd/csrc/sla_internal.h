@@ -106,6 +106,23 @@ struct BwdArgs {
   char* ws;  // workspace, ws_backward_bytes
 };
 size_t backward_ws_bytes(const Shape& s);   // (backward.hip)
+// How the key-side kernel walks the column lists.  A unit of work is a list, or a piece of it: lists longer
+// than `piece` entries give up pieces of that many, each with float sums of its own (a slot of `part`),
+// which a second launch adds up.  Every unit is four ints, written by a wave per head of the query-side launch
+// (kv_plan):
+//   extra e < ecap             key block, first entry, entries (0: none), slot
+//   ecap + r, r < T            the rest of the list of rank r: key block, first entry, entries, slot or -1
+//   ecap + T + m, m < ecap     a key block that was cut: key block, slot of the rest, slot of the first extra, extras
+struct KvSplit {
+  int piece, ecap;
+  int4* units;   // [BH][2 ecap + T]
+  float* part;   // [BH][2 ecap] slots of 2 x 64 x d floats
+};
+KvSplit kv_split(const Shape& s);   // piece and ecap (backward.hip)
+struct KvPlanArgs {
+  KvSplit split;
+  const int32_t *col_ptr, *col_order;
+};
 // The sum of dW's partial d x d sums, done by extra workgroups of the key-side kernel's launch.
 struct DwSum {
   const float* part;
@@ -118,10 +135,15 @@ struct DwSum {
 // vectors at state_z_offset); the dK/dV kernel turns them into the linear-branch parts of dK and
 // dV itself.  Both may be null (no marginal block).
 hipError_t mfma_backward_sparse(const Shape& s, const BwdArgs& a, const float* Ds, const void* dHZcol, const DwSum& dw,
-                                hipStream_t st);
+                                const KvSplit& kv, hipStream_t st);
 // the float path's backward pass; the workspace pieces are carved by backward()
 hipError_t f32_backward(const Shape& s, const BwdArgs& a, float* Ds, float* dHZ, float* dHZcol, float* dWpart,
-                        int nparts, hipStream_t st);
+                        int nparts, const KvSplit& kv, hipStream_t st);
+// Whether a workgroup of its key side owns a quarter of a key block, or half of one.  Quarters fill the chip where
+// there are few blocks (key side with the adding launch, quarters -> halves, us: 3 heads x 64 blocks, d = 64, 50 -> 72;
+// 2 x 122 of 12, d = 128, 152 -> 160); with more the tiles that they fetch cost more (4 x 122 of 6 169 -> 157;
+// 12 x 63 of 6 252 -> 236; 1 x 127 of 19, below the line, 141 -> 129).
+inline bool f32_key_quarters(const Shape& s) { return s.BH * s.T < 384; }
 hipError_t backward(const Shape& s, const BwdArgs& a, hipStream_t st);
 
 // ---- bf16 matrix-core path (mfma_fwd.hip)
@@ -145,7 +167,7 @@ hipError_t aggregate_alt(int method, const void* in, const unsigned long long* i
 // scratch for the linear part of dQ (only used with query blocks of two or four tiles).
 // dWpart: nparts partial sums of dW = sum O^l^T dO.
 hipError_t mfma_backward_query(const Shape& s, const BwdArgs& a, float* Ds, void* dHZ16, float* dQlin, float* dWpart,
-                               int nparts, hipStream_t st);
+                               int nparts, const KvSplit& kv, hipStream_t st);
 
 // Brackets one kernel launch with events when profiling is on (profile.hip).
 class KernelTimer {

@@ -241,6 +241,32 @@ def test_key_blocks_that_nearly_every_query_block_selects(oracle, T, d, tail):
     _full_case(oracle, x, "bf16", 0.08, 0.2)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("T,d,H,phi,bq,k_l", [(35, 64, 3, 0, 64, 0.2), (36, 64, 3, 1, 64, 0.2), (37, 128, 2, 0, 64, 0.2),
+                                               (49, 64, 5, 0, 128, 0.2), (61, 128, 1, 0, 64, 0.95), (73, 64, 3, 1, 256, 0.1)])
+def test_column_lists_cut_into_pieces(oracle, dtype, T, d, H, phi, bq, k_l):
+    # with few entries in all a list longer than twelve is walked in pieces (from 36 blocks on) and a second
+    # launch adds the sums: lists of T, T - 1, .. entries of which the rest is one entry, a full piece or between,
+    # key blocks without any, a ragged last block, no marginal block; the same bits on every call
+    N = 64 * T - 11
+    rng = np.random.default_rng(T + d)
+    u = rng.standard_normal(d).astype(np.float32)
+    u /= np.linalg.norm(u)
+    x = {k: rng.standard_normal((1, H, N, d)).astype(np.float32) for k in ("Q", "K", "V", "dO")}
+    x["Q"] += 1.5 * u
+    for j in (2, T // 2, T - 1):
+        x["K"][:, :, 64 * j:64 * (j + 1)] += 4.0 * u
+    x["Proj"] = (rng.standard_normal((d, d)) * 0.05).astype(np.float32)
+    if dtype == "bf16":
+        x = {k: wl.round_to_bf16(v) for k, v in x.items()}
+    k_h = 4.2 / T
+    Mc = oracle.build_mask(x["Q"], x["K"], k_h, k_l, bq=bq)
+    assert (Mc == 1).sum(-2).max() * (bq // 64) >= T - 2
+    _full_case(oracle, x, dtype, k_h, k_l, phi=phi, bq=bq)
+    first, again = (run_gpu(x, dtype, k_h, k_l, phi=phi, bq=bq) for _ in range(2))
+    assert all(np.array_equal(first[n], again[n]) for n in ("dQ", "dK", "dV", "dW"))
+
+
 @pytest.mark.parametrize("name", ["small_bf16", "small_bf16_d64", "small_fp32"])
 def test_token_major_tensors(oracle, name):
     # [B,N,H,d] tensors: the same kernels walk the same values with another row pitch, so every
