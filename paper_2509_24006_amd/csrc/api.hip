@@ -165,11 +165,11 @@ Tables tables(const Shape& s, const sla_sizes_t& z, int8_t* Mc, void* luts) {
   return t;
 }
 
-// at most 64 key blocks: everything behind the pooling (or behind given scores) in one launch
-hipError_t mask_small(const Shape& s, const float* qbar, const float* kbar, const float* given, float* scores,
-                      const Tables& t, hipStream_t st) {
-  return launch_mask_small(qbar, kbar, given, s, scores, t.Mc, t.row_idx, t.ind, t.ind_t, t.col.ptr, t.col.order, t.col.rows,
-                           st);
+// at most 64 key blocks: everything behind the pooling (with `pool` that too, or behind given scores) in one launch
+hipError_t mask_small(const Shape& s, const PoolArgs* pool, const float* qbar, const float* kbar, const float* given,
+                      float* scores, const Tables& t, hipStream_t st) {
+  return launch_mask_small(pool, qbar, kbar, given, s, scores, t.Mc, t.row_idx, t.ind, t.ind_t, t.col.ptr,
+                           t.col.order, t.col.rows, st);
 }
 // more of them: labels, row table, bit masks and column counts of given scores
 hipError_t classify(const Shape& s, const float* scores, const Tables& t, hipStream_t st) {
@@ -201,8 +201,17 @@ struct MaskCall {
     t = tables(s, z, Mc, luts);
     return SLA_OK;
   }
+  // Whether the mask kernel of a short sequence pools as well: one launch less, but a head's Q and K then come
+  // through one CU, and with many heads per CU its workgroups of sixteen waves use less of the memory's rate than the
+  // pooling kernel.  (Two launches -> one, us, bf16: 1 head x 16 blocks, d = 64, 13.5 -> 12.3; 16 x 24 15.3 -> 14.5;
+  // 256 x 16 23.2 -> 21.8; 1 x 16, d = 128, 0.5 MB, 16.1 -> 16.0, 1 x 24 16.7 -> 18.4; 1 x 64, d = 64, 1 MB, 21.9 ->
+  // 24.8; 1024 x 4 29.6 -> 54.2, 1024 x 16 65.9 -> 81.4; float, 1 x 4 10.0 -> 9.0, 1 x 16, 0.5 MB, 12.6 -> 12.8.)
+  bool pools_itself() const {
+    const long long head = 2ll * s.N * s.d * (s.dtype == SLA_F32 ? 4 : 2);
+    return s.T <= kBlk && head <= 450000 && s.BH <= 256;
+  }
   hipError_t behind_pool(hipStream_t st) const {
-    if (s.T <= kBlk) return mask_small(s, qbar, kbar, nullptr, scores, t, st);
+    if (s.T <= kBlk) return mask_small(s, nullptr, qbar, kbar, nullptr, scores, t, st);
     const hipError_t e = launch_scores(qbar, kbar, s, scores, st);
     return e == hipSuccess ? classify(s, scores, t, st) : e;
   }
@@ -271,7 +280,8 @@ int sla_classify_scores(const sla_params* p, const float* scores, int8_t* Mc, vo
   fill_sizes(s, &z);
   hipStream_t st = (hipStream_t)stream;
   const Tables t = tables(s, z, Mc, luts);
-  hipError_t e = s.T <= kBlk ? mask_small(s, nullptr, nullptr, scores, nullptr, t, st) : classify(s, scores, t, st);
+  hipError_t e =
+      s.T <= kBlk ? mask_small(s, nullptr, nullptr, nullptr, scores, nullptr, t, st) : classify(s, scores, t, st);
   if (e == hipSuccess && s.T > kBlk) e = launch_col_tables(t.col, s, st);
   return hip_status(e);
 }
@@ -282,6 +292,7 @@ int sla_build_mask(const sla_params* p, const void* Q, const void* K, int8_t* Mc
   const int rc = m.open(p, Q, K, Mc, luts, workspace, workspace_bytes);
   if (rc != SLA_OK) return rc;
   hipStream_t st = (hipStream_t)stream;
+  if (m.pools_itself()) return hip_status(mask_small(m.s, &m.pool, m.qbar, m.kbar, nullptr, m.scores, m.t, st));
   hipError_t e = launch_pool(m.pool, m.s, st);
   if (e == hipSuccess) e = m.behind_pool(st);
   if (e == hipSuccess && m.s.T > kBlk) e = launch_col_tables(m.t.col, m.s, st);

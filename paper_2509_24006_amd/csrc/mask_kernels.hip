@@ -4,6 +4,8 @@
 // All arithmetic that decides the mask is float in one fixed order so that the integer
 // result is reproducible: sequential add over a block's tokens, one IEEE division, a
 // fused multiply-add chain over the features, one multiply by 1/sqrt(d).
+#include <type_traits>
+
 #include "mask_parts.h"
 
 namespace sla {
@@ -292,9 +294,11 @@ __global__ __launch_bounds__(256) void col_tables_kernel(ColArgs a) {
 // per thread, 32 TT >= T.  (256 heads of 16 blocks, d = 64:
 // 14.5 -> 8.5 us a launch with the gap before it; 2 of 18, d = 128: 19 -> 10.3 us.)
 constexpr int kSmallWaves = 16;
-template <int TT>
+struct NoPool {};
+// PT: the tensors' type where the head's blocks are pooled here too (D features), or NoPool.
+template <int TT, typename PT, int D>
 __global__ __launch_bounds__(64 * kSmallWaves) void mask_small_kernel(
-    const float* __restrict__ qbar, const float* __restrict__ kbar, const float* __restrict__ given, int Tq, int rq,
+    PoolArgs pool, const float* qbar, const float* kbar, const float* __restrict__ given, int Tq, int rq,
     int T, int d, float scale, int n_h, int n_l, float* __restrict__ s_out, int8_t* __restrict__ Mc,
     int32_t* __restrict__ row_idx, unsigned long long* __restrict__ ind, unsigned long long* __restrict__ indT,
     int32_t* __restrict__ col_ptr, int32_t* __restrict__ col_order, int32_t* __restrict__ col_rows) {
@@ -305,6 +309,10 @@ __global__ __launch_bounds__(64 * kSmallWaves) void mask_small_kernel(
   __shared__ int cnt[64], cptr[64];
   const int bh = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const unsigned long long below = (1ull << lane) - 1ull;
+  if constexpr (!std::is_same_v<PT, NoPool>) {
+    pool_head<PT, D>(pool, bh, kSmallWaves);
+    __syncthreads();
+  }
   if (given) {
     const float* g = given + (size_t)bh * Tq * T;
     for (int e = tid; e < Tq * T; e += 64 * kSmallWaves) sc[e / T][e % T] = g[e];
@@ -489,13 +497,19 @@ hipError_t launch_col_tables(const ColArgs& a, const Shape& s, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_mask_small(const float* qbar, const float* kbar, const float* given, const Shape& s, float* scores,
-                             int8_t* Mc, int32_t* row_idx, unsigned long long* ind, unsigned long long* indT,
+hipError_t launch_mask_small(const PoolArgs* pool, const float* qbar, const float* kbar, const float* given,
+                             const Shape& s, float* scores, int8_t* Mc, int32_t* row_idx, unsigned long long* ind, unsigned long long* indT,
                              int32_t* col_ptr, int32_t* col_order, int32_t* col_rows, hipStream_t st) {
   KernelTimer kt("mask_small", st);
-  auto kern = s.T <= 32 ? mask_small_kernel<1> : mask_small_kernel<2>;
-  kern<<<s.BH, 64 * kSmallWaves, 0, st>>>(qbar, kbar, given, s.Tq, s.rq, s.T, s.d, s.scale, s.n_h, s.n_l, scores, Mc, row_idx,
-                                          ind, indT, col_ptr, col_order, col_rows);
+  typedef __hip_bfloat16 bf;
+  auto pick = [&](auto t1, auto t2) { return s.T <= 32 ? t1 : t2; };
+  auto kern = !pool ? pick(mask_small_kernel<1, NoPool, 64>, mask_small_kernel<2, NoPool, 64>)
+            : s.dtype == 0 ? (s.d == 64 ? pick(mask_small_kernel<1, float, 64>, mask_small_kernel<2, float, 64>)
+                                        : pick(mask_small_kernel<1, float, 128>, mask_small_kernel<2, float, 128>))
+                           : (s.d == 64 ? pick(mask_small_kernel<1, bf, 64>, mask_small_kernel<2, bf, 64>)
+                                        : pick(mask_small_kernel<1, bf, 128>, mask_small_kernel<2, bf, 128>));
+  kern<<<s.BH, 64 * kSmallWaves, 0, st>>>(pool ? *pool : PoolArgs{}, qbar, kbar, given, s.Tq, s.rq, s.T, s.d, s.scale,
+                                          s.n_h, s.n_l, scores, Mc, row_idx, ind, indT, col_ptr, col_order, col_rows);
   return hipGetLastError();
 }
 

@@ -14,17 +14,18 @@ namespace sla {
 // rows.  The first half of the 2 a.wgs workgroups takes Q (blocks of len0 tokens, Tn0 per head), the
 // other K (len1, Tn1).
 template <typename T, int D>
-__device__ __forceinline__ void pool_part(const PoolArgs& a, int wg) {
-  constexpr int V = 16 / sizeof(T), LPB = D / V, BPW = 64 / LPB;
-  const bool second = wg >= a.wgs;
+struct PoolWave {
+  static constexpr int V = 16 / sizeof(T), LPB = D / V, BPW = 64 / LPB;   // lanes per block, blocks per wave
+};
+// block i of head bh (or none, lane by lane) by the LPB lanes that share it
+template <typename T, int D>
+__device__ __forceinline__ void pool_block(const PoolArgs& a, bool second, int bh, int i) {
+  constexpr int V = PoolWave<T, D>::V, LPB = PoolWave<T, D>::LPB;
   const T* X = reinterpret_cast<const T*>(second ? a.X1 : a.X0);
   float* out = second ? a.out1 : a.out0;
   const int Tn = second ? a.Tn1 : a.Tn0, len = second ? a.len1 : a.len0;
   const Lay lay = a.lay;
-  const int lane = threadIdx.x & 63, sub = lane / LPB, fl = lane % LPB;
-  const long blk = ((long)(second ? wg - a.wgs : wg) * 4 + (threadIdx.x >> 6)) * BPW + sub;
-  if (blk >= (long)a.BH * Tn) return;
-  const int bh = (int)(blk / Tn), i = (int)(blk % Tn);
+  const int fl = (threadIdx.x & 63) % LPB;
   const int cnt = min(len, a.N - i * len);
   const T* p = X + lay.head(bh) + (size_t)i * len * lay.ts + fl * V;
   float s[V];
@@ -50,11 +51,32 @@ __device__ __forceinline__ void pool_part(const PoolArgs& a, int wg) {
     for (int v = 0; v < V; ++v) s[v] = s[v] + to_f32(e[v]);
   }
   const float c = (float)cnt;
-  float* o = out + (size_t)blk * D + fl * V;
+  float* o = out + ((size_t)bh * Tn + i) * D + fl * V;
 #pragma unroll
   for (int v = 0; v < V; v += 4)
     *reinterpret_cast<float4*>(o + v) = float4{__fdiv_rn(s[v], c), __fdiv_rn(s[v + 1], c), __fdiv_rn(s[v + 2], c),
                                                __fdiv_rn(s[v + 3], c)};
+}
+
+template <typename T, int D>
+__device__ __forceinline__ void pool_part(const PoolArgs& a, int wg) {
+  using P = PoolWave<T, D>;
+  const bool second = wg >= a.wgs;
+  const int Tn = second ? a.Tn1 : a.Tn0;
+  const long blk = ((long)(second ? wg - a.wgs : wg) * 4 + (threadIdx.x >> 6)) * P::BPW + (threadIdx.x & 63) / P::LPB;
+  if (blk < (long)a.BH * Tn) pool_block<T, D>(a, second, (int)(blk / Tn), (int)(blk % Tn));
+}
+
+// both tensors of one head by the `waves` waves of a workgroup
+template <typename T, int D>
+__device__ __forceinline__ void pool_head(const PoolArgs& a, int bh, int waves) {
+  using P = PoolWave<T, D>;
+  const int u0 = (a.Tn0 + P::BPW - 1) / P::BPW, u1 = (a.Tn1 + P::BPW - 1) / P::BPW;
+  for (int u = threadIdx.x >> 6; u < u0 + u1; u += waves) {
+    const bool second = u >= u0;
+    const int i = (second ? u - u0 : u) * P::BPW + (threadIdx.x & 63) / P::LPB;
+    if (i < (second ? a.Tn1 : a.Tn0)) pool_block<T, D>(a, second, bh, i);
+  }
 }
 
 // ---------------------------------------------------------------- column tables (CSC)

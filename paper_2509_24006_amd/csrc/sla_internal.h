@@ -71,11 +71,12 @@ struct Beside {
   const ColArgs* col = nullptr;
 };
 
-// T <= 64: scores (computed from qbar, kbar and written to `scores`, or read from `given`),
-// classification and all tables in one launch
-hipError_t launch_mask_small(const float* qbar, const float* kbar, const float* given, const Shape& s, float* scores,
-                             int8_t* Mc, int32_t* row_idx, unsigned long long* ind, unsigned long long* indT,
-                             int32_t* col_ptr, int32_t* col_order, int32_t* col_rows, hipStream_t st);
+// T <= 64: with `pool` the block means first (into qbar and kbar); scores (computed from qbar, kbar and written to
+// `scores`, or read from `given`), classification and all tables in one launch
+hipError_t launch_mask_small(const PoolArgs* pool, const float* qbar, const float* kbar, const float* given,
+                             const Shape& s, float* scores, int8_t* Mc, int32_t* row_idx, unsigned long long* ind,
+                             unsigned long long* indT, int32_t* col_ptr, int32_t* col_order, int32_t* col_rows,
+                             hipStream_t st);
 
 // n floats from p on become 0 (mfma_fwd.hip)
 hipError_t launch_fill_zero(float* p, size_t n, hipStream_t st);

@@ -496,6 +496,24 @@ def test_scores_are_the_same_with_tiles_of_either_size(T, H, bq):
         assert torch.equal(m1[0, 0], Mc[0, h])
 
 
+@pytest.mark.parametrize("N,d,bq,dtype", [(1, 64, 64, torch.bfloat16), (1015, 64, 64, torch.bfloat16),
+                                          (1728, 64, 128, torch.bfloat16), (800, 128, 64, torch.bfloat16),
+                                          (833, 64, 256, torch.float32), (430, 128, 64, torch.float32)])
+def test_short_masks_with_the_pooling_in_their_launch(N, d, bq, dtype):
+    # 257 heads are pooled by a kernel of its own, one head by the mask kernel: the same bits
+    from paper_2509_24006_amd import binding as sla
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N)
+    Q, K = (torch.randn(1, 257, N, d, generator=g, device="cuda").to(dtype) for _ in range(2))
+    mk = lambda h: sla.make_params(1, h, N, d, 0.2, 0.2, dtype, bq=bq)
+    Mc, luts, ws = sla.sla_build_mask(mk(257), Q, K)
+    ref = {**sla.mask_ws_views(mk(257), ws), **sla.lut_views(mk(257), luts), "Mc": Mc}
+    for h in (0, 100, 256):
+        m1, l1, w1 = sla.sla_build_mask(mk(1), Q[:, h:h + 1], K[:, h:h + 1])
+        for k, x in {**sla.mask_ws_views(mk(1), w1), **sla.lut_views(mk(1), l1), "Mc": m1}.items():
+            assert torch.equal(x.flatten(0, 1)[0], ref[k].flatten(0, 1)[h]), k
+
+
 def test_forward_without_saved_matches(oracle):
     from paper_2509_24006_amd import binding as sla
     from tests.gpu_util import to_dev, f64
