@@ -279,9 +279,10 @@ __global__ __launch_bounds__(256) void indicator_kernel(const int8_t* __restrict
   }
 }
 
-__global__ __launch_bounds__(256) void col_tables_kernel(ColArgs a) {
+template <int NW>
+__global__ __launch_bounds__(64 * NW) void col_tables_kernel(ColArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  col_tables_part(smem, a, blockIdx.x, blockIdx.y);
+  col_tables_part<NW>(smem, a, blockIdx.x, blockIdx.y);
 }
 
 // ---------------------------------------------------------------- short sequences
@@ -493,13 +494,20 @@ hipError_t launch_indicator(const int8_t* Mc, const Shape& s, int32_t* col_cnt, 
 hipError_t launch_col_tables(const ColArgs& a, const Shape& s, hipStream_t st) {
   const int Tw = (s.T + 63) / 64;
   KernelTimer kt("col_tables", st);
-  col_tables_kernel<<<dim3(Tw, s.BH), 256, col_tables_lds(Tw), st>>>(a);
+  // The waves of a workgroup share its row tiles, of which they walk one after the other, so more than four row
+  // tiles take eight waves; sixteen pay where there are many and the workgroups leave the chip idle.  (4, 8, 16
+  // waves, us: 24 heads x 250 blocks 10.1, 9.7, 9.8; 12 x 512 15.6, 11.4, 11.2, 20 % critical 20.3, 14.0, 13.8; 40 x
+  // 512 20.2, 19.0, 22.2; 40 x 1182 48.7, 45.2, 52.4; 2 x 2500 56.6, 36.2, 28.3; 512 x 130 17.5, 22.1, 39.0.)
+  const int nw = Tw <= 4 ? 4 : Tw > 16 && Tw * s.BH <= 256 ? 16 : 8;
+  auto kern = nw == 4 ? col_tables_kernel<4> : nw == 8 ? col_tables_kernel<8> : col_tables_kernel<16>;
+  kern<<<dim3(Tw, s.BH), 64 * nw, col_tables_lds(Tw, nw), st>>>(a);
   return hipGetLastError();
 }
 
 hipError_t launch_mask_small(const PoolArgs* pool, const float* qbar, const float* kbar, const float* given,
-                             const Shape& s, float* scores, int8_t* Mc, int32_t* row_idx, unsigned long long* ind, unsigned long long* indT,
-                             int32_t* col_ptr, int32_t* col_order, int32_t* col_rows, hipStream_t st) {
+                             const Shape& s, float* scores, int8_t* Mc, int32_t* row_idx, unsigned long long* ind,
+                             unsigned long long* indT, int32_t* col_ptr, int32_t* col_order, int32_t* col_rows,
+                             hipStream_t st) {
   KernelTimer kt("mask_small", st);
   typedef __hip_bfloat16 bf;
   auto pick = [&](auto t1, auto t2) { return s.T <= 32 ? t1 : t2; };

@@ -138,9 +138,12 @@ __device__ __forceinline__ ColumnVotes<R> column_votes(const int8_t* __restrict_
 constexpr int kLongList = 12;   // rows of a column's list in a tile from which the wave writes it
 constexpr int kManyLong = 24;   // such columns in a tile from which it writes all 64 without a choice
 constexpr int kKeyBits = 12;   // column index in a sort key: kMaxT of the interface is below 2^12
-__host__ __device__ constexpr int col_tables_lds(int Tw) { return 64 * Tw * 4 + 64 * Tw * 8 + (4 * 64 + 64 + 4) * 4; }
+__host__ __device__ constexpr int col_tables_lds(int Tw, int waves) {
+  return 64 * Tw * 4 + 64 * Tw * 8 + (waves * 64 + 64 + waves) * 4;
+}
 
-// columns [64 jt, +64) of head bh; smem: col_tables_lds bytes
+// columns [64 jt, +64) of head bh by NW waves; smem: col_tables_lds bytes
+template <int NW>
 __device__ __forceinline__ void col_tables_part(unsigned char* smem, const ColArgs& a, int jt, int bh) {
   const int8_t* __restrict__ Mc = a.Mc;
   const int32_t* __restrict__ cnt_g = a.cnt;
@@ -150,18 +153,18 @@ __device__ __forceinline__ void col_tables_part(unsigned char* smem, const ColAr
   uint32_t* key = reinterpret_cast<uint32_t*>(smem);   // (count, column descending) of the head; 0 past T
   unsigned long long* crit = reinterpret_cast<unsigned long long*>(smem + 64 * Tw * 4);   // [row tile][column]
   int (*part)[64] = reinterpret_cast<int (*)[64]>(smem + 64 * Tw * 12);   // [wave][column]
-  int *cptr = part[4], *wsum = part[5];
+  int *cptr = part[NW], *wsum = part[NW + 1];
   const int j0 = jt * 64;
   const int tid = threadIdx.x, l = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int32_t* cg = cnt_g + (size_t)bh * T;
   int before = 0;   // this thread's share of the counts of the columns before j0
-  for (int j = tid; j < 64 * Tw; j += 256) {
+  for (int j = tid; j < 64 * Tw; j += 64 * NW) {
     const int c = j < T ? cg[j] : 0;
     key[j] = j < T ? (uint32_t)c << kKeyBits | (uint32_t)((1 << kKeyBits) - 1 - j) : 0u;
     if (j < j0) before += c;
   }
   if (n_h > 0)
-    for (int t = w; t < Tw; t += 4) {
+    for (int t = w; t < Tw; t += NW) {
       const ColumnVotes<64> v = column_votes<64, false>(Mc + (size_t)bh * Tq * T, T, rq, 64 * t, j0, l);
       crit[64 * t + l] = (unsigned long long)v.crit[1] << 32 | v.crit[0];
     }
@@ -180,31 +183,38 @@ __device__ __forceinline__ void col_tables_part(unsigned char* smem, const ColAr
       const int v = __shfl_up(incl, o);
       if (l >= o) incl += v;
     }
-    const int p = wsum[0] + wsum[1] + wsum[2] + wsum[3] + incl - c;
+    int p = incl - c;
+#pragma unroll
+    for (int x = 0; x < NW; ++x) p += wsum[x];
     cptr[l] = p;
     if (j < T) ptr[(size_t)bh * (T + 1) + j] = p;
     if (j == T - 1) ptr[(size_t)bh * (T + 1) + T] = p + c;
   }
-  // rank of this workgroup's columns; the four waves share the comparisons of a column
+  // rank of this workgroup's columns; the waves share the comparisons of a column
   {
     int rank = 0;
-    const uint4* k4 = reinterpret_cast<const uint4*>(key) + 4 * Tw * w;
+    const uint4* k4 = reinterpret_cast<const uint4*>(key) + 16 / NW * Tw * w;
 #pragma unroll 4
-    for (int k = 0; k < 4 * Tw; ++k) {
+    for (int k = 0; k < 16 / NW * Tw; ++k) {
       const uint4 x = k4[k];
       rank += (x.x > mine) + (x.y > mine) + (x.z > mine) + (x.w > mine);
     }
     part[w][l] = rank;
   }
   __syncthreads();
-  if (w == 0 && j0 + l < T) order[(size_t)bh * T + part[0][l] + part[1][l] + part[2][l] + part[3][l]] = j0 + l;
+  if (w == 0 && j0 + l < T) {
+    int rank = 0;
+#pragma unroll
+    for (int x = 0; x < NW; ++x) rank += part[x][l];
+    order[(size_t)bh * T + rank] = j0 + l;
+  }
   if (n_h == 0) return;
   // rows of the critical blocks: wave w writes those of the row tiles it voted
   int32_t* out = rows + (size_t)bh * T * n_h;
   int pos = cptr[l];   // where the rows of the next row tile go
   for (int t = 0; t < Tw; ++t) {
     const unsigned long long m = crit[64 * t + l];
-    if ((t & 3) == w) {
+    if (t % NW == w) {
       const unsigned mlo = (unsigned)m, mhi = (unsigned)(m >> 32);
       auto column = [&](int c) {   // the wave writes column c's rows
         const unsigned lo = __builtin_amdgcn_readlane(mlo, c), hi = __builtin_amdgcn_readlane(mhi, c);

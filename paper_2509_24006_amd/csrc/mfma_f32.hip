@@ -268,7 +268,7 @@ __global__ __launch_bounds__(256, 2) void f32_states_kernel(const float* __restr
     const int Tw = (Tn + 63) / 64, first = BESIDE == 1 ? 2 * pool.wgs : Tw * pool.BH;
     if (j < first) {
       if constexpr (BESIDE == 1) pool_part<float, D>(pool, j);
-      else col_tables_part(smem, col, j % Tw, j / Tw);
+      else col_tables_part<4>(smem, col, j % Tw, j / Tw);
       return;
     }
     j -= first;
@@ -1037,7 +1037,7 @@ template <int D>
 hipError_t states_impl(const Shape& s, const FwdArgs& a, const Beside& b, hipStream_t st) {
   const int Tw = (s.T + 63) / 64;
   constexpr int tiles = 2 * FTile<D>::BYTES;
-  const int lds = b.col ? max(tiles, col_tables_lds(Tw)) : tiles;
+  const int lds = b.col ? max(tiles, col_tables_lds(Tw, 4)) : tiles;
   const int first = b.pool ? 2 * b.pool->wgs : b.col ? Tw * s.BH : 0;
   PoolArgs pool = {};
   if (b.pool) pool = *b.pool;

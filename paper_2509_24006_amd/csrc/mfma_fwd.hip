@@ -78,7 +78,7 @@ __global__ __launch_bounds__(256, 4) void states_mfma_kernel(const bf16* __restr
     const int Tw = (Tn + 63) / 64, first = BESIDE == 1 ? 2 * pool.wgs : Tw * (pool.BH);
     if (j < first) {
       if constexpr (BESIDE == 1) pool_part<bf16, D>(pool, j);
-      else col_tables_part(smem, col, j % Tw, j / Tw);
+      else col_tables_part<4>(smem, col, j % Tw, j / Tw);
       return;
     }
     j -= first;
@@ -597,7 +597,7 @@ __global__ void fill_zero_f32_kernel(float* __restrict__ p, size_t n) {
 
 template <int D>
 hipError_t states_impl(const Shape& s, const FwdArgs& a, bf16* hz16, bf16* WTp, const Beside& b, hipStream_t st) {
-  const int Tw = (s.T + 63) / 64, lds = b.col ? max(states_lds<D>(), col_tables_lds(Tw)) : states_lds<D>();
+  const int Tw = (s.T + 63) / 64, lds = b.col ? max(states_lds<D>(), col_tables_lds(Tw, 4)) : states_lds<D>();
   const int first = b.pool ? 2 * b.pool->wgs : b.col ? Tw * s.BH : 0;
   PoolArgs pool = {};
   if (b.pool) pool = *b.pool;

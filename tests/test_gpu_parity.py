@@ -409,6 +409,25 @@ def test_column_lists_short_and_long_in_one_tile(oracle, T, bq, hot, k_h):
                v["col_order"])
 
 
+@pytest.mark.parametrize("T,H,bq,hot,k_h", [(256, 3, 256, 23, 0.14), (257, 2, 256, 24, 0.24), (321, 2, 64, 22, 0.14),
+                                            (577, 2, 256, 10, 1.0), (1025, 2, 256, 24, 0.1), (1100, 15, 256, 23, 0.05)])
+def test_column_tables_by_four_eight_and_sixteen_waves(oracle, T, H, bq, hot, k_h):
+    # up to four row tiles, more of them, more than sixteen with few heads (15 heads of 18 tiles: eight waves)
+    from paper_2509_24006_amd import binding as sla
+    rng = np.random.default_rng(T + hot)
+    p = sla.make_params(1, H, T * 64, 64, k_h, 0.0, torch.bfloat16, bq=bq)
+    z = sla.sla_sizes(p)
+    s = rng.standard_normal((1, H, z.Tq, z.T)).astype(np.float32)
+    s[..., 3:3 + hot] += 8.0
+    ref = oracle.classify(s, *oracle.counts(z.T, k_h, 0.0))
+    Mc, luts = sla.sla_classify_scores(p, torch.from_numpy(s).cuda())
+    torch.cuda.synchronize()
+    assert np.array_equal(Mc.cpu().numpy(), ref)
+    v = {k: t.cpu().numpy() for k, t in sla.lut_views(p, luts).items()}
+    check_luts(per_tile(ref, bq // 64, z.T), v["row_idx"], v["col_ptr"], v["col_rows"], v["ind"], v["ind_t"],
+               v["col_order"])
+
+
 @pytest.mark.parametrize("bq,N", [(128, 130 * 64), (192, 130 * 64 - 40), (256, 33 * 64)])
 def test_classify_given_scores_with_ties_and_larger_query_blocks(oracle, bq, N):
     # rectangular score matrices (one row per block of bq queries), heavy ties; N is chosen so that
