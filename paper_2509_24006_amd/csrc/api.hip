@@ -12,7 +12,6 @@ using namespace sla;
 
 namespace {
 
-constexpr int kMaxT = 3072;  // classify keeps 4 rows of keys and labels in 64 KB of LDS
 
 int make_shape(const sla_params* p, Shape* s) {
   if (!p) return SLA_EINVAL;

@@ -97,50 +97,16 @@ __device__ __forceinline__ uint32_t order_key(float f) {
   return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
 }
 
-__device__ __forceinline__ int wave_sum(int v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-
-// k-th largest key of a row held in LDS (k >= 1), found bit by bit: the result is the
-// largest t with #{key >= t} >= k.  Entries whose key is 0 never count.
-__device__ uint32_t kth_largest(const uint32_t* keys, int T, int k, int lane) {
-  uint32_t prefix = 0;
-  for (int bit = 31; bit >= 0; --bit) {
-    const uint32_t cand = prefix | (1u << bit);
-    int c = 0;
-    for (int j = lane; j < T; j += 64) c += (keys[j] >= cand);
-    if (wave_sum(c) >= k) prefix = cand;
-  }
-  return prefix;
-}
-
-// Marks with `label` the k entries that come first under (key descending, index
-// ascending) among the entries with a non-zero key.
-__device__ void mark_top(const uint32_t* keys, int8_t* lab, int T, int k, int8_t label, int lane) {
-  if (k <= 0) return;
-  const uint32_t thr = kth_largest(keys, T, k, lane);
-  int c = 0;
-  for (int j = lane; j < T; j += 64) c += (keys[j] > thr);
-  int need = k - wave_sum(c);  // how many of the entries equal to thr are taken, lowest index first
-  for (int j0 = 0; j0 < T; j0 += 64) {
-    const int j = j0 + lane;
-    const uint32_t key = (j < T) ? keys[j] : 0u;
-    const bool eq = (j < T) && (key == thr);
-    const unsigned long long m = __ballot(eq);
-    const int before = __popcll(m & ((1ull << lane) - 1ull));
-    if (j < T && (key > thr || (eq && before < need))) lab[j] = label;
-    need -= __popcll(m);
-  }
-}
-
-// The same with the row in registers (entry j = 64 i + lane in slot i, key 0 past the end): every
+// Marks with `label` the k entries that come first under (key descending, index ascending) among
+// the entries with a non-zero key.  The threshold, the largest t with #{key >= t} >= k, is found bit
+// by bit, with the row in registers (entry j = 64 i + lane in slot i, key 0 past the end): every
 // count is a handful of wave votes tallied on the scalar side, no LDS and no cross-lane shuffles.
 // Bound by the issue of these tallies (two scalar instructions per slot and bit), so the search
 // ends as soon as exactly k keys reach the candidate: the lower bits of the threshold cannot
-// change which keys those are.  (40 heads x 1182 rows of 1182, with 19 slots a lane instead of 32:
-// 515 -> 237 us a launch; 12 x 512 of 512: 25 -> 20 us.)
+// change which keys those are, and the labels are one comparison a slot.  (40 heads x 1182 rows of
+// 1182, with 19 slots a lane instead of 32: 515 -> 237 us a launch, with the labels by one
+// comparison 221 -> 207; 12 x 512 of 512: 25 -> 20 -> 18.6 us.  Rows of more than 2048 entries in
+// LDS, with shuffles: 2 x 2500 360 -> 100 us, 8 x 3000 2550 -> 449.)
 template <int KPL>
 __device__ __forceinline__ void mark_top_reg(const uint32_t (&key)[KPL], int8_t (&lab)[KPL], int k, int8_t label,
                                              int lane) {
@@ -152,11 +118,16 @@ __device__ __forceinline__ void mark_top_reg(const uint32_t (&key)[KPL], int8_t 
 #pragma unroll
     for (int i = 0; i < KPL; ++i) c += __popcll(__ballot(key[i] >= cand));
     if (c >= k) thr = cand;
-    if (c == k) break;
+    if (c == k) {   // no entries equal to the threshold to choose among
+#pragma unroll
+      for (int i = 0; i < KPL; ++i) lab[i] = key[i] >= cand ? label : lab[i];
+      return;
+    }
   }
   int need = k;
 #pragma unroll
   for (int i = 0; i < KPL; ++i) need -= __popcll(__ballot(key[i] > thr));
+  asm volatile("" : "+s"(thr));   // compared anew: the votes above would be kept, two scalar registers a slot
 #pragma unroll
   for (int i = 0; i < KPL; ++i) {   // ascending index: slot by slot, lane by lane
     const bool eq = key[i] == thr;
@@ -202,49 +173,6 @@ __global__ __launch_bounds__(256) void classify_reg_kernel(const float* __restri
     if (j < T) Mc[(size_t)row * T + j] = lab[i];
     const unsigned long long m = __ballot(lab[i] == 1);
     if (lab[i] == 1) {
-      const int pos = base + __popcll(m & ((1ull << lane) - 1ull));
-      for (int r = 0; r < nrep; ++r) row_idx[(t0 + r) * n_h + pos] = j;
-    }
-    base += __popcll(m);
-  }
-}
-
-// One wavefront per row of the score matrix.
-__global__ __launch_bounds__(256) void classify_kernel(const float* __restrict__ s, int rows, int Tq, int rq, int T,
-                                                       int n_h, int n_l, int8_t* __restrict__ Mc,
-                                                       int32_t* __restrict__ row_idx,
-                                                       int32_t* __restrict__ col_cnt) {
-  extern __shared__ unsigned char smem[];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  uint32_t* keys = reinterpret_cast<uint32_t*>(smem) + (size_t)wave * T;
-  int8_t* lab = reinterpret_cast<int8_t*>(smem + (size_t)4 * T * sizeof(uint32_t)) + (size_t)wave * T;
-  const long row_raw = (long)blockIdx.x * 4 + wave;
-  const bool live = row_raw < rows;  // surplus wavefronts redo the last row and store nothing
-  const long row = live ? row_raw : rows - 1;
-  const size_t t0 = (size_t)(row / Tq) * T + (size_t)(row % Tq) * rq;   // first query tile of this row of the mask
-  const int nrep = min(rq, T - (int)(row % Tq) * rq);
-  if (live && lane < nrep) col_cnt[t0 + lane] = 0;   // cleared for the column count that follows
-  const float* sr = s + (size_t)row * T;
-  for (int j = lane; j < T; j += 64) {
-    keys[j] = order_key(sr[j]);
-    lab[j] = 0;
-  }
-  __syncthreads();
-  mark_top(keys, lab, T, n_h, (int8_t)1, lane);
-  __syncthreads();
-  // negligible: lowest scores among the rest = largest inverted keys; critical entries get
-  // key 0 and drop out
-  for (int j = lane; j < T; j += 64) keys[j] = (lab[j] == 1) ? 0u : ~keys[j];
-  __syncthreads();
-  mark_top(keys, lab, T, n_l, (int8_t)-1, lane);
-  __syncthreads();
-  int base = 0;
-  for (int j0 = 0; j0 < T; j0 += 64) {
-    const int j = j0 + lane;
-    const int8_t v = (j < T) ? lab[j] : (int8_t)0;
-    if (live && j < T) Mc[(size_t)row * T + j] = v;
-    const unsigned long long m = __ballot(v == 1);
-    if (live && v == 1) {
       const int pos = base + __popcll(m & ((1ull << lane) - 1ull));
       for (int r = 0; r < nrep; ++r) row_idx[(t0 + r) * n_h + pos] = j;
     }
@@ -460,25 +388,22 @@ hipError_t launch_scores(const float* qbar, const float* kbar, const Shape& s, f
 hipError_t launch_classify(const float* scores, const Shape& s, int8_t* Mc, int32_t* row_idx,
                            int32_t* col_cnt, hipStream_t st) {
   const int rows = s.BH * s.Tq;
-  const size_t lds = (size_t)4 * s.T * (sizeof(uint32_t) + 1);
   {
     KernelTimer kt("classify", st);
     const dim3 grid((rows + 3) / 4);
     // slots per lane as the row needs them (the kernel's time goes with the slots): the fewest
     // instances with which no row pays for more than a fifth more slots than it needs
     const int slots = (s.T + 63) / 64;
-    if (slots <= 32) {
-      auto kern = slots <= 2 ? classify_reg_kernel<2>
-                : slots <= 3 ? classify_reg_kernel<3> : slots <= 4 ? classify_reg_kernel<4>
-                : slots <= 6 ? classify_reg_kernel<6> : slots <= 8 ? classify_reg_kernel<8>
-                : slots <= 10 ? classify_reg_kernel<10> : slots <= 13 ? classify_reg_kernel<13>
-                : slots <= 16 ? classify_reg_kernel<16> : slots <= 19 ? classify_reg_kernel<19>
-                : slots <= 22 ? classify_reg_kernel<22> : slots <= 27 ? classify_reg_kernel<27>
-                : classify_reg_kernel<32>;
-      kern<<<grid, 256, 0, st>>>(scores, rows, s.Tq, s.rq, s.T, s.n_h, s.n_l, Mc, row_idx, col_cnt);
-    } else {
-      classify_kernel<<<grid, 256, lds, st>>>(scores, rows, s.Tq, s.rq, s.T, s.n_h, s.n_l, Mc, row_idx, col_cnt);
-    }
+    auto kern = slots <= 2 ? classify_reg_kernel<2>
+              : slots <= 3 ? classify_reg_kernel<3> : slots <= 4 ? classify_reg_kernel<4>
+              : slots <= 6 ? classify_reg_kernel<6> : slots <= 8 ? classify_reg_kernel<8>
+              : slots <= 10 ? classify_reg_kernel<10> : slots <= 13 ? classify_reg_kernel<13>
+              : slots <= 16 ? classify_reg_kernel<16> : slots <= 19 ? classify_reg_kernel<19>
+              : slots <= 22 ? classify_reg_kernel<22> : slots <= 27 ? classify_reg_kernel<27>
+              : slots <= 32 ? classify_reg_kernel<32> : slots <= 39 ? classify_reg_kernel<39>
+              : classify_reg_kernel<48>;
+    static_assert(kMaxT <= 48 * 64);
+    kern<<<grid, 256, 0, st>>>(scores, rows, s.Tq, s.rq, s.T, s.n_h, s.n_l, Mc, row_idx, col_cnt);
   }
   return hipGetLastError();
 }

@@ -15,6 +15,7 @@
 namespace sla {
 
 constexpr int kBlk = 64;  // tile of every kernel: b_kv, and b_q or the unit b_q is a multiple of (Section 6.1)
+constexpr int kMaxT = 3072;  // longest sequence in blocks: classification keeps 48 entries of a row per lane
 
 // Where the caller's Q, K, V, O, dO, dQ, dK, dV keep token n of head bh = b H + h: element
 // offset head(bh) + n ts.  [B,H,N,d]: ts = d; [B,N,H,d]: ts = H d.  (Everything the library

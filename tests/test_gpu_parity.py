@@ -410,9 +410,11 @@ def test_column_lists_short_and_long_in_one_tile(oracle, T, bq, hot, k_h):
 
 
 @pytest.mark.parametrize("T,H,bq,hot,k_h", [(256, 3, 256, 23, 0.14), (257, 2, 256, 24, 0.24), (321, 2, 64, 22, 0.14),
-                                            (577, 2, 256, 10, 1.0), (1025, 2, 256, 24, 0.1), (1100, 15, 256, 23, 0.05)])
+                                            (577, 2, 256, 10, 1.0), (1025, 2, 256, 24, 0.1), (1100, 15, 256, 23, 0.05),
+                                            (2496, 1, 256, 24, 0.03), (2497, 1, 256, 24, 0.03)])
 def test_column_tables_by_four_eight_and_sixteen_waves(oracle, T, H, bq, hot, k_h):
-    # up to four row tiles, more of them, more than sixteen with few heads (15 heads of 18 tiles: eight waves)
+    # up to four row tiles, more of them, more than sixteen with few heads (15 heads of 18 tiles: eight waves);
+    # the last two: classification with 39 and 48 entries of a row per lane
     from paper_2509_24006_amd import binding as sla
     rng = np.random.default_rng(T + hot)
     p = sla.make_params(1, H, T * 64, 64, k_h, 0.0, torch.bfloat16, bq=bq)
