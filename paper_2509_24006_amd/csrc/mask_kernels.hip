@@ -22,7 +22,11 @@ __global__ __launch_bounds__(256) void pool_kernel(PoolArgs a) {
 // chunks of 64 and read four at a time; each output keeps one fused multiply-add chain in
 // ascending feature order.
 // acc[a][b] = sum over features (ascending, one fused multiply-add chain) of
-// qb[i0 + ty + 16 a][.] kb[j0 + tx + 16 b][.]; rows past Tq / T count as zeros.
+// qb[i0 + ty + 16 a][.] kb[j0 + tx + 16 b][.]; past Tq / T the last row counts again (a select
+// between a row and zeros went through scratch memory).  A chunk is on its way while the one before
+// it is multiplied.  (Chunks one after the other through that select -> now, us a launch: 12 heads x 73 x 146
+// scores 8.3 -> 7.0, 40 x 1182 x 1182 236 -> 203; the same in the mask kernel of short sequences, 2 x 18, 12.6 ->
+// 10.7; d = 128.)
 template <int R>
 __device__ __forceinline__ void score_tile(const float* __restrict__ qb, const float* __restrict__ kb, int Tq, int T,
                                            int d, int i0, int j0, float (*qs)[68], float (*ks)[68],
@@ -32,18 +36,26 @@ __device__ __forceinline__ void score_tile(const float* __restrict__ qb, const f
   for (int a = 0; a < R; ++a)
 #pragma unroll
     for (int b = 0; b < R; ++b) acc[a][b] = 0.0f;
-  for (int k0 = 0; k0 < d; k0 += 64) {
-    // thread t brings 16 bytes: piece t % 16 of rows t / 16 + 16 q (d is a multiple of 64)
+  // thread t brings 16 bytes: piece t % 16 of rows t / 16 + 16 q (d is a multiple of 64)
+  const int c = 4 * tx;
+  typedef float f4 __attribute__((ext_vector_type(4)));
+  f4 qn[R], kn[R];
+  auto fetch = [&](int k0) {
 #pragma unroll
     for (int q = 0; q < R; ++q) {
-      const int r = (tid >> 4) + 16 * q, c = 4 * (tid & 15);
-      const float4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
-      *reinterpret_cast<float4*>(&qs[r][c]) =
-          (i0 + r < Tq) ? *reinterpret_cast<const float4*>(qb + (size_t)(i0 + r) * d + k0 + c) : zero;
-      *reinterpret_cast<float4*>(&ks[r][c]) =
-          (j0 + r < T) ? *reinterpret_cast<const float4*>(kb + (size_t)(j0 + r) * d + k0 + c) : zero;
+      qn[q] = *reinterpret_cast<const f4*>(qb + (size_t)min(i0 + ty + 16 * q, Tq - 1) * d + k0 + c);
+      kn[q] = *reinterpret_cast<const f4*>(kb + (size_t)min(j0 + ty + 16 * q, T - 1) * d + k0 + c);
+    }
+  };
+  fetch(0);
+  for (int k0 = 0; k0 < d; k0 += 64) {
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+      *reinterpret_cast<f4*>(&qs[ty + 16 * q][c]) = qn[q];
+      *reinterpret_cast<f4*>(&ks[ty + 16 * q][c]) = kn[q];
     }
     __syncthreads();
+    if (k0 + 64 < d) fetch(k0 + 64);
 #pragma unroll 4
     for (int k = 0; k < 64; k += 4) {
       float4 av[R], bv[R];
@@ -256,11 +268,17 @@ __global__ __launch_bounds__(64 * kSmallWaves) void mask_small_kernel(
     for (int a = 0; a < TT; ++a)
 #pragma unroll
       for (int b = 0; b < TT; ++b) acc[a][b] = 0.0f;
+    const float* qr = qb + (size_t)min(lr, Tq - 1) * d + lc;
+    const float* kr = kb + (size_t)min(lr, T - 1) * d + lc;
+    float4 qn = *reinterpret_cast<const float4*>(qr), kn = *reinterpret_cast<const float4*>(kr);
     for (int k0 = 0; k0 < d; k0 += 64) {
-      const float4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
-      *reinterpret_cast<float4*>(&qs[lr][lc]) = lr < Tq ? *reinterpret_cast<const float4*>(qb + (size_t)lr * d + k0 + lc) : zero;
-      *reinterpret_cast<float4*>(&ks[lr][lc]) = lr < T ? *reinterpret_cast<const float4*>(kb + (size_t)lr * d + k0 + lc) : zero;
+      *reinterpret_cast<float4*>(&qs[lr][lc]) = qn;
+      *reinterpret_cast<float4*>(&ks[lr][lc]) = kn;
       __syncthreads();
+      if (k0 + 64 < d) {
+        qn = *reinterpret_cast<const float4*>(qr + k0 + 64);
+        kn = *reinterpret_cast<const float4*>(kr + k0 + 64);
+      }
 #pragma unroll 4
       for (int k = 0; k < 64; k += 4) {
         float4 av[TT], bv[TT];
@@ -374,7 +392,7 @@ hipError_t launch_pool(const PoolArgs& a, const Shape& s, hipStream_t st) {
 hipError_t launch_scores(const float* qbar, const float* kbar, const Shape& s, float* scores,
                          hipStream_t st) {
   // Tiles of 64 x 64 scores read half as much from LDS per product as those of 32 x 32, but up to two of them
-  // per CU leave most of the chip idle.  (Tiles of 64 -> 32, us: 12 heads x 73 x 146 scores, 72 tiles of 64,
+  // per CU leave most of the chip idle.  (Tiles of 64 -> 32, us, before chunks were fetched ahead: 12 heads x 73 x 146 scores, 72 tiles of 64,
   // 13.6 -> 8.4; 4 x 122 x 122, 16 tiles, 13.3 -> 8.3; 24 x 250 x 250, d = 64, 384 tiles, 11.1 -> 10.6;
   // 12 x 512 x 512, 768 tiles, 20.2 -> 22.9; 40 x 1182 x 1182 235 -> 297.)
   const bool wide = (s.T + 63) / 64 * ((s.Tq + 63) / 64) * s.BH > 512;
