@@ -47,16 +47,16 @@ hipError_t backward_bf16(const Shape& s, const BwdArgs& a, hipStream_t st) {
 
 }  // namespace
 
-// Whether and into what the column lists are cut.  They are very uneven (on video-like inputs the longest holds
-// four to thirty times the average), and where a workgroup slot of the chip has few entries the launch lasts as
-// long as the longest list.  A cut list costs float sums out and back and a launch that adds them.  So a
-// piece lasts about as long as a slot's share of everything (a key block's fixed cost is that of four entries;
-// with floats, where an entry takes several times as long, it does not count), and nothing is cut where a third of
-// the longest list there can be, T, is shorter than a piece, nor above 256 blocks: there all but a handful of
-// heads are balanced as they are (16 x 387 of 19, d = 128, whole -> pieces of a quarter: 644 -> 679; 12 x 512 of 26
-// 776 -> 813), and a head's gradients stay the same bits with any number of heads in the call.  Below, the rounding of dK and dV
-// follows the pieces and so the number of heads; a rule by T alone would cost many heads more than it gives few
-// (pieces of a third, 64 x 254 of 10, d = 64: 585 -> 623; 256 x 42 of 5 241 -> 271).  (Key side with the adding launch, whole ->
+// Whether and into what the column lists are cut.  They are very uneven (on video-like inputs the longest holds four
+// to thirty times the average), and where a workgroup slot of the chip has few entries the launch lasts as long as
+// the longest list.  A cut list costs float sums out and back and a launch that adds them.  So a piece lasts about
+// as long as a slot's share of everything (a key block's fixed cost is that of four entries; with floats, where an
+// entry takes several times as long, it does not count), and nothing is cut where a third of the longest list there
+// can be, T, is shorter than a piece, nor above 256 blocks: there all but a handful of heads are balanced as they
+// are (16 x 387 of 19, d = 128, whole -> pieces of a quarter: 644 -> 679; 12 x 512 of 26 776 -> 813), and a head's
+// gradients stay the same bits with any number of heads in the call.  Below, the rounding of dK and dV follows the
+// pieces and so the number of heads; a rule by T alone would cost many heads more than it gives few (pieces of a
+// third, 64 x 254 of 10, d = 64: 585 -> 623; 256 x 42 of 5 241 -> 271).  (Key side with the adding launch, whole ->
 // cut, us: 12 x 146 of 7, d = 128, 139 -> 113; 14 x 68 of 2 80 -> 51; 8 x 254 of 10, d = 64, 107 -> 78; 8 x 42 of 7
 // 42 -> 30; where the lists happen to be short, 16 x 58 of 2, d = 128, at most 21: 41 -> 48.  Floats: 4 x 122 of 6,
 // d = 128, 175 -> 157; 2 x 122 of 12 201 -> 152; 8 x 122 of 6, d = 64, 228 -> 139; 16 x 63 of 5 157 -> 125.)

@@ -267,6 +267,27 @@ def test_column_lists_cut_into_pieces(oracle, dtype, T, d, H, phi, bq, k_l):
     assert all(np.array_equal(first[n], again[n]) for n in ("dQ", "dK", "dV", "dW"))
 
 
+def test_a_head_alone_above_the_longest_cut_lists():
+    # from 257 blocks on nothing is cut: one head gives the bits that it gives among twenty
+    from paper_2509_24006_amd import binding as sla
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1)
+    N, d = 257 * 64 - 5, 64
+    x = [torch.randn(1, 20, N, d, generator=g, device="cuda").bfloat16() for _ in range(4)]
+    x[1][:, :, 640:704] += 0.5   # a long list
+    W = (0.02 * torch.randn(d, d, generator=g, device="cuda")).bfloat16()
+
+    def grads(H):
+        Q, K, V, dO = (t[:, :H].contiguous() for t in x)
+        p = sla.make_params(1, H, N, d, 0.02, 0.1, torch.bfloat16)
+        Mc, luts, _ = sla.sla_build_mask(p, Q, K)
+        O, saved = sla.sla_forward(p, Q, K, V, W, Mc, luts)
+        return sla.sla_backward(p, Q, K, V, W, Mc, luts, saved, dO)[:3]
+
+    for a, b in zip(grads(1), grads(20)):
+        assert torch.equal(a[:, 0], b[:, 0])
+
+
 @pytest.mark.parametrize("name", ["small_bf16", "small_bf16_d64", "small_fp32"])
 def test_token_major_tensors(oracle, name):
     # [B,N,H,d] tensors: the same kernels walk the same values with another row pitch, so every
