@@ -764,7 +764,11 @@ __device__ __forceinline__ void phi_fragments(const bf16x8 (&xf)[KT], int phi, b
 }
 
 // phi without the softmax map's normaliser (the exponentials relative to the token's maximum): enough
-// where phi enters numerator and denominator of the same quotient.
+// where phi enters numerator and denominator of the same quotient.  The exponent is one fused multiply-add, whose
+// rounded second term, mx log2(e), puts the same factor before every feature: 2^(half a unit in its last place),
+// at most 2^(1/16) up to kRawMax.  It cancels in the quotient, but grows with mx (from 2^31 on it is infinite), so
+// larger maxima, and those that are not finite, take the form above.
+constexpr float kRawMax = 1048576.0f;
 template <int KT>
 __device__ __forceinline__ void phi_fragments_raw(const bf16x8 (&xf)[KT], int phi, bf16x8 (&out)[KT]) {
   if (phi != 0) {
@@ -778,7 +782,7 @@ __device__ __forceinline__ void phi_fragments_raw(const bf16x8 (&xf)[KT], int ph
 #pragma unroll
     for (int s = 0; s < 8; ++s) mx = fmaxf(mx, (float)xf[t][s]);
   mx = half_max(mx);
-  if (__any(!(fabsf(mx) <= 1e38f))) {   // (the product below would overflow)
+  if (__any(!(fabsf(mx) <= kRawMax))) {
     float inv;
     phi_fragments<KT>(xf, phi, out, mx, inv);
     return;

@@ -145,6 +145,29 @@ def test_small_and_large_score_magnitudes(oracle, name, scale, backward):
     _full_case(oracle, x, w.dtype, w.k_h, w.k_l, backward=backward)
 
 
+@pytest.mark.parametrize("mag", [1.0e6, 1.1e6, 3.0e9, 1.0e10, 1.0e20, 1.0e30])
+@pytest.mark.parametrize("d", [64, 128])
+def test_tokens_with_very_large_features(oracle, wide_tiles, d, mag):
+    # phi(Q) is formed relative to the token's largest feature, whatever its size (several features share it here);
+    # K is as small as the scores need to stay of order one.  Both sides of the size up to which the exponent
+    # is one fused multiply-add.
+    rng = np.random.default_rng(int(np.log2(mag)) + d)
+    N = 5 * 64 + 9
+    x = {k: rng.standard_normal((1, 2, N, d)).astype(np.float32) for k in ("Q", "K", "V")}
+    for sign, first in ((1.0, 0), (-1.0, 1)):
+        big = x["Q"][:, :, first::3]
+        x["Q"][:, :, first::3] = sign * mag * (1.0 + 0.01 * big)
+    x["K"] *= 0.5 / mag
+    x["Proj"] = (rng.standard_normal((d, d)) * 0.05).astype(np.float32)
+    x = {k: wl.round_to_bf16(v) for k, v in x.items()}
+    Mc, _, f, _ = _oracle_all(oracle, x, 0.4, 0.0, backward=False, bq=128)
+    r = run_gpu(x, "bf16", 0.4, 0.0, backward=False, bq=128)
+    assert np.array_equal(r["Mc"], Mc)
+    for k in ("O", "Os", "Ol"):
+        assert np.isfinite(r[k]).all(), k
+        _compare(k, r[k], f[k], TOL["bf16"], block_tol=BLOCK_TOL["bf16"])
+
+
 @pytest.mark.parametrize("N", [1, 63, 64, 65, 130])
 def test_short_sequences(oracle, N):
     rng = np.random.default_rng(N)
