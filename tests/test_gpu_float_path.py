@@ -2,7 +2,8 @@
 import numpy as np
 import pytest
 
-from tests.gpu_util import run_gpu
+from tests import pins
+from tests.gpu_util import TOL, run_gpu
 from tests.test_gpu_parity import _full_case
 
 pytestmark = pytest.mark.gpu
@@ -95,3 +96,27 @@ def test_state_sums_of_many_short_heads(T, d):
         fin = torch.isfinite(b)
         assert torch.equal(torch.isfinite(a), fin) and (n == "Zi" or not bool(fin.all()))
         assert bool(((a - b).abs()[fin] <= 2 * T * 2.0 ** -24 * m[fin]).all())
+
+
+@pytest.mark.parametrize("T,d", [(257, 64), (300, 128), (380, 64)])
+def test_key_side_of_one_and_two_heads_above_256_blocks(oracle, T, d):
+    # fewer than 768 blocks in all, whole lists: a quarter of a key block per workgroup with one head and with two,
+    # so a head's gradients are the same bits in both; against the oracle
+    import torch
+    from paper_2509_24006_amd import binding as sla
+    rng = np.random.default_rng(T)
+    N = T * 64 - 21
+    x = {k: rng.standard_normal((1, 2, N, d)).astype(np.float32) for k in ("Q", "K", "V", "dO")}
+    x["K"][:, :, 640:704] += 0.4   # a longer list
+    x["Q"] += 0.2
+    x["Proj"] = (rng.standard_normal((d, d)) * 0.05).astype(np.float32)
+    two = run_gpu(x, "fp32", 0.01, 0.3)
+    x1 = {k: v[:, :1] if v.ndim == 4 else v for k, v in x.items()}
+    one = run_gpu(x1, "fp32", 0.01, 0.3)
+    for k in ("dK", "dV"):
+        assert np.array_equal(one[k], two[k][:, :1]), k
+    if T == 300:
+        f = oracle.forward(x1["Q"], x1["K"], x1["V"], x1["Proj"], one["Mc"])
+        g = oracle.backward(x1["Q"], x1["K"], x1["V"], x1["Proj"], one["Mc"], f, x1["dO"])
+        for k in ("dQ", "dK", "dV", "dW"):
+            assert pins.rel_l2(one[k], g[k]) <= TOL["fp32"], k
