@@ -60,14 +60,29 @@ hipError_t backward_bf16(const Shape& s, const BwdArgs& a, hipStream_t st) {
 // cut, us: 12 x 146 of 7, d = 128, 139 -> 113; 14 x 68 of 2 80 -> 51; 8 x 254 of 10, d = 64, 107 -> 78; 8 x 42 of 7
 // 42 -> 30; where the lists happen to be short, 16 x 58 of 2, d = 128, at most 21: 41 -> 48.  Floats: 4 x 122 of 6,
 // d = 128, 175 -> 157; 2 x 122 of 12 201 -> 152; 8 x 122 of 6, d = 64, 228 -> 139; 16 x 63 of 5 157 -> 125.)
-KvSplit kv_split(const Shape& s) {
+namespace {
+KvSplit split_for(const Shape& s, int parts) {   // parts: workgroups per key block
   const bool f32 = s.dtype == 0;
   const long long slots = s.d == 64 && !f32 ? 768 : 512;
-  const long long cols = (long long)s.BH * s.T * (!f32 ? 1 : f32_key_quarters(s) ? 4 : 2);
+  const long long cols = (long long)s.BH * s.T * parts;
   long long piece = (cols * s.n_h + slots - 1) / slots + (f32 ? 0 : 4 * cols / slots);
   piece = piece < 12 ? 12 : piece;
   if (s.n_h == 0 || s.T > 256 || 3 * piece > s.T) return KvSplit{0x7fffffff, 0, nullptr, nullptr};
   return KvSplit{(int)piece, (int)((long long)s.T * s.n_h / piece), nullptr, nullptr};
+}
+}  // namespace
+KvSplit kv_split(const Shape& s) { return split_for(s, s.dtype != 0 ? 1 : f32_key_quarters(s) ? 4 : 2); }
+
+// Quarters fill the chip where there are few blocks; with more the tiles that they fetch cost more.  Where the long
+// lists are cut the line is lower, as the longest list no longer sets the length of the launch.
+// (Key side with the adding launch, quarters -> halves, us.  Lists cut: 3 heads x 64 blocks, d = 64, 50 -> 72;
+// 2 x 122 of 12, d = 128, 152 -> 160; 4 x 122 of 6 169 -> 157; 12 x 63 of 6 252 -> 236; the number of blocks does
+// not separate them all: 1 x 127 of 19, below the line, 141 -> 129.  Whole lists: 1 x 500 of 25, d = 128, 622 -> 986;
+// 2 x 300 of 15 519 -> 801; 1 x 625 of 31, d = 64, 477 -> 706; too dense to cut, d = 64, 3 x 160 of 32
+// 310 -> 430, 8 x 48 of 14 124 -> 160, too short, 24 x 30 of 3 71 -> 82; 4 x 122 of 24, d = 128, 484 -> 523.)
+bool f32_key_quarters(const Shape& s) {
+  const int blocks = s.BH * s.T;
+  return blocks < 384 || (blocks < 768 && split_for(s, 2).ecap == 0);
 }
 
 size_t backward_ws_bytes(const Shape& s) { return carve_bwd(s, nullptr).bytes; }

@@ -141,13 +141,7 @@ hipError_t mfma_backward_sparse(const Shape& s, const BwdArgs& a, const float* D
 // the float path's backward pass; the workspace pieces are carved by backward()
 hipError_t f32_backward(const Shape& s, const BwdArgs& a, float* Ds, float* dHZ, float* dHZcol, float* dWpart,
                         int nparts, const KvSplit& kv, hipStream_t st);
-// Whether a workgroup of its key side owns a quarter of a key block, or half of one.  Quarters fill the chip where
-// there are few blocks; with more the tiles that they fetch cost more.  Where long lists are cut (kv_split, up to 256
-// blocks a head) the line is lower, as the longest list no longer sets the length of the launch.
-// (Key side with the adding launch, quarters -> halves, us: 3 heads x 64 blocks, d = 64, 50 -> 72; 2 x 122 of 12,
-// d = 128, 152 -> 160; 4 x 122 of 6 169 -> 157; 12 x 63 of 6 252 -> 236; 1 x 127 of 19, below the line, 141 -> 129.
-// Whole lists: 1 x 500 of 25, d = 128, 622 -> 986; 2 x 300 of 15 519 -> 801; 1 x 625 of 31, d = 64, 477 -> 706.)
-inline bool f32_key_quarters(const Shape& s) { return s.BH * s.T < (s.T <= 256 ? 384 : 768); }
+bool f32_key_quarters(const Shape& s);   // whether a workgroup of its key side owns a quarter of a key block, or half of one (backward.hip)
 hipError_t backward(const Shape& s, const BwdArgs& a, hipStream_t st);
 
 // ---- bf16 matrix-core path (mfma_fwd.hip)
