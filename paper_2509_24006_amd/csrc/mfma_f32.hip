@@ -414,29 +414,29 @@ __global__ __launch_bounds__(256) void f32_aggregate_kernel(const float* __restr
 }
 
 // The same for the shortest sequences, where the matrix form's 32 states and 32 rows are nearly all
-// padding: a thread owns four columns, holds them of every state and writes the sums of every row, so
+// padding: a thread owns V columns, holds them of every state and writes the sums of every row, so
 // that the states are read once and nothing but the traffic is left.  (One block, d = 64: 256 heads
 // 31.9 -> 6.6 us a launch, 4096 heads 396 -> 24.6; four blocks, 256 heads, d = 128: 103 -> 23.)
-template <int kFew>
+template <int kFew, int V>
 __global__ __launch_bounds__(256) void f32_aggregate_few_kernel(const float* __restrict__ in,
                                                                 const unsigned long long* __restrict__ ind, int T,
                                                                 int row_len, float* __restrict__ out) {
-  const int c = 4 * (blockIdx.x * 256 + threadIdx.x), bh = blockIdx.y;
+  typedef float vec __attribute__((ext_vector_type(V)));
+  const int c = V * (blockIdx.x * 256 + threadIdx.x), bh = blockIdx.y;
   if (c >= row_len) return;   // (row_len is a multiple of 4)
   const size_t o = (size_t)bh * T * row_len + c;
-  f32x4 x[kFew];
+  vec x[kFew];
 #pragma unroll
-  for (int k = 0; k < kFew; ++k)
-    x[k] = k < T ? *reinterpret_cast<const f32x4*>(in + o + (size_t)k * row_len) : zero4();
+  for (int k = 0; k < kFew; ++k) x[k] = k < T ? *reinterpret_cast<const vec*>(in + o + (size_t)k * row_len) : vec(0.0f);
 #pragma unroll
   for (int i = 0; i < kFew; ++i) {
     if (i >= T) break;
     const unsigned bits = (unsigned)ind[(size_t)bh * T + i];   // (one word a row; no bits past T)
-    f32x4 s = zero4();
+    vec s = vec(0.0f);
 #pragma unroll
     for (int k = 0; k < kFew; ++k)
       if ((bits >> k) & 1u) s += x[k];
-    *reinterpret_cast<f32x4*>(out + o + (size_t)i * row_len) = s;
+    *reinterpret_cast<vec*>(out + o + (size_t)i * row_len) = s;
   }
 }
 
@@ -1017,12 +1017,16 @@ hipError_t f32_aggregate(const float* in, const unsigned long long* ind, const S
   const int row_len = s.state_row(), Tw = (s.T + 63) / 64;
   const int gx = (row_len / 32 + 3) / 4;
   KernelTimer kt("aggregate", st);
-  // From five blocks on the matrix form takes less with few heads (eight blocks, d = 64, 16 heads: 6.4 us against
-  // 8.0 with the short form); with many, up to eight blocks, the short form runs at the memory's rate (five
-  // blocks, 256 heads, d = 128: 63 against 28 us; eight, 512 heads, d = 64: 39 against 23).
-  if (s.T <= 4 || (s.T <= 8 && s.BH >= 128)) {
-    auto few = s.T <= 4 ? f32_aggregate_few_kernel<4> : f32_aggregate_few_kernel<8>;
-    few<<<dim3((row_len / 4 + 255) / 256, s.BH), 256, 0, st>>>(in, ind, s.T, row_len, out);
+  // Up to eight blocks the short form, whatever the number of heads, which must not change a head's sums.  With many it
+  // runs at the memory's rate (matrix -> short form, us: five blocks, 256 heads, d = 128, 63 -> 28; eight, 512 heads,
+  // d = 64, 39 -> 23); with few it has one column a thread, as four leave most CUs without a workgroup
+  // (16 heads x 8, d = 64, matrix 6.6, four columns 8.0, one 6.6; matrix -> one column: 16 x 5, d = 128, 10.0 -> 7.5,
+  // 40 x 8 14.7 -> 11.3).
+  if (s.T <= 8) {
+    const bool one = s.T > 4 && (long long)s.BH * row_len < 512 * 1024;
+    auto few = s.T <= 4 ? f32_aggregate_few_kernel<4, 4> : one ? f32_aggregate_few_kernel<8, 1> : f32_aggregate_few_kernel<8, 4>;
+    const int columns = one ? 256 : 1024;
+    few<<<dim3((row_len + columns - 1) / columns, s.BH), 256, 0, st>>>(in, ind, s.T, row_len, out);
     return hipGetLastError();
   }
   // up to 128 rows per wave (the states are read ceil(T / 128) times), in tiles of 32 dealt evenly
