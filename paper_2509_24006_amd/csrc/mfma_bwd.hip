@@ -41,7 +41,7 @@ struct KvLds {
 // this lane's place in a slot of kv.part: per wave 8 HT pieces of 16 bytes a lane, dV^T then dK^T
 template <int D>
 __device__ __forceinline__ f32x4* kv_slot(const KvSplit& kv, int bh, int slot, int w, int l) {
-  return reinterpret_cast<f32x4*>(kv.part + ((size_t)bh * 2 * kv.ecap + slot) * (2 * kBlk * D)) + w * (D / 8 * 64) + l;
+  return reinterpret_cast<f32x4*>(kv.part + ((size_t)bh * (kv.ecap + kv.cuts) + slot) * (2 * kBlk * D)) + w * (D / 8 * 64) + l;
 }
 // this wave's quarter of dK_j, dV_j (accumulators as the loop leaves them) leaves as whole rows
 template <int D>
@@ -55,7 +55,8 @@ __device__ __forceinline__ void store_kv(unsigned char* stage, const f32x16 (&dv
   store_rows_bf16<D / 64>(stage, dkT, dK + o0, ts, rows, l);
 }
 
-template <int D, int PHI>
+// FOLD: a workgroup walks all pieces of a list (kv.ecap = 0).
+template <int D, int PHI, bool FOLD>
 __global__ __launch_bounds__(256, 2) void bwd_dkdv_mfma_kernel(
     const bf16* __restrict__ Q, const bf16* __restrict__ K, const bf16* __restrict__ V,
     const bf16* __restrict__ dO, const float* __restrict__ L, const float* __restrict__ Ds,
@@ -113,7 +114,7 @@ __global__ __launch_bounds__(256, 2) void bwd_dkdv_mfma_kernel(
   }
   int j, beg, cnt, slot = -1;
   if (kv.ecap > 0) {
-    const int4 unit = kv.units[(size_t)bh * (2 * kv.ecap + Tn) + place];
+    const int4 unit = kv.units[(size_t)bh * (kv.ecap + Tn + kv.cuts) + place];
     j = unit.x;
     beg = unit.y;
     cnt = unit.z;
@@ -125,7 +126,7 @@ __global__ __launch_bounds__(256, 2) void bwd_dkdv_mfma_kernel(
     cnt = ptr[j + 1] - beg;
   }
   if (index < 0 && cnt == 0) return;
-  const bf16* dHcol = index < 0 ? nullptr : dHcol_all;   // (the linear branch goes with the rest of a list)
+  const bf16* dHcol = index < 0 ? nullptr : dHcol_all;   // (the linear branch goes with the first piece of a list)
   const int k0 = j * kBlk, cols = min(kBlk, N - k0);
   const int krow = kh * 32 + ln;
   const bool kok = krow < cols;
@@ -398,15 +399,30 @@ __global__ __launch_bounds__(256, 2) void bwd_dkdv_mfma_kernel(
       sched_fence();
     }
   };
-  for (int s = 0; s < cnt; s += 2) {
-    step(s, 0);
-    if (s + 1 < cnt) step(s + 1, 1);
-  }
-  // ---- each wave owns keys 32 kh .., features (D / 2) x .. of dK_j and dV_j: whole-row stores
-  // through its own staging area
-  wait_vm0_known();        // the last step's surplus request has landed
-  if (slot >= 0) {   // part of a cut list: the sums as they lie in the registers
-    f32x4* o = kv_slot<D>(kv, bh, slot, w, l);
+  // a long list that is not shared out: the sums of its pieces (of an even number of entries) meet in the list's slot
+  const int fold = FOLD ? kv.piece : cnt;
+  auto slot_at = [&](int slot_) __attribute__((always_inline)) {
+    slot_ = wave_uniform(slot_);
+    asm volatile("" : "+s"(slot_));   // (formed where it is used, or the address takes up registers in the loop)
+    return kv_slot<D>(kv, bh, slot_, w, lane_id());
+  };
+  auto add_slot = [&]() __attribute__((always_inline)) {
+    const f32x4* o = slot_at(place);
+#pragma unroll
+    for (int dt = 0; dt < HT; ++dt)
+#pragma unroll
+      for (int r4 = 0; r4 < 4; ++r4) {
+        const f32x4 v = o[(4 * dt + r4) * 64], k = o[(4 * (HT + dt) + r4) * 64];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          dvT[dt][4 * r4 + r] += v[r];
+          dkT[dt][4 * r4 + r] += k[r];
+        }
+        if (r4 % 2) sched_fence();   // (16 registers of the slot at a time: all at once spilled)
+      }
+  };
+  auto store_slot = [&](int slot_) __attribute__((always_inline)) {   // the sums as they lie in the registers
+    f32x4* o = slot_at(slot_);
 #pragma unroll
     for (int dt = 0; dt < HT; ++dt)
 #pragma unroll
@@ -414,28 +430,50 @@ __global__ __launch_bounds__(256, 2) void bwd_dkdv_mfma_kernel(
         o[(4 * dt + r4) * 64] = f32x4{dvT[dt][4 * r4], dvT[dt][4 * r4 + 1], dvT[dt][4 * r4 + 2], dvT[dt][4 * r4 + 3]};
         o[(4 * (HT + dt) + r4) * 64] = f32x4{dkT[dt][4 * r4], dkT[dt][4 * r4 + 1], dkT[dt][4 * r4 + 2], dkT[dt][4 * r4 + 3]};
       }
+  };
+  for (int s = 0;;) {
+    const int end = min(cnt - s, fold) + s;
+    for (; s < end; s += 2) {
+      step(s, 0);
+      if (s + 1 < cnt) step(s + 1, 1);
+    }
+    if (!FOLD || end == cnt) break;
+    if (end > fold) add_slot();
+    store_slot(place);
+#pragma unroll
+    for (int dt = 0; dt < HT; ++dt) {
+      dvT[dt] = zero_f32x16();
+      dkT[dt] = zero_f32x16();
+    }
+  }
+  // ---- each wave owns keys 32 kh .., features (D / 2) x .. of dK_j and dV_j: whole-row stores
+  // through its own staging area
+  wait_vm0_known();        // the last step's surplus request has landed
+  if (slot >= 0) {   // a piece of a list that is shared out
+    store_slot(slot);
     return;
   }
+  if (FOLD && cnt > fold) add_slot();
   __syncthreads();   // every wave is done with the tiles
   store_kv<D>(smem + wu * Lds::STG, dvT, dkT, scale, dV, dK,
               lay.head(bh) + (size_t)(k0 + 32 * kh) * lay.ts + (D / 2) * xh, lay.ts, cols - 32 * kh, l);
 }
 
-// dK_j, dV_j of the key blocks whose lists were cut: the sums of the rest and of the extras, in that order.
+// dK_j, dV_j of the key blocks whose lists were cut: the sums of the pieces in order.
 // Bound by its traffic (64 KB a slot at d = 128) and the launch.
 template <int D>
 __global__ __launch_bounds__(256) void kv_merge_kernel(KvSplit kv, int BH, int N, int Tn, Lay lay, float scale,
                                                        bf16* __restrict__ dK, bf16* __restrict__ dV) {
   constexpr int HT = D / 64;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  const int bh = blockIdx.x % BH, m = blockIdx.x / BH;
-  const int4 unit = kv.units[(size_t)bh * (2 * kv.ecap + Tn) + kv.ecap + Tn + m];
-  const int j = unit.x, first = unit.z, extras = unit.w;
+  const int bh = blockIdx.x % BH, r = blockIdx.x / BH;
+  const int4 unit = kv.units[(size_t)bh * (kv.ecap + Tn + kv.cuts) + kv.ecap + Tn + r];
+  const int j = unit.x, first = unit.y, extras = unit.z;
   if (extras == 0) return;
   const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, kh = w & 1, xh = w >> 1;
   constexpr int NQ = 2 * HT * 4;
   f32x4 s[NQ];
-  const f32x4* p = kv_slot<D>(kv, bh, unit.y, w, l);
+  const f32x4* p = kv_slot<D>(kv, bh, kv.ecap + r, w, l);
 #pragma unroll
   for (int q = 0; q < NQ; ++q) s[q] = p[q * 64];
   for (int e = 0; e < extras; e += 2) {   // (two in flight; past the end: the last again, not added)
@@ -479,10 +517,12 @@ hipError_t sparse_impl(const Shape& s, const BwdArgs& a, const float* Ds, const 
         dw);
     return hipSuccess;
   };
-  SLA_TRY(s.phi == 0 ? launch_kv(bwd_dkdv_mfma_kernel<D, 0>) : launch_kv(bwd_dkdv_mfma_kernel<D, 1>));
+  const bool fold = kv.cuts > 0 && kv.ecap == 0;
+  SLA_TRY(s.phi == 0 ? launch_kv(fold ? bwd_dkdv_mfma_kernel<D, 0, true> : bwd_dkdv_mfma_kernel<D, 0, false>)
+                     : launch_kv(fold ? bwd_dkdv_mfma_kernel<D, 1, true> : bwd_dkdv_mfma_kernel<D, 1, false>));
   if (kv.ecap > 0) {
     KernelTimer kt("kv_merge", st);
-    kv_merge_kernel<D><<<s.BH * kv.ecap, 256, 4 * KvLds<D>::STG, st>>>(kv, s.BH, s.N, s.T, s.lay(), s.scale, (bf16*)a.dK,
+    kv_merge_kernel<D><<<s.BH * kv.cuts, 256, 4 * KvLds<D>::STG, st>>>(kv, s.BH, s.N, s.T, s.lay(), s.scale, (bf16*)a.dK,
                                                                       (bf16*)a.dV);
   }
   return hipGetLastError();

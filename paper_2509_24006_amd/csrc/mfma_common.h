@@ -623,8 +623,8 @@ __device__ __forceinline__ void kv_plan(const KvPlanArgs& a, int T, int bh) {
   const int P = a.split.piece, ecap = a.split.ecap, l = threadIdx.x & 63;
   const int32_t* ptr = a.col_ptr + (size_t)bh * (T + 1);
   const int32_t* order = a.col_order + (size_t)bh * T;
-  int4* u = a.split.units + (size_t)bh * (2 * ecap + T);
-  int ebase = 0, mbase = 0;
+  int4* u = a.split.units + (size_t)bh * (ecap + T + a.split.cuts);
+  int base = 0, cuts = 0;
   for (int r0 = 0; r0 < T; r0 += 64) {
     const int r = r0 + l;
     int j = 0, beg = 0, cnt = 0;
@@ -633,25 +633,22 @@ __device__ __forceinline__ void kv_plan(const KvPlanArgs& a, int T, int bh) {
       beg = ptr[j];
       cnt = ptr[j + 1] - beg;
     }
-    const int extra = cnt > P ? (cnt - 1) / P : 0, cut = extra > 0;
-    int e = extra, m = cut;   // sums up to this lane
+    const int extra = cnt > P ? (cnt - 1) / P : 0;
+    int e = extra;   // sum up to this lane
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
-      const int eo = __shfl_up(e, o), mo = __shfl_up(m, o);
-      if (l >= o) {
-        e += eo;
-        m += mo;
-      }
+      const int eo = __shfl_up(e, o);
+      if (l >= o) e += eo;
     }
-    const int first = ebase + e - extra, which = mbase + m - cut;   // slot of the first extra, which cut list
-    if (r < T) u[ecap + r] = int4{j, beg + extra * P, cnt - extra * P, cut ? ecap + which : -1};
-    for (int q = 0; q < extra; ++q) u[first + q] = int4{j, beg + q * P, P, first + q};
-    if (cut) u[ecap + T + which] = int4{j, ecap + which, first, extra};
-    ebase += __shfl(e, 63);
-    mbase += __shfl(m, 63);
+    const int first = base + e - extra;   // slot of the first extra
+    if (r < T) u[ecap + r] = int4{j, beg, min(cnt, P), extra ? ecap + r : -1};
+    for (int q = 0; q < extra; ++q) u[first + q] = int4{j, beg + (q + 1) * P, min(P, cnt - (q + 1) * P), first + q};
+    if (extra) u[ecap + T + r] = int4{j, first, extra, 0};
+    base += __shfl(e, 63);
+    cuts += __popcll(__ballot(extra > 0));
   }
-  for (int e = ebase + l; e < ecap; e += 64) u[e] = int4{0, 0, 0, 0};
-  for (int m = mbase + l; m < ecap; m += 64) u[ecap + T + m] = int4{0, 0, 0, 0};
+  for (int e = base + l; e < ecap; e += 64) u[e] = int4{0, 0, 0, 0};
+  for (int r = cuts + l; r < a.split.cuts; r += 64) u[ecap + T + r] = int4{0, 0, 0, 0};
 }
 
 // dW = sum of the partial d x d sums, elements [32 block, +32).  Bound by the latency of its loads (64

@@ -770,7 +770,7 @@ __global__ __launch_bounds__(256, 2) void f32_bwd_query_kernel(
 // LDS once, after the loop; each then finishes its share of the features.  Q and dO go through
 // one slot each; every load lands under a product that reads the other one.  Lists that would still outlast
 // the rest are cut: the first workgroups walk pieces of them and leave their sums as rows of a slot, which
-// f32_kv_merge_kernel adds to what the rest of the list gave.
+// f32_kv_merge_kernel adds to what the first piece of the list gave.
 template <int QW, int M>
 __device__ __forceinline__ void pick_tiles(const f32x4* x, int wq, f32x4 (&y)[M]) {
   // y[m] = x[wq + QW m] with wq uniform, without indexing registers
@@ -787,16 +787,16 @@ __device__ __forceinline__ void pick_tiles(const f32x4* x, int wq, f32x4 (&y)[M]
 // a slot: the 64 rows of dK, then those of dV
 template <int D>
 __device__ __forceinline__ float* f32_kv_slot(const KvSplit& kv, int bh, int slot) {
-  return kv.part + ((size_t)bh * 2 * kv.ecap + slot) * (2 * kBlk * D);
+  return kv.part + ((size_t)bh * (kv.ecap + kv.cuts) + slot) * (2 * kBlk * D);
 }
 // dK_j, dV_j of the key blocks whose lists were cut += the sums of the extras, in order; a workgroup per
 // 16 rows of the two
 template <int D>
 __global__ __launch_bounds__(256) void f32_kv_merge_kernel(KvSplit kv, int BH, int N, int Tn, Lay lay,
                                                            float* __restrict__ dK, float* __restrict__ dV) {
-  const int bh = blockIdx.x % BH, m = blockIdx.x / BH;
-  const int4 unit = kv.units[(size_t)bh * (2 * kv.ecap + Tn) + kv.ecap + Tn + m];
-  if (unit.w == 0) return;
+  const int bh = blockIdx.x % BH, r = blockIdx.x / BH;
+  const int4 unit = kv.units[(size_t)bh * (kv.ecap + Tn + kv.cuts) + kv.ecap + Tn + r];
+  if (unit.z == 0) return;
   constexpr int C = D / 4;   // 16-byte pieces of a row
   for (int i = blockIdx.y * 16 * C + threadIdx.x; i < (blockIdx.y + 1) * 16 * C; i += 256) {
     const int row = i / C, c = 4 * (i % C), key = unit.x * kBlk + row % kBlk;
@@ -804,8 +804,8 @@ __global__ __launch_bounds__(256) void f32_kv_merge_kernel(KvSplit kv, int BH, i
     float* o = (row < kBlk ? dK : dV) + lay.head(bh) + (size_t)key * lay.ts + c;
     f32x4 s = *reinterpret_cast<const f32x4*>(o);
 #pragma unroll 4
-    for (int e = 0; e < unit.w; ++e)
-      s += *reinterpret_cast<const f32x4*>(f32_kv_slot<D>(kv, bh, unit.z + e) + (size_t)row * D + c);
+    for (int e = 0; e < unit.z; ++e)
+      s += *reinterpret_cast<const f32x4*>(f32_kv_slot<D>(kv, bh, unit.y + e) + (size_t)row * D + c);
     *reinterpret_cast<f32x4*>(o) = s;
   }
 }
@@ -836,7 +836,7 @@ __global__ __launch_bounds__(256, 2) void f32_bwd_key_kernel(
   const int bh = blockIdx.x, kg = blockIdx.y % QW;
   int j, t0 = 0, t1 = 0, slot = 0;
   if (kv.ecap > 0) {
-    const int4 unit = kv.units[(size_t)bh * (2 * kv.ecap + Tn) + blockIdx.y / QW];
+    const int4 unit = kv.units[(size_t)bh * (kv.ecap + Tn + kv.cuts) + blockIdx.y / QW];
     j = unit.x;
     t0 = unit.y;
     t1 = t0 + unit.z;
@@ -1086,7 +1086,7 @@ hipError_t launch_key(const Shape& s, const BwdArgs& a, const float* Ds, const f
   }
   if (kv.ecap > 0) {
     KernelTimer kt("kv_merge", st);
-    f32_kv_merge_kernel<D><<<dim3(s.BH * kv.ecap, 8), 256, 0, st>>>(kv, s.BH, s.N, s.T, s.lay(), (float*)a.dK, (float*)a.dV);
+    f32_kv_merge_kernel<D><<<dim3(s.BH * kv.cuts, 8), 256, 0, st>>>(kv, s.BH, s.N, s.T, s.lay(), (float*)a.dK, (float*)a.dV);
   }
   return hipGetLastError();
 }

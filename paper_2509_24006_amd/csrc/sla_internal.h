@@ -108,19 +108,22 @@ struct BwdArgs {
   char* ws;  // workspace, ws_backward_bytes
 };
 size_t backward_ws_bytes(const Shape& s);   // (backward.hip)
-// How the key-side kernel walks the column lists.  A unit of work is a list, or a piece of it: lists longer
-// than `piece` entries give up pieces of that many, each with float sums of its own (a slot of `part`),
-// which a second launch adds up.  Every unit is four ints, written by a wave per head of the query-side launch
-// (kv_plan):
-//   extra e < ecap             key block, first entry, entries (0: none), slot
-//   ecap + r, r < T            the rest of the list of rank r: key block, first entry, entries, slot or -1
-//   ecap + T + m, m < ecap     a key block that was cut: key block, slot of the rest, slot of the first extra, extras
+// How the key-side kernel walks the column lists.  A list longer than `piece` entries is summed in pieces of that
+// many (the last is shorter), each from zero, and the sums are added in order.
+// With ecap > 0 a piece is a unit of work: those behind the first, at most ecap per head, go to workgroups of their
+// own, which leave float sums in a slot of `part`, and a second launch adds them up.  Every unit is four ints, written
+// by a wave per head of the query-side launch (kv_plan):
+//   extra e < ecap             key block, first entry, entries (0: none), slot e
+//   ecap + r, r < T            the first piece of the list of rank r: key block, first entry, entries, slot ecap + r
+//                              where the list was cut (these are the first ranks), else -1
+//   ecap + T + r, r < cuts     a key block that was cut, or zeros: key block, slot of the first extra, extras, 0
+// With ecap = 0 (bf16) one workgroup walks all pieces, and the sum so far of the list of rank r waits in slot r.
 struct KvSplit {
-  int piece, ecap;
-  int4* units;   // [BH][2 ecap + T]
-  float* part;   // [BH][2 ecap] slots of 2 x 64 x d floats
+  int piece, ecap, cuts;   // cuts: at most this many lists of a head are longer than a piece
+  int4* units;   // [BH][ecap + T + cuts]
+  float* part;   // [BH][ecap + cuts] slots of 2 x 64 x d floats
 };
-KvSplit kv_split(const Shape& s);   // piece and ecap (backward.hip)
+KvSplit kv_split(const Shape& s);   // piece, ecap and cuts (backward.hip)
 struct KvPlanArgs {
   KvSplit split;
   const int32_t *col_ptr, *col_order;

@@ -266,11 +266,13 @@ def test_key_blocks_that_nearly_every_query_block_selects(oracle, T, d, tail):
 
 @pytest.mark.parametrize("dtype", ["bf16", "fp32"])
 @pytest.mark.parametrize("T,d,H,phi,bq,k_l", [(35, 64, 3, 0, 64, 0.2), (36, 64, 3, 1, 64, 0.2), (37, 128, 2, 0, 64, 0.2),
-                                               (49, 64, 5, 0, 128, 0.2), (61, 128, 1, 0, 64, 0.95), (73, 64, 3, 1, 256, 0.1)])
+                                               (49, 64, 5, 0, 128, 0.2), (61, 128, 1, 0, 64, 0.95), (73, 64, 3, 1, 256, 0.1),
+                                               (23, 64, 3, 0, 64, 0.2), (24, 128, 2, 1, 64, 0.2), (40, 64, 34, 0, 64, 0.2)])
 def test_column_lists_cut_into_pieces(oracle, dtype, T, d, H, phi, bq, k_l):
-    # with few entries in all a list longer than twelve is walked in pieces (from 36 blocks on) and a second
-    # launch adds the sums: lists of T, T - 1, .. entries of which the rest is one entry, a full piece or between,
-    # key blocks without any, a ragged last block, no marginal block; the same bits on every call
+    # a list longer than twelve is walked in pieces (from 24 blocks on, with floats from 36 and few entries in all), by
+    # workgroups of their own and a second launch that adds the sums, or (34 heads) by one workgroup: lists of T,
+    # T - 1, .. entries whose last piece is one entry, a full piece or between, key blocks without any, a ragged last
+    # block, no marginal block; the same bits on every call
     N = 64 * T - 11
     rng = np.random.default_rng(T + d)
     u = rng.standard_normal(d).astype(np.float32)
@@ -288,6 +290,41 @@ def test_column_lists_cut_into_pieces(oracle, dtype, T, d, H, phi, bq, k_l):
     _full_case(oracle, x, dtype, k_h, k_l, phi=phi, bq=bq)
     first, again = (run_gpu(x, dtype, k_h, k_l, phi=phi, bq=bq) for _ in range(2))
     assert all(np.array_equal(first[n], again[n]) for n in ("dQ", "dK", "dV", "dW"))
+
+
+@pytest.mark.parametrize("T,d,k_h,phi,bq,k_l", [(23, 64, 0.1, 0, 64, 0.2), (24, 64, 0.1, 0, 64, 0.2), (25, 128, 0.05, 1, 64, 0.2),
+                                                (48, 128, 0.1, 0, 128, 0.2), (66, 64, 0.25, 1, 64, 0.75), (146, 128, 0.05, 0, 64, 0.1),
+                                                (200, 64, 0.02, 0, 256, 0.1), (256, 64, 0.04, 1, 64, 0.1)])
+def test_gradients_of_a_head_among_few_and_many(T, d, k_h, phi, bq, k_l):
+    # pieces of long lists are workgroups of their own among one or two heads and one workgroup's among forty; the
+    # gradients of a head are the same bits in every call.  Lists of T, T - 1, .. entries and of lengths between
+    from paper_2509_24006_amd import binding as sla
+    g = torch.Generator(device="cuda")
+    g.manual_seed(T)
+    N, H = T * 64 - 5, 64
+    u = torch.randn(d, generator=g, device="cuda")
+    u /= u.norm()
+    x = [torch.randn(1, H, N, d, generator=g, device="cuda") for _ in range(4)]
+    # queries lean towards u more and more along the sequence, so the more key block j leans, the longer its list
+    x[0] += 3.0 * torch.linspace(0, 1, N, device="cuda")[:, None] * u
+    for j, c in ((2, 4.0), (T // 2, 1.0), (T // 3, 0.5), (T - 1, 2.0), (T // 4, 0.25)):
+        x[1][:, :, 64 * j:64 * (j + 1)] += c * u
+    x = [t.bfloat16() for t in x]
+    W = (0.02 * torch.randn(d, d, generator=g, device="cuda")).bfloat16()
+
+    def grads(H):
+        Q, K, V, dO = (t[:, :H].contiguous() for t in x)
+        p = sla.make_params(1, H, N, d, k_h, k_l, torch.bfloat16, phi=phi, bq=bq)
+        Mc, luts, _ = sla.sla_build_mask(p, Q, K)
+        ptr = sla.lut_views(p, luts)["col_ptr"][0, 0]
+        O, saved = sla.sla_forward(p, Q, K, V, W, Mc, luts)
+        return (ptr[1:] - ptr[:-1]).max().item(), sla.sla_backward(p, Q, K, V, W, Mc, luts, saved, dO)[:3]
+
+    longest, many = grads(H)
+    assert longest >= min(T // 2 + 2, T - 4)   # cut, if anything is
+    for few in (1, 2, 7):
+        for a, b in zip(grads(few)[1], many):
+            assert torch.equal(a, b[:, :few])
 
 
 def test_a_head_alone_above_the_longest_cut_lists():
