@@ -87,7 +87,7 @@ _host = None
 
 
 def _host_calls():
-    """The compiled host part of the three per-pass calls (csrc/host_calls.cpp): checks, allocations and
+    """The compiled host part of the per-pass calls (csrc/host_calls.cpp): checks, allocations and
     the library call in one go.  What it does not take as it stands it returns None for, and the Python
     code below, which does the same step by step, raises the error."""
     global _host

@@ -1,4 +1,4 @@
-// The host part of the three calls a layer makes per pass (mask, forward, backward) as a CPython
+// The host part of the calls a layer makes per pass (mask, forward, the two in one, backward) as a CPython
 // module: sizes, checks of the tensors, allocation of what the caller did not pass, and the call of
 // the C ABI.  A small layer is bound by this part, not by its kernels (one training step
 // of 2 heads x 1110 tokens, d = 128: 191 -> 126 us, of 2 x 1024 floats, d = 64, 186 -> 109; mask and forward
@@ -242,9 +242,9 @@ PyObject* backward(PyObject*, PyObject* const* a, Py_ssize_t n) {
     dV.fill([&] { return new_like(*V, c); });
     dW.fill([&] { return at::empty({c.p->d, c.p->d}, Q->options().dtype(wt).requires_grad(false)); });
     ws.fill([&] { return new_bytes(c.z.ws_backward_bytes, *Q); });
-    rc = sla_backward_typed(c.p, Q->data_ptr(), K->data_ptr(), V->data_ptr(), W->data_ptr(), (const int8_t*)Mc->data_ptr(),
-                      luts->data_ptr(), saved->data_ptr(), dO->data_ptr(), dQ.ptr(), dK.ptr(), dV.ptr(), dW.ptr(),
-                            w16 ? SLA_BF16 : SLA_F32, ws.ptr(), ws.size(), st);
+    rc = sla_backward_typed(c.p, Q->data_ptr(), K->data_ptr(), V->data_ptr(), W->data_ptr(),
+                            (const int8_t*)Mc->data_ptr(), luts->data_ptr(), saved->data_ptr(), dO->data_ptr(),
+                            dQ.ptr(), dK.ptr(), dV.ptr(), dW.ptr(), w16 ? SLA_BF16 : SLA_F32, ws.ptr(), ws.size(), st);
   }
   if (rc != SLA_OK) return PyLong_FromLong(rc);
   return pack({dQ.object(), dK.object(), dV.object(), dW.object()});

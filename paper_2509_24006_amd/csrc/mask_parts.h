@@ -9,7 +9,7 @@ namespace sla {
 
 // ---------------------------------------------------------------- pool
 // A lane owns the 16 bytes of a token row that hold V adjacent features and walks the rows of
-// its block in order (the sum over a block's tokens is sequential, see above); D / V lanes cover
+// its block in order (the sum over a block's tokens is sequential, so that the mask is reproducible); D / V lanes cover
 // a block, so a wavefront pools 64 V / D blocks at once and each of its loads fetches whole
 // rows.  The first half of the 2 a.wgs workgroups takes Q (blocks of len0 tokens, Tn0 per head), the
 // other K (len1, Tn1).

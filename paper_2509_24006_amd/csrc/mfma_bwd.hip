@@ -89,7 +89,7 @@ __global__ __launch_bounds__(256, 2) void bwd_dkdv_mfma_kernel(
   // of few heads at a time; most tile loads of this kernel miss the L2.
   int bh, place;   // head, place among its units
   if (index < 0) {
-    // pieces of long lists: all of the same length, and the longest units there are
+    // pieces of long lists: all but the last ones as long as the longest units there are
     bh = blockIdx.x % BH;
     place = blockIdx.x / BH;
     if (place >= kv.ecap) return;

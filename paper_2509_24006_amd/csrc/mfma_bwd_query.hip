@@ -473,7 +473,7 @@ __global__ __launch_bounds__(256 * QT, QT == 1 ? (D == 64 ? 3 : 2) : 1) void bwd
   // (a last block of a single tile: the second group runs along with no valid query and stores nothing)
   const int i = QT * ib + grp;
   // group 0 takes Q_i, dO_i in through the second pair buffer and stages its output over the pair
-  // buffers; group 1 has DqLds<D>::GROUP bytes behind them for both
+  // buffers; group 1 has PairLds<D>::GROUP bytes behind them for both
   unsigned char* gsm = smem + (grp ? Lds::BYTES - Lds::BUF : 0);
   const int q0 = i * kBlk, rows = max(0, min(kBlk, N - q0));
   const int qrow = qh * 32 + ln;

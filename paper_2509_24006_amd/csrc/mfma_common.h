@@ -22,9 +22,7 @@ typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
-typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
-typedef __attribute__((ext_vector_type(2))) unsigned int u32x2;
 
 __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
@@ -62,19 +60,6 @@ __device__ __forceinline__ unsigned bits16bf(unsigned x) {
   return (x & (0x00010001u << K)) * (0x3f80u >> K);
 }
 
-// eight consecutive floats -> bf16x8 (round to nearest even)
-__device__ __forceinline__ bf16x8 cvt8(const float* p) {
-  const f32x4 a = *reinterpret_cast<const f32x4*>(p);
-  const f32x4 b = *reinterpret_cast<const f32x4*>(p + 4);
-  bf16x8 r;
-#pragma unroll
-  for (int s = 0; s < 4; ++s) {
-    r[s] = (__bf16)a[s];
-    r[4 + s] = (__bf16)b[s];
-  }
-  return r;
-}
-
 // registers 8u..8u+7 of a C tile as a bf16 operand
 __device__ __forceinline__ bf16x8 c_to_operand(const f32x16& c, int u) {
   bf16x8 r;
@@ -83,101 +68,7 @@ __device__ __forceinline__ bf16x8 c_to_operand(const f32x16& c, int u) {
   return r;
 }
 
-// 4 x 4 transpose of bf16 held as four 8-byte rows: out[i] = (in[0][i], in[1][i], in[2][i], in[3][i])
-__device__ __forceinline__ void transpose4x4(const u32x2 (&in)[4], u32x2 (&out)[4]) {
-  // in[k].x = (e0, e1), in[k].y = (e2, e3) of key k
-  out[0].x = (in[0].x & 0xffffu) | (in[1].x << 16);
-  out[0].y = (in[2].x & 0xffffu) | (in[3].x << 16);
-  out[1].x = (in[0].x >> 16) | (in[1].x & 0xffff0000u);
-  out[1].y = (in[2].x >> 16) | (in[3].x & 0xffff0000u);
-  out[2].x = (in[0].y & 0xffffu) | (in[1].y << 16);
-  out[2].y = (in[2].y & 0xffffu) | (in[3].y << 16);
-  out[3].x = (in[0].y >> 16) | (in[1].y & 0xffff0000u);
-  out[3].y = (in[2].y >> 16) | (in[3].y & 0xffff0000u);
-}
-
 typedef __hip_bfloat16 bf16;
-
-// ---- transposing tile stage
-// A 4-row x 4-feature patch (rows k4..k4+3, features f4..f4+3) of a row-major [rows][D]
-// bf16 tile is loaded as four 8-byte pieces and stored transposed into an LDS tile laid out
-// [feature][row position] (stride elements per feature) at row position `pos`.
-__device__ __forceinline__ void load_patch(const bf16* __restrict__ src, int D, int k4, int f4,
-                                           int rows_valid, u32x2 (&x)[4]) {
-#pragma unroll
-  for (int kk = 0; kk < 4; ++kk) {
-    if (k4 + kk < rows_valid)
-      x[kk] = *reinterpret_cast<const u32x2*>(src + (size_t)(k4 + kk) * D + f4);
-    else
-      x[kk] = u32x2{0u, 0u};
-  }
-}
-
-__device__ __forceinline__ void store_patch_t(bf16* dst, int stride, int f4, int pos,
-                                              const u32x2 (&x)[4]) {
-  u32x2 y[4];
-  transpose4x4(x, y);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) *reinterpret_cast<u32x2*>(dst + (f4 + i) * stride + pos) = y[i];
-}
-
-// position of row group kg (rows 4kg..4kg+3 of a 64-row tile) under perm16
-__device__ __forceinline__ int pos_of_kg(int kg) { return ((kg >> 2) << 4) + perm16((kg & 3) << 2); }
-
-constexpr int kVS = kBlk + 8;  // LDS stride (elements) of a transposed [feature][64 rows] tile
-
-// One staging unit = rows 4rg..4rg+3, features 8fg..8fg+7 of a 64 x D row-major tile, loaded
-// as four 16-byte pieces (zero beyond rows_valid).
-__device__ __forceinline__ void load_unit(const bf16* __restrict__ src, int D, int rg, int fg,
-                                          int rows_valid, u32x4 (&x)[4]) {
-#pragma unroll
-  for (int rr = 0; rr < 4; ++rr) {
-    if (4 * rg + rr < rows_valid)
-      x[rr] = *reinterpret_cast<const u32x4*>(src + (size_t)(4 * rg + rr) * D + 8 * fg);
-    else
-      x[rr] = u32x4{0u, 0u, 0u, 0u};
-  }
-}
-
-// row-major copy: dst[row][feature], stride RS elements
-__device__ __forceinline__ void store_unit_rows(bf16* dst, int RS, int rg, int fg, const u32x4 (&x)[4]) {
-#pragma unroll
-  for (int rr = 0; rr < 4; ++rr) *reinterpret_cast<u32x4*>(dst + (4 * rg + rr) * RS + 8 * fg) = x[rr];
-}
-
-// transposed copy: dst[feature][perm16 row position], stride kVS
-__device__ __forceinline__ void store_unit_t(bf16* dst, int rg, int fg, const u32x4 (&x)[4]) {
-  u32x2 lo[4], hi[4];
-#pragma unroll
-  for (int rr = 0; rr < 4; ++rr) {
-    lo[rr] = u32x2{x[rr].x, x[rr].y};
-    hi[rr] = u32x2{x[rr].z, x[rr].w};
-  }
-  store_patch_t(dst, kVS, 8 * fg, pos_of_kg(rg), lo);
-  store_patch_t(dst, kVS, 8 * fg + 4, pos_of_kg(rg), hi);
-}
-
-// A operand (rows = 32 features f0.., k = 16 tile rows r0.. in the order a C tile hands them
-// over, see perm16) read from a ROW-MAJOR LDS tile [row][feature] (stride elements) with the
-// transposing LDS read: in each group of 16 lanes, lane 4e + a supplies the address of 4
-// consecutive features of one row, and lane 4a + c receives feature c of the rows of lanes
-// a, 4 + a, 8 + a, 12 + a.  Two reads give the eight k-values of a lane.
-__device__ __forceinline__ bf16x8 read_tr_operand(const bf16* tile, int stride, int r0, int f0, int l) {
-  typedef __attribute__((ext_vector_type(4))) short s16x4;
-  typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-  const int G = l >> 4, e = (l >> 2) & 3, a = l & 3;
-  const bf16* p = tile + (r0 + 4 * (G >> 1) + e) * stride + f0 + 16 * (G & 1) + 4 * a;
-  const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p));
-  const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 8 * stride));
-  bf16x8 r;
-  const bf16x4 lo4 = *reinterpret_cast<const bf16x4*>(&lo), hi4 = *reinterpret_cast<const bf16x4*>(&hi);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    r[i] = lo4[i];
-    r[4 + i] = hi4[i];
-  }
-  return r;
-}
 
 // Raw buffer descriptor (base address, no stride, byte count, 32-bit raw format) over `bytes`
 // bytes starting at p: loads through it return zero beyond the end.  p must be wave-uniform.
@@ -205,13 +96,6 @@ __device__ __forceinline__ void load_to_lds16(BufDesc desc, int voff, int soff, 
 // LDS byte address of the dynamic LDS array, as a wave-uniform integer
 __device__ __forceinline__ unsigned lds_base(unsigned char* smem) {
   return __builtin_amdgcn_readfirstlane((unsigned)reinterpret_cast<size_t>((lds_void*)smem));
-}
-
-// p[idx] for 0 <= idx < count, else 0, without a branch (range-checked buffer load); p uniform
-__device__ __forceinline__ float load_f32_or_zero(const float* p, int count, int idx) {
-  const __amdgpu_buffer_rsrc_t r =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), 0, count * 4, 0x00020000);
-  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, idx * 4, 0, 0));
 }
 
 // One wave-wide 4-byte-per-lane load global -> LDS: lane L's dword at byte offset voff of the buffer
@@ -431,35 +315,6 @@ struct RunLoader {
   }
 };
 
-// A operand whose 32 rows are tile rows r0 + (l % 32) and whose k-values are features 16 t + 8 g ..
-template <int D>
-__device__ __forceinline__ bf16x8 read_row_swz(const unsigned char* tile, int r0, int t, int l) {
-  return *reinterpret_cast<const bf16x8*>(tile + swz_chunk_off<D>(r0 + (l & 31), 2 * t + (l >> 5)));
-}
-
-// A operand with rows = features 32 et .. and k = tile rows r0 .. r0 + 15 (r0 a multiple of 16) in
-// the order a C tile hands them over, via the transposing read (see read_tr_operand).
-template <int D>
-__device__ __forceinline__ bf16x8 read_tr_swz(const unsigned char* tile, int r0, int et, int l) {
-  typedef __attribute__((ext_vector_type(4))) short s16x4;
-  typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-  const int G = l >> 4, e = (l >> 2) & 3, a = l & 3;
-  const int chunk = 4 * et + 2 * (G & 1) + (a >> 1);
-  const int row0 = r0 + 4 * (G >> 1) + e;
-  const unsigned char* p0 = tile + swz_chunk_off<D>(row0, chunk) + 8 * (a & 1);
-  const unsigned char* p1 = tile + swz_chunk_off<D>(row0 + 8, chunk) + 8 * (a & 1);
-  const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p0));
-  const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p1));
-  const bf16x4 lo4 = *reinterpret_cast<const bf16x4*>(&lo), hi4 = *reinterpret_cast<const bf16x4*>(&hi);
-  bf16x8 r;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    r[i] = lo4[i];
-    r[4 + i] = hi4[i];
-  }
-  return r;
-}
-
 // Per-lane byte offsets into a swizzled tile, kept as a handful of registers:
 //   row(t)     16-byte chunk 2t + g of row r0 + (l % 32)                 (operand read by rows)
 //   tr(h, et)  8 bytes of the transposing read h of feature tile et, tile rows r0 + 0..15; rows
@@ -491,10 +346,6 @@ struct TileAddr {
   __device__ __forceinline__ void refresh() { asm volatile("" : "+v"(sx), "+v"(fx)); }
   __device__ __forceinline__ int row(int t) const { return rb + ((t << 5) ^ sx); }
   __device__ __forceinline__ int tr(int h, int et) const { return tb[h] + ((et << 6) ^ fx); }
-  // the same with the per-lane base already moved to a tile slot: base = rb + slot (rows),
-  // base = tb[h] + slot (transposing reads)
-  __device__ __forceinline__ int row_at(int t, int base) const { return base + ((t << 5) ^ sx); }
-  __device__ __forceinline__ int tr_at(int et, int base) const { return base + ((et << 6) ^ fx); }
 };
 
 typedef __attribute__((ext_vector_type(4))) short lds_s16x4_val;
@@ -505,7 +356,10 @@ __device__ __forceinline__ bf16x8 lds_row(const unsigned char* smem, int off) {
   return *reinterpret_cast<const bf16x8*>(smem + off);
 }
 
-// transposed operand from the two precomputed read offsets (off, off + 8 rows)
+// A operand with rows = 32 features and k = 16 tile rows in the order a C tile hands them over (see perm16), from a
+// row-major tile by the transposing LDS read: in each group of 16 lanes, lane 4e + a supplies the address of 4
+// consecutive features of one row, and lane 4a + c receives feature c of the rows of lanes a, 4 + a, 8 + a, 12 + a.
+// Two reads, 8 rows apart, give the eight k-values of a lane; off0, off1: their precomputed offsets.
 template <int D>
 __device__ __forceinline__ bf16x8 lds_tr(const unsigned char* smem, int off0, int off1) {
   const lds_s16x4_val lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)(smem + off0));
@@ -546,26 +400,6 @@ __device__ __forceinline__ void store_rows_bf16(unsigned char* stage, const f32x
     const int idx = it * 64 + l, row = idx / PPR, pc = idx % PPR;
     const u32x4 v = *reinterpret_cast<const u32x4*>(stage + row * PB + pc * 16);
     if (row < rows_valid) *reinterpret_cast<u32x4*>(dst + (size_t)row * row_stride + pc * 8) = v;
-  }
-}
-
-// The float counterpart of store_rows_bf16: `stage` needs 32 * (128 NT + 16) bytes.
-template <int NT>
-__device__ __forceinline__ void store_rows_f32(unsigned char* stage, const f32x16 (&c)[NT], float* dst,
-                                               int row_stride, int rows_valid, int l) {
-  constexpr int PB = 128 * NT + 16, PPR = 8 * NT;
-  const int g = l >> 5, ln = l & 31;
-#pragma unroll
-  for (int t = 0; t < NT; ++t)
-#pragma unroll
-    for (int r4 = 0; r4 < 4; ++r4)
-      *reinterpret_cast<f32x4*>(stage + ln * PB + (32 * t + 8 * r4 + 4 * g) * 4) =
-          f32x4{c[t][4 * r4], c[t][4 * r4 + 1], c[t][4 * r4 + 2], c[t][4 * r4 + 3]};
-#pragma unroll
-  for (int it = 0; it < 32 * PPR / 64; ++it) {
-    const int idx = it * 64 + l, row = idx / PPR, pc = idx % PPR;
-    const u32x4 v = *reinterpret_cast<const u32x4*>(stage + row * PB + pc * 16);
-    if (row < rows_valid) *reinterpret_cast<u32x4*>(dst + (size_t)row * row_stride + pc * 4) = v;
   }
 }
 
@@ -693,31 +527,9 @@ __device__ __forceinline__ void dw_sum(const DwSum& a, int block, unsigned char*
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
-// phi statistics of a token whose features sit in B-operand fragments (lane holds features
-// 16 t + 8 g + s, its partner lane l ^ 32 the others): softmax max and 1 / sum.
-template <int KT>
-__device__ __forceinline__ void phi_stats(const bf16x8 (&xf)[KT], int phi, float& mx, float& inv) {
-  mx = 0.0f;
-  inv = 1.0f;
-  if (phi != 0) return;
-  mx = -INFINITY;
-#pragma unroll
-  for (int t = 0; t < KT; ++t)
-#pragma unroll
-    for (int s = 0; s < 8; ++s) mx = fmaxf(mx, (float)xf[t][s]);
-  mx = half_max(mx);
-  float sum = 0.0f;
-#pragma unroll
-  for (int t = 0; t < KT; ++t)
-#pragma unroll
-    for (int s = 0; s < 8; ++s) sum += fast_exp2(((float)xf[t][s] - mx) * kLog2e);
-  sum = half_sum(sum);
-  inv = 1.0f / sum;
-}
-
 // phi of a token whose features sit in B-operand fragments, as bf16 operand fragments; for the
 // softmax map every exponential is formed once (kept in registers between the sum and the values).
-// mx, inv: the softmax statistics (0 and 1 for the other map), as phi_stats returns them.
+// mx, inv: the softmax statistics, largest feature and 1 / sum of the exponentials (0 and 1 for the other map).
 template <int KT>
 __device__ __forceinline__ void phi_fragments(const bf16x8 (&xf)[KT], int phi, bf16x8 (&out)[KT], float& mx, float& inv) {
   mx = 0.0f;
