@@ -313,10 +313,11 @@ __global__ __launch_bounds__(256, 2) void f32_states_kernel(const float* __restr
 // accumulators are rounded less often.  A wave owns 32 columns and 32 MT rows i and reads every state
 // once, straight into the B operand (lane = column, 128 contiguous bytes per half wave), so no LDS and
 // no barriers.  The k-index runs over rows such that the two of a dword lie 16 apart, as their indicator
-// bits then do in the dword's place (bits16bf).  A state that is not finite would reach every row
-// through its product with 0: such values are taken out of the product and added only to the rows that
-// hold the bit.
-constexpr float kMaxFinite = 3.402823466e38f;
+// bits then do in the dword's place (bits16bf).  The last bits of the last piece of a value below 2^-110 would
+// lie below the smallest bf16 there is, 2^-133, so the pieces are those of 2^16 times the value.  A state that is not
+// finite would reach every row through its product with 0, and one above 2^99 could overflow the scaled sum of 3072:
+// such values are taken out of the product and added only to the rows that hold the bit.
+constexpr float kAggScale = 65536.0f, kAggMax = 0x1p99f;
 
 template <int MT>
 __global__ __launch_bounds__(256) void f32_aggregate_kernel(const float* __restrict__ in,
@@ -364,9 +365,9 @@ __global__ __launch_bounds__(256) void f32_aggregate_kernel(const float* __restr
       unsigned y[2][3];
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        const bool fin = fabsf(x[q + h]) <= kMaxFinite;
-        bad |= !fin;
-        float v = fin ? x[q + h] : 0.0f;
+        const bool in_range = fabsf(x[q + h]) <= kAggMax;
+        bad |= !in_range;
+        float v = in_range ? x[q + h] * kAggScale : 0.0f;
 #pragma unroll
         for (int e = 0; e < 3; ++e) {   // the top 16 bits are a bf16, and what is left of v is exact
           y[h][e] = __float_as_uint(v) & 0xffff0000u;
@@ -400,7 +401,7 @@ __global__ __launch_bounds__(256) void f32_aggregate_kernel(const float* __restr
   for (int m = 0; m < MT; ++m)
 #pragma unroll
     for (int r = 0; r < 16; ++r)   // row m0 + 32 m + c_row(r, g); rows past T are dropped
-      __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[m][r]), orsrc,
+      __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[m][r] * (1.0f / kAggScale)), orsrc,
                                             (m0 + 32 * m + c_row(r, g)) * pitch + (c0 + n) * 4, 0, 0);
   if (!__any(bad)) return;
   // this lane's column again, for the rows it has just written
@@ -408,7 +409,7 @@ __global__ __launch_bounds__(256) void f32_aggregate_kernel(const float* __restr
     float* o = out + ((size_t)bh * T + i) * row_len + c0 + n;
     for (int k = 0; k < T; ++k) {
       const float v = src[(size_t)k * row_len];
-      if (!(fabsf(v) <= kMaxFinite) && ((ib[(size_t)i * Tw + (k >> 6)] >> (k & 63)) & 1ull)) *o += v;
+      if (!(fabsf(v) <= kAggMax) && ((ib[(size_t)i * Tw + (k >> 6)] >> (k & 63)) & 1ull)) *o += v;
     }
   }
 }

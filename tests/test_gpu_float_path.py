@@ -51,6 +51,40 @@ def test_a_state_that_is_not_finite_reaches_only_the_rows_that_add_it(oracle, T)
     assert np.abs(r["Hi"][fin] - f["Hi"][fin]).max() <= 1e-5 * np.abs(f["Hi"][fin]).max()
 
 
+@pytest.mark.parametrize("T,d", [(12, 64), (40, 64), (130, 128)])
+def test_states_of_any_magnitude(T, d):
+    # V and dO scaled by powers of two, from where a state's last bits are the smallest floats to where a scaled sum of
+    # states would overflow; all states, or every second feature, so that the columns differ.  A state is rounded
+    # to 2^-149 at most once per product and sum (64 tokens, T blocks), and either side's float sums to 2^-24 of their
+    # terms' magnitudes in each addition
+    import torch
+    from paper_2509_24006_amd import binding as sla
+    g = torch.Generator(device="cuda")
+    g.manual_seed(T)
+    N = 64 * T - 5
+    Q, K, V, dO = (torch.randn(1, 1, N, d, generator=g, device="cuda") for _ in range(4))
+    W = 0.05 * torch.randn(d, d, generator=g, device="cuda")
+    p = sla.make_params(1, 1, N, d, 0.1, 0.2, torch.float32)
+    Mc, luts, _ = sla.sla_build_mask(p, Q, K)
+
+    def states(V):
+        return sla.saved_views(p, sla.sla_forward(p, Q, K, V, W, Mc, luts)[1])["Hi"].double()   # [.., c, e]
+
+    _, saved = sla.sla_forward(p, Q, K, V, W, Mc, luts)
+    grads = lambda dO: [t.double() for t in sla.sla_backward(p, Q, K, V, W, Mc, luts, saved, dO)[1:3]]
+    ref, mag, gref = states(V), states(V.abs()), grads(dO)
+    for e in (-122, -116, -104, -60, 60, 93, 101, 112):
+        for step in (1, 2):
+            f = torch.ones(d, device="cuda", dtype=torch.float64)
+            f[::step] = 2.0 ** e
+            got = states((V.double() * f).float())
+            bound = 2 * (64 + T) * 2.0 ** -24 * mag * f + 64 * T * 2.0 ** -149
+            assert bool(((got - ref * f).abs() <= bound).all()), (e, step)
+        for a, b in zip(grads((dO.double() * 2.0 ** e).float()) if e < 0 else (), gref):
+            # (rounding to 2^-149 in each of its sums and products: no more than 2^-149 / 2^(e - 6) of the norm each)
+            assert (a * 2.0 ** -e - b).norm() <= (1e-6 + 64 * 2.0 ** (-149 - e)) * b.norm(), e
+
+
 @pytest.mark.parametrize("T,d,k_h", [(1, 64, 0.0), (1, 128, 0.0), (2, 64, 0.0), (3, 128, 0.3), (4, 64, 0.2), (4, 128, 0.0),
                                      (5, 64, 0.2), (5, 128, 0.0)])
 def test_sums_of_the_states_of_a_few_blocks(oracle, T, d, k_h):
