@@ -572,11 +572,12 @@ __device__ __forceinline__ void phi_fragments(const bf16x8 (&xf)[KT], int phi, b
   phi_fragments<KT>(xf, phi, out, mx, inv);
 }
 
-// phi without the softmax map's normaliser (the exponentials relative to the token's maximum): enough
-// where phi enters numerator and denominator of the same quotient.  The exponent is one fused multiply-add, whose
-// rounded second term, mx log2(e), puts the same factor before every feature: 2^(half a unit in its last place),
-// at most 2^(1/16) up to kRawMax.  It cancels in the quotient, but grows with mx (from 2^31 on it is infinite), so
-// larger maxima, and those that are not finite, take the form above.
+// phi without the softmax map's normaliser (the exponentials relative to the token's maximum, divided by the number
+// of features so that their sum stays below one and what they multiply does not overflow): enough where phi enters
+// numerator and denominator of the same quotient.  The exponent is one fused multiply-add, whose rounded second term,
+// mx log2(e) and the division, puts the same factor before every feature: 2^(half a unit in its last place), at most
+// 2^(1/16) up to kRawMax.  It cancels in the quotient, but grows with mx (from 2^31 on it is infinite), so larger maxima,
+// and those that are not finite, take the form above.
 constexpr float kRawMax = 1048576.0f;
 template <int KT>
 __device__ __forceinline__ void phi_fragments_raw(const bf16x8 (&xf)[KT], int phi, bf16x8 (&out)[KT]) {
@@ -596,7 +597,8 @@ __device__ __forceinline__ void phi_fragments_raw(const bf16x8 (&xf)[KT], int ph
     phi_fragments<KT>(xf, phi, out, mx, inv);
     return;
   }
-  const float off = -mx * kLog2e;
+  static_assert(KT == 4 || KT == 8, "64 or 128 features");
+  const float off = fmaf(-mx, kLog2e, KT == 4 ? -6.0f : -7.0f);
 #pragma unroll
   for (int t = 0; t < KT; ++t)
 #pragma unroll

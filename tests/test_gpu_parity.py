@@ -168,6 +168,29 @@ def test_tokens_with_very_large_features(oracle, wide_tiles, d, mag):
         _compare(k, r[k], f[k], TOL["bf16"], block_tol=BLOCK_TOL["bf16"])
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("e", [-100, 100, 120])
+def test_values_near_the_ends_of_the_float_range(wide_tiles, d, e):
+    # V scaled by a power of two scales O, O^l exactly (no sum leaves the normal floats): with nearly equal features
+    # phi(Q) is as flat as it gets, and its sums over the features must not overflow before O^l does
+    from paper_2509_24006_amd import binding as sla
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d)
+    N = 20 * 64 - 5
+    Q, K, V = (torch.randn(1, 2, N, d, generator=g, device="cuda") for _ in range(3))
+    Q, K, V = (0.1 * Q).bfloat16(), K.bfloat16(), (0.25 * V + 1).bfloat16()
+    W = (0.02 * torch.randn(d, d, generator=g, device="cuda")).bfloat16()
+    p = sla.make_params(1, 2, N, d, 0.1, 0.2, torch.bfloat16, bq=128)
+    Mc, luts, _ = sla.sla_build_mask(p, Q, K)
+
+    def out(V):
+        O, saved = sla.sla_forward(p, Q, K, V, W, Mc, luts)
+        return O.double(), sla.saved_views(p, saved)["Ol"].double()
+
+    for a, b in zip(out((V.double() * 2.0 ** e).bfloat16()), out(V)):
+        assert torch.equal(a, b * 2.0 ** e)
+
+
 @pytest.mark.parametrize("N", [1, 63, 64, 65, 130])
 def test_short_sequences(oracle, N):
     rng = np.random.default_rng(N)
