@@ -26,12 +26,13 @@ def test_float_tile_edges(oracle, N, d, phi):
 
 
 # 8 heads x 100 blocks: enough of them for the key-side kernel that gives a workgroup half of a key
-# block's keys (from 768 on), and four row tiles of 32 in the sums of the states, in both directions;
-# every block of 64 rows of dK and dV on its own.  With and without marginal blocks, and one head less
-# than the line (7 x 109 = 763 blocks) on the other side of it
+# block's keys (from 768 on, from 384 where long lists are cut, as with 7 x 109 and 4 x 96; a quarter below, as with
+# 3 x 127), and four row tiles of 32 in the sums of the states, in both directions; every block of 64 rows of dK and
+# dV on its own.  With and without marginal blocks
 @pytest.mark.timeout(300)
 @pytest.mark.parametrize("H,T,d,phi,k_l", [(8, 100, 64, 0, 0.2), (8, 100, 128, 1, 0.2), (8, 100, 128, 0, 1.0),
-                                           (8, 96, 64, 1, 0.1), (7, 109, 64, 0, 0.1)])
+                                           (8, 96, 64, 1, 0.1), (7, 109, 64, 0, 0.1), (4, 96, 128, 1, 0.2),
+                                           (3, 127, 64, 0, 0.2)])
 def test_float_calls_of_many_blocks(oracle, say, H, T, d, phi, k_l):
     _full_case(oracle, _inputs(64 * T - 9, d, H), "fp32", 0.1, k_l, phi=phi)
     say(f"{H} heads x {T} blocks, d = {d}: done")

@@ -233,8 +233,7 @@ def test_image_shaped_batch_against_oracle(oracle):
 
 @pytest.mark.parametrize("T", [200, 700, 2050, 3072])
 def test_masks_of_very_long_sequences(oracle, T):
-    # 200 and 700 blocks: 4 and 16 keys of a row per lane in registers (the other register widths are
-    # covered by the workloads); beyond 2048 blocks the classification keeps a row's keys in LDS instead of registers;
+    # 200, 700, 2050 and 3072 blocks: 4, 13, 39 and 48 keys of a row per lane (other widths are covered by the workloads);
     # 3072 blocks is the longest sequence the library takes.  Masks and tables bit for bit.
     N, d, H = 64 * T - 57, 64, 1
     rng = np.random.default_rng(T)

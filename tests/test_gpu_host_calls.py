@@ -1,5 +1,7 @@
 """The compiled host part of the calls against the binding's own Python code: the same outputs for every
 layout and every choice of buffers passed in, the same errors for what does not fit."""
+import ctypes
+
 import pytest
 import torch
 
@@ -106,10 +108,24 @@ def test_subclasses_take_the_python_path():
     class Plain(torch.Tensor):
         pass
 
-    p, x, W = _tensors(sla.SLA_BHND, torch.bfloat16)
-    ref = sla.sla_build_mask(p, x[0], x[1])[0]
-    got = sla.sla_build_mask(p, x[0].as_subclass(Plain), x[1])[0]
-    assert torch.equal(ref, got)
+    p, (Q, K, V, dO), W = _tensors(sla.SLA_BHND, torch.bfloat16)
+    Mc, luts, _ = sla.sla_build_mask(p, Q, K)
+    O, saved = sla.sla_forward(p, Q, K, V, W, Mc, luts)
+    assert torch.equal(Mc, sla.sla_build_mask(p, Q.as_subclass(Plain), K)[0])
+    # the compiled calls hand every tensor of a subclass back, in any place, and take parameters
+    host, addr = sla._host_calls(), ctypes.addressof(p)
+    new = torch.empty_like
+    ws = torch.empty(max(sla.sla_sizes(p).ws_backward_bytes, sla.sla_sizes(p).ws_mask_bytes), dtype=torch.uint8, device="cuda")
+    calls = [(host.build_mask, [Q, K, ws, new(Mc), new(luts)], []),
+             (host.forward, [Q, K, V, W, Mc, luts, new(O), new(saved), ws], [True]),
+             (host.mask_forward, [Q, K, V, W], [True]),
+             (host.backward, [Q, K, V, W, Mc, luts, saved, dO, ws, new(Q), new(K), new(V), torch.empty_like(W, dtype=torch.float32)],
+              [False])]
+    for call, tensors, rest in calls:
+        assert type(call(addr, *tensors, *rest)) is tuple
+        assert type(call(addr, *[torch.nn.Parameter(t, requires_grad=False) for t in tensors], *rest)) is tuple
+        for i, t in enumerate(tensors):
+            assert call(addr, *tensors[:i], t.as_subclass(Plain), *tensors[i + 1:], *rest) is None, (call, i)
 
 
 @pytest.mark.parametrize("saved", [True, False])
