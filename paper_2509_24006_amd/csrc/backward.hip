@@ -63,12 +63,12 @@ hipError_t backward_bf16(const Shape& s, const BwdArgs& a, hipStream_t st) {
 // one and a half times the average.  Key side with the adding launch and dW's sums, us:
 //                                            d    whole   T / 8   T / 6   T / 4
 //   1 head x 146 blocks of 7                128      58      39      45      58
-//   12 x 146 of 7                           128     101     116     109     109
-//   the same with b_q = 128, longer lists   128     137     122     118     111
+//   12 x 146 of 7, the longest 66           128     101     116     109     109
+//   the same with b_q = 128, the longest 100 128    137     122     118     111
 //   3 x 254 of 10                            64     108      59      61      74
 //   40 x 146 of 7, one workgroup a list     128     309     319     318     318
 //   64 x 254 of 10, one workgroup a list     64     553     565     566     556
-// Where the lists happen to be short nothing is gained: 16 x 58 of 2, d = 128, at most 21, whole 42, shared out 50.
+// Where the lists happen to be short nothing is gained: 16 x 58 of 2, d = 128, at most 22, whole 42, shared out 50.
 // (2 x 250 of 50, d = 128, pieces of 50, 75, 100: 135, 141, 171; 64 x 128 of 13, one workgroup a list, pieces of 16, 20,
 // 26: 637, 624, 615, whole 605.)
 //
