@@ -64,7 +64,7 @@ hipError_t backward_bf16(const Shape& s, const BwdArgs& a, hipStream_t st) {
 //                                            d    whole   T / 8   T / 6   T / 4
 //   1 head x 146 blocks of 7                128      58      39      45      58
 //   12 x 146 of 7, the longest 66           128     101     116     109     109
-//   the same with b_q = 128, the longest 100 128    137     122     118     111
+//   the same, b_q = 128, the longest 100    128     137     122     118     111
 //   3 x 254 of 10                            64     108      59      61      74
 //   40 x 146 of 7, one workgroup a list     128     309     319     318     318
 //   64 x 254 of 10, one workgroup a list     64     553     565     566     556

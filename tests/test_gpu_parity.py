@@ -341,7 +341,11 @@ def test_gradients_of_a_head_among_few_and_many(T, d, k_h, phi, bq, k_l):
         Mc, luts, _ = sla.sla_build_mask(p, Q, K)
         ptr = sla.lut_views(p, luts)["col_ptr"][0, 0]
         O, saved = sla.sla_forward(p, Q, K, V, W, Mc, luts)
-        return (ptr[1:] - ptr[:-1]).max().item(), sla.sla_backward(p, Q, K, V, W, Mc, luts, saved, dO)[:3]
+        need = sla.sla_sizes(p).ws_backward_bytes   # (the pieces' sums lie at its end)
+        ws = torch.full((need + 65536,), 0x5a, dtype=torch.uint8, device="cuda")
+        g = sla.sla_backward(p, Q, K, V, W, Mc, luts, saved, dO, workspace=ws[:need])[:3]
+        assert bool((ws[need:] == 0x5a).all())
+        return (ptr[1:] - ptr[:-1]).max().item(), g
 
     longest, many = grads(H)
     assert longest >= min(T // 2 + 2, T - 4)   # cut, if anything is
